@@ -31,10 +31,10 @@ namespace ara {
 
 constexpr uint16_t kAdvance = 0x8000;
 constexpr uint16_t kSkip = 0xFFFF;
-constexpr int kRangeWindow = 1024;   // ranges tracked at once in a wavefront's LDS state
+constexpr int kChunk = 8192;         // occurrences of a trial group sorted by range at once
 
 struct Geometry {
-    int tg, tb, n_blocks, n_ranges, gbits;
+    int tg, tb, n_blocks, n_ranges;
     int slice_blocks;   // blocks per trial slice of the event-major copy
     size_t nseg;
 };
@@ -49,8 +49,6 @@ static Geometry geometry(int64_t n_trials, int32_t catalog) {
     g.tb = kGroups * g.tg;
     g.n_blocks = static_cast<int>((n_trials + g.tb - 1) / g.tb);
     g.n_ranges = (catalog + kRange - 1) / kRange;
-    g.gbits = 0;
-    while ((1 << g.gbits) < g.n_ranges) ++g.gbits;
     g.nseg = static_cast<size_t>(g.n_blocks) * g.n_ranges * kGroups;
     g.slice_blocks = std::max(1, (g.n_blocks + kSlices - 1) / kSlices);
     return g;
@@ -63,27 +61,61 @@ static int64_t max_codes(const Geometry &g, int64_t nnz) {
     return nnz + static_cast<int64_t>(g.nseg) * (2 * g.tg + 4 * kWave);
 }
 
-static size_t prepare_bytes(const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
-    Carver c(nullptr);
-    c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
-    c.take<int64_t>(g.nseg);
-    c.take<int32_t>(g.nseg);
-    c.take<uint8_t>(g.nseg * kWave);
-    c.take<int64_t>(32);
+// The pieces of the caller's buffer.
+struct Prepared {
+    uint16_t *code;
+    int64_t *seg_base;
+    int32_t *seg_run;
+    uint8_t *lane_start;
+    int64_t *misc;
+    int64_t *tr_off, *rtot;
+    uint32_t *tr_ent;
+    int64_t *t_off;
+    int32_t *t_ids, *t_cnt;
+    uint16_t *pos;
+    // scratch of the preparation
+    uint32_t *rec, *rsum;
+    uint16_t *rpos, *rstart;
+    int64_t *bsum;
+};
+
+static int64_t n_groups_of(const Geometry &g, int64_t n_trials) { return (n_trials + g.tg - 1) / g.tg; }
+
+static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
+    Prepared p{};
+    const size_t occ = static_cast<size_t>(std::max<int64_t>(nnz, 1));
+    p.code = c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
+    p.seg_base = c.take<int64_t>(g.nseg);
+    p.seg_run = c.take<int32_t>(g.nseg);
+    p.lane_start = c.take<uint8_t>(g.nseg * kWave);
+    p.misc = c.take<int64_t>(32);
     if (flags & ARA_PREP_TRANSPOSED) {
-        c.take<int64_t>(static_cast<size_t>(kSlices) * catalog + 1);
-        c.take<uint32_t>(static_cast<size_t>(std::max<int64_t>(nnz, 1)));
-        c.take<int64_t>(static_cast<size_t>(kSlices) * g.n_ranges);
+        p.tr_off = c.take<int64_t>(static_cast<size_t>(kSlices) * catalog + 1);
+        p.tr_ent = c.take<uint32_t>(occ);
+        p.rtot = c.take<int64_t>(static_cast<size_t>(kSlices) * g.n_ranges);
     }
     if (flags & ARA_PREP_TRIAL_MAJOR) {
-        c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
-        c.take<int32_t>(static_cast<size_t>(std::max<int64_t>(nnz, 1)));
-        c.take<int32_t>(static_cast<size_t>(catalog));
+        p.t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
+        p.t_ids = c.take<int32_t>(occ);
+        p.t_cnt = c.take<int32_t>(static_cast<size_t>(catalog));
     }
     if (flags & ARA_PREP_POSITIONS) {
-        c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
-        if (!(flags & ARA_PREP_TRIAL_MAJOR)) c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
+        p.pos = c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
+        if (!p.t_off) p.t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
     }
+    // the sorted records: in the event-major lists' place when there are any (those are written last)
+    p.rec = p.tr_ent ? p.tr_ent : c.take<uint32_t>(occ);
+    if (flags & ARA_PREP_POSITIONS) p.rpos = c.take<uint16_t>(occ);
+    const size_t chunks = static_cast<size_t>(nnz / kChunk + 2 * n_groups_of(g, n_trials) + 2);
+    p.rstart = c.take<uint16_t>(chunks * static_cast<size_t>(g.n_ranges + 1));
+    p.rsum = c.take<uint32_t>(chunks * static_cast<size_t>(g.n_ranges));
+    p.bsum = c.take<int64_t>(g.nseg / 4096 + 1);
+    return p;
+}
+
+static size_t prepare_bytes(const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
+    Carver c(nullptr);
+    carve(c, g, n_trials, nnz, catalog, flags);
     return c.bytes();
 }
 
@@ -91,122 +123,525 @@ __device__ __forceinline__ int64_t code_slot(int64_t base, int s, int lane) {
     return base + static_cast<int64_t>(s >> 2) * (4 * kWave) + 4 * lane + (s & 3);
 }
 
-// One pass over a wavefront's trial group, in trial order, per window of
-// ranges.  Pass one (SCATTER = false) counts each segment's codes and the
-// events, validating IDs and offsets; pass two writes the codes and the
-// lanes' starting trials.  Within a 64-ID chunk of a trial, the lanes of one
-// range are its occurrences in storage order (a stable multi-split by
-// ballots); the first of them settles what precedes them in the segment: gap
-// codes for skipped trials and the advance flag.  With `pos`, pass two also
-// writes each occurrence's position in its trial beside its code, and with
-// `long_trial`, pass one flags a trial of more than kMaxPositions occurrences.
-template <bool SCATTER>
-__global__ __launch_bounds__(1024) void k_prep_codes(const int64_t *__restrict__ off,
-                                                     const int32_t *__restrict__ ids, int64_t n_trials,
-                                                     int32_t catalog, int tg, int tb, int n_ranges, int gbits,
-                                                     int32_t *__restrict__ seg_codes,
-                                                     const int64_t *__restrict__ seg_base,
-                                                     const int32_t *__restrict__ seg_run,
-                                                     uint16_t *__restrict__ code, uint8_t *__restrict__ lane_start,
-                                                     uint16_t *__restrict__ pos, int32_t *__restrict__ err,
-                                                     int32_t *__restrict__ long_trial,
-                                                     unsigned long long *__restrict__ events) {
-    __shared__ int32_t cur_all[kGroups * kRangeWindow];   // codes so far per range
-    __shared__ int16_t last_all[kGroups * kRangeWindow];  // last trial seen per range, -1 none
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t *cur = cur_all + w * kRangeWindow;
-    int16_t *last = last_all + w * kRangeWindow;
-    const int64_t b = blockIdx.x;
-    const int64_t t0 = b * tb + static_cast<int64_t>(w) * tg;
-    const int64_t t1 = std::min<int64_t>(t0 + tg, n_trials);
-    auto seg_of = [&](int r) { return (static_cast<size_t>(b) * n_ranges + r) * kGroups + w; };
-    // position p of range r's segment gets code c (and, for an occurrence,
-    // its position `at` in the trial); the state before it is trial `start`
-    auto put = [&](int r, int64_t p, uint16_t c, int start, uint16_t at) {
-        const size_t si = seg_of(r);
-        const int run = seg_run[si];
-        const int lj = static_cast<int>(p / run);
-        const int s = static_cast<int>(p - static_cast<int64_t>(lj) * run);
-        const int64_t slot = code_slot(seg_base[si], s, lj);
-        code[slot] = c;
-        if (pos) pos[slot] = at;
-        if (s == 0) lane_start[si * kWave + lj] = static_cast<uint8_t>(start);
-    };
-    unsigned long long ev = 0;
-    for (int w0 = 0; w0 < n_ranges; w0 += kRangeWindow) {
-        const int wn = min(kRangeWindow, n_ranges - w0);
-        for (int r = lane; r < wn; r += kWave) {
-            cur[r] = 0;
-            last[r] = -1;
+// How the codes are made: a scattered store per code leaves every segment's
+// lines open from the first trial of a group to its last (2 GB of lines at
+// 1M x 1000: each 2-byte store became its own memory write), so nothing is
+// scattered to memory here.  k_prep_part sorts chunks of kChunk occurrences
+// of one trial group by range inside LDS (stably) and writes them back as
+// (trial, offset) records in runs; k_prep_sizes counts each segment's codes
+// from the runs' summaries; a scan gives the segments' bases; k_prep_emit
+// gathers one segment's runs, forms its codes in LDS in their final places
+// and writes the segment as whole lines.  Bound by the bytes moved (IDs,
+// records written and read, codes) and by the ballots of the sort; at 1M x
+// 1000 the two passes that scattered took 4.2 + 20.4 ms, these take 5.1 + 2.8.
+constexpr int kPartThreads = 512;
+constexpr int kPartWaves = kPartThreads / kWave;
+constexpr int kPartItems = kChunk / kPartThreads;   // slices of 64 occurrences per wavefront, at most
+constexpr int kPartWin = 256;                       // ranges sorted at once
+constexpr int kEmitThreads = 256;
+constexpr int kEmitWaves = kEmitThreads / kWave;
+
+// Words of the `misc` block of a prepared YET.
+enum { kMiscErr = 0, kMiscMaxOcc = 1, kMiscLong = 3, kMiscCodes = 4, kMiscMaxLen = 5, kMiscBadOff = 6 };
+
+// The chunks of trial group g, whose occurrences start at o0: chunk c of the
+// group holds occurrences [o0 + c kChunk, ...) and has index
+// chunk_base(g, o0) + c: a closed form that leaves every group room.
+__device__ __forceinline__ int64_t chunk_base(int64_t g, int64_t o0) { return o0 / kChunk + 2 * g; }
+
+// Offsets never decrease (with offsets[0] = 0 and offsets[n] = the number of
+// IDs, checked on the host, every trial then lies inside the IDs: the
+// kernels after this one read nothing when the check failed).  Also the
+// longest trial.
+__global__ __launch_bounds__(256) void k_prep_check(const int64_t *__restrict__ off, int64_t n_trials,
+                                                    int64_t *__restrict__ misc, int64_t max_len) {
+    int64_t longest = 0;
+    bool bad = false;
+    for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < n_trials;
+         t += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        const int64_t len = off[t + 1] - off[t];
+        bad = bad || len < 0;
+        longest = max(longest, len);
+    }
+    __shared__ int64_t red[4];
+    for (int o = 32; o > 0; o >>= 1) longest = max(longest, static_cast<int64_t>(__shfl_xor(longest, o)));
+    const bool any_bad = __any(bad);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = any_bad ? -1 : longest;
+    __syncthreads();
+    if (threadIdx.x != 0) return;   // one set of atomics per workgroup
+    longest = max(max(red[0], red[1]), max(red[2], red[3]));
+    if (min(min(red[0], red[1]), min(red[2], red[3])) < 0) {
+        atomicCAS(reinterpret_cast<int32_t *>(misc + kMiscErr), 0, ARA_E_RANGE);
+        atomicOr(reinterpret_cast<int32_t *>(misc + kMiscBadOff), 1);
+    }
+    if (longest > 0) atomicMax(reinterpret_cast<unsigned long long *>(misc + kMiscMaxLen), static_cast<unsigned long long>(longest));
+    if (longest > max_len) atomicOr(reinterpret_cast<int32_t *>(misc + kMiscLong), 1);
+}
+
+struct PartParams {
+    const int64_t *off;
+    const int32_t *ids;
+    int64_t n_trials;
+    int32_t catalog, tg, n_ranges;
+    uint32_t *rec;      // [nnz] trial in the group << 15 | offset in the range, sorted by range within each chunk
+    uint16_t *rpos;     // [nnz] their positions in the trial, or null
+    uint16_t *rstart;   // [chunk][n_ranges + 1] where each range's records start in the chunk
+    uint32_t *rsum;     // [chunk][n_ranges] extra codes | first trial << 8 | last trial << 16 | first offset is 0x7FFF << 24
+    int64_t *misc;
+};
+
+__device__ __forceinline__ uint32_t uni32(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// One workgroup per trial group, chunk by chunk.  Each wavefront takes an
+// eighth of the chunk's occurrences, in order, in 64-wide slices held in
+// registers; an occurrence's rank among its range's in the wavefront comes
+// from ballots over the range's bits (lane order = storage order) and a
+// counter per range in LDS.
+template <bool POS>
+__global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_prep_part(PartParams P) {
+    __shared__ uint32_t srec[kChunk];
+    __shared__ uint16_t spos[POS ? kChunk : 1];
+    __shared__ uint32_t cnt[kPartWaves][kPartWin];
+    __shared__ uint32_t ext[kPartWin];
+    __shared__ uint32_t wsum[kPartWaves];
+    __shared__ int32_t soff[kMaxTrialsPerGroup + 1];   // trial starts, relative to the chunk
+    if (P.misc[kMiscBadOff] != 0) return;   // uniform: only k_prep_check writes it
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = static_cast<int>(uni32(tid >> 6));
+    const int64_t g = blockIdx.x;
+    const int64_t t0 = g * P.tg;
+    if (t0 >= P.n_trials) return;
+    const int nt = static_cast<int>(min<int64_t>(P.tg, P.n_trials - t0));
+    const int64_t o0 = P.off[t0], o1 = P.off[t0 + nt];
+    const int64_t cb = chunk_base(g, o0);
+    for (int64_t ks = o0, ch = cb; ks < o1; ks += kChunk, ++ch) {
+        const int nin = static_cast<int>(min<int64_t>(kChunk, o1 - ks));
+        const int32_t far = 1 << 30;
+        __syncthreads();   // the previous chunk's LDS is free
+        for (int i = tid; i <= nt; i += kPartThreads)
+            soff[i] = static_cast<int32_t>(max<int64_t>(-far, min<int64_t>(far, P.off[t0 + i] - ks)));
+        int32_t id[kPartItems];
+        const int ns = (nin + kPartThreads - 1) / kPartThreads;   // slices per wavefront
+        const int kw = w * ns * kWave;
+        const int32_t *src = P.ids + ks;
+#pragma unroll
+        for (int s = 0; s < kPartItems; ++s) {
+            const uint32_t k = static_cast<uint32_t>(kw + s * kWave + lane);
+            id[s] = s < ns && k < static_cast<uint32_t>(nin) ? src[k] : 0;
         }
-        __builtin_amdgcn_wave_barrier();
-        for (int64_t t = t0; t < t1; ++t) {
-            const int i = static_cast<int>(t - t0);
-            const int64_t o0 = off[t], o1 = off[t + 1];
-            if (o1 < o0 || o0 < 0) {
-                if (!SCATTER && lane == 0 && w0 == 0) atomicCAS(err, 0, ARA_E_RANGE);
-                continue;
+        __syncthreads();
+        // each occurrence's trial in the group
+        uint32_t tr[kPartItems];   // later: trial << 16 | rank in the wavefront
+        {
+            int lo = 0, hi = nt;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (static_cast<int32_t>(uni32(static_cast<uint32_t>(soff[mid]))) <= kw) lo = mid;
+                else hi = mid;
             }
-            if (!SCATTER && long_trial && lane == 0 && w0 == 0 && o1 - o0 > kMaxPositions) atomicOr(long_trial, 1);
-            for (int64_t base = o0; base < o1; base += kWave) {
-                const int64_t k = base + lane;
-                const bool in = k < o1;
-                const int32_t id = in ? ids[k] : 0;
-                const bool bad = in && (id < 0 || id >= catalog);
-                if (!SCATTER && bad && w0 == 0) atomicCAS(err, 0, ARA_E_RANGE);
-                const int r = (in && !bad) ? (id >> kRangeBits) : -1;
-                const bool active = r >= w0 && r < w0 + wn;
+            int tcur = lo;
+#pragma unroll
+            for (int s = 0; s < kPartItems; ++s) {
+                if (s >= ns) break;
+                const int k = kw + s * kWave + lane, last = kw + s * kWave + (kWave - 1);
+                uint32_t tl = static_cast<uint32_t>(tcur);
+                while (tcur + 1 < nt) {
+                    const int b = static_cast<int32_t>(uni32(static_cast<uint32_t>(soff[tcur + 1])));
+                    if (b > last) break;
+                    tl += k >= b ? 1u : 0u;
+                    ++tcur;
+                }
+                tr[s] = tl << 16;
+            }
+        }
+        uint32_t woff = 0;   // records of the ranges before this window
+        for (int w0 = 0; w0 < P.n_ranges; w0 += kPartWin) {
+            const int wn = min(kPartWin, P.n_ranges - w0);
+            int gb = 0;
+            while ((1 << gb) < wn) ++gb;
+            for (int i = tid; i < kPartWaves * kPartWin; i += kPartThreads) (&cnt[0][0])[i] = 0u;
+            if (tid < kPartWin) ext[tid] = 0u;
+            __syncthreads();
+            volatile uint32_t *mycnt = cnt[w];
+#pragma unroll
+            for (int s = 0; s < kPartItems; ++s) {
+                if (s >= ns) break;
+                const int k = kw + s * kWave + lane;
+                const bool in = k < nin;
+                const bool bad = in && (id[s] < 0 || id[s] >= P.catalog);
+                if (bad && w0 == 0) atomicCAS(reinterpret_cast<int32_t *>(P.misc + kMiscErr), 0, ARA_E_RANGE);
+                const int r = (id[s] >> kRangeBits) - w0;
+                const bool active = in && !bad && r >= 0 && r < wn;
                 uint64_t peers = __ballot(active);
-                for (int bit = 0; bit < gbits; ++bit) {
+                for (int bit = 0; bit < gb; ++bit) {
                     const bool on = (r >> bit) & 1;
-                    const uint64_t m = __ballot(active && on);
+                    const uint64_t m = __ballot(on);
                     peers &= on ? m : ~m;
                 }
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(peers >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(peers), 0u));
-                const int tot = __popcll(peers);
-                const int leader = active ? __builtin_ctzll(peers) : lane;
-                const uint16_t local = static_cast<uint16_t>(id & (kRange - 1));
-                int p_open = 0, adv_open = 0;
-                if (active && rank == 0) {
-                    const int rl = r - w0;
-                    const int L = last[rl];
-                    int gap = 0;
-                    bool adv = false;
-                    if (L >= 0 && L != i) {       // opens trial i after trial L in this segment
-                        gap = i - L - 1;
-                        adv = true;
-                        if (local == (kRange - 1)) {   // offset 0x7FFF cannot carry the flag
-                            ++gap;
-                            adv = false;
-                        }
-                    }
-                    const int p0 = cur[rl];
-                    if (SCATTER)
-                        for (int q = 0; q < gap; ++q) put(r, p0 + q, kSkip, L + q, kSkip);   // each advances one trial
-                    cur[rl] = p0 + gap + tot;
-                    last[rl] = static_cast<int16_t>(i);
-                    p_open = p0 + gap;
-                    adv_open = adv ? 1 : 0;
-                }
-                if (!SCATTER) ev += active ? 1u : 0u;
-                p_open = __shfl(p_open, leader);
-                adv_open = __shfl(adv_open, leader);
-                if (SCATTER && active) {
-                    const int a = (rank == 0) ? adv_open : 0;
-                    put(r, p_open + static_cast<int>(rank), static_cast<uint16_t>((a ? kAdvance : 0) | local), i - a,
-                        static_cast<uint16_t>(k - o0));
-                }
-                __builtin_amdgcn_wave_barrier();
+                const uint32_t rank = lanes_below(peers);
+                uint32_t before = 0;
+                if (active) before = mycnt[r];
+                wave_fence();
+                if (active && rank == 0) mycnt[r] = before + static_cast<uint32_t>(__popcll(peers));
+                wave_fence();
+                tr[s] = (tr[s] & 0xFFFF0000u) | (before + rank);
             }
+            __syncthreads();
+            // where each (range, wavefront) starts (thread i < 256: range i)
+            uint32_t c[kPartWaves], tot = 0;
+#pragma unroll
+            for (int v = 0; v < kPartWaves; ++v) {
+                c[v] = tid < kPartWin ? cnt[v][tid] : 0u;
+                tot += c[v];
+            }
+            uint32_t incl = tot;
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t x = __shfl_up(incl, o);
+                if (lane >= o) incl += x;
+            }
+            if (lane == kWave - 1) wsum[w] = incl;
+            __syncthreads();
+            uint32_t start = woff + incl - tot, all = 0;
+            for (int v = 0; v < kPartWaves; ++v) {
+                start += v < w ? wsum[v] : 0u;
+                all += wsum[v];
+            }
+            uint32_t at = start;
+            if (tid < kPartWin) {
+#pragma unroll
+                for (int v = 0; v < kPartWaves; ++v) {
+                    cnt[v][tid] = at;
+                    at += c[v];
+                }
+            }
+            if (tid < wn) P.rstart[ch * (P.n_ranges + 1) + w0 + tid] = static_cast<uint16_t>(start);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < kPartItems; ++s) {
+                if (s >= ns) break;
+                const int k = kw + s * kWave + lane;
+                const int r = (id[s] >> kRangeBits) - w0;
+                if (k < nin && id[s] >= 0 && id[s] < P.catalog && r >= 0 && r < wn) {
+                    const uint32_t p = cnt[w][r] + (tr[s] & 0xFFFFu);
+                    const uint32_t tl = tr[s] >> 16;
+                    srec[p] = (static_cast<uint32_t>(r) << 23) | (tl << kRangeBits) | static_cast<uint32_t>(id[s] & (kRange - 1));
+                    if (POS) spos[p] = static_cast<uint16_t>(k - soff[tl]);
+                }
+            }
+            __syncthreads();
+            // the records out, and the codes a change of trial needs beside the event's own
+            for (uint32_t i = woff + tid; i < woff + all; i += kPartThreads) {
+                const uint32_t e = srec[i];
+                if (i > woff) {
+                    const uint32_t q = srec[i - 1];
+                    const uint32_t te = (e >> kRangeBits) & 255u, tq = (q >> kRangeBits) & 255u;
+                    if ((e >> 23) == (q >> 23) && te != tq) {
+                        const uint32_t x = te - tq - 1u + ((e & (kRange - 1)) == kRange - 1 ? 1u : 0u);
+                        if (x) atomicAdd(&ext[e >> 23], x);
+                    }
+                }
+                P.rec[ks + i] = e & 0x7FFFFFu;
+                if (POS) P.rpos[ks + i] = spos[i];
+            }
+            __syncthreads();
+            if (tid < wn) {
+                uint32_t sum = 0;
+                if (tot) {
+                    const uint32_t f = srec[start], l = srec[start + tot - 1];
+                    sum = ext[tid] | (((f >> kRangeBits) & 255u) << 8) | (((l >> kRangeBits) & 255u) << 16) |
+                          ((f & (kRange - 1)) == kRange - 1 ? 1u << 24 : 0u);
+                }
+                P.rsum[ch * P.n_ranges + w0 + tid] = sum;
+            }
+            woff += all;
+            __syncthreads();
         }
-        if (!SCATTER)
-            for (int r = lane; r < wn; r += kWave) seg_codes[seg_of(w0 + r)] = cur[r];
-        __builtin_amdgcn_wave_barrier();
+        if (tid == 0) P.rstart[ch * (P.n_ranges + 1) + P.n_ranges] = static_cast<uint16_t>(woff);
     }
-    if (!SCATTER) {
-        for (int o = 32; o > 0; o >>= 1) ev += __shfl_down(ev, o);
-        if (lane == 0 && ev) atomicAdd(events, ev);
+}
+
+// Codes per lane of every segment: its events, the gap codes inside its runs
+// and those between one run's last trial and the next run's first.
+__global__ __launch_bounds__(256) void k_prep_sizes(PartParams P, int n_groups, int32_t *__restrict__ seg_run) {
+    if (P.misc[kMiscBadOff] != 0) return;
+    const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    if (i >= static_cast<int64_t>(n_groups) * P.n_ranges) return;
+    const int64_t g = i / P.n_ranges;
+    const int r = static_cast<int>(i - g * P.n_ranges);
+    int64_t codes = 0;
+    const int64_t t0 = g * P.tg;
+    if (t0 < P.n_trials) {
+        const int64_t o0 = P.off[t0], o1 = P.off[min<int64_t>(t0 + P.tg, P.n_trials)];
+        int last = -1;
+        for (int64_t ks = o0, ch = chunk_base(g, o0); ks < o1; ks += kChunk, ++ch) {
+            const uint16_t *rs = P.rstart + ch * (P.n_ranges + 1) + r;
+            const int n = static_cast<int>(rs[1]) - static_cast<int>(rs[0]);
+            if (n <= 0) continue;
+            const uint32_t m = P.rsum[ch * P.n_ranges + r];
+            const int first = static_cast<int>((m >> 8) & 255u);
+            codes += n + static_cast<int>(m & 255u);
+            if (last >= 0 && first != last) codes += first - last - 1 + static_cast<int>((m >> 24) & 1u);
+            last = static_cast<int>((m >> 16) & 255u);
+        }
+    }
+    if (codes > (int64_t(1) << 31) - 512) {   // codes of a segment are counted in 32 bits
+        atomicCAS(reinterpret_cast<int32_t *>(P.misc + kMiscErr), 0, ARA_E_LIMIT);
+        codes = 0;
+    }
+    const int64_t b = g / kGroups;
+    seg_run[(b * P.n_ranges + r) * kGroups + g % kGroups] = static_cast<int32_t>(((codes + kWave - 1) / kWave + 3) & ~int64_t(3));
+}
+
+// Exclusive scan of 64 * seg_run into seg_base: workgroup sums, the scan of
+// the sums by one workgroup (which also leaves the total), then each
+// workgroup's own scan on top.
+constexpr int kScanPer = 4;
+constexpr int kScanBlock = 1024 * kScanPer;
+
+__device__ __forceinline__ int64_t scan1024_i64(int64_t v, int64_t *wsum, int64_t *total) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int64_t incl = v;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+    }
+    if (lane == kWave - 1) wsum[w] = incl;
+    __syncthreads();
+    int64_t before = 0, tot = 0;
+    for (int i = 0; i < 16; ++i) {
+        const int64_t c = wsum[i];
+        before += i < w ? c : 0;
+        tot += c;
+    }
+    *total = tot;
+    __syncthreads();
+    return before + incl - v;
+}
+
+__global__ __launch_bounds__(1024) void k_scan_sums(const int32_t *__restrict__ seg_run, int64_t n, int64_t *__restrict__ bsum) {
+    __shared__ int64_t wsum[16];
+    int64_t v = 0, tot = 0;
+    for (int q = 0; q < kScanPer; ++q) {
+        const int64_t i = blockIdx.x * static_cast<int64_t>(kScanBlock) + threadIdx.x * kScanPer + q;
+        if (i < n) v += seg_run[i];
+    }
+    scan1024_i64(v, wsum, &tot);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = tot * kWave;
+}
+
+// bsum[0..n) becomes its exclusive scan; *total gets the sum.
+__global__ __launch_bounds__(1024) void k_scan_top(int64_t *__restrict__ bsum, int64_t n, int64_t *__restrict__ total) {
+    __shared__ int64_t wsum[16];
+    int64_t run = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += 1024) {
+        const int64_t i = i0 + threadIdx.x;
+        const int64_t v = i < n ? bsum[i] : 0;
+        int64_t tot = 0;
+        const int64_t ex = scan1024_i64(v, wsum, &tot);
+        if (i < n) bsum[i] = run + ex;
+        run += tot;
+    }
+    if (threadIdx.x == 0) *total = run;
+}
+
+__global__ __launch_bounds__(1024) void k_scan_bases(const int32_t *__restrict__ seg_run, int64_t n,
+                                                     const int64_t *__restrict__ bsum, int64_t *__restrict__ seg_base) {
+    __shared__ int64_t wsum[16];
+    int64_t c[kScanPer], v = 0, tot = 0;
+    const int64_t i0 = blockIdx.x * static_cast<int64_t>(kScanBlock) + threadIdx.x * kScanPer;
+    for (int q = 0; q < kScanPer; ++q) {
+        c[q] = i0 + q < n ? static_cast<int64_t>(seg_run[i0 + q]) * kWave : 0;
+        v += c[q];
+    }
+    int64_t at = bsum[blockIdx.x] + scan1024_i64(v, wsum, &tot);
+    for (int q = 0; q < kScanPer; ++q) {
+        if (i0 + q < n) seg_base[i0 + q] = at;
+        at += c[q];
+    }
+}
+
+struct EmitParams {
+    PartParams part;
+    int32_t n_groups;
+    const int64_t *seg_base;
+    const int32_t *seg_run;
+    uint16_t *code, *pos;
+    uint8_t *lane_start;
+};
+
+// One wavefront per segment: the segment's runs in chunk order, each record
+// preceded by its gap codes, into LDS at the codes' final places, then out as
+// whole lines (padding included).  A segment of more than CAP codes per lane
+// is written to memory directly (CAP is chosen above the mean, so these are
+// segments of crowded ranges).  The last workgroup writes the skip codes
+// after the last code.
+template <int CAP, bool POS>
+__global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
+    __shared__ __align__(16) uint16_t scode_all[kEmitWaves][CAP * kWave];
+    __shared__ __align__(16) uint16_t spos_all[POS ? kEmitWaves : 1][POS ? CAP * kWave : 8];
+    __shared__ __align__(16) uint8_t sstart_all[kEmitWaves][kWave];
+    const int32_t *err = reinterpret_cast<const int32_t *>(P.part.misc + kMiscErr);
+    if (*err != 0) return;
+    const int lane = threadIdx.x & 63;
+    const int w = static_cast<int>(uni32(threadIdx.x >> 6));
+    const int nr = P.part.n_ranges;
+    if (blockIdx.x == gridDim.x - 1) {
+        const int64_t total = P.part.misc[kMiscCodes];
+        for (int i = threadIdx.x; i < kPadCodes; i += kEmitThreads) {
+            P.code[total + i] = kSkip;
+            if (POS) P.pos[total + i] = kSkip;
+        }
+        return;
+    }
+    const int64_t idx = blockIdx.x * static_cast<int64_t>(kEmitWaves) + w;
+    if (idx >= static_cast<int64_t>(P.n_groups) * nr) return;   // no barriers below
+    const int64_t g = idx / nr;
+    const int r = static_cast<int>(idx - g * nr);
+    const size_t si = (static_cast<size_t>(g / kGroups) * nr + r) * kGroups + static_cast<size_t>(g % kGroups);
+    const int R = static_cast<int>(uni32(static_cast<uint32_t>(P.seg_run[si])));
+    const int64_t base = P.seg_base[si];
+    uint8_t *ls = P.lane_start + si * kWave;
+    if (R == 0) {
+        ls[lane] = 0;
+        return;
+    }
+    const bool staged = R <= CAP;
+    uint16_t *sc = scode_all[w], *sp = spos_all[POS ? w : 0];
+    uint8_t *ss = sstart_all[w];
+    const uint4 ff = make_uint4(~0u, ~0u, ~0u, ~0u);
+    uint4 *gcode = reinterpret_cast<uint4 *>(P.code + base), *gpos = reinterpret_cast<uint4 *>(POS ? P.pos + base : nullptr);
+    if (staged) {
+        ss[lane] = 0;
+        for (int i = lane; i < 8 * R; i += kWave) {
+            reinterpret_cast<uint4 *>(sc)[i] = ff;
+            if (POS) reinterpret_cast<uint4 *>(sp)[i] = ff;
+        }
+        wave_fence();
+    } else {
+        ls[lane] = 0;
+        for (int i = lane; i < 8 * R; i += kWave) {
+            gcode[i] = ff;
+            if (POS) gpos[i] = ff;
+        }
+        __threadfence();   // before this wavefront's own stores to the same lines
+    }
+    const float inv = 1.0f / static_cast<float>(R);
+    // place q of the segment's stream: lane q / R, step q % R
+    auto put = [&](int64_t q, bool event, uint16_t c, uint32_t start, uint16_t at) {
+        int lj, s;
+        if (staged) {   // q < 64 CAP: the binary32 quotient is within one of the true one
+            lj = static_cast<int>(static_cast<float>(static_cast<int>(q)) * inv);
+            s = static_cast<int>(q) - lj * R;
+            if (s < 0) {
+                --lj;
+                s += R;
+            } else if (s >= R) {
+                ++lj;
+                s -= R;
+            }
+        } else {
+            lj = static_cast<int>(q / R);
+            s = static_cast<int>(q - static_cast<int64_t>(lj) * R);
+        }
+        const int slot = (s >> 2) * (4 * kWave) + 4 * lj + (s & 3);
+        if (staged) {
+            if (event) {
+                sc[slot] = c;
+                if (POS) sp[slot] = at;
+            }
+            if (s == 0) ss[lj] = static_cast<uint8_t>(start);
+        } else {
+            if (event) {
+                P.code[base + slot] = c;
+                if (POS) P.pos[base + slot] = at;
+            }
+            if (s == 0) ls[lj] = static_cast<uint8_t>(start);
+        }
+    };
+    const int64_t t0 = g * P.part.tg;
+    const int64_t o0 = P.part.off[t0], o1 = P.part.off[min<int64_t>(t0 + P.part.tg, P.part.n_trials)];
+    const int64_t cb = chunk_base(g, o0);
+    const int64_t nch = (o1 - o0 + kChunk - 1) / kChunk;
+    int64_t p = 0;        // codes placed (uniform)
+    int prev = -1;        // trial of the last record (uniform)
+    for (int64_t c0 = 0; c0 < nch; c0 += kWave) {
+        // the run bounds of up to 64 chunks, one per lane
+        uint32_t ra = 0, rb = 0;
+        if (c0 + lane < nch) {
+            const uint16_t *rs = P.part.rstart + (cb + c0 + lane) * (nr + 1) + r;
+            ra = rs[0];
+            rb = rs[1];
+        }
+        const int nc = static_cast<int>(min<int64_t>(kWave, nch - c0));
+        // the runs in steps of up to 64 records, the next step's loads in
+        // flight while one is placed
+        int c = -1, i = 0, end = 0;   // uniform: the run being read
+        uint32_t e = 0, e_nxt = 0;
+        uint16_t at = 0, at_nxt = 0;
+        auto fetch = [&]() -> int {   // records of the next step (0: none left)
+            while (i >= end) {
+                if (++c >= nc) return 0;
+                i = static_cast<int>(__builtin_amdgcn_readlane(ra, c));
+                end = static_cast<int>(__builtin_amdgcn_readlane(rb, c));
+            }
+            const int n = min(kWave, end - i);
+            const int64_t k = o0 + (c0 + c) * kChunk + i;
+            if (lane < n) {
+                e_nxt = P.part.rec[k + lane];
+                if (POS) at_nxt = P.part.rpos[k + lane];
+            }
+            i += n;
+            return n;
+        };
+        int n_nxt = fetch();
+        while (n_nxt > 0) {
+            const int n_in = n_nxt;
+            e = e_nxt;
+            at = at_nxt;
+            n_nxt = fetch();
+            const bool in = lane < n_in;
+            const int t = static_cast<int>(e >> kRangeBits);
+            const uint32_t local = e & (kRange - 1);
+            int tp = __shfl_up(t, 1);
+            if (lane == 0) tp = prev;
+            const bool opens = in && tp >= 0 && t != tp;
+            int gap = opens ? t - tp - 1 : 0;
+            bool adv = opens;
+            if (opens && local == kRange - 1) {   // offset 0x7FFF cannot carry the flag
+                ++gap;
+                adv = false;
+            }
+            int64_t q = p + lane;
+            int total = n_in;
+            if (__ballot(gap > 0) != 0) {
+                int incl = in ? 1 + gap : 0;
+                for (int o = 1; o < kWave; o <<= 1) {
+                    const int x = __shfl_up(incl, o);
+                    if (lane >= o) incl += x;
+                }
+                total = __shfl(incl, kWave - 1);
+                q = p + incl - 1;
+                for (int z = 0; z < gap; ++z) put(q - gap + z, false, kSkip, static_cast<uint32_t>(tp + z), kSkip);
+            }
+            if (in)
+                put(q, true, static_cast<uint16_t>((adv ? kAdvance : 0) | local), static_cast<uint32_t>(t - (adv ? 1 : 0)), at);
+            p += total;
+            prev = __builtin_amdgcn_readlane(t, n_in - 1);
+        }
+    }
+    if (staged) {
+        wave_fence();
+        ls[lane] = ss[lane];
+        for (int i = lane; i < 8 * R; i += kWave) {
+            gcode[i] = reinterpret_cast<const uint4 *>(sc)[i];
+            if (POS) gpos[i] = reinterpret_cast<const uint4 *>(sp)[i];
+        }
     }
 }
 
@@ -395,43 +830,18 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     if (buf_bytes < prepare_bytes(g, n_trials, nnz, catalog, flags)) return fail(ARA_E_NOSPACE, "ara_yet_prepare: buffer too small");
 
     Carver c(buf);
-    uint16_t *code = c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
-    int64_t *seg_base = c.take<int64_t>(g.nseg);
-    int32_t *seg_run = c.take<int32_t>(g.nseg);
-    uint8_t *lane_start = c.take<uint8_t>(g.nseg * kWave);
-    int64_t *misc = c.take<int64_t>(32);   // [0] error (int32), [1] max occurrences (int32), [2] events
-    int32_t *err = reinterpret_cast<int32_t *>(misc);
-    int32_t *max_occ = reinterpret_cast<int32_t *>(misc + 1);
-    unsigned long long *events = reinterpret_cast<unsigned long long *>(misc + 2);
-    const bool transposed = (flags & ARA_PREP_TRANSPOSED) != 0;
-    int64_t *tr_off = nullptr, *rtot = nullptr;
-    uint32_t *tr_ent = nullptr;
-    if (transposed) {
-        tr_off = c.take<int64_t>(static_cast<size_t>(kSlices) * catalog + 1);
-        tr_ent = c.take<uint32_t>(static_cast<size_t>(std::max<int64_t>(nnz, 1)));
-        rtot = c.take<int64_t>(static_cast<size_t>(kSlices) * g.n_ranges);
-    }
-    int64_t *t_off = nullptr;
-    int32_t *t_ids = nullptr, *t_cnt = nullptr;
+    const Prepared p = carve(c, g, n_trials, nnz, catalog, flags);
+    int32_t *max_occ = reinterpret_cast<int32_t *>(p.misc + kMiscMaxOcc);
+    const bool transposed = (flags & ARA_PREP_TRANSPOSED) != 0, positions = (flags & ARA_PREP_POSITIONS) != 0;
     if (flags & ARA_PREP_TRIAL_MAJOR) {
-        t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
-        t_ids = c.take<int32_t>(static_cast<size_t>(std::max<int64_t>(nnz, 1)));
-        t_cnt = c.take<int32_t>(static_cast<size_t>(catalog));
-        ARA_HIP(hipMemsetAsync(t_cnt, 0, static_cast<size_t>(catalog) * sizeof(int32_t), st));
+        ARA_HIP(hipMemsetAsync(p.t_cnt, 0, static_cast<size_t>(catalog) * sizeof(int32_t), st));
         if (nnz > 0)
-            ARA_HIP(hipMemcpyAsync(t_ids, ids, static_cast<size_t>(nnz) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+            ARA_HIP(hipMemcpyAsync(p.t_ids, ids, static_cast<size_t>(nnz) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     }
-    const bool positions = (flags & ARA_PREP_POSITIONS) != 0;
-    uint16_t *pos = nullptr;
-    if (positions) {
-        pos = c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
-        if (!t_off) t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
-    }
-    if (t_off)
-        ARA_HIP(hipMemcpyAsync(t_off, offsets, (static_cast<size_t>(n_trials) + 1) * sizeof(int64_t),
+    if (p.t_off)
+        ARA_HIP(hipMemcpyAsync(p.t_off, offsets, (static_cast<size_t>(n_trials) + 1) * sizeof(int64_t),
                                hipMemcpyDeviceToDevice, st));
-    ARA_HIP(hipMemsetAsync(misc, 0, 32 * sizeof(int64_t), st));
-    int32_t *long_trial = positions ? reinterpret_cast<int32_t *>(misc + 3) : nullptr;
+    ARA_HIP(hipMemsetAsync(p.misc, 0, 32 * sizeof(int64_t), st));
 
     ara_yet y{};
     y.n_trials = n_trials;
@@ -443,74 +853,95 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     y.trials_per_group = g.tg;
     y.trials_per_block = g.tb;
     y.n_blocks = g.n_blocks;
-    y.code = code;
-    y.seg_base = seg_base;
-    y.seg_run = seg_run;
-    y.lane_start = lane_start;
-    y.t_off = t_off;
-    y.t_ids = t_ids;
-    y.t_cnt = t_cnt;
-    y.pos = pos;
+    y.code = p.code;
+    y.seg_base = p.seg_base;
+    y.seg_run = p.seg_run;
+    y.lane_start = p.lane_start;
+    y.t_off = p.t_off;
+    y.t_ids = p.t_ids;
+    y.t_cnt = p.t_cnt;
+    y.pos = p.pos;
     if (transposed) {
         y.n_slices = kSlices;
         y.slice_trials = static_cast<int64_t>(g.slice_blocks) * g.tb;
-        y.tr_off = tr_off;
-        y.tr_ent = tr_ent;
+        y.tr_off = p.tr_off;
+        y.tr_ent = p.tr_ent;
         // every list is empty until the counting pass has run
-        ARA_HIP(hipMemsetAsync(tr_off, 0, (static_cast<size_t>(kSlices) * catalog + 1) * sizeof(int64_t), st));
+        ARA_HIP(hipMemsetAsync(p.tr_off, 0, (static_cast<size_t>(kSlices) * catalog + 1) * sizeof(int64_t), st));
     }
     if (g.n_blocks == 0) {
         ARA_HIP(hipStreamSynchronize(st));
         *out = y;
         return ARA_OK;
     }
-    // pass 1: codes per segment (into seg_run for now)
-    k_prep_codes<false><<<g.n_blocks, 1024, 0, st>>>(offsets, ids, n_trials, catalog, g.tg, g.tb, g.n_ranges,
-                                                     g.gbits, seg_run, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                     err, long_trial, events);
+    // the codes: sort by range, count, place
+    PartParams P{};
+    P.off = offsets;
+    P.ids = ids;
+    P.n_trials = n_trials;
+    P.catalog = catalog;
+    P.tg = g.tg;
+    P.n_ranges = g.n_ranges;
+    P.rec = p.rec;
+    P.rpos = p.rpos;
+    P.rstart = p.rstart;
+    P.rsum = p.rsum;
+    P.misc = p.misc;
+    const int64_t ng = n_groups_of(g, n_trials);
+    const int n_groups = g.n_blocks * kGroups;   // the last block's empty groups have segments too
+    k_prep_check<<<static_cast<unsigned>(std::min<int64_t>((n_trials + 255) / 256, 512)), 256, 0, st>>>(
+        offsets, n_trials, p.misc, positions ? kMaxPositions : INT64_MAX);
+    if (positions) k_prep_part<true><<<static_cast<unsigned>(ng), kPartThreads, 0, st>>>(P);
+    else k_prep_part<false><<<static_cast<unsigned>(ng), kPartThreads, 0, st>>>(P);
+    const int64_t n_segs = static_cast<int64_t>(g.nseg);
+    k_prep_sizes<<<static_cast<unsigned>((n_segs + 255) / 256), 256, 0, st>>>(P, n_groups, p.seg_run);
+    const int64_t n_scan = (n_segs + kScanBlock - 1) / kScanBlock;
+    k_scan_sums<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, p.bsum);
+    k_scan_top<<<1, 1024, 0, st>>>(p.bsum, n_scan, p.misc + kMiscCodes);
+    k_scan_bases<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, p.bsum, p.seg_base);
     ARA_HIP(hipGetLastError());
-    std::vector<int32_t> cnt(g.nseg);
-    int64_t head[4] = {0, 0, 0, 0};
-    ARA_HIP(hipMemcpyAsync(head, misc, sizeof(head), hipMemcpyDeviceToHost, st));
-    ARA_HIP(hipMemcpyAsync(cnt.data(), seg_run, g.nseg * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    int64_t head[8] = {};
+    ARA_HIP(hipMemcpyAsync(head, p.misc, sizeof(head), hipMemcpyDeviceToHost, st));
     ARA_HIP(hipStreamSynchronize(st));
-    const int32_t err_h = static_cast<int32_t>(head[0] & 0xffffffff);
+    const int32_t err_h = static_cast<int32_t>(head[kMiscErr] & 0xffffffff);
+    if (err_h == ARA_E_LIMIT) return fail(err_h, "ara_yet_prepare: 2^31 or more codes in one segment");
     if (err_h) return fail(err_h, "ara_yet_prepare: an event ID lies outside [0, catalog) or offsets decrease");
-    if (head[2] != nnz) return fail(ARA_E_RANGE, "ara_yet_prepare: offsets do not cover the IDs consistently");
-    if (head[3] != 0) return fail(ARA_E_LIMIT, "ara_yet_prepare: a trial holds more than 65536 occurrences (positions)");
-
-    std::vector<int64_t> base(g.nseg);
-    std::vector<int32_t> run(g.nseg);
-    int64_t total = 0;
-    for (size_t i = 0; i < g.nseg; ++i) {
-        run[i] = ((cnt[i] + kWave - 1) / kWave + 3) & ~3;   // codes per lane, a multiple of 4
-        base[i] = total;
-        total += static_cast<int64_t>(run[i]) * kWave;
-    }
+    if (head[kMiscLong] != 0)
+        return fail(ARA_E_LIMIT, "ara_yet_prepare: a trial holds more than 65536 occurrences (positions)");
+    const int64_t total = head[kMiscCodes];
     if (total > max_codes(g, nnz)) return fail(ARA_E_LIMIT, "ara_yet_prepare: code bound exceeded");
-    ARA_HIP(hipMemcpyAsync(seg_base, base.data(), g.nseg * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    ARA_HIP(hipMemcpyAsync(seg_run, run.data(), g.nseg * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    // padding, and the block of skip codes after the last code
-    ARA_HIP(hipMemsetAsync(code, 0xFF, static_cast<size_t>(total + kPadCodes) * sizeof(uint16_t), st));
-    if (pos) ARA_HIP(hipMemsetAsync(pos, 0xFF, static_cast<size_t>(total + kPadCodes) * sizeof(uint16_t), st));
-    ARA_HIP(hipMemsetAsync(lane_start, 0, g.nseg * kWave, st));
-    // pass 2: the codes themselves
-    k_prep_codes<true><<<g.n_blocks, 1024, 0, st>>>(offsets, ids, n_trials, catalog, g.tg, g.tb, g.n_ranges,
-                                                    g.gbits, nullptr, seg_base, seg_run, code, lane_start, pos, err,
-                                                    nullptr, nullptr);
+    EmitParams M{};
+    M.part = P;
+    M.n_groups = n_groups;
+    M.seg_base = p.seg_base;
+    M.seg_run = p.seg_run;
+    M.code = p.code;
+    M.pos = p.pos;
+    M.lane_start = p.lane_start;
+    // codes per lane staged in LDS: 48 leaves room for five workgroups on a
+    // CU and holds the segments of up to 40 codes per lane on average; 128
+    // (16 KB a wavefront) those of the densest groups
+    const bool small = static_cast<double>(nnz) <= 40.0 * kWave * static_cast<double>(ng) * g.n_ranges;
+    const unsigned ge = static_cast<unsigned>((n_segs + kEmitWaves - 1) / kEmitWaves + 1);
+    if (positions) {
+        if (small) k_prep_emit<48, true><<<ge, kEmitThreads, 0, st>>>(M);
+        else k_prep_emit<128, true><<<ge, kEmitThreads, 0, st>>>(M);
+    } else {
+        if (small) k_prep_emit<48, false><<<ge, kEmitThreads, 0, st>>>(M);
+        else k_prep_emit<128, false><<<ge, kEmitThreads, 0, st>>>(M);
+    }
     ARA_HIP(hipGetLastError());
-    ARA_HIP(hipStreamSynchronize(st));   // the host copies of base and run live in this scope
-    k_prep_max_occ<<<g.n_ranges, 1024, 0, st>>>(code, seg_base, seg_run, g.n_blocks, g.n_ranges, max_occ, catalog,
-                                                t_cnt);
+    k_prep_max_occ<<<g.n_ranges, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, g.n_blocks, g.n_ranges, max_occ, catalog,
+                                                p.t_cnt);
     ARA_HIP(hipGetLastError());
     if (transposed) {
         const dim3 grid(static_cast<unsigned>(g.n_ranges), kSlices);
-        k_tr_count<<<grid, 1024, 0, st>>>(code, seg_base, seg_run, g.n_blocks, g.n_ranges, g.slice_blocks, catalog,
-                                          tr_off, rtot);
+        k_tr_count<<<grid, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, g.n_blocks, g.n_ranges, g.slice_blocks, catalog,
+                                          p.tr_off, p.rtot);
         ARA_HIP(hipGetLastError());
         const size_t nreg = static_cast<size_t>(kSlices) * g.n_ranges;
         std::vector<int64_t> tot(nreg);
-        ARA_HIP(hipMemcpyAsync(tot.data(), rtot, nreg * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        ARA_HIP(hipMemcpyAsync(tot.data(), p.rtot, nreg * sizeof(int64_t), hipMemcpyDeviceToHost, st));
         ARA_HIP(hipStreamSynchronize(st));
         int64_t acc = 0;
         for (size_t i = 0; i < nreg; ++i) {   // regions in (slice, range) order = list order
@@ -521,12 +952,12 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
             acc += t;
         }
         if (acc != nnz) return fail(ARA_E_RANGE, "ara_yet_prepare: event-major copy lost occurrences");
-        ARA_HIP(hipMemcpyAsync(rtot, tot.data(), nreg * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        ARA_HIP(hipMemcpyAsync(tr_off + static_cast<size_t>(kSlices) * catalog, &acc, sizeof(int64_t),
+        ARA_HIP(hipMemcpyAsync(p.rtot, tot.data(), nreg * sizeof(int64_t), hipMemcpyHostToDevice, st));
+        ARA_HIP(hipMemcpyAsync(p.tr_off + static_cast<size_t>(kSlices) * catalog, &acc, sizeof(int64_t),
                                hipMemcpyHostToDevice, st));
         ARA_HIP(hipStreamSynchronize(st));   // the host sources live in this scope
-        k_tr_scatter<<<grid, 1024, 0, st>>>(code, seg_base, seg_run, lane_start, g.n_blocks, g.n_ranges, g.tg, g.tb,
-                                            g.slice_blocks, catalog, rtot, tr_off, tr_ent);
+        k_tr_scatter<<<grid, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, p.lane_start, g.n_blocks, g.n_ranges, g.tg, g.tb,
+                                            g.slice_blocks, catalog, p.rtot, p.tr_off, p.tr_ent);
         ARA_HIP(hipGetLastError());
     }
     int32_t mo = 0;

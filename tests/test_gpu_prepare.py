@@ -194,3 +194,36 @@ def test_forward_only_prepare_and_backward_refusal(ara):
     cot = torch.ones((1,) + tuple(ylt.shape), dtype=torch.float64, device="cuda")
     with pytest.raises(ara.AraError, match="TRANSPOSED"):
         ara.ylt_backward(tables, yet, layers, et, lt, s_pre, cot)
+
+
+@pytest.mark.parametrize("lens", [(8191, 8192, 8193), (20_000, 1, 0, 3000), (70_000,)])
+def test_trials_beyond_one_sorted_chunk(ara, lens):
+    """Trials around and beyond the 8192 occurrences sorted at once, among
+    short ones, crowded into one range (segments beyond the codes staged in
+    LDS: 48 and 128 per lane) and spread over several.  The longest trial
+    exceeds the positions' limit of 65536, so it is checked without them."""
+    g = np.random.default_rng(sum(lens))
+    for crowd in (True, False):
+        trials = []
+        for k in range(400):
+            n = lens[(k // 20) % len(lens)] if k % 20 == 0 else int(g.integers(0, 30))
+            hi = 3000 if crowd and n > 1000 else 200_000
+            trials.append(g.integers(0, hi, size=n))
+        off = np.zeros(len(trials) + 1, np.int64)
+        np.cumsum([len(x) for x in trials], out=off[1:])
+        yet_np = synth.Yet(200_000, off, np.concatenate(trials).astype(np.int32))
+        if max(lens) <= 65536:
+            check(ara, yet_np)
+        else:
+            with pytest.raises(ara.AraError) as ex:
+                ara.PreparedYet.from_numpy(yet_np, "cuda", positions=True)
+            assert ex.value.status == 6
+            check_codes(ara.PreparedYet.from_numpy(yet_np, "cuda"), yet_np)
+
+
+def test_decreasing_offsets_are_refused(ara):
+    off = np.arange(0, 5001, 5, dtype=np.int64)
+    off[400], off[401] = off[401], off[400]
+    with pytest.raises(ara.AraError) as ex:
+        ara.PreparedYet.from_numpy(synth.Yet(1000, off, np.zeros(5000, np.int32)), "cuda")
+    assert ex.value.status == 2
