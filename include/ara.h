@@ -122,7 +122,7 @@ typedef struct ara_yet {
     uint8_t  *lane_start;        /* device [n_blocks][n_ranges][groups][64]: each lane's first trial */
     /* event-major copy (ARA_PREP_TRANSPOSED; n_slices = 0 and NULL otherwise) */
     int32_t   n_slices;          /* 8 */
-    int32_t   reserved;
+    int32_t   reserved;          /* 1: the buffer also holds the trials' blocks ordered by event (library use) */
     int64_t   slice_trials;      /* a multiple of trials_per_block */
     int64_t  *tr_off;            /* device [n_slices * catalog + 1] */
     uint32_t *tr_ent;            /* device [nnz] */
@@ -160,9 +160,9 @@ int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, ui
  *          holds the prepared YET afterwards and must outlive every use of *out.
  * Validates every ID (ARA_E_RANGE) and every offset.  SYNCHRONISES `stream`
  * (it sizes the layout from device-side counts); one-time cost.
- * ARA_E_LIMIT if one (slice, catalogue range) of the event-major copy would
- * hold 2^32 occurrences or more, or with ARA_PREP_POSITIONS if a trial holds
- * more than 65536 occurrences.
+ * ARA_E_LIMIT if one (slice, catalogue range) of the event-major copy, or
+ * 8192 consecutive trials, would hold 2^32 occurrences or more, or with
+ * ARA_PREP_POSITIONS if a trial holds more than 65536 occurrences.
  */
 int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, int64_t n_trials,
                         int32_t catalog, uint32_t flags, void *buf, size_t buf_bytes,

@@ -22,16 +22,17 @@
 // first index; 0xFFFF for gap codes and padding), so that a walk of the code
 // stream can name each occurrence by its trial-major index.  Trials then hold
 // at most 65536 occurrences.
-#include "ara_internal.h"
+#include "evblk.h"
 
 #include <algorithm>
-#include <vector>
 
 namespace ara {
 
 constexpr uint16_t kAdvance = 0x8000;
 constexpr uint16_t kSkip = 0xFFFF;
 constexpr int kChunk = 8192;         // occurrences of a trial group sorted by range at once
+constexpr int kScanPer = 4;          // segments per thread of the scan of their sizes
+constexpr int kScanBlock = 1024 * kScanPer;
 
 struct Geometry {
     int tg, tb, n_blocks, n_ranges;
@@ -68,15 +69,22 @@ struct Prepared {
     int32_t *seg_run;
     uint8_t *lane_start;
     int64_t *misc;
-    int64_t *tr_off, *rtot;
+    int64_t *tr_off, *ssum;
     uint32_t *tr_ent;
     int64_t *t_off;
     int32_t *t_ids, *t_cnt;
     uint16_t *pos;
+    // event-ordered blocks
+    uint16_t *ent;
+    uint2 *hdr;
+    uint32_t *start;
+    int64_t *ev_base;
     // scratch of the preparation
     uint32_t *rec, *rsum;
     uint16_t *rpos, *rstart;
     int64_t *bsum;
+    uint16_t *tstart;
+    uint32_t *tbase, *mark;
 };
 
 static int64_t n_groups_of(const Geometry &g, int64_t n_trials) { return (n_trials + g.tg - 1) / g.tg; }
@@ -92,7 +100,7 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     if (flags & ARA_PREP_TRANSPOSED) {
         p.tr_off = c.take<int64_t>(static_cast<size_t>(kSlices) * catalog + 1);
         p.tr_ent = c.take<uint32_t>(occ);
-        p.rtot = c.take<int64_t>(static_cast<size_t>(kSlices) * g.n_ranges);
+        p.ssum = c.take<int64_t>(ev_major_sums(catalog));
     }
     if (flags & ARA_PREP_TRIAL_MAJOR) {
         p.t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
@@ -103,13 +111,24 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
         p.pos = c.take<uint16_t>(static_cast<size_t>(max_codes(g, nnz)) + kPadCodes);
         if (!p.t_off) p.t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
     }
-    // the sorted records: in the event-major lists' place when there are any (those are written last)
+    const EvGeometry eg = ev_geometry(n_trials, nnz, catalog);
+    const size_t neb = static_cast<size_t>(eg.neb);
+    p.ent = c.take<uint16_t>(occ + kEvPad);
+    if (eg.dense) p.start = c.take<uint32_t>(neb * (static_cast<size_t>(catalog) + 1));
+    else p.hdr = c.take<uint2>(neb * static_cast<size_t>(eg.ng));
+    p.ev_base = c.take<int64_t>(neb + 1);
+    // the sorted records: in the event-major lists' place when there are any
+    // (those are written last); their positions in the place of the blocks'
+    // entries (written after the codes)
     p.rec = p.tr_ent ? p.tr_ent : c.take<uint32_t>(occ);
-    if (flags & ARA_PREP_POSITIONS) p.rpos = c.take<uint16_t>(occ);
+    if (flags & ARA_PREP_POSITIONS) p.rpos = p.ent;
     const size_t chunks = static_cast<size_t>(nnz / kChunk + 2 * n_groups_of(g, n_trials) + 2);
     p.rstart = c.take<uint16_t>(chunks * static_cast<size_t>(g.n_ranges + 1));
     p.rsum = c.take<uint32_t>(chunks * static_cast<size_t>(g.n_ranges));
-    p.bsum = c.take<int64_t>(g.nseg / 4096 + 1);
+    p.bsum = c.take<int64_t>(g.nseg / kScanBlock + 1);
+    p.tstart = c.take<uint16_t>(static_cast<size_t>(eg.n_chunks) * static_cast<size_t>(eg.n_tiles + 1));
+    p.tbase = c.take<uint32_t>(neb * static_cast<size_t>(eg.n_tiles + 1));
+    p.mark = c.take<uint32_t>(static_cast<size_t>(eg.n_marks));
     return p;
 }
 
@@ -117,10 +136,6 @@ static size_t prepare_bytes(const Geometry &g, int64_t n_trials, int64_t nnz, in
     Carver c(nullptr);
     carve(c, g, n_trials, nnz, catalog, flags);
     return c.bytes();
-}
-
-__device__ __forceinline__ int64_t code_slot(int64_t base, int s, int lane) {
-    return base + static_cast<int64_t>(s >> 2) * (4 * kWave) + 4 * lane + (s & 3);
 }
 
 // How the codes are made: a scattered store per code leaves every segment's
@@ -140,9 +155,6 @@ constexpr int kPartItems = kChunk / kPartThreads;   // slices of 64 occurrences 
 constexpr int kPartWin = 256;                       // ranges sorted at once
 constexpr int kEmitThreads = 256;
 constexpr int kEmitWaves = kEmitThreads / kWave;
-
-// Words of the `misc` block of a prepared YET.
-enum { kMiscErr = 0, kMiscMaxOcc = 1, kMiscLong = 3, kMiscCodes = 4, kMiscMaxLen = 5, kMiscBadOff = 6 };
 
 // The chunks of trial group g, whose occurrences start at o0: chunk c of the
 // group holds occurrences [o0 + c kChunk, ...) and has index
@@ -204,7 +216,7 @@ __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_A
 // from ballots over the range's bits (lane order = storage order) and a
 // counter per range in LDS.
 template <bool POS>
-__global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_prep_part(PartParams P) {
+__global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_prep_part(PartParams P) {
     __shared__ uint32_t srec[kChunk];
     __shared__ uint16_t spos[POS ? kChunk : 1];
     __shared__ uint32_t cnt[kPartWaves][kPartWin];
@@ -236,8 +248,8 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4,
             id[s] = s < ns && k < static_cast<uint32_t>(nin) ? src[k] : 0;
         }
         __syncthreads();
-        // each occurrence's trial in the group
-        uint32_t tr[kPartItems];   // later: trial << 16 | rank in the wavefront
+        // each occurrence's trial in the group, by way of its place in srec
+        uint32_t tr[kPartItems];   // trial << 16 | rank in the wavefront
         {
             int lo = 0, hi = nt;
             while (hi - lo > 1) {
@@ -246,9 +258,8 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4,
                 else hi = mid;
             }
             int tcur = lo;
-#pragma unroll
-            for (int s = 0; s < kPartItems; ++s) {
-                if (s >= ns) break;
+#pragma unroll 1
+            for (int s = 0; s < ns; ++s) {
                 const int k = kw + s * kWave + lane, last = kw + s * kWave + (kWave - 1);
                 uint32_t tl = static_cast<uint32_t>(tcur);
                 while (tcur + 1 < nt) {
@@ -257,8 +268,10 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4,
                     tl += k >= b ? 1u : 0u;
                     ++tcur;
                 }
-                tr[s] = tl << 16;
+                srec[k] = tl << 16;
             }
+#pragma unroll
+            for (int s = 0; s < kPartItems; ++s) tr[s] = s < ns ? srec[kw + s * kWave + lane] : 0u;
         }
         uint32_t woff = 0;   // records of the ranges before this window
         for (int w0 = 0; w0 < P.n_ranges; w0 += kPartWin) {
@@ -401,9 +414,6 @@ __global__ __launch_bounds__(256) void k_prep_sizes(PartParams P, int n_groups, 
 // Exclusive scan of 64 * seg_run into seg_base: workgroup sums, the scan of
 // the sums by one workgroup (which also leaves the total), then each
 // workgroup's own scan on top.
-constexpr int kScanPer = 4;
-constexpr int kScanBlock = 1024 * kScanPer;
-
 __device__ __forceinline__ int64_t scan1024_i64(int64_t v, int64_t *wsum, int64_t *total) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     int64_t incl = v;
@@ -645,157 +655,35 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
     }
 }
 
-// Largest number of occurrences of any single event (bounds the backward's
-// fixed-point accumulators), and on request every event's count (ev_count,
-// [catalog]).  0xFFFF never encodes an occurrence, so the counts are exact.
-__global__ __launch_bounds__(1024) void k_prep_max_occ(const uint16_t *__restrict__ code,
-                                                       const int64_t *__restrict__ seg_base,
-                                                       const int32_t *__restrict__ seg_run, int n_blocks,
-                                                       int n_ranges, int32_t *__restrict__ max_occ,
-                                                       int32_t catalog, int32_t *__restrict__ ev_count) {
-    __shared__ uint32_t hist[kRange];
-    __shared__ uint32_t red[16];
-    for (int i = threadIdx.x; i < kRange; i += blockDim.x) hist[i] = 0;
-    __syncthreads();
-    const int r = blockIdx.x;
-    for (int b = 0; b < n_blocks; ++b) {
-        for (int g = 0; g < kGroups; ++g) {
-            const size_t sidx = (static_cast<size_t>(b) * n_ranges + r) * kGroups + g;
-            const int64_t sb = seg_base[sidx];
-            const int64_t n = static_cast<int64_t>(seg_run[sidx]) * kWave;
-            for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-                const uint16_t c = code[sb + i];
-                if (c != kSkip) atomicAdd(&hist[c & (kRange - 1)], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    if (ev_count)
-        for (int i = threadIdx.x; i < kRange; i += blockDim.x) {
-            const int64_t e = static_cast<int64_t>(r) * kRange + i;
-            if (e < catalog) ev_count[e] = static_cast<int32_t>(hist[i]);
-        }
-    uint32_t m = 0;
-    for (int i = threadIdx.x; i < kRange; i += blockDim.x) m = std::max(m, hist[i]);
-    for (int o = 32; o > 0; o >>= 1) m = std::max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t mm = 0;
-        for (int i = 0; i < static_cast<int>(blockDim.x >> 6); ++i) mm = std::max(mm, red[i]);
-        atomicMax(max_occ, static_cast<int32_t>(mm));
-    }
-}
+// Marks a prepared YET whose buffer holds event-ordered blocks: their place
+// follows from the sizes and flags, like every piece's.
+constexpr int32_t kHasEvBlocks = 1;
 
-// Event-major copy, pass 1: per (catalogue range r, trial slice x) count the
-// occurrences of each event of the range in the slice's blocks; counts go to
-// tr_off[x*catalog + e] and the region's total to rtot[x*n_ranges + r].
-__global__ __launch_bounds__(1024) void k_tr_count(const uint16_t *__restrict__ code,
-                                                   const int64_t *__restrict__ seg_base,
-                                                   const int32_t *__restrict__ seg_run, int n_blocks, int n_ranges,
-                                                   int slice_blocks, int32_t catalog, int64_t *__restrict__ tr_off,
-                                                   int64_t *__restrict__ rtot) {
-    __shared__ uint32_t hist[kRange];
-    __shared__ unsigned long long red[16];
-    const int r = blockIdx.x, x = blockIdx.y, tid = threadIdx.x;
-    for (int i = tid; i < kRange; i += blockDim.x) hist[i] = 0;
-    __syncthreads();
-    const int b0 = x * slice_blocks, b1 = min(n_blocks, b0 + slice_blocks);
-    for (int b = b0; b < b1; ++b)
-        for (int g = 0; g < kGroups; ++g) {
-            const size_t sidx = (static_cast<size_t>(b) * n_ranges + r) * kGroups + g;
-            const int64_t sb = seg_base[sidx];
-            const int64_t n = static_cast<int64_t>(seg_run[sidx]) * kWave;
-            for (int64_t i = tid; i < n; i += blockDim.x) {
-                const uint16_t c = code[sb + i];
-                if (c != kSkip) atomicAdd(&hist[c & (kRange - 1)], 1u);
-            }
-        }
-    __syncthreads();
-    const int64_t e0 = static_cast<int64_t>(r) * kRange;
-    const int nloc = static_cast<int>(min<int64_t>(kRange, catalog - e0));
-    unsigned long long sum = 0;
-    for (int l = tid; l < nloc; l += blockDim.x) {
-        tr_off[static_cast<int64_t>(x) * catalog + e0 + l] = hist[l];
-        sum += hist[l];
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
-    if ((tid & 63) == 0) red[tid >> 6] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        unsigned long long t = 0;
-        for (int i = 0; i < static_cast<int>(blockDim.x >> 6); ++i) t += red[i];
-        rtot[static_cast<size_t>(x) * n_ranges + r] = static_cast<int64_t>(t);
-    }
-}
-
-// Event-major copy, pass 2: turn the region's counts into list starts (the
-// region begins at rbase[x*n_ranges + r]) and scatter each occurrence's
-// slice-local trial index into its event's list.  Wavefront g decodes the
-// segments of trial group g, each lane its own run.
-__global__ __launch_bounds__(1024) void k_tr_scatter(const uint16_t *__restrict__ code,
-                                                     const int64_t *__restrict__ seg_base,
-                                                     const int32_t *__restrict__ seg_run,
-                                                     const uint8_t *__restrict__ lane_start, int n_blocks,
-                                                     int n_ranges, int tg, int tb, int slice_blocks, int32_t catalog,
-                                                     const int64_t *__restrict__ rbase, int64_t *__restrict__ tr_off,
-                                                     uint32_t *__restrict__ tr_ent) {
-    constexpr int kPer = kRange / 1024;
-    __shared__ uint32_t cur[kRange];
-    __shared__ uint32_t wsum[16];
-    const int r = blockIdx.x, x = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t e0 = static_cast<int64_t>(r) * kRange;
-    const int nloc = static_cast<int>(min<int64_t>(kRange, catalog - e0));
-    const int64_t rb = rbase[static_cast<size_t>(x) * n_ranges + r];
-    int64_t *off = tr_off + static_cast<int64_t>(x) * catalog + e0;
-    uint32_t c[kPer];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int l = tid * kPer + k;
-        c[k] = l < nloc ? static_cast<uint32_t>(off[l]) : 0u;
-        s += c[k];
-    }
-    // exclusive scan of the per-thread sums over the workgroup
-    uint32_t inc = s;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t v = __shfl_up(inc, o);
-        if (lane >= o) inc += v;
-    }
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    uint32_t pre = 0;
-    for (int i = 0; i < w; ++i) pre += wsum[i];
-    uint32_t ex = pre + inc - s;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int l = tid * kPer + k;
-        cur[l] = ex;
-        if (l < nloc) off[l] = rb + ex;
-        ex += c[k];
-    }
-    __syncthreads();
-    const int b0 = x * slice_blocks, b1 = min(n_blocks, b0 + slice_blocks);
-    for (int b = b0; b < b1; ++b) {
-        const size_t sidx = (static_cast<size_t>(b) * n_ranges + r) * kGroups + w;
-        const int64_t sb = seg_base[sidx];
-        const int run = seg_run[sidx];
-        const uint32_t tbase = static_cast<uint32_t>(b - b0) * static_cast<uint32_t>(tb) +
-                               static_cast<uint32_t>(w) * static_cast<uint32_t>(tg);
-        int t = lane_start[sidx * kWave + lane];
-        for (int s4 = 0; s4 < run; s4 += 4) {
-            const uint2 q = *reinterpret_cast<const uint2 *>(code + code_slot(sb, s4, lane));
-#pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                const uint32_t cd = ((h < 2 ? q.x : q.y) >> (16 * (h & 1))) & 0xFFFFu;
-                t += static_cast<int>(cd >> 15);
-                if (cd != kSkip) {
-                    const uint32_t pos = atomicAdd(&cur[cd & (kRange - 1)], 1u);
-                    tr_ent[rb + pos] = tbase + static_cast<uint32_t>(t);
-                }
-            }
-        }
-    }
+bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
+    if (yet->reserved != kHasEvBlocks || yet->n_blocks == 0) return false;
+    const uint32_t flags = (yet->tr_ent ? ARA_PREP_TRANSPOSED : 0u) | (yet->t_cnt ? ARA_PREP_TRIAL_MAJOR : 0u) |
+                           (yet->pos ? ARA_PREP_POSITIONS : 0u);
+    Geometry g{};
+    g.tg = yet->trials_per_group;
+    g.tb = yet->trials_per_block;
+    g.n_blocks = yet->n_blocks;
+    g.n_ranges = yet->n_ranges;
+    g.nseg = static_cast<size_t>(g.n_blocks) * g.n_ranges * kGroups;
+    Carver c(yet->code);
+    const Prepared p = carve(c, g, yet->n_trials, yet->nnz, yet->catalog, flags);
+    const EvGeometry eg = ev_geometry(yet->n_trials, yet->nnz, yet->catalog);
+    out->ent = p.ent;
+    out->hdr = p.hdr;
+    out->start = p.start;
+    out->base = p.ev_base;
+    out->misc = p.misc;
+    out->n_trials = yet->n_trials;
+    out->et = eg.et;
+    out->neb = eg.neb;
+    out->ng = eg.ng;
+    out->dense = eg.dense;
+    out->catalog = yet->catalog;
+    return true;
 }
 
 }  // namespace ara
@@ -835,8 +723,6 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     const bool transposed = (flags & ARA_PREP_TRANSPOSED) != 0, positions = (flags & ARA_PREP_POSITIONS) != 0;
     if (flags & ARA_PREP_TRIAL_MAJOR) {
         ARA_HIP(hipMemsetAsync(p.t_cnt, 0, static_cast<size_t>(catalog) * sizeof(int32_t), st));
-        if (nnz > 0)
-            ARA_HIP(hipMemcpyAsync(p.t_ids, ids, static_cast<size_t>(nnz) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     }
     if (p.t_off)
         ARA_HIP(hipMemcpyAsync(p.t_off, offsets, (static_cast<size_t>(n_trials) + 1) * sizeof(int64_t),
@@ -866,10 +752,10 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
         y.slice_trials = static_cast<int64_t>(g.slice_blocks) * g.tb;
         y.tr_off = p.tr_off;
         y.tr_ent = p.tr_ent;
-        // every list is empty until the counting pass has run
-        ARA_HIP(hipMemsetAsync(p.tr_off, 0, (static_cast<size_t>(kSlices) * catalog + 1) * sizeof(int64_t), st));
     }
     if (g.n_blocks == 0) {
+        if (transposed)   // every list is empty
+            ARA_HIP(hipMemsetAsync(p.tr_off, 0, (static_cast<size_t>(kSlices) * catalog + 1) * sizeof(int64_t), st));
         ARA_HIP(hipStreamSynchronize(st));
         *out = y;
         return ARA_OK;
@@ -931,40 +817,36 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
         else k_prep_emit<128, false><<<ge, kEmitThreads, 0, st>>>(M);
     }
     ARA_HIP(hipGetLastError());
-    k_prep_max_occ<<<g.n_ranges, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, g.n_blocks, g.n_ranges, max_occ, catalog,
-                                                p.t_cnt);
-    ARA_HIP(hipGetLastError());
-    if (transposed) {
-        const dim3 grid(static_cast<unsigned>(g.n_ranges), kSlices);
-        k_tr_count<<<grid, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, g.n_blocks, g.n_ranges, g.slice_blocks, catalog,
-                                          p.tr_off, p.rtot);
-        ARA_HIP(hipGetLastError());
-        const size_t nreg = static_cast<size_t>(kSlices) * g.n_ranges;
-        std::vector<int64_t> tot(nreg);
-        ARA_HIP(hipMemcpyAsync(tot.data(), p.rtot, nreg * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        ARA_HIP(hipStreamSynchronize(st));
-        int64_t acc = 0;
-        for (size_t i = 0; i < nreg; ++i) {   // regions in (slice, range) order = list order
-            if (tot[i] >= (int64_t(1) << 32))
-                return fail(ARA_E_LIMIT, "ara_yet_prepare: 2^32 or more occurrences in one (slice, range)");
-            const int64_t t = tot[i];
-            tot[i] = acc;
-            acc += t;
-        }
-        if (acc != nnz) return fail(ARA_E_RANGE, "ara_yet_prepare: event-major copy lost occurrences");
-        ARA_HIP(hipMemcpyAsync(p.rtot, tot.data(), nreg * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        ARA_HIP(hipMemcpyAsync(p.tr_off + static_cast<size_t>(kSlices) * catalog, &acc, sizeof(int64_t),
-                               hipMemcpyHostToDevice, st));
-        ARA_HIP(hipStreamSynchronize(st));   // the host sources live in this scope
-        k_tr_scatter<<<grid, 1024, 0, st>>>(p.code, p.seg_base, p.seg_run, p.lane_start, g.n_blocks, g.n_ranges, g.tg, g.tb,
-                                            g.slice_blocks, catalog, p.rtot, p.tr_off, p.tr_ent);
-        ARA_HIP(hipGetLastError());
-    }
-    int32_t mo = 0;
-    ARA_HIP(hipMemcpyAsync(&mo, max_occ, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    ARA_HIP(hipStreamSynchronize(st));
-    y.max_occ = mo;
+    EvBuild E{};
+    E.g = ev_geometry(n_trials, nnz, catalog);
+    E.off = offsets;
+    E.ids = ids;
+    E.n_trials = n_trials;
+    E.nnz = nnz;
+    E.catalog = catalog;
+    E.ent = p.ent;
+    E.hdr = p.hdr;
+    E.start = p.start;
+    E.base = p.ev_base;
+    E.misc = p.misc;
+    E.t_ids = p.t_ids;
+    E.rec = p.rec;
+    E.tstart = p.tstart;
+    E.tbase = p.tbase;
+    E.mark = p.mark;
+    int32_t rc = ev_build(E, st);
+    if (rc) return rc;
+    y.reserved = kHasEvBlocks;
     y.n_codes = total;
+    EvBlocks B{};
+    ev_blocks(&y, &B);
+    if ((rc = ev_count(B, p.t_cnt, st))) return rc;
+    if (transposed && (rc = ev_major(B, y.slice_trials, p.tr_off, p.tr_ent, p.ssum, p.misc, st))) return rc;
+    ARA_HIP(hipMemcpyAsync(head, p.misc, sizeof(head), hipMemcpyDeviceToHost, st));
+    ARA_HIP(hipStreamSynchronize(st));
+    if ((head[kMiscErr] & 0xffffffff) != 0)
+        return fail(ARA_E_LIMIT, "ara_yet_prepare: 2^32 or more occurrences in one (slice, range) or one block of 8192 trials");
+    y.max_occ = static_cast<int32_t>(head[kMiscMaxOcc] & 0xffffffff);
     *out = y;
     return ARA_OK;
 }

@@ -227,3 +227,26 @@ def test_decreasing_offsets_are_refused(ara):
     with pytest.raises(ara.AraError) as ex:
         ara.PreparedYet.from_numpy(synth.Yet(1000, off, np.zeros(5000, np.int32)), "cuda")
     assert ex.value.status == 2
+
+
+@pytest.mark.parametrize("n,mean,catalog", [
+    (9000, 40, 30_000),      # blocks of 4500 trials that the slices cut, sparse headers
+    (20_000, 12, 5_000),     # 7 blocks of trials, lists of about 7 occurrences: dense headers
+    (8193, 3, 64),           # two blocks, one tile of the smallest size class
+    (300, 200, 9),           # crowded events: tiles read twice (more records than held in registers)
+    (70_000, 5, 3_000_000),  # many empty lists
+])
+def test_event_blocks(ara, n, mean, catalog):
+    """The event-ordered blocks, through what is derived from them: the
+    event-major lists, every event's count and the largest one (check), with
+    block sizes that the slices do and do not cut, both header forms, counts
+    of fifteen and more among short lists, and tiles beyond the registers."""
+    g = np.random.default_rng(n)
+    lens = g.poisson(mean, size=n)
+    lens[::11] = 0
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    ids[g.random(ids.shape[0]) < 0.02] = catalog - 1       # a long list in the last group
+    ids[g.random(ids.shape[0]) < 0.01] = catalog // 2
+    check(ara, synth.Yet(catalog, off, ids))
