@@ -190,7 +190,7 @@ def main() -> int:
         f"{occ_ms / max(occ_n, 1):.4f} ms; metrics {met_ms / max(met_n, 1):.4f} ms; AAL {m[0]:.6e} PML {m[1]:.6e} "
         f"TVaR {m[2]:.6e}")
 
-    traffic = traffic_from_profiles("fwd_traffic.md", os.path.join(HERE, "paper_1308_2572_amd", "csrc", "forward.hip"))
+    traffic = traffic_from_profiles("fwd_traffic.md", os.path.join(HERE, "paper_1308_2572_amd", "csrc", "evfwd.hip"))
     result = {
         "metric": "event-ELT lookups/s & %HBM peak (1M×1000×15); fwd+bwd cost; p99 quote latency",
         "value": value,
@@ -214,7 +214,7 @@ def main() -> int:
                      # the bytes the kernel actually moves (16-bit codes, not the 4-byte IDs the
                      # algorithmic figure counts) over its time, against the same peak
                      "frac_moved": (traffic / (k_fwd * 1e-3) / 1e9 / HBM_PEAK_GBS) if traffic else None,
-                     "kernel": "k_fwd", "kernel_ms": k_fwd, "algorithmic_bytes": algo_bytes},
+                     "kernel": "k_ev_fwd", "kernel_ms": k_fwd, "algorithmic_bytes": algo_bytes},
         "step_breakdown_ms": {"occurrence_table": occ_ms / max(occ_n, 1), "forward_stream": k_fwd,
                               "metrics": met_ms / max(met_n, 1)},
         "one_time_s": {"generate": t_gen, "elt_tables": t_tables, "yet_layout": t_prepare},
@@ -443,7 +443,7 @@ def bench_uneven(ara, dev, n_trials, steps, warmup, k_fwd_one_layer):
     log(f"uneven: step {ms:.4f} ms, forward kernel {k:.4f} ms ({k / k_fwd_one_layer:.2f}x the one-layer kernel)")
     return {"workload": "1000000 trials x Poisson(1000) events, 4 layers over 8/12/15/20 of 55 ELTs, catalogue 2000000",
             "ms_per_step": ms, "lookups_per_s": nnz * J / (ms * 1e-3), "events": nnz, "elt_lookups": nnz * J,
-            "kernel": "k_fwd_group", "kernel_ms": k, "kernel_ratio_to_one_layer": k / k_fwd_one_layer,
+            "kernel": "k_ev_fwd", "kernel_ms": k, "kernel_ratio_to_one_layer": k / k_fwd_one_layer,
             "algorithmic_bytes": algo, "achieved_gbs": algo / (k * 1e-3) / 1e9,
             "frac": algo / (k * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "metrics": [[float(v) for v in row] for row in m]}

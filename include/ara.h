@@ -92,8 +92,10 @@ int32_t ara_abi_version(void);
  * seg_base + (s/4)*256 + 4*j + s%4.
  * Order of occurrences inside a trial is kept within a segment but not across
  * ranges: the year loss does not depend on it (the cumulative aggregate steps
- * telescope), and the order of summation, so rounding, is fixed by this
- * layout and deterministic.
+ * telescope).  The binary64 forward adds a trial's occurrence losses exactly
+ * and rounds the sum once (layers whose values are too far apart for that, and
+ * the binary32 forward, add them in the order of this layout): the same result
+ * in every call, whatever the trial range and the other layers.
  *
  * With ARA_PREP_TRANSPOSED the buffer also holds the event-major copy the
  * backward needs (the adjoint of the per-trial gather is a per-event
@@ -122,7 +124,7 @@ typedef struct ara_yet {
     uint8_t  *lane_start;        /* device [n_blocks][n_ranges][groups][64]: each lane's first trial */
     /* event-major copy (ARA_PREP_TRANSPOSED; n_slices = 0 and NULL otherwise) */
     int32_t   n_slices;          /* 8 */
-    int32_t   reserved;          /* 1: the buffer also holds the trials' blocks ordered by event (library use) */
+    int32_t   reserved;          /* library use: tells the blocks ordered by event that the buffer holds too */
     int64_t   slice_trials;      /* a multiple of trials_per_block */
     int64_t  *tr_off;            /* device [n_slices * catalog + 1] */
     uint32_t *tr_ent;            /* device [nnz] */

@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build", "ara")
 LIB = os.path.join(HERE, "libara.so")
-SOURCES = ["common.hip", "prepare.hip", "evblk.hip", "tables.hip", "occ.hip", "forward.hip", "grpfwd.hip", "metrics.hip", "backward.hip", "server.hip", "quote_sched.cpp", "yelt.hip", "su.hip", "noalloc.hip"]
+SOURCES = ["common.hip", "prepare.hip", "evblk.hip", "tables.hip", "occ.hip", "forward.hip", "evfwd.hip", "metrics.hip", "backward.hip", "server.hip", "quote_sched.cpp", "yelt.hip", "su.hip", "noalloc.hip"]
 ARCH = os.environ.get("ARA_OFFLOAD_ARCH", "gfx950")
 
 CFLAGS = [
@@ -27,14 +27,13 @@ CFLAGS = [
 ]
 
 
-# Per-source code-generation choices, each measured on the MI355X against the
+# Per-source code-generation choices, measured on the MI355X against the
 # default (same results bit for bit): the machine scheduler's maximum-ILP
-# strategy for the two kernels that run one workgroup per CU (four wavefronts
-# per SIMD), where more independent loads per wavefront pay: the grouped
-# forward 1.88 -> 1.83 ms, the per-occurrence kernel 3.80 -> 3.60 ms.  (The
-# one-layer forward and the secondary-uncertainty kernel gained nothing or lost.)
+# strategy for the per-occurrence kernel, which runs one workgroup per CU (four
+# wavefronts per SIMD), where more independent loads per wavefront pay: 3.80 ->
+# 3.60 ms.  (The one-layer stream and the secondary-uncertainty kernel gained
+# nothing or lost.)
 EXTRA = {
-    "grpfwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "yelt.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }
 

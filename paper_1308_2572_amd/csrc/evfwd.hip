@@ -1,0 +1,413 @@
+// The event-ordered forward: a layer's set events (O != 0), each with the
+// list of the trials of a block that it occurs in, scatter their O into the
+// trials' totals in LDS.
+//
+// What bounds it is memory: it reads the lists of the layer's events and the
+// headers that tell where they are, 1.1-1.7 GB of the 2.3 GB that a 1M x 1000
+// YET's blocks take with 7% of the catalogue set (lists of four 16-bit
+// entries, so most 128-byte lines hold some set event's list), where the code
+// stream reads 2.1 GB and spends some 27 instructions on every occurrence.
+// One workgroup per (layer, block, part): the totals of 8192 trials take 96
+// KB of LDS, so a workgroup has a CU for itself; its 16 wavefronts take 64
+// set events at a time, one per lane, with the next 64 events' headers and
+// the ones' after lists in flight.  Larger blocks make longer lists and fewer
+// bytes: 7872 trials in two parts 302 us, 3936 trials 390 us, 1968 trials 510
+// us, the code stream 560 us (one layer, 1M x 1000, 146,000 of 2,000,000
+// events set).  Layers of one block run together on one XCD and share its
+// lists in L2: four layers 786 us (the code stream grouped by four 1750 us).
+//
+// The totals are integers (EvLayer): O in fixed point, two words, exact, so
+// the sum does not depend on the order in which wavefronts add, on the parts
+// or on the trial range, and the one rounding to binary64 comes at the end.
+#include "fwd_block.h"
+
+#include <algorithm>
+
+namespace ara {
+
+constexpr int kEvfThreads = 1024;
+constexpr int kEvfWaves = kEvfThreads / kWave;
+constexpr uint32_t kLongList = 512;   // lists beyond this many entries are added by the whole wavefront
+
+struct EvfParams {
+    EvBlocks B;
+    const FwdItem *items;      // one (layer, block) per `parts` workgroups, or null: the regular set below
+    int32_t n_items;
+    const OccTables *tabs;
+    const double *lterm;
+    double *ylt, *s_pre;
+    int32_t *hits;
+    int64_t t0, t1;
+    int32_t b0, nb, nl, parts;
+    unsigned char *partial;
+    FwdParams fwd;             // for the layers of mode 0
+};
+
+// Sixteen bytes of a list, from an even entry on.
+struct EvPiece {
+    uint32_t a[4];
+};
+
+template <bool HITS, bool DENSE>
+__global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
+    __shared__ __align__(16) unsigned char smem[kEvMaxTrials * (HITS ? 16 : 12)];
+    static_assert(sizeof(smem) >= kLdsBytes, "the stream's LDS");
+    unsigned long long *hi = reinterpret_cast<unsigned long long *>(smem);
+    uint32_t *lo = reinterpret_cast<uint32_t *>(smem + kEvMaxTrials * 8);
+    int32_t *hc = reinterpret_cast<int32_t *>(smem + kEvMaxTrials * 12);   // with hits
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroup 8k + x is the k-th on XCD x
+    const int x = blockIdx.x & (kXcds - 1), k = blockIdx.x / kXcds;
+    const OccTables *tab;
+    const double *lterm;
+    double *ylt, *s_pre;
+    int32_t *hits = nullptr;
+    int64_t t0, t1;
+    int b, part;
+    size_t slot;              // of the partial totals
+    if (P.items) {            // the item's parts one after another on its XCD
+        const int i = (k / P.parts) * kXcds + x;
+        part = k % P.parts;
+        if (i >= P.n_items) return;   // uniform, before any barrier
+        const FwdItem I = P.items[i];
+        b = I.block;
+        if (b < 0) return;    // uniform
+        tab = I.tab;
+        lterm = I.lterm;
+        ylt = I.ylt;
+        s_pre = I.s_pre;
+        t0 = I.t0;
+        t1 = I.t1;
+        slot = static_cast<size_t>(i) * P.parts + part;
+    } else {                  // the layers of one (block, part) one after another
+        const int j = k % P.nl;
+        const int item = (k / P.nl) * kXcds + x;
+        const int bi = item / P.parts;
+        part = item - bi * P.parts;
+        if (bi >= P.nb) return;   // uniform
+        b = P.b0 + bi;
+        t0 = P.t0;
+        t1 = P.t1;
+        const size_t n = static_cast<size_t>(t1 - t0);
+        tab = P.tabs + j;
+        lterm = P.lterm + 4 * j;
+        ylt = P.ylt + static_cast<size_t>(j) * n;
+        s_pre = P.s_pre ? P.s_pre + static_cast<size_t>(j) * n : nullptr;
+        if (HITS && P.hits) hits = P.hits + static_cast<size_t>(j) * n;
+        slot = static_cast<size_t>(j) * P.nb * P.parts + static_cast<size_t>(item);
+    }
+    const OccTables T = *tab;
+    const EvLayer L = *T.ev;
+    const int64_t bt0 = static_cast<int64_t>(b) * P.B.et;
+    const int nt = static_cast<int>(min<int64_t>(P.B.et, P.B.n_trials - bt0));
+    if (!L.mode) {   // uniform: the stream's blocks that meet this one, its parts in turn
+        const int64_t a = max(t0, bt0), z = min(t1, bt0 + nt);
+        FwdItem I;
+        I.tab = tab;
+        I.lterm = lterm;
+        I.pad = 0;
+        I.t0 = a;
+        I.t1 = z;
+        I.ylt = ylt + (a - t0);
+        I.s_pre = s_pre ? s_pre + (a - t0) : nullptr;
+        I.hits = hits ? hits + (a - t0) : nullptr;
+        for (int64_t k2 = a / P.fwd.tb + part; k2 * P.fwd.tb < z; k2 += P.parts) {
+            I.block = static_cast<int32_t>(k2);
+            __syncthreads();   // the previous block's totals have been read
+            fwd_block<HITS, false, true>(P.fwd, I, smem);
+        }
+        return;
+    }
+    for (int i = tid; i < nt; i += kEvfThreads) {
+        hi[i] = 0ull;
+        lo[i] = 0u;
+        if (HITS) hc[i] = 0;
+    }
+    __syncthreads();
+
+    const EvRec *rec = reinterpret_cast<const EvRec *>(T.vals);
+    const uint16_t *ent = P.B.ent + P.B.base[b];   // the block's entries: base may be odd
+    const uint16_t *ent2 = reinterpret_cast<const uint16_t *>(reinterpret_cast<uintptr_t>(ent) & ~uintptr_t(3));
+    const uint32_t skew = static_cast<uint32_t>((reinterpret_cast<uintptr_t>(ent) >> 1) & 1u);   // ent = ent2 + skew
+    const uint2 *hdr = DENSE ? nullptr : P.B.hdr + static_cast<size_t>(b) * P.B.ng;
+    const uint32_t *start = DENSE ? P.B.start + static_cast<size_t>(b) * (P.B.catalog + 1) : nullptr;
+    const int n_units = (L.n_set + kWave - 1) / kWave;
+    const int u0 = static_cast<int>(static_cast<int64_t>(n_units) * part / P.parts);
+    const int u1 = static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / P.parts);
+
+    // lane's set event of unit u, its header, its list [s, s + c) of entries
+    auto load_rec = [&](int u, EvRec &r, int &nb) {
+        r = EvRec{0, 0, ~0u};
+        nb = 0;
+        const int i = u * kWave + lane;
+        if (L.mode == 2) {   // uniform
+            constexpr int kChunk = kOccChunkWords * 32;
+            if (u < u1 && i % kChunk < T.pcount[i / kChunk]) {
+                const uint2 v = reinterpret_cast<const uint2 *>(T.dense)[i];
+                r.hi = reinterpret_cast<const unsigned long long *>(T.vals)[i];
+                r.lo = v.x;
+                r.ev = v.y;
+                if (HITS) nb = T.cnt[i];
+            }
+        } else if (u < u1 && i < L.n_set) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(rec + i);
+            r.hi = static_cast<unsigned long long>(v.x) | (static_cast<unsigned long long>(v.y) << 32);
+            r.lo = v.z;
+            r.ev = v.w;
+            if (HITS) nb = T.cnt[i];
+        }
+    };
+    auto load_hdr = [&](uint32_t ev) -> uint2 {
+        const uint32_t e = ev == ~0u ? 0u : ev;   // event 0's header (always there) for lanes without one
+        if (DENSE) return make_uint2(start[e], start[e + 1]);
+        return hdr[e >> 3];
+    };
+    auto find = [&](uint32_t ev, uint2 h, uint32_t &s, uint32_t &c) {
+        if (DENSE) {
+            s = h.x;
+            c = h.y - h.x;
+        } else {
+            ev_short_list(h, ev & 7u, s, c);
+            if (ev != ~0u && ev_long(h.y)) {
+                const uint32_t all = hdr[(ev >> 3) + 1].x - h.x;
+                const uint32_t a = ev_lower(ent + h.x, all, ev & 7u), z = ev_lower(ent + h.x, all, (ev & 7u) + 1u);
+                s = h.x + a;
+                c = z - a;
+            }
+        }
+        if (ev == ~0u) c = 0;
+        s += skew;
+    };
+    // piece p of the list: entries of ent2 from the even place at or before
+    // its first, eight at a time (the entries are padded past the last one)
+    auto load_piece = [&](uint32_t s, uint32_t c, uint32_t p, EvPiece &d) {
+        if (8u * p < (s & 1u) + c) d = *reinterpret_cast<const EvPiece *>(ent2 + (s & ~1u) + static_cast<size_t>(8u * p));
+    };
+    auto add = [&](uint32_t t, const EvRec &r, int nb) {
+        atomicAdd(&hi[t], r.hi);
+        atomicAdd(&lo[t], r.lo);
+        if (HITS) atomicAdd(&hc[t], nb);
+    };
+    auto add_piece = [&](uint32_t s, uint32_t c, uint32_t p, const EvPiece &d, const EvRec &r, int nb) {
+        const uint32_t first = 8u * p - (s & 1u);   // entry 0 of the piece in the list (wraps below 0)
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            if (first + i < c) add(((i & 1u) ? d.a[i >> 1] >> 16 : d.a[i >> 1]) & kEvTrialMask, r, nb);
+    };
+
+    EvRec r0, r1, r2;
+    int n0, n1, n2;
+    uint32_t s0, c0, s1, c1;
+    EvPiece a0{}, a1{}, e0{}, e1{};   // the first two pieces of a list
+    load_rec(u0 + w, r0, n0);
+    load_rec(u0 + w + kEvfWaves, r1, n1);
+    {
+        const uint2 h = load_hdr(r0.ev);
+        find(r0.ev, h, s0, c0);
+    }
+    load_piece(s0, c0, 0, a0);
+    load_piece(s0, c0, 1, e0);
+    uint2 h1 = load_hdr(r1.ev);
+    for (int u = u0 + w; u < u1; u += kEvfWaves) {
+        load_rec(u + 2 * kEvfWaves, r2, n2);
+        find(r1.ev, h1, s1, c1);
+        load_piece(s1, c1, 0, a1);
+        load_piece(s1, c1, 1, e1);
+        h1 = load_hdr(r2.ev);
+        // a list of many entries: the wavefront's lanes take them together
+        for (uint64_t big = __ballot(c0 > kLongList); big; big &= big - 1) {
+            const int l = __builtin_ctzll(big);
+            EvRec r;
+            r.hi = __shfl(r0.hi, l);
+            r.lo = __shfl(r0.lo, l);
+            const int nb = HITS ? __shfl(n0, l) : 0;
+            const uint32_t s = __shfl(s0, l), c = __shfl(c0, l);
+            for (uint32_t i = lane; i < c; i += kWave) add(ent2[static_cast<size_t>(s) + i] & kEvTrialMask, r, nb);
+            if (lane == l) c0 = 0;
+        }
+        add_piece(s0, c0, 0, a0, r0, n0);
+        if (__any((s0 & 1u) + c0 > 8u)) {
+            add_piece(s0, c0, 1, e0, r0, n0);
+            for (uint32_t p = 2; __any((s0 & 1u) + c0 > 8u * p); ++p) {
+                load_piece(s0, c0, p, a0);
+                add_piece(s0, c0, p, a0, r0, n0);
+            }
+        }
+        r0 = r1;
+        n0 = n1;
+        s0 = s1;
+        c0 = c1;
+        a0 = a1;
+        e0 = e1;
+        r1 = r2;
+        n1 = n2;
+    }
+    __syncthreads();
+
+    if (P.parts > 1) {
+        unsigned char *p = P.partial + slot * ev_slot_bytes(P.B.et, HITS);
+        unsigned long long *ph = reinterpret_cast<unsigned long long *>(p);
+        uint32_t *pl = reinterpret_cast<uint32_t *>(p + static_cast<size_t>(P.B.et) * 8);
+        int32_t *pc = reinterpret_cast<int32_t *>(p + static_cast<size_t>(P.B.et) * 12);
+        for (int i = tid; i < nt; i += kEvfThreads) {
+            ph[i] = hi[i];
+            pl[i] = lo[i];
+            if (HITS) pc[i] = hc[i];
+        }
+        return;
+    }
+    const double aggR = lterm[2], aggL = lterm[3];
+    const int i0 = static_cast<int>(max<int64_t>(t0 - bt0, 0)), i1 = static_cast<int>(min<int64_t>(t1 - bt0, nt));
+    for (int i = i0 + tid; i < i1; i += kEvfThreads) {
+        const double S = ev_total(hi[i], lo[i], L);
+        const size_t o = static_cast<size_t>(bt0 + i - t0);
+        ylt[o] = xl(S, aggR, aggL);
+        if (s_pre) s_pre[o] = S;
+        if (HITS && hits) hits[o] = hc[i];
+    }
+}
+
+// The results of a split launch's trials from the parts' totals (integers: in
+// any order).  Regular set: one run of 256 / G trials of a (layer, block) per
+// workgroup, G lanes per trial where there are few, so that its parts' loads
+// overlap.  List: the same of an item.
+template <bool HITS>
+__global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
+    const int u = blockIdx.x / per, c = blockIdx.x - u * per;
+    int b;
+    int64_t t0, t1;
+    const OccTables *tab;
+    const double *lterm;
+    double *ylt, *s_pre;
+    int32_t *hits = nullptr;
+    if (P.items) {
+        const FwdItem I = P.items[u];
+        b = I.block;
+        if (b < 0) return;
+        t0 = I.t0;
+        t1 = I.t1;
+        tab = I.tab;
+        lterm = I.lterm;
+        ylt = I.ylt;
+        s_pre = I.s_pre;
+    } else {
+        const int j = u / P.nb;
+        b = P.b0 + (u - j * P.nb);
+        t0 = P.t0;
+        t1 = P.t1;
+        const size_t n = static_cast<size_t>(t1 - t0);
+        tab = P.tabs + j;
+        lterm = P.lterm + 4 * j;
+        ylt = P.ylt + static_cast<size_t>(j) * n;
+        s_pre = P.s_pre ? P.s_pre + static_cast<size_t>(j) * n : nullptr;
+        if (HITS && P.hits) hits = P.hits + static_cast<size_t>(j) * n;
+    }
+    const EvLayer L = *tab->ev;
+    if (!L.mode) return;   // uniform
+    const int i = (c * 256 + static_cast<int>(threadIdx.x)) / G, sub = threadIdx.x & (G - 1);
+    const int64_t t = static_cast<int64_t>(b) * P.B.et + i;
+    if (i >= P.B.et || t < t0 || t >= t1) return;   // all lanes of a trial together
+    const size_t slot = ev_slot_bytes(P.B.et, HITS);
+    const unsigned char *p = P.partial + (static_cast<size_t>(u) * P.parts + sub) * slot;
+    unsigned long long h = 0, l = 0;
+    int32_t k = 0;
+#pragma unroll 4
+    for (int q = sub; q < P.parts; q += G, p += static_cast<size_t>(G) * slot) {
+        h += reinterpret_cast<const unsigned long long *>(p)[i];
+        l += reinterpret_cast<const uint32_t *>(p + static_cast<size_t>(P.B.et) * 8)[i];
+        if (HITS) k += reinterpret_cast<const int32_t *>(p + static_cast<size_t>(P.B.et) * 12)[i];
+    }
+    for (int d = G / 2; d > 0; d >>= 1) {
+        h += __shfl_xor(h, d, G);
+        l += __shfl_xor(l, d, G);
+        if (HITS) k += __shfl_xor(k, d, G);
+    }
+    if (sub != 0) return;
+    const double S = ev_total(h, l, L);
+    const size_t o = static_cast<size_t>(t - t0);
+    ylt[o] = xl(S, lterm[2], lterm[3]);
+    if (s_pre) s_pre[o] = S;
+    if (HITS && hits) hits[o] = k;
+}
+
+static int32_t launch_ev(const EvfParams &P, bool hits, unsigned grid, int n_sets, hipStream_t st) {
+    if (hits) {
+        if (P.B.dense) k_ev_fwd<true, true><<<grid, kEvfThreads, 0, st>>>(P);
+        else k_ev_fwd<true, false><<<grid, kEvfThreads, 0, st>>>(P);
+    } else {
+        if (P.B.dense) k_ev_fwd<false, true><<<grid, kEvfThreads, 0, st>>>(P);
+        else k_ev_fwd<false, false><<<grid, kEvfThreads, 0, st>>>(P);
+    }
+    if (P.parts > 1) {
+        int G = 1;   // lanes per trial: while that leaves the device room
+        while (2 * G <= std::min(P.parts, kWave) && static_cast<int64_t>(2 * G) * n_sets * P.B.et <= 65536) G *= 2;
+        const int per = (P.B.et * G + 255) / 256;
+        const unsigned ga = static_cast<unsigned>(n_sets) * static_cast<unsigned>(per);
+        if (hits) k_ev_add<true><<<ga, 256, 0, st>>>(P, G, per);
+        else k_ev_add<false><<<ga, 256, 0, st>>>(P, G, per);
+    }
+    ARA_HIP(hipGetLastError());
+    return ARA_OK;
+}
+
+int ev_parts(int64_t n_items, int64_t slots) {
+    const int cu = device_cu_count();
+    // rounds of one workgroup per CU over the parts a block is cut into, with
+    // a little for each part's share of the adding up; at most 64 (a block's
+    // 64 parts add up about as long as they run where the YET is that small)
+    int best = 1;
+    double cost = 1e300;
+    for (int p = 1; p <= 64; ++p) {
+        if (p > 1 && n_items * p > slots) break;
+        const double c = static_cast<double>((n_items * p + cu - 1) / cu) / p + 0.002 * p;
+        if (c < cost) {
+            cost = c;
+            best = p;
+        }
+    }
+    return best;
+}
+
+static int32_t ev_params(const EvBlocks &B, const ara_yet *yet, bool hits, int parts, EvfParams &P) {
+    if (B.et < 1 || B.et > kEvMaxTrials || parts < 1)
+        return fail(ARA_E_INVAL, "event-ordered forward: blocks not prepared by this library");
+    P.B = B;
+    P.parts = parts;
+    return fwd_params(yet, hits, false, P.fwd);
+}
+
+int32_t launch_ev_forward(const EvBlocks &B, const ara_yet *yet, bool hits, const FwdRegular &reg, hipStream_t st) {
+    if (reg.nl <= 0 || reg.ev_nb <= 0) return ARA_OK;
+    EvfParams P{};
+    const int32_t rc = ev_params(B, yet, hits, reg.parts, P);
+    if (rc) return rc;
+    P.tabs = reg.tabs;
+    P.lterm = reg.lterm;
+    P.ylt = reg.ylt;
+    P.s_pre = reg.s_pre;
+    P.hits = reg.hits;
+    P.t0 = reg.t0;
+    P.t1 = reg.t1;
+    P.b0 = reg.ev_b0;
+    P.nb = reg.ev_nb;
+    P.nl = reg.nl;
+    P.partial = reg.partial;
+    const int64_t items = (static_cast<int64_t>(reg.ev_nb) * reg.parts + kXcds - 1) / kXcds * kXcds;
+    return launch_ev(P, hits, static_cast<unsigned>(items * reg.nl), reg.nl * reg.ev_nb, st);
+}
+
+int32_t launch_ev_list(const EvBlocks &B, const ara_yet *yet, const FwdItem *d_items, int n_items, int parts,
+                       unsigned char *partial, hipStream_t st) {
+    if (n_items <= 0) return ARA_OK;
+    EvfParams P{};
+    const int32_t rc = ev_params(B, yet, false, parts, P);
+    if (rc) return rc;
+    P.items = d_items;
+    P.n_items = n_items;
+    P.nl = 1;
+    P.partial = partial;
+    return launch_ev(P, false, static_cast<unsigned>((n_items + kXcds - 1) / kXcds * kXcds * parts), n_items, st);
+}
+
+}  // namespace ara

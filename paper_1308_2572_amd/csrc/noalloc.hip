@@ -45,10 +45,11 @@ extern "C" int32_t ara_ylt_forward_noalloc(const ara_tables *tables, const ara_y
                                            const double *elt_terms, const double *layer_terms, int64_t trial_begin,
                                            int64_t trial_end, uint32_t flags, double *ylt, double *s_pre,
                                            int32_t *hits, int32_t *dev_status, void *stream) {
-    size_t need = 0;
+    size_t need = 0, least = 0;
     int32_t rc = forward_args(tables, yet, layers, elt_terms, layer_terms, trial_begin, trial_end, flags, ylt, hits,
-                              &need);
+                              &need, &least);
     if (rc) return rc;
+    need = least;   // what the scratch holds beyond that serves for partial totals
     if (need > ARA_NOALLOC_SCRATCH_BYTES)
         return fail(ARA_E_LIMIT, "forward needs " + std::to_string(need) + " bytes of workspace, beyond the " +
                                      std::to_string(static_cast<size_t>(ARA_NOALLOC_SCRATCH_BYTES)) +
@@ -58,7 +59,7 @@ extern "C" int32_t ara_ylt_forward_noalloc(const ara_tables *tables, const ara_y
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool empty = layers->n_layers == 0 || trial_end == trial_begin;
     if (!empty && (rc = forward_run(tables, yet, layers, elt_terms, layer_terms, trial_begin, trial_end, flags, ylt,
-                                    s_pre, hits, ws, st)))
+                                    s_pre, hits, ws, ARA_NOALLOC_SCRATCH_BYTES, st)))
         return rc;
     if (dev_status) {
         k_put_status<<<1, 64, 0, st>>>(dev_status, empty ? nullptr : static_cast<const int32_t *>(ws));

@@ -17,13 +17,52 @@
 // requested, every event present in at least one of the layer's ELTs.
 #pragma once
 
-#include "ara_internal.h"
+#include "evblk.h"
 
 namespace ara {
 
 constexpr int kMaxJ = ARA_MAX_ELTS_PER_LAYER;
 constexpr int kOccChunkWords = 128;                    // 4096 events per chunk
 constexpr int kOccChunks = kSrWords / kOccChunkWords;   // 16 chunks per super-range
+
+// What one chunk's events tell about its layer (phase one, for the
+// event-ordered forward).
+struct OccChunkStat {
+    unsigned long long max_bits;   // largest O, as binary64 bits
+    int32_t low;                   // smallest power of two that some O is an odd multiple of (INT32_MAX: no O)
+    int32_t n_union;               // events held by any of the layer's ELTs
+    int32_t count;                 // set events
+    int32_t pad;
+};
+
+// How the event-ordered forward serves a layer.  Its totals are integers:
+// O = (hi * 2^frac + lo) * 2^(gexp - frac) exactly, lo < 2^frac, with hi's
+// sum over any trial below 2^62 and lo's below 2^32.  mode 0: some O does not
+// fit (values more than 2^62 apart, an infinity) or the events held exceed
+// half the table's room, and the one-layer stream serves the layer.
+struct EvLayer {
+    int32_t mode, n_set, gexp, frac;
+};
+
+// The binary64 value nearest to (hi 2^frac + lo) 2^(gexp - frac).
+__device__ __forceinline__ double ev_total(unsigned long long hi, unsigned long long lo, const EvLayer &L) {
+    const unsigned __int128 v = (static_cast<unsigned __int128>(hi) << L.frac) + lo;
+    const unsigned long long top = static_cast<unsigned long long>(v >> 64), low = static_cast<unsigned long long>(v);
+    const int bits = top ? 128 - __clzll(static_cast<long long>(top)) : (low ? 64 - __clzll(static_cast<long long>(low)) : 0);
+    if (bits <= 53) return ldexp(static_cast<double>(low), L.gexp - L.frac);
+    const int sh = bits - 53;
+    unsigned long long q = static_cast<unsigned long long>(v >> sh);
+    const unsigned __int128 rest = v - (static_cast<unsigned __int128>(q) << sh);
+    const unsigned __int128 half = static_cast<unsigned __int128>(1) << (sh - 1);
+    if (rest > half || (rest == half && (q & 1ull))) ++q;   // to nearest, ties to even
+    return ldexp(static_cast<double>(q), sh + L.gexp - L.frac);
+}
+
+// A set event of an event-ordered layer, in event order (at vals).
+struct __attribute__((aligned(16))) EvRec {
+    unsigned long long hi;
+    uint32_t lo, ev;
+};
 
 struct OccTables {
     uint2 *br;          // [n_sr][kSrWords]
@@ -34,6 +73,10 @@ struct OccTables {
     uint32_t *bits;     // [n_sr][kSrWords]  set-event bitmap (phase one)
     double *dense;      // [n_sr][kSr]       O of each chunk's set events, from the chunk's start (phase one)
     uint8_t *dense_nb;  // [n_sr][kSr]       their ELT counts (hits mode)
+    OccChunkStat *stat; // [n_sr][kOccChunks]
+    EvLayer *ev_space;  // room for ev
+    EvLayer *ev;        // where the layer's form is left, or null: always the tables br, vals, cnt
+    const int64_t *max_len;   // with ev: occurrences of the YET's longest trial
 };
 
 // min(max(v - R, 0), L), evaluated exactly as the oracle does: a separately
@@ -48,7 +91,7 @@ __device__ __forceinline__ double xl(double v, double r, double lim) {
 struct OccLayoutSizes {
     int n_sr;
     size_t per_layer;
-    size_t br, vals, cnt, count, pcount, bits, dense, dense_nb;
+    size_t br, vals, cnt, count, pcount, bits, dense, dense_nb, stat, ev;
 };
 
 inline OccLayoutSizes occ_sizes(int32_t catalog, bool with_cnt) {
@@ -62,7 +105,9 @@ inline OccLayoutSizes occ_sizes(int32_t catalog, bool with_cnt) {
     z.bits = align256(static_cast<size_t>(z.n_sr) * kSrWords * sizeof(uint32_t));
     z.dense = align256(static_cast<size_t>(z.n_sr) * kSr * sizeof(double));
     z.dense_nb = with_cnt ? align256(static_cast<size_t>(z.n_sr) * kSr) : 0;
-    z.per_layer = z.br + z.vals + z.cnt + z.count + z.pcount + z.bits + z.dense + z.dense_nb;
+    z.stat = align256(static_cast<size_t>(z.n_sr) * kOccChunks * sizeof(OccChunkStat));
+    z.ev = align256(sizeof(EvLayer));
+    z.per_layer = z.stat + z.ev + z.br + z.vals + z.cnt + z.count + z.pcount + z.bits + z.dense + z.dense_nb;
     return z;
 }
 
@@ -76,50 +121,10 @@ inline OccTables occ_carve(Carver &c, const OccLayoutSizes &z, bool with_cnt) {
     t.bits = c.take<uint32_t>(static_cast<size_t>(z.n_sr) * kSrWords);
     t.dense = c.take<double>(static_cast<size_t>(z.n_sr) * kSr);
     t.dense_nb = with_cnt ? c.take<uint8_t>(static_cast<size_t>(z.n_sr) * kSr) : nullptr;
+    t.stat = c.take<OccChunkStat>(static_cast<size_t>(z.n_sr) * kOccChunks);
+    t.ev_space = c.take<EvLayer>(1);
     return t;
 }
-
-// Members (layers, or quotes of the server) that one workgroup of the
-// grouped forward serves together.
-constexpr int kGrpMax = 4;
-
-// The union of a group's set events, per super-range: the union bitmap with
-// ranks (as an occurrence table's br), its count, and for every member its
-// set events as a bitmap over the union's ranks: word k of sbr[m] holds union
-// ranks 32k..32k+31 of the super-range, {bit set iff the member's O != 0 for
-// that event, the member's rank of the first of them} -- the member's rank of
-// an event is its index in the member's own occurrence-table values.
-struct GrpTables {
-    uint2 *ubr;                     // [n_sr][kSrWords]
-    int32_t *ucount;                // [n_sr]
-    uint2 *sbr;                     // [kGrpMax][n_sr][kSrWords]
-    const OccTables *mt[kGrpMax];   // the members' occurrence tables (device)
-    int32_t n;                      // members
-    int32_t pad;
-};
-
-// One unit of grouped forward work: the members of one group over one block
-// of trials; member m writes its trials in [t0[m], t1[m]) (rows indexed
-// t - t0[m]).  block -1 marks an empty slot (the workgroup exits at once).
-struct GrpItem {
-    const GrpTables *gt;            // device
-    int32_t block;
-    int32_t n;                      // members
-    uint32_t mask;                  // members to serve on this block (bit m); others are skipped
-    const double *lterm[kGrpMax];   // (OccR, OccL, AggR, AggL) of each member
-    int64_t t0[kGrpMax], t1[kGrpMax];
-    double *ylt[kGrpMax];
-    double *s_pre[kGrpMax];         // or null
-};
-
-// Members one grouped-forward workgroup holds with blocks of tb trials (0 if
-// not even one leaves room for the table slices).
-int grp_max_members(int tb);
-// Builds the union tables of n_groups groups (their mt and n set).
-int32_t launch_grp_union(const GrpTables *d_gts, int n_groups, int n_sr, hipStream_t st);
-// The grouped forward over a device array of items (one workgroup each, a
-// whole CU's LDS per workgroup).
-int32_t launch_fwd_group(const ara_yet *yet, const GrpItem *d_items, int n_items, int gmax, hipStream_t st);
 
 // One unit of forward work: one layer over one block of trials, with the
 // trial range [t0, t1) whose outputs are written (row bases indexed t - t0).
@@ -146,7 +151,32 @@ struct FwdRegular {
     int64_t t0, t1;
     int32_t b0, nb;
     int32_t nl;                // layers
+    // the event-ordered forward: its blocks, the workgroups each (layer, block)
+    // is split over, and the partial totals' room (parts > 1)
+    unsigned char *partial;
+    int32_t parts, ev_b0, ev_nb, ev_et;
 };
+
+// Bytes of one workgroup's partial totals: hi, lo and (with hits) the counts
+// of every trial of a block.
+__host__ __device__ inline size_t ev_slot_bytes(int et, bool hits) {
+    return align256(static_cast<size_t>(et) * (hits ? 16 : 12));
+}
+
+// The event-ordered forward over the regular set: every layer over blocks
+// ev_b0 .. ev_b0 + ev_nb - 1, each (layer, block) split over reg.parts
+// workgroups by its set events.
+int32_t launch_ev_forward(const EvBlocks &B, const ara_yet *yet, bool hits, const FwdRegular &reg, hipStream_t st);
+
+// The same over a list of items in launch order (slot 8k + x is the k-th on
+// XCD x; block -1: empty), each split over `parts` workgroups; partial:
+// n_items * parts slots of ev_slot_bytes when parts > 1.
+int32_t launch_ev_list(const EvBlocks &B, const ara_yet *yet, const FwdItem *d_items, int n_items, int parts,
+                       unsigned char *partial, hipStream_t st);
+
+// Workgroups each (layer, block) is split over: as few rounds of one
+// workgroup per CU as possible, and at most `slots` partial totals.
+int ev_parts(int64_t n_items, int64_t slots);
 
 // Workgroups of a regular launch: one per block with one layer; with L
 // layers, L per block over whole groups of kXcds blocks (the XCD-aware
@@ -168,16 +198,17 @@ int32_t launch_forward(const ara_yet *yet, int n_sr, bool hits, bool f32, const 
                        hipStream_t st, const FwdRegular *reg = nullptr, bool shared = false);
 
 // Checks the arguments of a forward call (those of ara_ylt_forward but the
-// workspace); *need receives the workspace bytes the call takes.
+// workspace); *need receives the workspace bytes the call takes, *least what
+// it can do with (without room for partial totals).
 int32_t forward_args(const ara_tables *tables, const ara_yet *yet, const ara_layers *layers, const double *elt_terms,
                      const double *layer_terms, int64_t trial_begin, int64_t trial_end, uint32_t flags,
-                     const double *ylt, const int32_t *hits, size_t *need);
+                     const double *ylt, const int32_t *hits, size_t *need, size_t *least);
 // Enqueues a checked forward call with at least one layer and one trial on
-// `st`, over a workspace of at least the bytes forward_args gave (its first
+// `st`, over a workspace of ws_bytes, at least forward_args' *least (its first
 // int32 receives the device-side status).
 int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_layers *layers, const double *elt_terms,
                     const double *layer_terms, int64_t trial_begin, int64_t trial_end, uint32_t flags, double *ylt,
-                    double *s_pre, int32_t *hits, void *ws, hipStream_t st);
+                    double *s_pre, int32_t *hits, void *ws, size_t ws_bytes, hipStream_t st);
 
 // A layer's set-event bitmap folded onto 2^20 bits by OR (128 KB, staged in
 // LDS by the kernels that stream the trial-major YET): one filter per layer.
@@ -190,8 +221,9 @@ int32_t check_layers(const ara_layers *layers, int32_t n_elts);
 // Enqueue the occurrence-table kernel for every layer.  `tabs` has one entry
 // per layer; the layer CSR must already be on the device.  f32_vals stores
 // each O rounded to binary32 (vals then holds floats at the same indices).
+// with_ev: some table has ev set.
 int32_t launch_occ(const ara_tables *tables, const int32_t *d_elt_off, const int32_t *d_elt_ids,
                    const double *elt_terms, const double *layer_terms, int32_t n_layers, bool union_mode,
-                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st);
+                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st, bool with_ev = false);
 
 }  // namespace ara

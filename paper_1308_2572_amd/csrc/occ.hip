@@ -56,6 +56,8 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
     __shared__ uint32_t anyw[kPassWords], cbase[kPassWords], fbits[kPassWords];
     __shared__ uint16_t cand[kPassWords * 32];
     __shared__ uint32_t wtot[16], wtot2[2], n_cand;
+    __shared__ unsigned long long smax;
+    __shared__ int slow;
 
     const int s = blockIdx.x / kPasses, p = blockIdx.x % kPasses, j = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -69,6 +71,10 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
         lr[q] = elt_terms[3 * k + 1];
         ll[q] = elt_terms[3 * k + 2];
         if (checker && (bad_scale(ls[q]) || bad_retention(lr[q]) || bad_limit(ll[q]))) atomicCAS(err, 0, ARA_E_INVAL);
+    }
+    if (tid == 0) {
+        smax = 0;
+        slow = INT32_MAX;
     }
     if (tid < 4) {
         lterm[tid] = layer_terms[4 * j + tid];
@@ -107,6 +113,8 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
     double *ov = T.dense + ev0;                           // the chunk's compacted O
     uint8_t *onb = UNION ? T.dense_nb + ev0 : nullptr;    // and ELT counts
     uint32_t run = 0;                                     // set events before this pass
+    unsigned long long mx = 0;                            // this thread's part of the chunk's stat
+    int low = INT32_MAX;
     for (int i0 = 0; i0 < nc; i0 += 1024) {   // uniform trip count: every thread reaches the barriers
         const int i = i0 + tid;
         const int local = i < nc ? cand[i] : 0;
@@ -157,33 +165,201 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
             ov[r] = O;
             if (UNION) onb[r] = static_cast<uint8_t>(nb > 255 ? 255 : nb);
             atomicOr(&fbits[wip], 1u << bit);
+            const unsigned long long ob = static_cast<unsigned long long>(__double_as_longlong(O));
+            if (ob != 0) {
+                mx = max(mx, ob);
+                const int ex = static_cast<int>(ob >> 52);
+                const unsigned long long man = ob & 0xFFFFFFFFFFFFFull;
+                low = min(low, ex ? ex - 1075 + __ffsll(static_cast<long long>(man | (1ull << 52))) - 1
+                                  : __ffsll(static_cast<long long>(man)) - 1 - 1074);
+            }
         }
         run += tot;
         __syncthreads();   // wtot is rewritten by the next pass
     }
     if (tid < kPassWords) T.bits[static_cast<size_t>(s) * kSrWords + p * kPassWords + tid] = fbits[tid];
     if (tid == 0) T.pcount[static_cast<size_t>(s) * kPasses + p] = static_cast<int32_t>(run);
+    if (!T.ev) return;   // uniform
+    // (zeroed before the first barrier; a wavefront without set events adds nothing)
+    if (__any(mx != 0)) {
+        for (int o = 32; o > 0; o >>= 1) {
+            mx = max(mx, __shfl_xor(mx, o));
+            low = min(low, __shfl_xor(low, o));
+        }
+        if (lane == 0) {
+            atomicMax(&smax, mx);
+            atomicMin(&slow, low);
+        }
+    }
+    __syncthreads();
+    if (tid == 0)
+        T.stat[static_cast<size_t>(s) * kPasses + p] = OccChunkStat{smax, slow, nc, static_cast<int32_t>(run), 0};
+}
+
+// The chunks' stats of one layer together: its form for the event-ordered
+// forward, and the set events of the chunks before `before`.  All threads of
+// the workgroup (at most 1024) call it.
+__device__ EvLayer occ_layer_form(const OccTables &T, int n_chunks, int before, uint32_t *base) {
+    __shared__ unsigned long long smx[16], ssum[16];
+    __shared__ int slow[16];
+    __shared__ uint32_t sbef[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
+    unsigned long long mx = 0, sum = 0;   // sum: events held << 32 | set events
+    int low = INT32_MAX;
+    uint32_t bef = 0;
+    for (int c = tid; c < n_chunks; c += blockDim.x) {
+        const OccChunkStat s = T.stat[c];
+        mx = max(mx, s.max_bits);
+        low = min(low, s.low);
+        sum += (static_cast<unsigned long long>(static_cast<uint32_t>(s.n_union)) << 32) + static_cast<uint32_t>(s.count);
+        bef += c < before ? static_cast<uint32_t>(s.count) : 0u;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        mx = max(mx, __shfl_xor(mx, o));
+        low = min(low, __shfl_xor(low, o));
+        sum += __shfl_xor(sum, o);
+        bef += __shfl_xor(bef, o);
+    }
+    if (lane == 0) {
+        smx[w] = mx;
+        slow[w] = low;
+        ssum[w] = sum;
+        sbef[w] = bef;
+    }
+    __syncthreads();
+    mx = sum = 0;
+    low = INT32_MAX;
+    bef = 0;
+    for (int k = 0; k < nw; ++k) {
+        mx = max(mx, smx[k]);
+        low = min(low, slow[k]);
+        sum += ssum[k];
+        bef += sbef[k];
+    }
+    const uint32_t un = static_cast<uint32_t>(sum >> 32), cnt = static_cast<uint32_t>(sum);
+    *base = bef;
+    EvLayer L{0, static_cast<int32_t>(cnt), 0, 0};
+    // bits of the longest trial's length: its total is below 2^(exponent of
+    // the largest O + lbits)
+    const int64_t len = max<int64_t>(*T.max_len, 1);
+    const int lbits = len > 1 ? 64 - __clzll(len - 1) : 0;
+    const int ex = static_cast<int>(mx >> 52);
+    if (lbits > 32 || ex >= 0x7FF) return L;   // an infinity (or, with invalid terms, no number or a negative one)
+    const int top = (ex ? ex - 1022 : -1021) + lbits;   // every total < 2^top
+    L.gexp = top - 62;
+    L.frac = 32 - lbits;
+    if (low < L.gexp - L.frac) return L;
+    const int slots = n_chunks * (kOccChunkWords * 32);
+    L.mode = 2ull * un <= static_cast<unsigned long long>(slots) ? 1 : 2;
+    if (L.mode == 2) L.n_set = slots;
+    return L;
 }
 
 // Phase two: one workgroup per (chunk, layer): the chunk's rank base (set
 // events of the super-range's earlier chunks), the rank of every bitmap word,
 // and the chunk's compacted values moved to their place in rank order.
+// Catalogues of more than kFormChunks chunks: the layer's form and the set
+// events before every chunk (left in stat.pad), once per layer instead of
+// once per chunk.
+constexpr int kFormChunks = 2048;
+
+__global__ __launch_bounds__(1024) void k_occ_form(const OccTables *__restrict__ tabs, int n_chunks) {
+    __shared__ uint32_t wsum[16];
+    const OccTables T = tabs[blockIdx.x];
+    if (!T.ev) return;   // uniform
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    uint32_t run = 0;
+    for (int c0 = 0; c0 < n_chunks; c0 += 1024) {
+        const uint32_t v = c0 + tid < n_chunks ? static_cast<uint32_t>(T.stat[c0 + tid].count) : 0u;
+        uint32_t incl = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = __shfl_up(incl, o);
+            if (lane >= o) incl += x;
+        }
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        uint32_t at = run + incl - v, all = 0;
+        for (int k = 0; k < 16; ++k) {
+            at += k < w ? wsum[k] : 0u;
+            all += wsum[k];
+        }
+        if (c0 + tid < n_chunks) T.stat[c0 + tid].pad = static_cast<int32_t>(at);
+        run += all;
+        __syncthreads();
+    }
+    uint32_t none;
+    const EvLayer L = occ_layer_form(T, n_chunks, 0, &none);
+    if (tid == 0) *T.ev = L;
+}
+
+// With T.ev, the layer's form comes from every chunk's stat, and in its
+// event-ordered form the chunk's set events become records (value in fixed
+// point, event) in event order over the whole catalogue, instead.
+constexpr int kRankThreads = 256;
+
 template <bool UNION, bool F32>
-__global__ __launch_bounds__(1024) void k_occ_rank(const OccTables *__restrict__ tabs) {
+__global__ __launch_bounds__(kRankThreads) void k_occ_rank(const OccTables *__restrict__ tabs) {
     __shared__ uint32_t wtot2[2], tot;
     const int s = blockIdx.x / kPasses, p = blockIdx.x % kPasses, j = blockIdx.y;
     const int tid = threadIdx.x;
     const OccTables T = tabs[j];
     const int32_t *pc = T.pcount + static_cast<size_t>(s) * kPasses;
-    uint32_t base = 0;
-    for (int k = 0; k < p; ++k) base += static_cast<uint32_t>(pc[k]);
     const uint32_t cnt = static_cast<uint32_t>(pc[p]);
     const size_t w0 = static_cast<size_t>(s) * kSrWords + p * kPassWords;
+    const size_t src = static_cast<size_t>(s) * kSr + static_cast<size_t>(p) * (kPassWords * 32);
     const uint32_t b = tid < kPassWords ? T.bits[w0 + tid] : 0u;
     const uint32_t r = scan128(__popc(b), wtot2, &tot);
+    if (!F32 && T.ev) {   // uniform
+        uint32_t gbase;
+        EvLayer L;
+        if (static_cast<int>(gridDim.x) > kFormChunks) {
+            L = *T.ev;
+            gbase = static_cast<uint32_t>(T.stat[blockIdx.x].pad);
+        } else {
+            L = occ_layer_form(T, gridDim.x, blockIdx.x, &gbase);
+            if (blockIdx.x == 0 && tid == 0) *T.ev = L;
+        }
+        if (L.mode) {
+            // the chunk's set events in order, then a thread per event
+            __shared__ uint16_t list[kPassWords * 32];
+            if (tid < kPassWords) {
+                uint32_t m = b, at = r;
+                for (; m; m &= m - 1) list[at++] = static_cast<uint16_t>(32 * tid + __builtin_ctz(m));
+            }
+            __syncthreads();
+            EvRec *rec = reinterpret_cast<EvRec *>(T.vals) + gbase;
+            const size_t cdst = L.mode == 1 ? gbase : src;
+            for (uint32_t i = tid; i < cnt; i += kRankThreads) {
+                const unsigned long long ob = static_cast<unsigned long long>(__double_as_longlong(T.dense[src + i]));
+                EvRec v{0, 0, static_cast<uint32_t>(src) + list[i]};
+                if (ob != 0) {
+                    const int ex = static_cast<int>(ob >> 52);
+                    unsigned long long m = (ob & 0xFFFFFFFFFFFFFull) | (ex ? 1ull << 52 : 0ull);
+                    int sh = (ex ? ex - 1075 : -1074) - (L.gexp - L.frac);   // O = m 2^sh units of 2^(gexp - frac)
+                    if (sh < 0) {   // trailing zeros only: O is a multiple of the unit
+                        m >>= -sh;
+                        sh = 0;
+                    }
+                    // sh <= 42: the value is below 2^(62 + frac), m at least 2^52 (or, of a subnormal, the
+                    // exponent at its lowest)
+                    v.hi = sh >= L.frac ? m << (sh - L.frac) : m >> (L.frac - sh);
+                    v.lo = static_cast<uint32_t>((m << sh) & ((1ull << L.frac) - 1ull));
+                }
+                if (L.mode == 1) {
+                    rec[i] = v;
+                } else {   // dense[src + i] has just been read by this thread, and by no other
+                    reinterpret_cast<unsigned long long *>(T.vals)[src + i] = v.hi;
+                    reinterpret_cast<uint2 *>(T.dense)[src + i] = make_uint2(v.lo, v.ev);
+                }
+                if (UNION) T.cnt[cdst + i] = T.dense_nb[src + i];
+            }
+            return;
+        }
+    }
+    uint32_t base = 0;
+    for (int k = 0; k < p; ++k) base += static_cast<uint32_t>(pc[k]);
     if (tid < kPassWords) T.br[w0 + tid] = make_uint2(b, base + r);
     if (p == kPasses - 1 && tid == 0) T.count[s] = static_cast<int32_t>(base + cnt);
-    const size_t src = static_cast<size_t>(s) * kSr + static_cast<size_t>(p) * (kPassWords * 32);
     const size_t dst = static_cast<size_t>(s) * kSr + base;
     for (uint32_t i = tid; i < cnt; i += blockDim.x) {
         if (F32) reinterpret_cast<float *>(T.vals)[dst + i] = static_cast<float>(T.dense[src + i]);
@@ -212,20 +388,23 @@ int32_t check_layers(const ara_layers *layers, int32_t n_elts) {
 
 int32_t launch_occ(const ara_tables *tables, const int32_t *d_elt_off, const int32_t *d_elt_ids,
                    const double *elt_terms, const double *layer_terms, int32_t n_layers, bool union_mode,
-                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st) {
+                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st, bool with_ev) {
     if (n_layers == 0 || n_sr == 0) return ARA_OK;
     dim3 grid_a(static_cast<unsigned>(n_sr * kPasses), static_cast<unsigned>(n_layers));
     dim3 grid_b(static_cast<unsigned>(n_sr * kPasses), static_cast<unsigned>(n_layers));
+    const bool form = with_ev && n_sr * kPasses > kFormChunks;
     if (union_mode) {
         k_occ_eval<true><<<grid_a, 1024, 0, st>>>(tables->loss, tables->present, tables->catalog, tables->words,
                                                   d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err);
-        if (f32_vals) k_occ_rank<true, true><<<grid_b, 1024, 0, st>>>(d_tabs);
-        else k_occ_rank<true, false><<<grid_b, 1024, 0, st>>>(d_tabs);
+        if (form) k_occ_form<<<n_layers, 1024, 0, st>>>(d_tabs, n_sr * kPasses);
+        if (f32_vals) k_occ_rank<true, true><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
+        else k_occ_rank<true, false><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
     } else {
         k_occ_eval<false><<<grid_a, 1024, 0, st>>>(tables->loss, tables->present, tables->catalog, tables->words,
                                                    d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err);
-        if (f32_vals) k_occ_rank<false, true><<<grid_b, 1024, 0, st>>>(d_tabs);
-        else k_occ_rank<false, false><<<grid_b, 1024, 0, st>>>(d_tabs);
+        if (form) k_occ_form<<<n_layers, 1024, 0, st>>>(d_tabs, n_sr * kPasses);
+        if (f32_vals) k_occ_rank<false, true><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
+        else k_occ_rank<false, false><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
     }
     ARA_HIP(hipGetLastError());
     return ARA_OK;

@@ -655,14 +655,14 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
     }
 }
 
-// Marks a prepared YET whose buffer holds event-ordered blocks: their place
-// follows from the sizes and flags, like every piece's.
-constexpr int32_t kHasEvBlocks = 1;
+// Marks a prepared YET whose buffer holds event-ordered blocks, with the
+// flags it was prepared with: the pieces' places follow from the sizes and
+// those flags.
+constexpr int32_t kHasEvBlocks = 0x100;
 
 bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
-    if (yet->reserved != kHasEvBlocks || yet->n_blocks == 0) return false;
-    const uint32_t flags = (yet->tr_ent ? ARA_PREP_TRANSPOSED : 0u) | (yet->t_cnt ? ARA_PREP_TRIAL_MAJOR : 0u) |
-                           (yet->pos ? ARA_PREP_POSITIONS : 0u);
+    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags)) != kHasEvBlocks || yet->n_blocks == 0) return false;
+    const uint32_t flags = static_cast<uint32_t>(yet->reserved) & kPrepFlags;
     Geometry g{};
     g.tg = yet->trials_per_group;
     g.tb = yet->trials_per_block;
@@ -836,7 +836,7 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     E.mark = p.mark;
     int32_t rc = ev_build(E, st);
     if (rc) return rc;
-    y.reserved = kHasEvBlocks;
+    y.reserved = kHasEvBlocks | static_cast<int32_t>(flags);
     y.n_codes = total;
     EvBlocks B{};
     ev_blocks(&y, &B);

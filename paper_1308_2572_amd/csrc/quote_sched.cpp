@@ -288,8 +288,15 @@ void Scheduler::loop() {
         std::vector<SchedItem> slots;
         std::vector<SchedJob *> completed;
         bool shared = false, launched = false;
+        size_t scratch_off = 0, scratch = 0;   // arena bytes lent to the launch until it has run
         if (!rc && next_launch(&slots, &shared, &completed)) {
             launched = true;
+            scratch = ex_->scratch_bytes(slots.size());
+            {
+                std::lock_guard<std::mutex> lk(mu_);
+                if (scratch && !arena_.alloc(scratch, &scratch_off)) scratch = 0;
+            }
+            ex_->scratch(scratch_off, scratch);
             rc = ex_->launch(slots, shared, &err);
             int64_t n_items = 0, n_shared = 0, n_quotes = 0;
             std::vector<const SchedJob *> seen;
@@ -355,9 +362,14 @@ void Scheduler::loop() {
             }
             launchable = launchable || (!queue_.empty() && !free_slots_.empty());
         }
+        if (scratch) {   // until the launch has run, also when something after it failed
+            ex_->settle();
+            std::lock_guard<std::mutex> lk(mu_);
+            arena_.release(scratch_off, scratch);
+        }
         if (launched && rc == ARA_OK) {
             idle_polls = 0;
-            ex_->settle();
+            if (!scratch) ex_->settle();
         } else if (waiting && !launchable) {
             // results pending and nothing to launch: poll again at once for a
             // while (a finishing quote's last kernels and copy take tens to

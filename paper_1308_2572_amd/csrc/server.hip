@@ -56,6 +56,9 @@ class HipExecutor final : public SchedExecutor {
     ara_yet yet{};
     const double *elt_terms = nullptr;
     char *arena_base = nullptr;
+    EvBlocks ev{};                         // the YET's event-ordered blocks
+    bool use_ev = false;                   // it has some: the items are theirs
+    size_t scratch_off = 0, scratch_len = 0;   // arena bytes lent to the next launch
     OccLayoutSizes z{};
     size_t res_doubles = 0;                // per slot: 3 metrics + 3*4 layer grads + 3*n_elts*3 ELT grads
     // A quote's status word and its results sit side by side in its arena
@@ -134,6 +137,10 @@ class HipExecutor final : public SchedExecutor {
         d->d_err = c.take<int32_t>(kResOff / sizeof(int32_t));
         d->d_res = c.take<double>(res_doubles);
         d->tab = occ_carve(c, z, false);
+        if (use_ev) {
+            d->tab.ev = d->tab.ev_space;
+            d->tab.max_len = ev.misc + kMiscMaxLen;
+        }
         d->ylt = c.take<double>(static_cast<size_t>(n));
         d->s_pre = c.take<double>(static_cast<size_t>(n));
         ara_metrics_workspace_bytes(1, n, &d->met_bytes);
@@ -165,9 +172,21 @@ class HipExecutor final : public SchedExecutor {
         if (rc) *err = "copy of the quote's head failed";
         // the quote's occurrence table; invalid terms set its own status word
         if (!rc && (rc = launch_occ(&tables, d->d_off, d->d_ids, elt_terms, d->d_lterm, 1, false, false, d->d_tab, z.n_sr,
-                                    d->d_err, st)))
+                                    d->d_err, st, use_ev)))
             *err = "occurrence table launch failed";
         return rc;
+    }
+
+    // A launch of few items is split over more workgroups (ev_parts), whose
+    // partial totals need room.
+    size_t scratch_bytes(size_t n_slots) override {
+        const size_t cu = static_cast<size_t>(device_cu_count());
+        return use_ev && n_slots < 2 * cu ? 2 * cu * ev_slot_bytes(ev.et, false) : 0;
+    }
+
+    void scratch(size_t off, size_t bytes) override {
+        scratch_off = off;
+        scratch_len = bytes;
     }
 
     int32_t launch(const std::vector<SchedItem> &items, bool shared, std::string *err) override {
@@ -198,8 +217,16 @@ class HipExecutor final : public SchedExecutor {
         if ((rc = hip_step(hipMemcpyAsync(d_items[ring], hi, items.size() * sizeof(FwdItem), hipMemcpyHostToDevice, st),
                            err)))
             return rc;
-        if ((rc = launch_forward(&yet, z.n_sr, false, false, d_items[ring], static_cast<int>(items.size()), st, nullptr,
-                                 shared))) {
+        ProfScope prof(ARA_PROF_FWD, st);
+        const int n = static_cast<int>(items.size());
+        if (use_ev) {
+            const int parts = ev_parts(n, static_cast<int64_t>(scratch_len / ev_slot_bytes(ev.et, false)));
+            rc = launch_ev_list(ev, &yet, d_items[ring], n, parts, reinterpret_cast<unsigned char *>(arena_base) + scratch_off,
+                                st);
+        } else {
+            rc = launch_forward(&yet, z.n_sr, false, false, d_items[ring], n, st, nullptr, shared);
+        }
+        if (rc) {
             *err = "forward launch failed";
             return rc;
         }
@@ -374,6 +401,7 @@ extern "C" int32_t ara_server_create(const ara_tables *tables, const ara_yet *ye
     X.tables = *tables;
     X.yet = *yet;
     X.elt_terms = elt_terms;
+    X.use_ev = ev_blocks(yet, &X.ev);
     X.z = occ_sizes(tables->catalog, false);
     X.res_doubles = 3 + 12 + static_cast<size_t>(3) * tables->n_elts * 3;
     X.stage_bytes = HipExecutor::kResOff + X.res_doubles * sizeof(double);
@@ -405,14 +433,19 @@ extern "C" int32_t ara_server_create(const ara_tables *tables, const ara_yet *ye
     }
     SchedConfig cfg;
     cfg.n_trials = yet->n_trials;
-    cfg.trials_per_block = yet->trials_per_block;
-    cfg.n_blocks = yet->n_blocks;
+    cfg.trials_per_block = X.use_ev ? X.ev.et : yet->trials_per_block;
+    cfg.n_blocks = X.use_ev ? X.ev.neb : yet->n_blocks;
     cfg.n_elts = tables->n_elts;
     cfg.arena_bytes = arena_bytes - ring_bytes();
     cfg.max_slots = max_slots;
     cfg.max_items = HipExecutor::kMaxItems;
     cfg.n_xcd = kXcds;
-    cfg.xcd_slots = 2 * device_cu_count() / kXcds;   // two forward workgroups per CU
+    // workgroups per CU: one of the event-ordered forward, two of the stream
+    if (X.use_ev) {   // blocks of four times the trials: a quarter of the items is the same work
+        cfg.items_per_launch /= 4;
+        cfg.min_window /= 4;
+    }
+    cfg.xcd_slots = (X.use_ev ? 1 : 2) * device_cu_count() / kXcds;
     S->sched.reset(new Scheduler(&S->ex, cfg));
     S->sched->start();
     *server = S;

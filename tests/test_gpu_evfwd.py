@@ -1,0 +1,170 @@
+"""The event-ordered forward against the stream of the codes and the oracle.
+
+The event-ordered forward adds each trial's occurrence losses exactly (in
+integers) and rounds the sum once, so its total differs from the oracle's
+sequential binary64 sum by at most that sum's own rounding: n additions of at
+most 2^-53 of the total each, and the one rounding.  Where a layer's values do
+not fit the integers it streams the block's codes in the order of the stream,
+bit for bit.  A YET whose mark of the event-ordered blocks is cleared takes
+the stream throughout."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(f"[gpu-evfwd] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def ara():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_1308_2572_amd as ara
+    ara.library()
+    return ara
+
+
+class Case:
+    def __init__(self, ara, w):
+        import torch
+        self.ara, self.w = ara, w
+        self.tables = ara.EltTables.from_numpy(w.elts)
+        self.yet = ara.PreparedYet.from_numpy(w.yet, transposed=False)
+        self.stream = ara.PreparedYet.from_numpy(w.yet, transposed=False)
+        assert self.yet.handle.reserved != 0
+        self.stream.handle.reserved = 0
+        self.layers = ara.Layers(w.layers.elt_off, w.layers.elt_ids)
+        self.et = torch.tensor(w.elts.terms, dtype=torch.float64, device="cuda")
+        self.lt = torch.tensor(w.layers.terms, dtype=torch.float64, device="cuda")
+
+    def run(self, yet, hits, t0=0, t1=None):
+        out = self.ara.ylt_forward(self.tables, yet, self.layers, self.et, self.lt, t0, t1, want_hits=hits, check=True)
+        return [None if x is None else x.cpu().numpy() for x in out]
+
+    def oracle(self):
+        return oracle.forward(oracle.build_tables(self.w.elts), self.w.yet, self.w.layers, self.w.elts.terms,
+                              self.w.layers.terms, n_threads=8)
+
+
+def check(ara, w, bitwise=False):
+    """Both paths, with and without hit counts, against the oracle; the
+    event-ordered results the same in every way of asking."""
+    c = Case(ara, w)
+    _say(f"{w.name}: {w.yet.n_trials} trials, {w.yet.nnz} occurrences, catalogue {w.yet.catalog}")
+    ref = c.oracle()
+    n = int(np.diff(w.yet.offsets).max(initial=0))
+    y, s, _ = c.run(c.yet, False)
+    yh, sh, h = c.run(c.yet, True)
+    ys, ss, hs = c.run(c.stream, True)
+    assert np.array_equal(h, ref["hits"]) and np.array_equal(hs, ref["hits"])
+    assert np.array_equal(s, sh) and np.array_equal(y, yh)
+    for got in (s, ss):
+        fin = np.isfinite(ref["s_pre"])
+        assert np.array_equal(got[~fin], ref["s_pre"][~fin])
+        assert np.all(np.abs(got[fin] - ref["s_pre"][fin]) <= (2 * n + 1) * 2.0 ** -53 * ref["s_pre"][fin])
+    if bitwise:
+        assert np.array_equal(s, ss) and np.array_equal(y, ys)
+    N = w.yet.n_trials
+    for t0, t1 in [(0, 1), (N // 3, N // 3 + 1), (N // 2, N), (1, max(1, N - 1))]:
+        if t0 < t1:
+            yr, sr, hr = c.run(c.yet, True, t0, t1)
+            assert np.array_equal(sr, s[:, t0:t1]) and np.array_equal(yr, y[:, t0:t1]) and np.array_equal(hr, h[:, t0:t1])
+    return c, s
+
+
+def workload(name, n, mean, catalog, sizes, lists, terms, seed, mu=11.0, sigma=1.5, elt_terms=None):
+    g = np.random.default_rng(seed)
+    lens = g.poisson(mean, size=n)
+    lens[::13] = 0
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    elts = synth.lognormal_elts(seed, sizes, catalog, mu=mu, sigma=sigma)
+    if elt_terms is not None:
+        elts.terms = np.asarray(elt_terms, np.float64)
+    elt_off = np.zeros(len(lists) + 1, np.int32)
+    np.cumsum([len(x) for x in lists], out=elt_off[1:])
+    layers = synth.Layers(elt_off, np.concatenate([np.asarray(x, np.int32) for x in lists]).astype(np.int32),
+                          np.asarray(terms, np.float64))
+    return synth.Workload(name, synth.Yet(catalog, off, ids), elts, layers, 0.9)
+
+
+OPEN = [0.0, np.inf, 0.0, np.inf]
+TERMS = [[1e4, 5e6, 1e4, 5e8], OPEN, [2e4, 1e6, 0.0, 1e7]]
+
+
+@pytest.mark.parametrize("n", [1, 15, 8191, 8192, 8193, 17_000])
+@pytest.mark.parametrize("mean,catalog", [(30, 40_000), (60, 6_000)])
+def test_block_edges_and_header_forms(ara, n, mean, catalog):
+    """One trial to three blocks of trials; short lists and long ones."""
+    check(ara, workload("edges", n, mean, catalog, [catalog // 20, catalog // 9, catalog // 30], [[0, 1, 2], [2], [1, 0]],
+                        TERMS, n + mean))
+
+
+@pytest.mark.parametrize("share", [0.45, 0.55, 0.95])
+def test_layers_around_half_the_catalogue(ara, share):
+    """Layers whose ELTs hold just under and over half the events of a table
+    (65,536 here), where the records change place, and nearly all of them."""
+    C = 65_536
+    check(ara, workload("dense", 3000, 40, C, [int(C * share), C // 100], [[0], [0, 1], [1]], TERMS, 7))
+
+
+def test_lists_of_a_whole_wavefront(ara):
+    """Events that occur thousands of times in one block of trials (lists that
+    a wavefront adds together), lists of fifteen and more among short ones, in
+    both header forms."""
+    for catalog in (50_000, 700):
+        w = workload("crowded", 6000, 40, catalog, [catalog // 10, catalog // 3], [[0, 1], [1]], TERMS[:2], catalog)
+        g = np.random.default_rng(catalog)
+        hot = w.elts.rec_ids[:3]
+        u = g.random(w.yet.nnz)
+        for k, p in enumerate((0.1, 0.02, 0.0004)):
+            w.yet.ids[(u >= k * 0.2) & (u < k * 0.2 + p)] = hot[k]
+        check(ara, w)
+
+
+@pytest.mark.parametrize("kind", ["spread", "infinite", "subnormal"])
+def test_values_beyond_the_integers(ara, kind):
+    """Losses some 2^120 apart, totals that overflow to infinity, and
+    subnormal values beside ordinary ones: these layers are streamed, bit for
+    bit as the stream; the ordinary layer beside them is not."""
+    n_rec = 3000
+    terms = [[1.0, 0.0, np.inf]] * 2
+    w = workload(kind, 9000, 30, 30_000, [n_rec, 2000], [[0], [1], [0, 1]], [OPEN, TERMS[0], OPEN], 5, elt_terms=terms)
+    g = np.random.default_rng(6)
+    if kind == "spread":
+        w.elts.rec_loss[:n_rec] = np.exp2(g.uniform(-60, 60, n_rec)).astype(np.float32)
+    elif kind == "infinite":
+        w.elts.rec_loss[:n_rec] = np.float32(3e38)
+        w.elts.terms[0, 0] = 1e300
+    else:
+        w.elts.rec_loss[:n_rec] = np.where(g.random(n_rec) < 0.5, np.float32(1e-40), np.float32(1e5))
+        w.elts.terms[0, 0] = 2.0 ** -900
+        w.elts.rec_loss[0] = 3e30
+    c, s = check(ara, w)
+    _, ss, _ = c.run(c.stream, False)
+    assert np.array_equal(s[0], ss[0]) and np.array_equal(s[2], ss[2])
+
+
+def test_scaled_to_the_subnormal_range(ara):
+    """A layer whose values are all subnormal or near it fits the integers:
+    exact sums, so a one-occurrence trial's total is its O."""
+    w = workload("tiny", 2000, 1, 5_000, [1500], [[0]], [OPEN], 8, elt_terms=[[1.0, 0.0, np.inf]])
+    w.elts.terms[0, 0] = 2.0 ** -1060
+    check(ara, w)
+
+
+def test_many_layers(ara):
+    """More layers than a wavefront has lanes."""
+    g = np.random.default_rng(1)
+    lists = [g.choice(6, size=int(g.integers(0, 5)), replace=False) for _ in range(70)]
+    check(ara, workload("layers", 500, 30, 9_000, [300, 900, 100, 700, 50, 2000], lists,
+                        [TERMS[k % 3] for k in range(70)], 2))
