@@ -68,6 +68,7 @@ struct MetCall {
     MetState *st;
     MetPart *part;
     uint64_t *cand;
+    int32_t *hdr;       // the workspace's error word, for k_met_small to clear
 };
 
 __device__ __forceinline__ MetRow met_row(const MetCall &c, int l) {
@@ -267,9 +268,12 @@ __device__ __forceinline__ void each_cand(bool in_lds, const uint64_t *cs, const
     }
 }
 
-// Gathers every value whose 23-bit prefix is the selected one (a wavefront
-// reserves its slots with one atomic), with their smallest and largest key.
-// The last workgroup finishes digits 2..5 on them.
+// Gathers every value whose 23-bit prefix is the selected one, with their
+// smallest and largest key.  A workgroup reserves the slots of a sweep with
+// one atomic and reports its extremes with two (one set per wavefront made
+// 6000 atomics on three addresses of a row capped at one limit:
+// 100 us for four rows of a million, 35 now).  The last workgroup finishes digits 2..5
+// on them.
 __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
     __shared__ uint64_t cs[kCandCap];
     __shared__ uint32_t h[kBins];
@@ -279,9 +283,16 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
     __shared__ unsigned long long wkm[kMetThreads / 64];
     __shared__ long long wkn[kMetThreads / 64];
     __shared__ int flag;
+    __shared__ uint32_t sweep_n;
+    __shared__ unsigned long long sweep_at, skmax, skminc;
     const int wg = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const MetRow R = met_row(call, blockIdx.y);
     if (wg >= R.nwg) return;   // uniform over the workgroup, before any barrier
+    if (tid == 0) {
+        sweep_n = 0;
+        skmax = skminc = 0;
+    }
+    __syncthreads();
     const int64_t n = R.n;
     const int nwg = R.nwg;
     MetState &S = *reinterpret_cast<MetState *>(R.st);
@@ -324,10 +335,16 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
                 }
             }
         }
-        if (mine) {   // uniform: the wavefront reserves its slots itself
-            unsigned long long base = 0;
-            if (lane == 0) base = atomicAdd(&S.cand_n, static_cast<unsigned long long>(mine));
-            int64_t off = static_cast<int64_t>(__shfl(base, 0));
+        // the wavefronts' places in the sweep, then the sweep's in the copy
+        uint32_t wat = 0;
+        if (mine && lane == 0) wat = atomicAdd(&sweep_n, static_cast<uint32_t>(mine));
+        __syncthreads();
+        const uint32_t all = sweep_n;
+        if (tid == 0 && all) sweep_at = atomicAdd(&S.cand_n, static_cast<unsigned long long>(all));
+        __syncthreads();
+        if (tid == 0) sweep_n = 0;   // the next sweep's first atomics come after its barrier below
+        if (mine) {   // uniform over the wavefront
+            int64_t off = static_cast<int64_t>(sweep_at) + __shfl(wat, 0);
 #pragma unroll
             for (int u = 0; u < kMetUnroll; ++u) {
                 if ((m[u] >> lane) & 1ull) {
@@ -338,6 +355,7 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
                 off += __popcll(m[u]);
             }
         }
+        __syncthreads();
     }
     unsigned long long wk = 0ull;   // the wavefront's largest gathered key and its count
     long long wn = 0;
@@ -351,8 +369,8 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
         wn = (nkmax > 0 && my_kmax == kmax) ? nkmax : 0;
         for (int o = 32; o > 0; o >>= 1) wn += __shfl_xor(wn, o);
         if (lane == 0) {
-            atomicMax(&S.kmax, static_cast<unsigned long long>(kmax));
-            atomicMax(&S.kminc, static_cast<unsigned long long>(~kmin));
+            atomicMax(&skmax, static_cast<unsigned long long>(kmax));
+            atomicMax(&skminc, static_cast<unsigned long long>(~kmin));
         }
     }
     if (lane == 0) {
@@ -361,8 +379,12 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
     }
     {
         double t2[2] = {s_above, static_cast<double>(n_above)};
-        block_sums(t2, red);   // also publishes wkm and wkn
+        block_sums(t2, red);   // also publishes wkm, wkn and the extremes
         if (tid == 0) {
+            if (skmax | skminc) {   // something was gathered
+                atomicMax(&S.kmax, skmax);
+                atomicMax(&S.kminc, skminc);
+            }
             MetPart *pw = part + wg;
             put(&pw->sum_gt, t2[0]);
             put(&pw->cnt_gt, static_cast<int64_t>(t2[1]));
@@ -507,26 +529,135 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
     }
 }
 
+// d(AAL, PML, TVaR) / d(year loss) of a row, from its PML value and the counts
+// above and at it.
+struct MetWeights {
+    double thr, inv_n, w_pml, w_gt, w_eq;
+    __device__ __forceinline__ MetWeights(int64_t n, int64_t r, int64_t gt, int64_t eq, double t)
+        : thr(t),
+          inv_n(1.0 / static_cast<double>(n)),
+          w_pml(1.0 / static_cast<double>(eq)),
+          w_gt(1.0 / static_cast<double>(r)),
+          w_eq(static_cast<double>(r - gt) / (static_cast<double>(r) * static_cast<double>(eq))) {}
+    __device__ __forceinline__ void put(const MetRow &R, int64_t i, double v) const {
+        R.w[i] = inv_n;
+        R.w[R.wstride + i] = (v == thr) ? w_pml : 0.0;
+        R.w[2 * R.wstride + i] = (v > thr) ? w_gt : ((v == thr) ? w_eq : 0.0);
+    }
+};
+
+// Rows of at most kMetSweep values (one workgroup of the passes above): the
+// whole selection in one kernel, the keys in registers throughout, where the
+// passes spend their time on launches (2000 trials: 25 -> 16 us).  The same
+// sums over the same threads in the same order, so the same results.
+__global__ __launch_bounds__(kMetThreads) void k_met_small(MetCall call) {
+    __shared__ uint32_t h[kBins];
+    __shared__ FindShared fs;
+    __shared__ double red[3][16];
+    __shared__ unsigned long long ired[4][16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const MetRow R = met_row(call, blockIdx.y);
+    const int n = static_cast<int>(R.n);
+    const int64_t r = R.r;
+    if (blockIdx.y == 0 && tid == 0) *call.hdr = 0;
+    uint64_t k[kMetUnroll];
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < kMetUnroll; ++u) {
+        const int i = u * kMetThreads + tid;
+        const double v = i < n ? R.ylt[i] : 0.0;
+        k[u] = key_of(v);
+        s += v;
+    }
+    // radix select from the top digit on
+    uint64_t pre = 0, bin = 0;   // bin: the 23-bit prefix
+    int64_t need = r;
+    for (int d = 0; d < kDigits; ++d) {
+        for (int i = tid; i < kBins; i += kMetThreads) h[i] = 0;
+        __syncthreads();
+        const int sh = kShift[d], hb = kShift[d] + kWidth[d];
+        const uint32_t mask = (1u << kWidth[d]) - 1u;
+#pragma unroll
+        for (int u = 0; u < kMetUnroll; ++u) {
+            const bool want = u * kMetThreads + tid < n && (k[u] >> hb) == pre;
+            const uint32_t dg = static_cast<uint32_t>((k[u] >> sh) & mask);
+            const uint64_t act = __ballot(want);   // one digit for the lanes that share it, as above
+            if (act) {
+                const int leader = __builtin_ctzll(act);
+                const uint32_t ld = __builtin_amdgcn_readlane(dg, leader);
+                const uint64_t same = __ballot(want && dg == ld);
+                if (lane == leader) atomicAdd(&h[ld], static_cast<uint32_t>(__popcll(same)));
+                if (want && dg != ld) atomicAdd(&h[dg], 1u);
+            }
+        }
+        __syncthreads();
+        find_digit(h, 1 << kWidth[d], need, fs);
+        pre = (pre << kWidth[d]) | static_cast<uint64_t>(fs.digit);
+        need = fs.need;
+        if (d == 1) bin = pre;
+        __syncthreads();   // fs and h are used again
+    }
+    const uint64_t bits = pre;
+    double s_above = 0.0, n_above = 0.0;   // values above the bin
+    unsigned long long v[4] = {0, 0, 0, 0};   // the bin's values above the PML value as integers, their count, the ties
+#pragma unroll
+    for (int u = 0; u < kMetUnroll; ++u) {
+        if (u * kMetThreads + tid >= n) continue;
+        const uint64_t b = k[u] >> kShift[1];
+        if (b > bin) {
+            s_above += __longlong_as_double(static_cast<long long>(k[u]));
+            n_above += 1.0;
+        } else if (k[u] > bits) {
+            const uint64_t e = (k[u] >> 52) & 0x7FFull;
+            const uint64_t sig = (k[u] & ((1ull << 52) - 1ull)) | (e ? (1ull << 52) : 0ull);
+            v[0] += sig >> 26;
+            v[1] += sig & ((1ull << 26) - 1ull);
+            ++v[2];
+        } else if (k[u] == bits) {
+            ++v[3];
+        }
+    }
+    double t[3] = {s, s_above, n_above};
+    block_sums(t, red);
+    const int w = tid >> 6;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o);
+        if (lane == 0) ired[q][w] = v[q];
+    }
+    __syncthreads();
+    unsigned long long a[4] = {0, 0, 0, 0};
+    for (int i = 0; i < kMetThreads / 64; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] += ired[q][i];
+    const double thr = __longlong_as_double(static_cast<long long>(bits));
+    const int64_t gt = static_cast<int64_t>(t[2]) + static_cast<int64_t>(a[2]), eq = static_cast<int64_t>(a[3]);
+    if (tid == 0) {
+        const int e = static_cast<int>((bin >> 11) & 0x7FFu);   // the bin's exponent field
+        const double scale = ldexp(1.0, (e ? e : 1) - 1075);     // value of one significand unit
+        const double cand_sum = (ldexp(static_cast<double>(a[0]), 26) + static_cast<double>(a[1])) * scale;
+        const double tsg = t[1] + cand_sum;
+        R.out[0] = t[0] / static_cast<double>(R.n);
+        R.out[1] = thr;
+        R.out[2] = (tsg + static_cast<double>(r - gt) * thr) / static_cast<double>(r);
+    }
+    if (!R.w) return;
+    const MetWeights mw(R.n, r, gt, eq, thr);
+#pragma unroll
+    for (int u = 0; u < kMetUnroll; ++u) {
+        const int i = u * kMetThreads + tid;
+        if (i < n) mw.put(R, i, R.ylt[i]);
+    }
+}
+
 __global__ void k_met_weights(MetCall call) {
     const MetRow R = met_row(call, blockIdx.y);
     if (!R.w) return;
     const MetState &S = *reinterpret_cast<const MetState *>(R.st);
-    const int64_t n = R.n;
-    const double thr = S.thr;
-    const int64_t r = S.r, gt = S.cnt_gt, eq = S.cnt_eq;
-    const double inv_n = 1.0 / static_cast<double>(n);
-    const double w_pml = 1.0 / static_cast<double>(eq);
-    const double w_gt = 1.0 / static_cast<double>(r);
-    const double w_eq = static_cast<double>(r - gt) / (static_cast<double>(r) * static_cast<double>(eq));
-    const double *y = R.ylt;
-    double *wa = R.w, *wp = R.w + R.wstride, *wt = R.w + 2 * R.wstride;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const double v = y[i];
-        wa[i] = inv_n;
-        wp[i] = (v == thr) ? w_pml : 0.0;
-        wt[i] = (v > thr) ? w_gt : ((v == thr) ? w_eq : 0.0);
-    }
+    const MetWeights mw(R.n, S.r, S.cnt_gt, S.cnt_eq, S.thr);
+    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < R.n;
+         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+        mw.put(R, i, R.ylt[i]);
 }
 
 __global__ void k_met_vjp(const double *__restrict__ w, int64_t n, int n_layers, const double *__restrict__ g,
@@ -606,6 +737,25 @@ extern "C" int32_t ara_metrics(const double *ylt, int32_t n_layers, int64_t n, d
     MetState *state = c.take<MetState>(static_cast<size_t>(n_layers));
     MetPart *part = c.take<MetPart>(static_cast<size_t>(n_layers) * nwg);
     uint64_t *cand = c.take<uint64_t>(static_cast<size_t>(n_layers) * n);
+    if (n_layers > 0 && nwg == 1) {
+        ProfScope prof(ARA_PROF_METRICS, st);
+        MetCall call{};
+        call.ylt = ylt;
+        call.out = out;
+        call.w = weights;
+        call.n = n;
+        call.r = met_rank(n, p);
+        call.nwg = 1;
+        call.n_rows = n_layers;
+        call.hist = hist;
+        call.st = state;
+        call.part = part;
+        call.cand = cand;
+        call.hdr = hdr;
+        k_met_small<<<dim3(1, static_cast<unsigned>(n_layers)), kMetThreads, 0, st>>>(call);
+        ARA_HIP(hipGetLastError());
+        return ARA_OK;
+    }
     // header, histograms and states are contiguous: clear them at once
     const size_t clear = reinterpret_cast<char *>(part) - reinterpret_cast<char *>(hdr);
     ARA_HIP(hipMemsetAsync(hdr, 0, clear, st));

@@ -326,6 +326,29 @@ def test_metrics_subnormal_and_zero_bins(ara):
         np.testing.assert_array_equal(wts, oracle.metric_weights(y, p))
 
 
+@pytest.mark.parametrize("n", [1, 2, 1025, 8191, 8192, 8193])
+@pytest.mark.parametrize("kind", ["spread", "tied", "zero", "subnormal"])
+def test_metrics_around_one_workgroup(ara, n, kind):
+    """Rows of up to 8192 values are selected by one workgroup in one kernel,
+    longer ones by passes over the row."""
+    import torch
+    g = np.random.default_rng(n)
+    y = g.lognormal(15, 2, size=(2, n))
+    if kind == "tied":
+        y = np.minimum(y, np.quantile(y, 0.7))
+    elif kind == "zero":
+        y[:, g.random(n) < 0.97] = 0.0
+    elif kind == "subnormal":
+        y[0] = np.ldexp(g.integers(0, 1 << 50, size=n).astype(np.float64), -1074)
+    for p in [0.01, 0.5, 0.99]:
+        out, wts = ara.metrics(torch.tensor(y, device="cuda"), p, want_weights=True)
+        out, wts = out.cpu().numpy(), wts.cpu().numpy()
+        ref = oracle.metrics(y, p)
+        assert np.array_equal(out[:, 1], ref[:, 1])
+        np.testing.assert_allclose(out[:, [0, 2]], ref[:, [0, 2]], rtol=TOL, atol=0)
+        np.testing.assert_array_equal(wts, oracle.metric_weights(y, p))
+
+
 def test_metrics_repeatable_and_layers_independent(ara):
     """Same answer twice (order-free gathering) and each layer as if alone."""
     import torch
