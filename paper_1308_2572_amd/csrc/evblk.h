@@ -13,6 +13,8 @@
 //           found by the numbers in its entries
 //   dense   the first entry of every event (4 bytes per event): lists long
 //           enough that the lengths would not fit four bits
+// A YET prepared with positions holds, in the entries' order, each
+// occurrence's position in its trial too.
 // A kernel that needs only some events (those with a loss in a layer: a few
 // per cent of the catalogue) reads only their lists.
 #pragma once
@@ -32,6 +34,7 @@ enum { kMiscErr = 0, kMiscMaxOcc = 1, kMiscLong = 3, kMiscCodes = 4, kMiscMaxLen
 
 struct EvBlocks {
     const uint16_t *ent;     // [nnz + kEvPad]
+    const uint16_t *pos;     // [nnz + kEvPad] position in the trial of each entry, or null
     const uint2 *hdr;        // sparse form: [neb][ng], the last group of a block holds its end
     const uint32_t *start;   // dense form: [neb][catalog + 1]
     const int64_t *base;     // [neb + 1] first entry of each block
@@ -112,6 +115,7 @@ struct EvBuild {
     int32_t catalog;
     // the layout
     uint16_t *ent;
+    uint16_t *pos;         // or null
     uint2 *hdr;
     uint32_t *start;
     int64_t *base;
@@ -119,6 +123,7 @@ struct EvBuild {
     int32_t *t_ids;        // the copy of the IDs to write alongside, or null
     // scratch
     uint32_t *rec;         // [nnz]
+    uint16_t *rpos;        // [nnz] with pos
     uint16_t *tstart;      // [n_chunks][n_tiles + 1]
     uint32_t *tbase;       // [neb][n_tiles + 1]
     uint32_t *mark;        // [n_marks]

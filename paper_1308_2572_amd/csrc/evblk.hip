@@ -10,6 +10,9 @@
 // then gathered from the blocks (2.8 ms; scattering each entry to its place
 // cost one memory write per entry: 26.7 ms), and the events' counts from the
 // headers (0.24 ms; from the code stream, one workgroup per range, 8.7 ms).
+// With positions each record carries its occurrence's position through both
+// levels beside it, in half the workgroups per CU (250,000 x 1000: 0.88 and
+// 1.2 ms).
 #include "evblk.h"
 
 #include <algorithm>
@@ -89,8 +92,10 @@ __device__ __forceinline__ int64_t ev_chunk0(const int64_t *base, int b) { retur
 // One workgroup per chunk: records (trial in the block << 14 | event in the
 // tile) sorted by tile inside LDS, each tile's start in the chunk, and the
 // copy of the IDs.
-__global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ev_part(EvBuild B) {
+template <bool POS>
+__global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(POS ? 4 : 8, 8))) void k_ev_part(EvBuild B) {
     __shared__ uint32_t srec[kEvChunk];
+    __shared__ uint16_t spos[POS ? kEvChunk : 1];
     __shared__ uint32_t cnt[kEvWin];
     __shared__ uint32_t wsum[kEvWaves];
     __shared__ int32_t s_b;
@@ -155,6 +160,15 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     uint32_t tr[kEvItems];
 #pragma unroll
     for (int s = 0; s < kEvItems; ++s) tr[s] = srec[kw + s * kWave + lane];
+    uint32_t at[POS ? kEvItems : 1];   // positions in the trial
+    if (POS) {
+        const int64_t *first = B.off + static_cast<int64_t>(b) * B.g.et;
+#pragma unroll
+        for (int s = 0; s < kEvItems; ++s) {
+            const int k = kw + s * kWave + lane;
+            at[s] = id[s] >= 0 ? static_cast<uint32_t>(ks + k - first[tr[s]]) : 0u;
+        }
+    }
     if (tcopy)
 #pragma unroll
         for (int s = 0; s < kEvItems; ++s)
@@ -186,21 +200,24 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
         }
         if (lane == kWave - 1) wsum[w] = incl;
         __syncthreads();
-        uint32_t at = woff + incl - c, all = 0;
+        uint32_t to = woff + incl - c, all = 0;
         for (int v = 0; v < kEvWaves; ++v) {
-            at += v < w ? wsum[v] : 0u;
+            to += v < w ? wsum[v] : 0u;
             all += wsum[v];
         }
-        cnt[tid] = at;
-        if (tid < wn) ts[w0 + tid] = static_cast<uint16_t>(at);
+        cnt[tid] = to;
+        if (tid < wn) ts[w0 + tid] = static_cast<uint16_t>(to);
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < kEvItems; ++s) {
             int v = id[s];
             keep_apart(v);
             const int r = (v >> B.g.te_bits) - w0;
-            if (v >= 0 && r >= 0 && r < wn)
-                srec[atomicAdd(&cnt[r], 1u)] = (tr[s] << kEvSlotBits) | (static_cast<uint32_t>(v) & emask);
+            if (v >= 0 && r >= 0 && r < wn) {
+                const uint32_t to = atomicAdd(&cnt[r], 1u);
+                srec[to] = (tr[s] << kEvSlotBits) | (static_cast<uint32_t>(v) & emask);
+                if (POS) spos[to] = static_cast<uint16_t>(at[s]);
+            }
         }
         woff += all;
         __syncthreads();
@@ -208,6 +225,10 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     if (tid == 0) ts[B.g.n_tiles] = static_cast<uint16_t>(woff);
     uint32_t *dst = B.rec + ks + lo;
     for (uint32_t i = tid; i < woff; i += kEvThreads) dst[i] = srec[i];
+    if (POS) {
+        uint16_t *pdst = B.rpos + ks + lo;
+        for (uint32_t i = tid; i < woff; i += kEvThreads) pdst[i] = spos[i];
+    }
 }
 
 // Each block's first entry of every tile (relative to the block).
@@ -250,7 +271,8 @@ __global__ __launch_bounds__(1024) void k_ev_tiles(EvBuild B) {
 // entries placed in LDS and written out in order.  A tile of at most kSortCap
 // records is read once (held in registers between counting and placing); a
 // larger one is read twice and its entries are stored directly.
-__global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ev_sort(EvBuild B) {
+template <bool POS>
+__global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(POS ? 4 : 8, 8))) void k_ev_sort(EvBuild B) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int te = 1 << B.g.te_bits;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(smem);                       // [te]
@@ -258,6 +280,7 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
     uint32_t *rsrc = rcum + kSortRuns + 1;                                    // [kSortRuns] each run's first record in the block
     uint32_t *wsum = rsrc + kSortRuns;                                        // [kEvWaves]
     uint16_t *out = reinterpret_cast<uint16_t *>(wsum + kEvWaves);            // [kSortCap]
+    uint16_t *outp = out + kSortCap;                                          // [kSortCap] with positions
     if (ev_failed(B.misc)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = static_cast<int>(uni32(tid >> 6));
@@ -314,9 +337,12 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
         return lo;
     };
     const uint32_t *rec = B.rec + o0;
+    const uint16_t *rpos = POS ? B.rpos + o0 : nullptr;
     uint16_t *ent = B.ent + o0 + t0;
+    uint16_t *pos = POS ? B.pos + o0 + t0 : nullptr;
     const bool in_regs = total <= static_cast<uint32_t>(kSortCap) && c1 - c0 <= kSortRuns;   // uniform
     uint32_t rv[kSortItems];
+    uint16_t pv[POS ? kSortItems : 1];
     if (in_regs) {
         const int n = static_cast<int>(c1 - c0);
         list_runs(c0, n);
@@ -335,7 +361,11 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                     ++r;
                     my += i >= next ? 1 : 0;
                 }
-                if (i < total) rv[s] = rec[rsrc[my] + (i - rcum[my])];
+                if (i < total) {
+                    const uint32_t from = rsrc[my] + (i - rcum[my]);
+                    rv[s] = rec[from];
+                    if (POS) pv[s] = rpos[from];
+                }
             }
         }
 #pragma unroll
@@ -405,10 +435,14 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
         for (int s = 0; s < kSortItems; ++s) {
             if (rv[s] != ~0u) {
                 const uint32_t e = rv[s] & ((1u << kEvSlotBits) - 1u);
-                out[atomicAdd(&cnt[e], 1u)] = static_cast<uint16_t>(((e & 7u) << kEvTrialBits) | (rv[s] >> kEvSlotBits));
+                const uint32_t to = atomicAdd(&cnt[e], 1u);
+                out[to] = static_cast<uint16_t>(((e & 7u) << kEvTrialBits) | (rv[s] >> kEvSlotBits));
+                if (POS) outp[to] = pv[s];
             }
         }
         __syncthreads();
+        if (POS)
+            for (uint32_t i = tid; i < total; i += kEvThreads) pos[i] = outp[i];
         // two entries per store once the place is even
         const uint32_t odd = static_cast<uint32_t>((o0 + t0) & 1);
         if (odd && tid == 0 && total > 0) ent[0] = out[0];
@@ -428,9 +462,12 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(8, 8
                     if (rcum[mid] <= i) lo = mid;
                     else hi = mid;
                 }
-                const uint32_t v = rec[rsrc[lo] + (i - rcum[lo])];
+                const uint32_t from = rsrc[lo] + (i - rcum[lo]);
+                const uint32_t v = rec[from];
                 const uint32_t e = v & ((1u << kEvSlotBits) - 1u);
-                ent[atomicAdd(&cnt[e], 1u)] = static_cast<uint16_t>(((e & 7u) << kEvTrialBits) | (v >> kEvSlotBits));
+                const uint32_t to = atomicAdd(&cnt[e], 1u);
+                ent[to] = static_cast<uint16_t>(((e & 7u) << kEvTrialBits) | (v >> kEvSlotBits));
+                if (POS) pos[to] = rpos[from];
             }
         }
     }
@@ -440,12 +477,15 @@ int32_t ev_build(const EvBuild &B, hipStream_t st) {
     if (B.g.neb <= 0) return ARA_OK;
     const unsigned gm = static_cast<unsigned>(std::min<int64_t>((std::max<int64_t>(B.n_trials, B.g.neb + 1) + 255) / 256, 4096));
     k_ev_marks<<<gm, 256, 0, st>>>(B);
-    k_ev_part<<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
+    if (B.pos) k_ev_part<true><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
+    else k_ev_part<false><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
     k_ev_tiles<<<static_cast<unsigned>(B.g.neb), 1024, 0, st>>>(B);
-    const size_t lds = ((size_t(1) << B.g.te_bits) + 2 * kSortRuns + 1 + kEvWaves) * sizeof(uint32_t) + kSortCap * sizeof(uint16_t);
-    ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_ev_sort), hipFuncAttributeMaxDynamicSharedMemorySize,
+    const size_t lds = ((size_t(1) << B.g.te_bits) + 2 * kSortRuns + 1 + kEvWaves) * sizeof(uint32_t) +
+                       (B.pos ? 2 : 1) * kSortCap * sizeof(uint16_t);
+    const auto sort = B.pos ? k_ev_sort<true> : k_ev_sort<false>;
+    ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sort), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(lds)));
-    k_ev_sort<<<static_cast<unsigned>(B.g.neb) * static_cast<unsigned>(B.g.n_tiles), kEvThreads, lds, st>>>(B);
+    sort<<<static_cast<unsigned>(B.g.neb) * static_cast<unsigned>(B.g.n_tiles), kEvThreads, lds, st>>>(B);
     ARA_HIP(hipGetLastError());
     return ARA_OK;
 }

@@ -75,13 +75,13 @@ struct Prepared {
     int32_t *t_ids, *t_cnt;
     uint16_t *pos;
     // event-ordered blocks
-    uint16_t *ent;
+    uint16_t *ent, *ev_pos;
     uint2 *hdr;
     uint32_t *start;
     int64_t *ev_base;
     // scratch of the preparation
     uint32_t *rec, *rsum;
-    uint16_t *rpos, *rstart;
+    uint16_t *rpos, *rstart, *ev_rpos;
     int64_t *bsum;
     uint16_t *tstart;
     uint32_t *tbase, *mark;
@@ -129,6 +129,10 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     p.tstart = c.take<uint16_t>(static_cast<size_t>(eg.n_chunks) * static_cast<size_t>(eg.n_tiles + 1));
     p.tbase = c.take<uint32_t>(neb * static_cast<size_t>(eg.n_tiles + 1));
     p.mark = c.take<uint32_t>(static_cast<size_t>(eg.n_marks));
+    if (flags & ARA_PREP_POSITIONS) {
+        p.ev_pos = c.take<uint16_t>(occ + kEvPad);
+        p.ev_rpos = c.take<uint16_t>(occ);
+    }
     return p;
 }
 
@@ -673,6 +677,7 @@ bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
     const Prepared p = carve(c, g, yet->n_trials, yet->nnz, yet->catalog, flags);
     const EvGeometry eg = ev_geometry(yet->n_trials, yet->nnz, yet->catalog);
     out->ent = p.ent;
+    out->pos = p.ev_pos;
     out->hdr = p.hdr;
     out->start = p.start;
     out->base = p.ev_base;
@@ -825,6 +830,8 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     E.nnz = nnz;
     E.catalog = catalog;
     E.ent = p.ent;
+    E.pos = p.ev_pos;
+    E.rpos = p.ev_rpos;
     E.hdr = p.hdr;
     E.start = p.start;
     E.base = p.ev_base;

@@ -9,18 +9,19 @@
 //   * a scan of those counts and a fill pass lay out, per union event and in
 //     the layer's listed ELT order, one entry per ELT holding it: the
 //     lognormal's parameters (m, s), the mean, the ELT's position and index;
-//   * the streaming kernel walks the trial-major YET (the occurrence index
-//     keys the draws, so storage order matters): one wavefront per trial, a
-//     1-Mbit LDS filter of the union, a queue of union occurrences drawn 64
-//     at a time: the draws of each one's entries, the ELT terms (step two)
-//     summed in listed order, the occurrence terms (step three); the trial's
-//     occurrence losses meet in a DPP wavefront sum and the aggregate terms
-//     give the year loss (step four, telescoped).
+//   * k_su_ev reads the lists of the union events in the YET's event-ordered
+//     blocks, with each occurrence's position in its trial (the occurrence
+//     index keys the draw), queues them and draws 64 at a time: the draws of
+//     each one's entries, the ELT terms (step two) summed in listed order, the
+//     occurrence terms (step three), added to its trial's total in integers;
+//     the aggregate terms give the year loss (step four, telescoped).  Layers
+//     without finite limits are served by k_su_fwd from the code stream.
 // The draw: Philox4x32-10 (Salmon, Moraes, Dror and Shaw, SC'11) block of
 // counter words (occurrence low, high, ELT index, 0) under key words (seed
 // low, high); two uniforms from the top 52 bits of the word pairs (w1 w0)
 // and (w3 w2), Box-Muller, x = exp(m + s z), with the logarithm, cosine and
 // exponential of su_math.h.
+#include "evblk.h"
 #include "occ.h"
 #include "su_math.h"
 #include "wave.h"
@@ -126,15 +127,56 @@ __device__ T block_exclusive_scan(const T *in, T *out, int n, T *wsum) {
     return total;
 }
 
+// How a layer's occurrence losses are added up where the YET has
+// event-ordered blocks.  None exceeds B = min(occurrence limit, sum of the
+// ELT limits) <= 2^e, so in units of 2^(e - 46) a trial's (at most 65536)
+// add up to less than 2^62, and the 48 bits below the unit of each to less
+// than 2^64: two integers per trial, and a total that does not depend on the
+// order.  What a loss holds below 2^(e - 94) is rounded away: less than 2^-54
+// of every loss of at least 2^-16 of the smallest (scaled) mean, which a
+// layer has to have above 2^(e - 24).  gexp is e - 46; mode 0: some layer's
+// terms or means do not fit this (no finite limit, for one), and the stream
+// of the codes serves it.
+struct SuBound {
+    double most;      // B
+    uint32_t least;   // bitwise complement of the smallest positive scaled mean, a binary32 value rounded down (0: none)
+    uint32_t pad;
+};
+
+__device__ __forceinline__ EvLayer su_form(const SuBound &b) {
+    EvLayer f{};
+    if (!(b.most >= 0.0) || !(b.most < 0x1p900)) return f;
+    int e = 0;
+    frexp(b.most, &e);
+    f.gexp = e - 46;
+    f.frac = 48;
+    const double low = static_cast<double>(__uint_as_float(~b.least));   // NaN without a positive mean
+    f.mode = e > -800 && !(low < ldexp(1.0, e - 24));
+    return f;
+}
+
 // Per layer: union-rank bases of the super-ranges (ubase, from the
 // occurrence table's counts) and bases of their further entries (obase,
-// after all first entries); every entry must fit the layer's capacity.
+// after all first entries); every entry must fit the layer's capacity.  Also
+// the bound of an occurrence's loss.
 __global__ __launch_bounds__(kSuThreads) void k_su_base(const OccTables *__restrict__ tabs, const uint32_t *__restrict__ otot,
                                                         int n_sr, const uint64_t *__restrict__ ecap,
                                                         uint32_t *__restrict__ ubase, uint32_t *__restrict__ obase,
-                                                        uint64_t *__restrict__ eused, int32_t *__restrict__ err) {
+                                                        uint64_t *__restrict__ eused, int32_t *__restrict__ err,
+                                                        const int32_t *__restrict__ elt_off,
+                                                        const int32_t *__restrict__ elt_ids,
+                                                        const double *__restrict__ elt_terms,
+                                                        const double *__restrict__ layer_terms,
+                                                        SuBound *__restrict__ bound) {
     __shared__ uint32_t wsum[kSuThreads / kWave];
     const int j = blockIdx.x;
+    if (threadIdx.x < kWave) {
+        double b = 0.0;
+        for (int q = elt_off[j] + threadIdx.x; q < elt_off[j + 1]; q += kWave) b += elt_terms[3 * elt_ids[q] + 2];
+        for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o);
+        const double occL = layer_terms[4 * j + 1];
+        if (threadIdx.x == 0) bound[j].most = b < occL ? b : occL;
+    }
     const OccTables T = tabs[j];
     uint32_t *ub = ubase + static_cast<size_t>(j) * (n_sr + 1);
     uint32_t *ob = obase + static_cast<size_t>(j) * n_sr;
@@ -166,7 +208,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
                                                         const uint32_t *__restrict__ obase,
                                                         const uint64_t *__restrict__ ecap,
                                                         const uint64_t *__restrict__ eregion,
-                                                        SuEntry *__restrict__ ent) {
+                                                        SuEntry *__restrict__ ent, int32_t *__restrict__ uev) {
     __shared__ int32_t lk[kSuMaxJ];
     const int s = blockIdx.x / kSuFillChunks, p = blockIdx.x % kSuFillChunks, j = blockIdx.y;
     const int tid = threadIdx.x;
@@ -194,6 +236,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
         const uint64_t next = static_cast<uint64_t>(ob) + oo[r];
         uint64_t o = first;
         int h = 0;
+        if (first < cap) uev[eregion[j] + first] = static_cast<int32_t>(ev);
         // eight ELTs at a time: their presence words loaded together, then
         // the losses and deviations of the present ones, then the entries in
         // listed order
@@ -239,16 +282,21 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
 // Per layer: each entry's lognormal parameters from its mean and deviation,
 // s^2 = ln(1 + sigma^2/mu^2), m = ln mu - s^2/2 (0, 0 for an exact entry), one
 // thread per entry so that the binary64 logarithms run on full wavefronts.
+// Also the smallest positive scaled mean of the layer's records.
 __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ eregion,
                                                    const uint64_t *__restrict__ ecap,
-                                                   const uint64_t *__restrict__ eused, SuEntry *__restrict__ ent) {
+                                                   const uint64_t *__restrict__ eused, SuEntry *__restrict__ ent,
+                                                   const double *__restrict__ elt_terms, SuBound *__restrict__ bound) {
     const int j = blockIdx.y;
     const uint64_t cap = ecap[j], used = eused[j];
     if (used > cap) return;   // nothing laid out (flagged by k_su_base)
     SuEntry *E = ent + eregion[j];
+    uint32_t low = 0;
     for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < used;
          i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
         SuEntry &e = E[i];
+        const double sm = elt_terms[3 * e.k] * static_cast<double>(e.mu);
+        if (sm > 0.0) low = max(low, ~__float_as_uint(__double2float_rd(sm)));
         if (e.exact) continue;
         const double mu = static_cast<double>(e.mu);
         const double rr = e.s / mu;
@@ -256,6 +304,13 @@ __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ 
         e.m = log(mu) - 0.5 * s2;
         e.s = sqrt(s2);
     }
+    for (int o = 32; o > 0; o >>= 1) low = max(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), o)));
+    __shared__ uint32_t most;   // one atomic per workgroup, and few of those: most workgroups' is no news
+    if (threadIdx.x == 0) most = 0u;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0 && low != 0u) atomicMax(&most, low);
+    __syncthreads();
+    if (threadIdx.x == 0 && most > *static_cast<volatile uint32_t *>(&bound[j].least)) atomicMax(&bound[j].least, most);
 }
 
 // ---------------------------------------------------------------------------
@@ -360,6 +415,7 @@ struct SuParams {
     const double *elt_terms, *layer_terms;
     uint64_t seed;
     double *ylt, *s_pre;
+    const SuBound *bound;        // [n_layers] with event-ordered blocks, or null
 };
 
 // Workgroup i's block (relative to b0) and layer: with one layer, block i;
@@ -401,6 +457,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fwd(SuParams P) {
     // call reports ARA_E_LIMIT): nothing of it is read or written
     const uint64_t cap = P.ecap[j];
     if (P.eused[j] > cap) return;
+    if (P.bound && su_form(P.bound[j]).mode) return;   // k_su_ev's
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tb = P.tb, G = P.n_ranges;
@@ -578,6 +635,286 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fwd(SuParams P) {
 }
 
 // ---------------------------------------------------------------------------
+// Event-ordered kernel: the union events' lists (evblk.h).
+//
+// The draw is bound by its arithmetic (some 250 instructions, 51 of them
+// binary64 multiply-adds); walking the codes spent 37 more on every
+// occurrence of the YET to find the one in seven whose event is in the union.
+// Here only the lists of union events are read.  One workgroup per (layer,
+// block, part): the block's totals (16 bytes a trial, at most 128 KB) leave
+// room for one workgroup on a CU; its 16 wavefronts take 64 union events at a
+// time, one per lane, whose lists' entries and positions go to the
+// wavefront's queue one step after another, the next unit's loads in flight;
+// 64 queued occurrences are drawn together as in the stream.  250,000 x 1000
+// over 2M events, 15 ELTs of 20,000 (37.5M draws): 576 us, 230M vector
+// instructions, where the stream takes 916 us and 326M.  With each entry
+// loaded one step ahead of its use 619 us.
+
+constexpr int kSuEvQCap = 128;                    // fewer than 64 waiting + one step's
+constexpr uint32_t kSuLongList = 256;             // lists beyond this many entries are queued by the whole wavefront
+
+struct SuEvParams {
+    EvBlocks B;
+    SuParams s;
+    const int32_t *uev;          // event of each union index, by the layers' regions
+    int32_t b0, nb, parts, pad;
+    unsigned char *partial;      // [n_layers][nb][parts] slots of su_slot_bytes, when parts > 1
+};
+
+// Eight 16-bit words.
+struct __attribute__((packed, aligned(2))) SuPiece {
+    uint32_t a[4];
+    __device__ __forceinline__ void drop() {   // the first
+        a[0] = __builtin_amdgcn_alignbit(a[1], a[0], 16);
+        a[1] = __builtin_amdgcn_alignbit(a[2], a[1], 16);
+        a[2] = __builtin_amdgcn_alignbit(a[3], a[2], 16);
+        a[3] >>= 16;
+    }
+};
+
+__host__ __device__ inline size_t su_slot_bytes(int et) { return static_cast<size_t>(et) * 16; }
+
+__global__ __launch_bounds__(kSuThreads) void k_su_ev(SuEvParams Q) {
+    const SuParams &P = Q.s;
+    __shared__ unsigned long long hi[kEvMaxTrials], lo[kEvMaxTrials];
+    __shared__ uint2 q_es[kGroups][kSuEvQCap];           // as in the stream
+    __shared__ double ls[kSuMaxJ], lr[kSuMaxJ], ll[kSuMaxJ];
+    // the layers of one (block, part) run one after another on one XCD
+    const int x = blockIdx.x & (kXcds - 1), k = blockIdx.x / kXcds;
+    const int j = k % P.n_layers;
+    const int item = (k / P.n_layers) * kXcds + x;
+    const int bi = item / Q.parts, part = item - bi * Q.parts;
+    if (bi >= Q.nb) return;   // uniform, before any barrier
+    const uint64_t cap = P.ecap[j];
+    if (P.eused[j] > cap) return;   // uniform: nothing laid out
+    const EvLayer L = su_form(P.bound[j]);
+    if (!L.mode) return;            // uniform: the stream's
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = Q.b0 + bi;
+    const int64_t bt0 = static_cast<int64_t>(b) * Q.B.et;
+    const int nt = static_cast<int>(min<int64_t>(Q.B.et, Q.B.n_trials - bt0));
+    const int i0 = static_cast<int>(max<int64_t>(P.t0 - bt0, 0)), i1 = static_cast<int>(min<int64_t>(P.t1 - bt0, nt));
+    for (int i = tid; i < nt; i += kSuThreads) {
+        hi[i] = 0ull;
+        lo[i] = 0ull;
+    }
+    const int a0 = P.elt_off[j], J = P.elt_off[j + 1] - a0;
+    for (int q = tid; q < J; q += kSuThreads) {
+        const int e = P.elt_ids[a0 + q];
+        ls[q] = P.elt_terms[3 * e + 0];
+        lr[q] = P.elt_terms[3 * e + 1];
+        ll[q] = P.elt_terms[3 * e + 2];
+    }
+    const uint64_t region = P.eregion[j];
+    const SuEntry *E = P.ent + region;
+    const int32_t *uev = Q.uev + region;
+    const int n_union = static_cast<int>(P.ubase[static_cast<size_t>(j) * (P.n_sr + 1) + P.n_sr]);
+    const double occR = P.layer_terms[4 * j + 0], occL = P.layer_terms[4 * j + 1];
+    const double up = ldexp(1.0, -L.gexp);
+    const uint16_t *ent = Q.B.ent + Q.B.base[b], *pos = Q.B.pos + Q.B.base[b];
+    const uint2 *hdr = Q.B.dense ? nullptr : Q.B.hdr + static_cast<size_t>(b) * Q.B.ng;
+    const uint32_t *start = Q.B.dense ? Q.B.start + static_cast<size_t>(b) * (Q.B.catalog + 1) : nullptr;
+    const int64_t *toff = P.t_off + bt0;
+    const int n_units = (n_union + kWave - 1) / kWave;
+    const int u0 = static_cast<int>(static_cast<int64_t>(n_units) * part / Q.parts);
+    const int u1 = static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / Q.parts);
+    __syncthreads();
+
+    uint2 *qes = q_es[w];
+    int qh = 0, qlen = 0;   // uniform: the queue's head slot and length
+    auto wrap = [](int v) { return v & (kSuEvQCap - 1); };
+    bool pend = false;
+    uint32_t pe = 0;
+    int pleft = 0;
+    int64_t pi = 0;
+    int ps = 0;
+    double px = 0.0;
+    // one draw per lane, as in the stream
+    auto round = [&]() {
+        const uint64_t freem = __ballot(!pend);
+        const int rank = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+            static_cast<uint32_t>(freem >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(freem), 0u)));
+        const int taken = min(qlen, static_cast<int>(__popcll(freem)));   // uniform
+        const bool take = !pend && rank < taken;
+        const bool act = take || pend;
+        const uint2 es = qes[wrap(qh + (take ? rank : 0))];
+        const int slot = take ? static_cast<int>(es.y >> 16) : ps;
+        const uint32_t ei = take ? es.x : (pend ? pe : 0u);
+        const SuEntry en = su_entry(E + ei);
+        const int64_t i = take ? toff[slot] + static_cast<int64_t>(es.y & 0xFFFFu) : pi;
+        const double v = su_draw(en, P.seed, i);
+        const double g = xl(ls[en.q] * v, lr[en.q], ll[en.q]);
+        const int left = take ? (static_cast<uint64_t>(en.next) + en.more <= cap ? en.more : 0) : pleft - 1;
+        px = act ? (take ? g : px + g) : px;
+        pi = i;
+        ps = slot;
+        pe = take ? en.next : pe + (act ? 1u : 0u);
+        pleft = act ? left : pleft;
+        const bool done = act && left <= 0;
+        pend = act && left > 0;
+        if (done) {
+            const double o = xl(px, occR, occL) * up;
+            const unsigned long long h = static_cast<unsigned long long>(o);
+            atomicAdd(&hi[ps], h);
+            atomicAdd(&lo[ps], static_cast<unsigned long long>(rint((o - static_cast<double>(h)) * 0x1p48)));
+        }
+        qh = wrap(qh + taken);
+        qlen -= taken;
+    };
+
+    // lane's union event of unit u (-1: none), its header, its list's first
+    // entry and length
+    auto load_ev = [&](int u) -> int {
+        const int i = u * kWave + lane;
+        return u < u1 && i < n_union ? uev[i] : -1;
+    };
+    auto load_hdr = [&](int ev) -> uint2 {
+        const int e = max(ev, 0);   // event 0's header (always there) for lanes without one
+        if (Q.B.dense) return make_uint2(start[e], start[e + 1]);
+        return hdr[e >> 3];
+    };
+    auto find = [&](int ev, uint2 h, uint32_t &s, uint32_t &c) {
+        const uint32_t n8 = static_cast<uint32_t>(ev) & 7u;
+        if (Q.B.dense) {
+            s = h.x;
+            c = h.y - h.x;
+        } else {
+            ev_short_list(h, n8, s, c);
+            if (ev >= 0 && ev_long(h.y)) {
+                const uint32_t all = hdr[(ev >> 3) + 1].x - h.x;
+                const uint32_t f = ev_lower(ent + h.x, all, n8), z = ev_lower(ent + h.x, all, n8 + 1u);
+                s = h.x + f;
+                c = z - f;
+            }
+        }
+        if (ev < 0) c = 0;
+    };
+    // a list's entries and positions eight at a time (the arrays are padded
+    // past their ends)
+    auto load8 = [&](uint32_t at, SuPiece &e, SuPiece &p) {
+        e = *reinterpret_cast<const SuPiece *>(ent + at);
+        p = *reinterpret_cast<const SuPiece *>(pos + at);
+    };
+    // Unit u's lists are found and their first eight entries loaded while the
+    // unit before is walked, the headers a unit earlier, the events one more.
+    int u = u0 + w;
+    uint32_t sn = 0, cn = 0;     // unit u's list
+    SuPiece en{}, pn{};          // its first entries
+    int ev1 = load_ev(u), ev2 = load_ev(u + kGroups);
+    uint2 h1 = load_hdr(ev1);
+    auto ahead = [&]() {
+        find(ev1, h1, sn, cn);
+        if (cn > 0) load8(sn, en, pn);
+        ev1 = ev2;
+        h1 = load_hdr(ev1);
+        ev2 = load_ev(u + 2 * kGroups);
+    };
+    ahead();
+    // the lists being walked: entry i of the lane's, i < c, from s on, of
+    // union index ui.  Long ones (from sl on, cl entries) are walked one at a
+    // time by the whole wavefront after the unit's others: entry i is then s +
+    // 64 i.
+    uint32_t s = 0, c = 0, i = 0, ui = 0, sl = 0, cl = 0;
+    SuPiece e8{}, p8{};
+    uint64_t big = 0;
+    bool wide = false;           // uniform: a long list
+    // moves on to the next lists; false when there are none
+    auto next = [&]() -> bool {
+        i = 0;
+        if (big) {   // uniform
+            const int l = __builtin_ctzll(big);
+            big &= big - 1;
+            const uint32_t n = __shfl(cl, l);
+            s = __shfl(sl, l) + static_cast<uint32_t>(lane);
+            c = n > static_cast<uint32_t>(lane) ? (n - static_cast<uint32_t>(lane) + kWave - 1) / kWave : 0u;
+            ui = static_cast<uint32_t>((u - kGroups) * kWave + l);
+            wide = true;
+            return true;
+        }
+        if (u >= u1) return false;
+        wide = false;
+        s = sl = sn;
+        cl = cn;
+        e8 = en;
+        p8 = pn;
+        big = __ballot(cl > kSuLongList);
+        c = cl > kSuLongList ? 0u : cl;
+        ui = static_cast<uint32_t>(u * kWave + lane);
+        u += kGroups;
+        ahead();
+        return true;
+    };
+    bool more = next();   // uniform
+    for (;;) {
+        const int tr = static_cast<int>(e8.a[0] & kEvTrialMask);
+        const bool on = more && i < c && tr >= i0 && tr < i1;
+        const uint2 es = make_uint2(ui, (static_cast<uint32_t>(tr) << 16) | (p8.a[0] & 0xFFFFu));
+        ++i;
+        if (more && !__any(i < c)) more = next();
+        else e8.drop(), p8.drop();
+        if (wide) {
+            if (i < c) {
+                e8.a[0] = ent[static_cast<size_t>(s) + static_cast<size_t>(i) * kWave];
+                p8.a[0] = pos[static_cast<size_t>(s) + static_cast<size_t>(i) * kWave];
+            }
+        } else if (i > 0 && (i & 7u) == 0u) {   // uniform
+            if (i < c) load8(s + i, e8, p8);
+        }
+        const uint64_t m = __ballot(on);
+        if (on)
+            qes[wrap(qh + qlen + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                                      static_cast<uint32_t>(m >> 32),
+                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u))))] = es;
+        qlen += static_cast<int>(__popcll(m));
+        __builtin_amdgcn_wave_barrier();
+        while (qlen >= kWave || (!more && (qlen > 0 || __ballot(pend) != 0ull))) round();
+        if (!more) break;
+    }
+    __syncthreads();
+    if (Q.parts > 1) {
+        unsigned long long *p = reinterpret_cast<unsigned long long *>(
+            Q.partial + ((static_cast<size_t>(j) * Q.nb + bi) * Q.parts + part) * su_slot_bytes(Q.B.et));
+        for (int t = tid; t < nt; t += kSuThreads) {
+            p[t] = hi[t];
+            p[Q.B.et + t] = lo[t];
+        }
+        return;
+    }
+    const double aggR = P.layer_terms[4 * j + 2], aggL = P.layer_terms[4 * j + 3];
+    const size_t row = static_cast<size_t>(j) * static_cast<size_t>(P.t1 - P.t0);
+    for (int t = i0 + tid; t < i1; t += kSuThreads) {
+        const double S = ev_total(hi[t], lo[t], L);
+        const size_t o = row + static_cast<size_t>(bt0 + t - P.t0);
+        P.ylt[o] = xl(S, aggR, aggL);
+        if (P.s_pre) P.s_pre[o] = S;
+    }
+}
+
+// The results from the parts' totals: 256 trials of a (layer, block) per
+// workgroup.
+__global__ __launch_bounds__(256) void k_su_add(SuEvParams Q, int per) {
+    const SuParams &P = Q.s;
+    const int k = blockIdx.x / per, t = (blockIdx.x - k * per) * 256 + static_cast<int>(threadIdx.x);
+    const int j = k / Q.nb, bi = k - j * Q.nb;
+    if (P.eused[j] > P.ecap[j]) return;
+    const EvLayer L = su_form(P.bound[j]);
+    const int64_t tt = static_cast<int64_t>(Q.b0 + bi) * Q.B.et + t;
+    if (!L.mode || t >= Q.B.et || tt < P.t0 || tt >= P.t1) return;
+    const unsigned char *p = Q.partial + static_cast<size_t>(k) * Q.parts * su_slot_bytes(Q.B.et);
+    unsigned long long h = 0, l = 0;
+#pragma unroll 4
+    for (int q = 0; q < Q.parts; ++q, p += su_slot_bytes(Q.B.et)) {
+        h += reinterpret_cast<const unsigned long long *>(p)[t];
+        l += reinterpret_cast<const unsigned long long *>(p)[Q.B.et + t];
+    }
+    const double S = ev_total(h, l, L);
+    const size_t o = static_cast<size_t>(j) * static_cast<size_t>(P.t1 - P.t0) + static_cast<size_t>(tt - P.t0);
+    P.ylt[o] = xl(S, P.layer_terms[4 * j + 2], P.layer_terms[4 * j + 3]);
+    if (P.s_pre) P.s_pre[o] = S;
+}
+
+// ---------------------------------------------------------------------------
 // Workspace.
 
 struct SuLayout {
@@ -624,6 +961,10 @@ static size_t su_workspace(const ara_tables *tables, const ara_layers *layers, c
     b += align256(static_cast<size_t>(std::max(L, 1)) * (n_sr + 1) * sizeof(uint32_t));   // ubase
     b += align256(static_cast<size_t>(std::max(L, 1)) * n_sr * sizeof(uint32_t));     // obase
     b += align256(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)) * sizeof(SuEntry));
+    b += align256(static_cast<size_t>(std::max(L, 1)) * sizeof(SuBound));             // bound
+    b += align256(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)) * sizeof(int32_t));   // uev
+    // partial totals: two rounds of one workgroup per CU, of the largest blocks
+    b += static_cast<size_t>(2 * device_cu_count()) * static_cast<size_t>(kEvMaxTrials) * 16;
     return b;
 }
 
@@ -715,6 +1056,7 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     uint64_t *d_cap = c.take<uint64_t>(static_cast<size_t>(L));
     uint64_t *d_region = c.take<uint64_t>(static_cast<size_t>(L));
     uint64_t *d_used = c.take<uint64_t>(static_cast<size_t>(L));
+    SuBound *bound = c.take<SuBound>(static_cast<size_t>(L));
     std::vector<OccTables> tabs(static_cast<size_t>(L));
     for (int j = 0; j < L; ++j) tabs[j] = occ_carve(c, S.z, true);
     uint32_t *ooff = c.take<uint32_t>(static_cast<size_t>(L) * n_sr * kSr);
@@ -722,6 +1064,7 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     uint32_t *ubase = c.take<uint32_t>(static_cast<size_t>(L) * (n_sr + 1));
     uint32_t *obase = c.take<uint32_t>(static_cast<size_t>(L) * n_sr);
     SuEntry *ent = c.take<SuEntry>(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)));
+    int32_t *uev = c.take<int32_t>(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)));
     HeadImage img(ws);
     img.cover(d_err + kWsHeaderBytes / sizeof(int32_t));
     img.put(d_off, layers->elt_off, static_cast<size_t>(L + 1));
@@ -729,6 +1072,7 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     img.put(d_tabs, tabs.data(), tabs.size());
     img.put(d_cap, S.cap.data(), S.cap.size());
     img.put(d_region, S.region.data(), S.region.size());
+    img.cover(bound + L);
     if ((rc = img.send(st))) return rc;
 
     {
@@ -738,13 +1082,13 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
         k_su_scan<<<dim3(static_cast<unsigned>(n_sr), static_cast<unsigned>(L)), kSuThreads, 0, st>>>(d_tabs, n_sr,
                                                                                                     ooff, otot);
         k_su_base<<<static_cast<unsigned>(L), kSuThreads, 0, st>>>(d_tabs, otot, n_sr, d_cap, ubase, obase, d_used,
-                                                                  d_err);
+                                                                  d_err, d_off, d_ids, elt_terms, layer_terms, bound);
         k_su_fill<<<dim3(static_cast<unsigned>(n_sr * kSuFillChunks), static_cast<unsigned>(L)), kSuThreads, 0, st>>>(
             tables->loss, sigma, tables->present, tables->catalog, tables->words, d_off, d_ids, d_tabs, n_sr, ooff,
-            ubase, obase, d_cap, d_region, ent);
+            ubase, obase, d_cap, d_region, ent, uev);
         const uint64_t most = *std::max_element(S.cap.begin(), S.cap.end());
-        const unsigned px = static_cast<unsigned>(std::max<uint64_t>(1, std::min<uint64_t>((most + 255) / 256, 4096)));
-        k_su_params<<<dim3(px, static_cast<unsigned>(L)), 256, 0, st>>>(d_region, d_cap, d_used, ent);
+        const unsigned px = static_cast<unsigned>(std::max<uint64_t>(1, std::min<uint64_t>((most + 255) / 256, 1024)));
+        k_su_params<<<dim3(px, static_cast<unsigned>(L)), 256, 0, st>>>(d_region, d_cap, d_used, ent, elt_terms, bound);
         ARA_HIP(hipGetLastError());
     }
     const int tb = yet->trials_per_block;
@@ -784,7 +1128,24 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     P.s_pre = s_pre;
     const int64_t groups = L == 1 ? P.nb : static_cast<int64_t>(kXcds) * ((P.nb + kXcds - 1) / kXcds) * L;
     if (groups > 0x7FFFFFFF) return fail(ARA_E_LIMIT, "too many workgroups");
+    SuEvParams Q{};
+    const bool ev = ev_blocks(yet, &Q.B) && Q.B.pos && Q.B.et >= 1 && Q.B.et <= kEvMaxTrials;
+    if (ev) P.bound = bound;
     ProfScope prof(ARA_PROF_SU, st);
+    if (ev) {
+        Q.s = P;
+        Q.uev = uev;
+        Q.b0 = static_cast<int32_t>(trial_begin / Q.B.et);
+        Q.nb = static_cast<int32_t>((trial_end + Q.B.et - 1) / Q.B.et) - Q.b0;
+        Q.partial = reinterpret_cast<unsigned char *>(ws) + c.bytes();
+        const int64_t sets = static_cast<int64_t>(L) * Q.nb;
+        Q.parts = ev_parts(sets, static_cast<int64_t>((ws_bytes - c.bytes()) / su_slot_bytes(Q.B.et)));
+        const int64_t items = (static_cast<int64_t>(Q.nb) * Q.parts + kXcds - 1) / kXcds * kXcds;
+        const int per = (Q.B.et + 255) / 256;
+        if (items * L > 0x7FFFFFFF || sets * per > 0x7FFFFFFF) return fail(ARA_E_LIMIT, "too many workgroups");
+        k_su_ev<<<static_cast<unsigned>(items * L), kSuThreads, 0, st>>>(Q);
+        if (Q.parts > 1) k_su_add<<<static_cast<unsigned>(sets * per), 256, 0, st>>>(Q, per);
+    }
     if (L == 1)
         k_su_fwd<false><<<static_cast<unsigned>(groups), kSuThreads, 0, st>>>(P);
     else
