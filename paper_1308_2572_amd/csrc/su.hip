@@ -35,7 +35,6 @@ namespace ara {
 
 constexpr int kSuThreads = 1024;
 constexpr int kSuMaxJ = ARA_MAX_ELTS_PER_LAYER;
-constexpr int kSuScanPer = kSr / kSuThreads;   // 64 ranks per thread in the count scan
 
 // One (union event, ELT of the layer) pair; 32 bytes.  The first ELT (in
 // listed order) holding a union event has its entry at the event's union
@@ -80,9 +79,13 @@ __global__ __launch_bounds__(kSuThreads) void k_su_scan(const OccTables *__restr
     const int cnt_s = T.count[s];
     const uint8_t *c = T.cnt + static_cast<size_t>(s) * kSr;
     uint32_t *oo = ooff + (static_cast<size_t>(j) * n_sr + s) * kSr;
-    const int r0 = tid * kSuScanPer;
+    // consecutive ranks per thread: a serial chain, so as few as the super-range's
+    // union takes (with a fixed 64, a seventh of the threads had all of the work
+    // of a union of 14%: 21 us against 8)
+    const int per = (cnt_s + kSuThreads - 1) / kSuThreads;
+    const int r0 = tid * per, r1 = min(r0 + per, cnt_s);
     uint32_t mine = 0;
-    for (int r = r0; r < min(r0 + kSuScanPer, cnt_s); ++r) mine += c[r] - 1u;
+    for (int r = r0; r < r1; ++r) mine += c[r] - 1u;
     uint32_t incl = mine;
     for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t v = __shfl_up(incl, o);
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_scan(const OccTables *__restr
     __syncthreads();
     uint32_t before = incl - mine;
     for (int i = 0; i < w; ++i) before += wsum[i];
-    for (int r = r0; r < min(r0 + kSuScanPer, cnt_s); ++r) {
+    for (int r = r0; r < r1; ++r) {
         oo[r] = before;
         before += c[r] - 1u;
     }
@@ -190,11 +193,13 @@ __global__ __launch_bounds__(kSuThreads) void k_su_base(const OccTables *__restr
     }
 }
 
-// Per (1024-event chunk, layer): the entries of every union event, in the
-// layer's listed ELT order; one event per thread, so that the chains of
-// dependent loads (bitmap word, rank, counts; presence; losses) of many
-// events are in flight at once.
-constexpr int kSuFillWords = kSuThreads / 32;      // 1024 events per workgroup
+// Per (4096-event chunk, layer): the entries of every union event, in the
+// layer's listed ELT order; one union event per thread, from a list in LDS.
+// Bound by each event's chain of dependent loads (rank, counts; presence;
+// losses), so what counts is the rounds of workgroups: with one event of the
+// catalogue per thread, where 14% are in the union, 2M events took 1953
+// workgroups in four rounds, 55 us; these are 489 in one, 26 us.
+constexpr int kSuFillWords = 128;                  // 4096 events per workgroup
 constexpr int kSuFillChunks = kSrWords / kSuFillWords;
 constexpr int kSuFillBatch = 8;                    // ELTs whose loads are in flight together
 
@@ -210,12 +215,27 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
                                                         const uint64_t *__restrict__ eregion,
                                                         SuEntry *__restrict__ ent, int32_t *__restrict__ uev) {
     __shared__ int32_t lk[kSuMaxJ];
+    __shared__ uint2 lw[kSuFillWords];               // the chunk's bitmap words with ranks
+    __shared__ uint16_t lev[kSuFillWords * 32];      // its union events
+    __shared__ uint32_t n_ev;
     const int s = blockIdx.x / kSuFillChunks, p = blockIdx.x % kSuFillChunks, j = blockIdx.y;
     const int tid = threadIdx.x;
+    const OccTables T = tabs[j];
+    if (tid < kSuFillWords) lw[tid] = T.br[static_cast<size_t>(s) * kSrWords + p * kSuFillWords + tid];
     const int a = elt_off[j], J = elt_off[j + 1] - a;
     for (int q = tid; q < J; q += blockDim.x) lk[q] = elt_ids[a + q];
     __syncthreads();
-    const OccTables T = tabs[j];
+    {
+        const uint32_t rank0 = lw[0].y;
+#pragma unroll
+        for (int it = 0; it < kSuFillWords * 32 / kSuThreads; ++it) {
+            const int local = it * kSuThreads + tid, bit = local & 31;
+            const uint2 q2 = lw[local >> 5];
+            if ((q2.x >> bit) & 1u) lev[q2.y - rank0 + __popc(q2.x & ((1u << bit) - 1u))] = static_cast<uint16_t>(local);
+        }
+        if (tid == 0) n_ev = lw[kSuFillWords - 1].y - rank0 + __popc(lw[kSuFillWords - 1].x);
+    }
+    __syncthreads();
     const uint64_t cap = ecap[j];
     const uint32_t ub = ubase[static_cast<size_t>(j) * (n_sr + 1) + s];
     const uint32_t n_union = ubase[static_cast<size_t>(j) * (n_sr + 1) + n_sr];
@@ -223,14 +243,11 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
     if (n_union > cap) return;   // flagged by k_su_base
     SuEntry *E = ent + eregion[j];
     const uint32_t *oo = ooff + (static_cast<size_t>(j) * n_sr + s) * kSr;
-    {
-        const int local = p * (kSuFillWords * 32) + tid;   // event within the super-range
+    const uint32_t r0 = lw[0].y, nev = n_ev;
+    for (uint32_t i = tid; i < nev; i += kSuThreads) {
+        const int local = p * (kSuFillWords * 32) + lev[i];   // event within the super-range
         const int64_t ev = static_cast<int64_t>(s) * kSr + local;
-        if (ev >= catalog) return;
-        const uint2 q2 = T.br[static_cast<size_t>(s) * kSrWords + (local >> 5)];
-        const int bit = local & 31;
-        if (!((q2.x >> bit) & 1u)) return;
-        const uint32_t r = q2.y + __popc(q2.x & ((1u << bit) - 1u));
+        const uint32_t r = r0 + i;
         const uint32_t nb = T.cnt[static_cast<size_t>(s) * kSr + r];
         const uint64_t first = static_cast<uint64_t>(ub) + r;
         const uint64_t next = static_cast<uint64_t>(ob) + oo[r];
