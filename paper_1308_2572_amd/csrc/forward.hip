@@ -224,7 +224,7 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
     {
         ProfScope prof(ARA_PROF_OCC, st);
         if ((rc = launch_occ(tables, d_off, d_ids, elt_terms, layer_terms, L, want_hits, f32, d_tabs, z.n_sr, d_err,
-                             st, ev)))
+                             layers_max_j(layers), st, ev)))
             return rc;
     }
     ProfScope prof(ARA_PROF_FWD, st);

@@ -221,9 +221,11 @@ int32_t check_layers(const ara_layers *layers, int32_t n_elts);
 // Enqueue the occurrence-table kernel for every layer.  `tabs` has one entry
 // per layer; the layer CSR must already be on the device.  f32_vals stores
 // each O rounded to binary32 (vals then holds floats at the same indices).
-// with_ev: some table has ev set.
+// max_j: at least the ELTs of any of the layers (layers_max_j).  with_ev: some
+// table has ev set.
+int32_t layers_max_j(const ara_layers *layers);
 int32_t launch_occ(const ara_tables *tables, const int32_t *d_elt_off, const int32_t *d_elt_ids,
                    const double *elt_terms, const double *layer_terms, int32_t n_layers, bool union_mode,
-                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st, bool with_ev = false);
+                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, int32_t max_j, hipStream_t st, bool with_ev = false);
 
 }  // namespace ara

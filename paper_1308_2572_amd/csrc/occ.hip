@@ -3,6 +3,7 @@
 // per catalogue event, then store the set events compactly in rank order.
 #include "occ.h"
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -10,7 +11,7 @@ namespace ara {
 
 constexpr int kPassWords = kOccChunkWords;      // 4096 events per chunk
 constexpr int kPasses = kOccChunks;             // 16 chunks per super-range
-constexpr int kLossBatch = 16;                  // ELT losses of one event loaded together
+constexpr int kLossBatch = 4;                   // ELT losses of one event loaded together
 
 __device__ __forceinline__ bool bad_scale(double s) { return !(s > 0.0) || !(s < INFINITY); }
 __device__ __forceinline__ bool bad_retention(double r) { return !(r >= 0.0) || !(r < INFINITY); }
@@ -37,40 +38,61 @@ __device__ __forceinline__ uint32_t scan128(uint32_t v, uint32_t *wtot, uint32_t
 
 // Phase one: one workgroup per (4096-event chunk, layer).  The events held
 // by at least one of the layer's ELTs are listed in event order; each is
-// evaluated once: g_k summed over the layer's ELTs in listed order (losses of
-// up to 16 ELTs are loaded together so their latencies overlap), then the occurrence
-// terms.  The set events are compacted in event order: the chunk's bitmap
-// words, its count, and O (and the ELT count) at the start of the chunk's
-// slice of the staging arrays.
-template <bool UNION>
-__global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ loss, const uint32_t *__restrict__ present,
+// evaluated once: g_k summed over the ELTs that hold it, in listed order
+// (four losses loaded together), then the occurrence terms.  The set events
+// are compacted in event order: the chunk's bitmap words, its count, and O
+// (and the ELT count) at the start of the chunk's slice of the staging arrays.
+//
+// A workgroup is a chain of dependent steps (the layer's list, 5 us with its
+// presence words; the losses, 5 us; the compaction and stores, 3 us), so what
+// counts is how many run at once.  512 threads for the chunk's some 600
+// candidates (15 ELTs of 1% each) and LDS sized by the largest layer let four
+// share a CU: four layers over 2M events, 1984 workgroups, 45 us, where 1024
+// threads with room for 128 ELTs took 71 us in four rounds; two layers 36 and
+// 22 us, one layer 18 and 15; 256 threads 47, 24 and 18.  With fewer
+// workgroups than CUs there is nothing to share, and 1024 threads are the
+// faster: 200,000 events 14.4 us, 512 threads 17.6.
+//
+// Asking every ELT for every candidate instead of those that hold it (a
+// twelfth of them) took a third more of a small catalogue's 17 us.
+struct __attribute__((aligned(16))) EltTerms {
+    double scale, ret, lim;
+    int64_t row;   // of the loss table
+};
+
+// LDS of k_occ_eval for layers of up to J ELTs: presence words, terms.
+static size_t eval_lds(int J) { return static_cast<size_t>(std::max(J, 1)) * (kPassWords * sizeof(uint32_t) + sizeof(EltTerms)); }
+
+template <bool UNION, int NT>
+__global__ __launch_bounds__(NT) void k_occ_eval(const float *__restrict__ loss, const uint32_t *__restrict__ present,
                                                    int32_t catalog, int32_t words, const int32_t *__restrict__ elt_off,
                                                    const int32_t *__restrict__ elt_ids,
                                                    const double *__restrict__ elt_terms,
                                                    const double *__restrict__ layer_terms,
-                                                   const OccTables *__restrict__ tabs, int32_t *__restrict__ err) {
-    __shared__ uint32_t stage[kMaxJ * kPassWords];
-    __shared__ int32_t lk[kMaxJ];
-    __shared__ double ls[kMaxJ], lr[kMaxJ], ll[kMaxJ];
+                                                   const OccTables *__restrict__ tabs, int32_t *__restrict__ err,
+                                                 int32_t max_j) {
+    constexpr int kWaves = NT / kWave;
+    extern __shared__ __align__(16) unsigned char smem[];
+    EltTerms *lt = reinterpret_cast<EltTerms *>(smem);               // [max_j]
+    uint32_t *stage = reinterpret_cast<uint32_t *>(lt + max_j);      // [max_j][kPassWords]
     __shared__ double lterm[4];
     __shared__ uint32_t anyw[kPassWords], cbase[kPassWords], fbits[kPassWords];
     __shared__ uint16_t cand[kPassWords * 32];
-    __shared__ uint32_t wtot[16], wtot2[2], n_cand;
+    __shared__ uint32_t wtot[kWaves], wtot2[2], n_cand;
     __shared__ unsigned long long smax;
     __shared__ int slow;
 
     const int s = blockIdx.x / kPasses, p = blockIdx.x % kPasses, j = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const OccTables T = tabs[j];
     const int a = elt_off[j];
     const int J = elt_off[j + 1] - a;
     const bool checker = blockIdx.x == 0;
-    for (int q = tid; q < J; q += blockDim.x) {
+    for (int q = tid; q < J; q += NT) {
         const int k = elt_ids[a + q];
-        lk[q] = k;
-        ls[q] = elt_terms[3 * k + 0];
-        lr[q] = elt_terms[3 * k + 1];
-        ll[q] = elt_terms[3 * k + 2];
-        if (checker && (bad_scale(ls[q]) || bad_retention(lr[q]) || bad_limit(ll[q]))) atomicCAS(err, 0, ARA_E_INVAL);
+        const EltTerms t{elt_terms[3 * k + 0], elt_terms[3 * k + 1], elt_terms[3 * k + 2], static_cast<int64_t>(k) * catalog};
+        lt[q] = t;
+        if (checker && (bad_scale(t.scale) || bad_retention(t.ret) || bad_limit(t.lim))) atomicCAS(err, 0, ARA_E_INVAL);
     }
     if (tid == 0) {
         smax = 0;
@@ -81,10 +103,24 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
         const bool bad = (tid & 1) ? bad_limit(lterm[tid]) : bad_retention(lterm[tid]);
         if (checker && bad) atomicCAS(err, 0, ARA_E_INVAL);
     }
-    for (int idx = tid; idx < J * kPassWords; idx += blockDim.x) {
-        const int q = idx / kPassWords, ww = idx % kPassWords;
+    {
+        // a thread's words are of one place in the rows of ELTs NT / 128 apart;
+        // four loads in flight
+        constexpr int kRows = NT / kPassWords;
+        const int ww = tid % kPassWords;
         const int64_t gw = static_cast<int64_t>(s) * kSrWords + p * kPassWords + ww;
-        stage[idx] = (gw < words) ? present[static_cast<size_t>(elt_ids[a + q]) * words + gw] : 0u;
+        const bool in = gw < words;
+        for (int q0 = tid / kPassWords; q0 < J; q0 += 4 * kRows) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = min(q0 + u * kRows, J - 1);
+                v[u] = in ? present[static_cast<size_t>(elt_ids[a + q]) * words + gw] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q0 + u * kRows < J) stage[(q0 + u * kRows) * kPassWords + ww] = v[u];
+        }
     }
     __syncthreads();
     // events held by any of the layer's ELTs, word by word, and where each
@@ -98,9 +134,8 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
     const uint32_t cb = scan128(__popc(any), wtot2, &n_cand);
     if (tid < kPassWords) cbase[tid] = cb;
     __syncthreads();
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int local = it * 1024 + tid;
+#pragma unroll 4
+    for (int local = tid; local < kPassWords * 32; local += NT) {
         const uint32_t m = anyw[local >> 5];
         const uint32_t bit = static_cast<uint32_t>(local & 31);
         if ((m >> bit) & 1u) cand[cbase[local >> 5] + __popc(m & ((1u << bit) - 1u))] = static_cast<uint16_t>(local);
@@ -108,14 +143,13 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
     __syncthreads();
     const int nc = static_cast<int>(n_cand);
     const double occR = lterm[0], occL = lterm[1];
-    const OccTables T = tabs[j];
     const int64_t ev0 = static_cast<int64_t>(s) * kSr + p * (kPassWords * 32);
     double *ov = T.dense + ev0;                           // the chunk's compacted O
     uint8_t *onb = UNION ? T.dense_nb + ev0 : nullptr;    // and ELT counts
     uint32_t run = 0;                                     // set events before this pass
     unsigned long long mx = 0;                            // this thread's part of the chunk's stat
     int low = INT32_MAX;
-    for (int i0 = 0; i0 < nc; i0 += 1024) {   // uniform trip count: every thread reaches the barriers
+    for (int i0 = 0; i0 < nc; i0 += NT) {   // uniform trip count: every thread reaches the barriers
         const int i = i0 + tid;
         const int local = i < nc ? cand[i] : 0;
         const int wip = local >> 5, bit = local & 31;
@@ -123,26 +157,30 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
         double x = 0.0;
         int nb = 0;
         if (i < nc) {
-            for (int q0 = 0; q0 < J; q0 += kLossBatch) {
-                float v[kLossBatch];
-                bool on[kLossBatch];
+            for (int q0 = 0; q0 < J; q0 += 32) {
+                // the ELTs among q0 .. q0 + 31 that hold the event
+                uint32_t held = 0;
+                const int nq = min(32, J - q0);
+#pragma unroll 4
+                for (int u = 0; u < nq; ++u) held |= ((stage[(q0 + u) * kPassWords + wip] >> bit) & 1u) << u;
+                nb += __popc(held);
+                while (held) {
+                    float v[kLossBatch];
+                    int q[kLossBatch];
 #pragma unroll
-                for (int u = 0; u < kLossBatch; ++u) {
-                    const int q = q0 + u;
-                    on[u] = q < J && ((stage[q * kPassWords + wip] >> bit) & 1u);
-                    // lanes without the event read element 0 (always valid) and ignore it,
-                    // so the eight loads are issued back to back
-                    const size_t idx = on[u] ? static_cast<size_t>(lk[q]) * catalog + ev : 0;
-                    v[u] = loss[idx];
-                }
-#pragma unroll
-                for (int u = 0; u < kLossBatch; ++u) {
-                    if (on[u]) {
-                        const int q = q0 + u;
-                        const double scaled = ls[q] * static_cast<double>(v[u]);
-                        x = x + xl(scaled, lr[q], ll[q]);
-                        ++nb;
+                    for (int u = 0; u < kLossBatch; ++u) {
+                        q[u] = held ? q0 + __builtin_ctz(held) : -1;
+                        held &= held - 1;
+                        // lanes with fewer read element 0 (always valid) and ignore it,
+                        // so the loads are issued back to back
+                        v[u] = loss[q[u] >= 0 ? lt[q[u]].row + ev : 0];
                     }
+#pragma unroll
+                    for (int u = 0; u < kLossBatch; ++u)
+                        if (q[u] >= 0) {
+                            const EltTerms t = lt[q[u]];
+                            x = x + xl(t.scale * static_cast<double>(v[u]), t.ret, t.lim);
+                        }
                 }
             }
         }
@@ -155,7 +193,7 @@ __global__ __launch_bounds__(1024) void k_occ_eval(const float *__restrict__ los
         if (lane == 0) wtot[w] = static_cast<uint32_t>(__popcll(m));
         __syncthreads();
         uint32_t wb = 0, tot = 0;
-        for (int k = 0; k < 16; ++k) {
+        for (int k = 0; k < kWaves; ++k) {
             const uint32_t c = wtot[k];
             wb += (k < w) ? c : 0u;
             tot += c;
@@ -386,25 +424,43 @@ int32_t check_layers(const ara_layers *layers, int32_t n_elts) {
     return ARA_OK;
 }
 
+template <bool UNION, int NT>
+static void eval(dim3 grid, const ara_tables *tables, const int32_t *d_elt_off, const int32_t *d_elt_ids,
+                 const double *elt_terms, const double *layer_terms, const OccTables *d_tabs, int32_t *d_err, int32_t max_j,
+                 hipStream_t st) {
+    const size_t lds = eval_lds(max_j);
+    if (lds > 48 * 1024)   // beside the fixed 11 KB
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_occ_eval<UNION, NT>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    k_occ_eval<UNION, NT><<<grid, NT, lds, st>>>(tables->loss, tables->present, tables->catalog, tables->words, d_elt_off,
+                                                 d_elt_ids, elt_terms, layer_terms, d_tabs, d_err, max_j);
+}
+
+int32_t layers_max_j(const ara_layers *layers) {
+    int32_t m = 1;
+    for (int32_t j = 0; j < layers->n_layers; ++j) m = std::max(m, layers->elt_off[j + 1] - layers->elt_off[j]);
+    return m;
+}
+
 int32_t launch_occ(const ara_tables *tables, const int32_t *d_elt_off, const int32_t *d_elt_ids,
                    const double *elt_terms, const double *layer_terms, int32_t n_layers, bool union_mode,
-                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, hipStream_t st, bool with_ev) {
+                   bool f32_vals, OccTables *d_tabs, int n_sr, int32_t *d_err, int32_t max_j, hipStream_t st, bool with_ev) {
     if (n_layers == 0 || n_sr == 0) return ARA_OK;
-    dim3 grid_a(static_cast<unsigned>(n_sr * kPasses), static_cast<unsigned>(n_layers));
-    dim3 grid_b(static_cast<unsigned>(n_sr * kPasses), static_cast<unsigned>(n_layers));
+    const dim3 grid(static_cast<unsigned>(n_sr * kPasses), static_cast<unsigned>(n_layers));
     const bool form = with_ev && n_sr * kPasses > kFormChunks;
+    const bool few = static_cast<int64_t>(n_sr) * kPasses * n_layers <= device_cu_count();
     if (union_mode) {
-        k_occ_eval<true><<<grid_a, 1024, 0, st>>>(tables->loss, tables->present, tables->catalog, tables->words,
-                                                  d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err);
+        if (few) eval<true, 1024>(grid, tables, d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err, max_j, st);
+        else eval<true, 512>(grid, tables, d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err, max_j, st);
         if (form) k_occ_form<<<n_layers, 1024, 0, st>>>(d_tabs, n_sr * kPasses);
-        if (f32_vals) k_occ_rank<true, true><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
-        else k_occ_rank<true, false><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
+        if (f32_vals) k_occ_rank<true, true><<<grid, kRankThreads, 0, st>>>(d_tabs);
+        else k_occ_rank<true, false><<<grid, kRankThreads, 0, st>>>(d_tabs);
     } else {
-        k_occ_eval<false><<<grid_a, 1024, 0, st>>>(tables->loss, tables->present, tables->catalog, tables->words,
-                                                   d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err);
+        if (few) eval<false, 1024>(grid, tables, d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err, max_j, st);
+        else eval<false, 512>(grid, tables, d_elt_off, d_elt_ids, elt_terms, layer_terms, d_tabs, d_err, max_j, st);
         if (form) k_occ_form<<<n_layers, 1024, 0, st>>>(d_tabs, n_sr * kPasses);
-        if (f32_vals) k_occ_rank<false, true><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
-        else k_occ_rank<false, false><<<grid_b, kRankThreads, 0, st>>>(d_tabs);
+        if (f32_vals) k_occ_rank<false, true><<<grid, kRankThreads, 0, st>>>(d_tabs);
+        else k_occ_rank<false, false><<<grid, kRankThreads, 0, st>>>(d_tabs);
     }
     ARA_HIP(hipGetLastError());
     return ARA_OK;

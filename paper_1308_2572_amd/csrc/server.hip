@@ -172,7 +172,7 @@ class HipExecutor final : public SchedExecutor {
         if (rc) *err = "copy of the quote's head failed";
         // the quote's occurrence table; invalid terms set its own status word
         if (!rc && (rc = launch_occ(&tables, d->d_off, d->d_ids, elt_terms, d->d_lterm, 1, false, false, d->d_tab, z.n_sr,
-                                    d->d_err, st, use_ev)))
+                                    d->d_err, std::max(d->h_off[1], 1), st, use_ev)))
             *err = "occurrence table launch failed";
         return rc;
     }
