@@ -179,6 +179,30 @@ __device__ void find_digit(const uint32_t *h, int bins, int64_t need, FindShared
     __syncthreads();
 }
 
+// The need-th largest of cn <= kFewKeys keys in LDS, by counting: a thread per
+// key.  A few hundred keys take one such pass (1 us) where each radix digit
+// takes four barriers and a walk over its 2048 bins (1.5 us).  Every thread of
+// the workgroup calls it, after a barrier that publishes the keys.
+constexpr int kFewKeys = 256;
+static_assert(kFewKeys <= kMetThreads, "a thread per key");
+
+__device__ uint64_t select_few(const uint64_t *keys, int cn, int64_t need, uint64_t *found) {
+    const int tid = threadIdx.x;
+    if (tid < cn) {
+        const uint64_t key = keys[tid];
+        int gt = 0, ge = 0;
+#pragma unroll 8
+        for (int i = 0; i < cn; ++i) {
+            const uint64_t o = keys[i];
+            gt += o > key ? 1 : 0;
+            ge += o >= key ? 1 : 0;
+        }
+        if (gt < need && need <= ge) *found = key;   // (the same from every thread that holds it)
+    }
+    __syncthreads();
+    return *found;
+}
+
 // Digit pass d (0 or 1) over the whole YLT row: histogram of digit d among
 // the values whose higher bits equal the prefix selected so far.  Pass 0 also
 // forms the fixed-partition partial sums for the mean.  The last workgroup
@@ -285,6 +309,7 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
     __shared__ int flag;
     __shared__ uint32_t sweep_n;
     __shared__ unsigned long long sweep_at, skmax, skminc;
+    __shared__ uint64_t found;
     const int wg = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const MetRow R = met_row(call, blockIdx.y);
     if (wg >= R.nwg) return;   // uniform over the workgroup, before any barrier
@@ -424,7 +449,10 @@ __global__ __launch_bounds__(kMetThreads) void k_met_collect(MetCall call) {
             for (int64_t i = tid; i < cn; i += kMetThreads) cs[i] = get(&c[i]);
         uint64_t pre = prefix;
         int64_t need = S.need[2];
-        for (int d = 2; d < kDigits; ++d) {
+        if (cn <= kFewKeys) {   // uniform
+            __syncthreads();
+            pre = select_few(cs, static_cast<int>(cn), need, &found);
+        } else for (int d = 2; d < kDigits; ++d) {
             for (int i = tid; i < kBins; i += kMetThreads) h[i] = 0;
             __syncthreads();
             const int sh = kShift[d], hbd = kShift[d] + kWidth[d];
@@ -555,10 +583,16 @@ __global__ __launch_bounds__(kMetThreads) void k_met_small(MetCall call) {
     __shared__ FindShared fs;
     __shared__ double red[3][16];
     __shared__ unsigned long long ired[4][16];
+    __shared__ uint64_t few[kFewKeys], found;
+    __shared__ uint32_t n_few;
     const int tid = threadIdx.x, lane = tid & 63;
     const MetRow R = met_row(call, blockIdx.y);
     const int n = static_cast<int>(R.n);
     const int64_t r = R.r;
+    if (tid == 0) {
+        n_few = 0;
+        found = 0;
+    }
     if (blockIdx.y == 0 && tid == 0) *call.hdr = 0;
     uint64_t k[kMetUnroll];
     double s = 0.0;
@@ -569,8 +603,8 @@ __global__ __launch_bounds__(kMetThreads) void k_met_small(MetCall call) {
         k[u] = key_of(v);
         s += v;
     }
-    // radix select from the top digit on
-    uint64_t pre = 0, bin = 0;   // bin: the 23-bit prefix
+    // radix select from the top digit on, until the digit's keys are few
+    uint64_t pre = 0;
     int64_t need = r;
     for (int d = 0; d < kDigits; ++d) {
         for (int i = tid; i < kBins; i += kMetThreads) h[i] = 0;
@@ -594,10 +628,18 @@ __global__ __launch_bounds__(kMetThreads) void k_met_small(MetCall call) {
         find_digit(h, 1 << kWidth[d], need, fs);
         pre = (pre << kWidth[d]) | static_cast<uint64_t>(fs.digit);
         need = fs.need;
-        if (d == 1) bin = pre;
+        const uint32_t left = h[fs.digit];
+        if (left <= static_cast<uint32_t>(kFewKeys) && d + 1 < kDigits) {   // uniform
+#pragma unroll
+            for (int u = 0; u < kMetUnroll; ++u)
+                if (u * kMetThreads + tid < n && (k[u] >> sh) == pre) few[atomicAdd(&n_few, 1u)] = k[u];
+            __syncthreads();
+            pre = select_few(few, static_cast<int>(left), need, &found);
+            break;
+        }
         __syncthreads();   // fs and h are used again
     }
-    const uint64_t bits = pre;
+    const uint64_t bits = pre, bin = pre >> kShift[1];   // the 23-bit prefix
     double s_above = 0.0, n_above = 0.0;   // values above the bin
     unsigned long long v[4] = {0, 0, 0, 0};   // the bin's values above the PML value as integers, their count, the ties
 #pragma unroll

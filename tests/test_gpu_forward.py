@@ -326,6 +326,27 @@ def test_metrics_subnormal_and_zero_bins(ara):
         np.testing.assert_array_equal(wts, oracle.metric_weights(y, p))
 
 
+@pytest.mark.parametrize("n", [4_000, 250_000])
+@pytest.mark.parametrize("n_crowd,ties", [(1, 0), (2, 0), (255, 0), (256, 0), (257, 0), (256, 256), (256, 100), (257, 256)])
+def test_metrics_few_keys_left(ara, n, n_crowd, ties):
+    """Around the 256 keys of one prefix bin up to which the rank is found by
+    counting, and its ties, in one workgroup's rows and in longer ones."""
+    import torch
+    g = np.random.default_rng(n_crowd + ties)
+    y = g.uniform(0.0, 9.9e5, size=(1, n))
+    crowd = 1e6 + np.arange(n_crowd, dtype=np.float64) * 1e-5
+    crowd[:ties] = crowd[ties - 1]
+    y[0, g.permutation(n)[:n_crowd]] = crowd
+    for r in sorted({1, max(1, n_crowd // 2), n_crowd, n_crowd + 1}):
+        p = (n - r) / n
+        out, wts = ara.metrics(torch.tensor(y, device="cuda"), p, want_weights=True)
+        out, wts = out.cpu().numpy(), wts.cpu().numpy()
+        ref = oracle.metrics(y, p)
+        assert np.array_equal(out[:, 1], ref[:, 1]), (r, out[:, 1], ref[:, 1])
+        np.testing.assert_allclose(out[:, [0, 2]], ref[:, [0, 2]], rtol=TOL, atol=0)
+        np.testing.assert_array_equal(wts, oracle.metric_weights(y, p))
+
+
 @pytest.mark.parametrize("n", [1, 2, 1025, 8191, 8192, 8193])
 @pytest.mark.parametrize("kind", ["spread", "tied", "zero", "subnormal"])
 def test_metrics_around_one_workgroup(ara, n, kind):
