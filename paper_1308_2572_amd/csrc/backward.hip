@@ -576,83 +576,128 @@ struct BwdGrad {
     const int64_t *W;              // [n_layers][n_cot][catalog] by hot index
     const int32_t *hot_base;       // [n_layers][n_sr + 1]
     const int32_t *hot_ev;         // [n_layers][catalog]
-    int32_t n_sr, n_cot, n_cw, n_elt_slots;   // cw = (workgroup, wavefront) slots; slots = ELT positions of all layers
+    int32_t n_sr, n_cot, n_cw, n_elt_slots;   // cw = (workgroup, wavefront); slots = ELT positions of all layers
     const VScale *vs;
-    double *part_elt;    // [n_cw][n_elt_slots][n_cot][3]
+    double *part_elt;    // [n_cw / kGradWaves][n_elt_slots][n_cot][3]
     double *part_occ;    // [n_layers][n_cw][n_cot][2]
 };
 
-constexpr int kGradThreads = 256;
+constexpr int kGradThreads = 256;                  // hot events per workgroup
 constexpr int kGradWaves = kGradThreads / kWave;   // 4
-constexpr int kGradHot = 4 * kGradThreads;         // hot events per workgroup
-constexpr int kGradBatch = 4;                      // ELTs whose presence words and losses are loaded together
+constexpr int kGradBatch = 16;                     // ELTs whose presence words are loaded together
+constexpr int kGradLoss = 4;                       // losses of one event loaded together
+
+// LDS of k_bwd_grad for layers of up to J ELTs: the ELTs' terms, and every
+// wavefront's sums.
+static size_t grad_lds(int J, int n_cot) {
+    return static_cast<size_t>(J) * (3 * sizeof(double) + sizeof(int64_t) + kGradWaves * n_cot * 3 * sizeof(double));
+}
 
 // (6) W(e) times the derivatives of O(e), over the layer's hot events
-// (the only ones with W): workgroup i takes hot indices 1024 i .. 1024 i +
-// 1023, each thread four of them.  Each wavefront reduces its lanes in a
-// fixed tree and writes its own partials, so no workgroup barrier sits in
-// the ELT loop and the final sums (a fixed order over workgroups and
-// wavefronts) are deterministic.  Every per-row array is indexed by
-// compile-time constants (rows beyond n_cot are zero), so nothing leaves
-// registers.
+// (the only ones with W), one per thread: workgroup i takes hot indices
+// 256 i .. 256 i + 255.  A thread asks only the ELTs that hold its event and
+// adds each one's terms to its wavefront's sums in LDS: additions of one
+// wavefront to one address apply in lane order and one instruction after
+// another, so a wavefront's sums have a fixed order; the workgroup's are its
+// wavefronts' in order, and the final sums (a fixed order over workgroups)
+// are deterministic.  Forming every ELT's sums over a wavefront's lanes
+// instead, nine reductions per ELT for three rows, took some 3900
+// instructions per wavefront and 37 us (15 ELTs, 146,000 hot events, one
+// row); 6.7 us.  Three rows among other work on the device 72 and 24 us.
 __global__ __launch_bounds__(kGradThreads) void k_bwd_grad(BwdGrad P) {
-    __shared__ int32_t lk[kMaxJ];
-    __shared__ double ls[kMaxJ], lr[kMaxJ], ll[kMaxJ];
+    extern __shared__ __align__(16) unsigned char smem[];
     const int hb = blockIdx.x, j = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int32_t *hbase = P.hot_base + static_cast<size_t>(j) * (P.n_sr + 1);
     const int H = hbase[P.n_sr];
-    const int g0 = hb * kGradHot;
+    const int g0 = hb * kGradThreads;
     if (g0 >= H) return;   // uniform; the final sums read only the slots of workgroups with hot events
     const int a = P.elt_off[j];
     const int J = P.elt_off[j + 1] - a;
-    for (int q = tid; q < J; q += blockDim.x) {
+    const int vals = P.n_cot * 3;                          // sums per ELT
+    double *ls = reinterpret_cast<double *>(smem);         // [J]
+    double *lr = ls + J, *ll = lr + J;
+    int64_t *lk = reinterpret_cast<int64_t *>(ll + J);     // [J] the ELT's index
+    double *sums = reinterpret_cast<double *>(lk + J);     // [waves][J][n_cot][3]
+    for (int q = tid; q < J; q += kGradThreads) {
         const int k = P.elt_ids[a + q];
         lk[q] = k;
         ls[q] = P.elt_terms[3 * k + 0];
         lr[q] = P.elt_terms[3 * k + 1];
         ll[q] = P.elt_terms[3 * k + 2];
     }
+    for (int i = tid; i < kGradWaves * J * vals; i += kGradThreads) sums[i] = 0.0;
     __syncthreads();
     const double occL = P.layer_terms[4 * j + 1];
     const OccTables T = P.tabs[j];
-    const int32_t *hev = P.hot_ev + static_cast<size_t>(j) * P.catalog;
 
-    // the thread's four hot events: weight per row and occurrence-clamp
-    // branch.  O = min(max(x - OccR, 0), OccL) is non-zero for these events,
-    // and it is below OccL exactly when the occurrence clamp is linear.
-    double W[4][kMaxCot];
-    bool lin_occ[4];
-    int ev[4];
-    double po[kMaxCot][2];
+    // the thread's hot event: weight per row and occurrence-clamp branch.  O =
+    // min(max(x - OccR, 0), OccL) is non-zero for these events, and it is
+    // below OccL exactly when the occurrence clamp is linear.
+    const int g = g0 + tid;
+    const bool valid = g < H;
+    const int e = valid ? P.hot_ev[static_cast<size_t>(j) * P.catalog + g] : 0;
+    const int sr = e >> kSrBits;
+    const double O = valid ? T.vals[static_cast<size_t>(sr) * kSr + (g - hbase[sr])] : 0.0;
+    const bool lin_occ = valid && (O < occL);
+    double W[kMaxCot], po[kMaxCot][2];
 #pragma unroll
-    for (int c = 0; c < kMaxCot; ++c) po[c][0] = po[c][1] = 0.0;
+    for (int c = 0; c < kMaxCot; ++c) {
+        W[c] = 0.0;
+        if (valid && c < P.n_cot) {
+            const int64_t acc = P.W[(static_cast<size_t>(j) * P.n_cot + c) * P.catalog + g];
+            W[c] = ldexp(static_cast<double>(acc), -P.vs[j * P.n_cot + c].sigma);
+        }
+        po[c][0] = lin_occ ? 0.0 - W[c] : 0.0;
+        po[c][1] = lin_occ ? 0.0 : W[c];
+    }
+    double *my = sums + static_cast<size_t>(w) * J * vals;
+    if (lin_occ)
+        for (int q0 = 0; q0 < J; q0 += kGradBatch) {
+            uint32_t pw[kGradBatch];
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int g = g0 + it * kGradThreads + tid;
-        const bool valid = g < H;
-        const int e = valid ? hev[g] : 0;
-        ev[it] = e;
-        const int sr = e >> kSrBits;
-        const double O = valid ? T.vals[static_cast<size_t>(sr) * kSr + (g - hbase[sr])] : 0.0;
-        lin_occ[it] = valid && (O < occL);
+            for (int u = 0; u < kGradBatch; ++u)
+                pw[u] = P.present[static_cast<size_t>(lk[min(q0 + u, J - 1)]) * P.words + (e >> 5)];
+            uint32_t held = 0;
 #pragma unroll
-        for (int c = 0; c < kMaxCot; ++c) {
-            double wv = 0.0;
-            if (valid && c < P.n_cot) {
-                const int64_t acc = P.W[(static_cast<size_t>(j) * P.n_cot + c) * P.catalog + g];
-                wv = ldexp(static_cast<double>(acc), -P.vs[j * P.n_cot + c].sigma);
-            }
-            W[it][c] = wv;
-            if (valid) {
-                if (lin_occ[it]) po[c][0] -= wv;
-                else po[c][1] += wv;
+            for (int u = 0; u < kGradBatch; ++u) held |= ((pw[u] >> (e & 31)) & 1u) << u;
+            held &= J - q0 < kGradBatch ? (1u << (J - q0)) - 1u : ~0u;
+            while (held) {
+                float lv[kGradLoss];
+                int q[kGradLoss];
+#pragma unroll
+                for (int u = 0; u < kGradLoss; ++u) {
+                    q[u] = held ? q0 + __builtin_ctz(held) : -1;
+                    held &= held - 1;
+                    // element 0 (always valid) for lanes with fewer ELTs
+                    lv[u] = P.loss[q[u] >= 0 ? lk[q[u]] * P.catalog + e : 0];
+                }
+#pragma unroll
+                for (int u = 0; u < kGradLoss; ++u) {
+                    if (q[u] < 0) continue;
+                    const double l = static_cast<double>(lv[u]);
+                    const double pre = ls[q[u]] * l - lr[q[u]];
+                    const double av = (pre > 0.0) ? pre : 0.0;
+                    double *to = my + q[u] * vals;
+                    if (pre > 0.0 && av < ll[q[u]]) {
+#pragma unroll
+                        for (int c = 0; c < kMaxCot; ++c)
+                            if (c < P.n_cot) {
+                                atomicAdd(to + 3 * c, W[c] * l);
+                                atomicAdd(to + 3 * c + 1, 0.0 - W[c]);
+                            }
+                    }
+                    if (av >= ll[q[u]]) {
+#pragma unroll
+                        for (int c = 0; c < kMaxCot; ++c)
+                            if (c < P.n_cot) atomicAdd(to + 3 * c + 2, W[c]);
+                    }
+                }
             }
         }
-    }
-    const size_t cw = static_cast<size_t>(hb) * kGradWaves + w;   // (workgroup, wave) partial slot
     // occurrence-term partials of this wavefront
     // (wavefront sums by DPP: lane 63 holds the total, in a fixed order)
+    const size_t cw = static_cast<size_t>(hb) * kGradWaves + w;
 #pragma unroll
     for (int c = 0; c < kMaxCot; ++c)
         if (c < P.n_cot) {
@@ -663,71 +708,19 @@ __global__ __launch_bounds__(kGradThreads) void k_bwd_grad(BwdGrad P) {
                     P.part_occ[((static_cast<size_t>(j) * P.n_cw + cw) * P.n_cot + c) * 2 + m] = v;
             }
         }
-    // ELT-term partials, kGradBatch ELTs' presence words and losses in flight at a time
-    for (int q0 = 0; q0 < J; q0 += kGradBatch) {
-        uint32_t pw[kGradBatch][4];
+    __syncthreads();
+    double *dst = P.part_elt + (static_cast<size_t>(hb) * P.n_elt_slots + a) * vals;
+    for (int i = tid; i < J * vals; i += kGradThreads) {
+        double v = 0.0;
 #pragma unroll
-        for (int b = 0; b < kGradBatch; ++b) {
-            const int qq = q0 + b;
-#pragma unroll
-            for (int it = 0; it < 4; ++it)
-                pw[b][it] = (qq < J && lin_occ[it]) ? P.present[static_cast<size_t>(lk[qq]) * P.words + (ev[it] >> 5)] : 0u;
-        }
-        float lv[kGradBatch][4];
-        bool on[kGradBatch][4];
-#pragma unroll
-        for (int b = 0; b < kGradBatch; ++b) {
-            const int qq = q0 + b;
-#pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                on[b][it] = (pw[b][it] >> (ev[it] & 31)) & 1u;
-                const size_t idx = on[b][it] ? static_cast<size_t>(lk[qq]) * P.catalog + ev[it] : 0;
-                lv[b][it] = P.loss[idx];   // element 0 (always valid) for events without the ELT
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < kGradBatch; ++b) {
-            const int qq = q0 + b;
-            if (qq >= J) break;
-            double pe[kMaxCot][3];
-#pragma unroll
-            for (int c = 0; c < kMaxCot; ++c) pe[c][0] = pe[c][1] = pe[c][2] = 0.0;
-#pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                if (!on[b][it]) continue;
-                const double l = static_cast<double>(lv[b][it]);
-                const double scaled = ls[qq] * l;
-                const double pre = scaled - lr[qq];
-                const double av = (pre > 0.0) ? pre : 0.0;
-                const bool lin = (pre > 0.0) && (av < ll[qq]);
-                const bool cap = av >= ll[qq];
-#pragma unroll
-                for (int c = 0; c < kMaxCot; ++c) {
-                    if (lin) {
-                        pe[c][0] += W[it][c] * l;
-                        pe[c][1] -= W[it][c];
-                    }
-                    if (cap) pe[c][2] += W[it][c];
-                }
-            }
-            double *dst = P.part_elt + (cw * P.n_elt_slots + (a + qq)) * P.n_cot * 3;
-#pragma unroll
-            for (int c = 0; c < kMaxCot; ++c)
-                if (c < P.n_cot) {
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) {
-                        const double v = wave_inclusive_sum(pe[c][m]);
-                        if (lane == 63) dst[c * 3 + m] = v;
-                    }
-                }
-        }
+        for (int k = 0; k < kGradWaves; ++k) v += sums[k * J * vals + i];
+        dst[i] = v;
     }
 }
 
-// Partial slots written for layer j: those of the workgroups that had hot events.
-__device__ __forceinline__ int grad_slots_used(const int32_t *hot_base, int n_sr, int j, int n_cw) {
-    const int H = hot_base[static_cast<size_t>(j) * (n_sr + 1) + n_sr];
-    return min(n_cw, ((H + kGradHot - 1) / kGradHot) * kGradWaves);
+// Workgroups of k_bwd_grad that wrote partials for layer j: those with hot events.
+__device__ __forceinline__ int grad_groups(const int32_t *hot_base, int n_sr, int j) {
+    return (hot_base[static_cast<size_t>(j) * (n_sr + 1) + n_sr] + kGradThreads - 1) / kGradThreads;
 }
 
 // (7) fixed-order sums into the outputs: one workgroup per output value,
@@ -749,15 +742,15 @@ __global__ __launch_bounds__(256) void k_bwd_final(const int32_t *__restrict__ e
         for (int j = 0; j < n_layers; ++j)
             for (int q = elt_off[j]; q < elt_off[j + 1]; ++q) {
                 if (elt_ids[q] != k) continue;
-                const int used = grad_slots_used(hot_base, n_sr, j, n_cw);
-                for (int cw = tid; cw < used; cw += blockDim.x)
-                    v += part_elt[((static_cast<size_t>(cw) * n_elt_slots + q) * n_cot + c) * 3 + m];
+                const int used = grad_groups(hot_base, n_sr, j);
+                for (int i = tid; i < used; i += blockDim.x)
+                    v += part_elt[((static_cast<size_t>(i) * n_elt_slots + q) * n_cot + c) * 3 + m];
             }
     } else {
         const int i = o - n_e;
         const int c = i / (n_layers * 4), j = (i / 4) % n_layers, m = i % 4;
         if (m < 2) {
-            const int used = grad_slots_used(hot_base, n_sr, j, n_cw);
+            const int used = grad_groups(hot_base, n_sr, j) * kGradWaves;
             for (int cw = tid; cw < used; cw += blockDim.x)
                 v += part_occ[((static_cast<size_t>(j) * n_cw + cw) * n_cot + c) * 2 + m];
         } else {
@@ -801,7 +794,7 @@ static BwdLayout bwd_layout(const ara_tables *tables, const ara_layers *layers, 
     const int L = layers->n_layers;
     const int nJ = L > 0 ? layers->elt_off[L] : 0;
     B.nwg_v = bwd_nwg_v(n);
-    B.n_cw = static_cast<int>((static_cast<int64_t>(tables->catalog) + kGradHot - 1) / kGradHot) * kGradWaves;
+    B.n_cw = static_cast<int>((static_cast<int64_t>(tables->catalog) + kGradThreads - 1) / kGradThreads) * kGradWaves;
     B.cs = bwd_cs(n_cot);
     const size_t cat = static_cast<size_t>(tables->catalog);
     Carver c(nullptr);
@@ -820,7 +813,7 @@ static BwdLayout bwd_layout(const ara_tables *tables, const ara_layers *layers, 
     d.take<int32_t>(static_cast<size_t>(L) * cat);
     d.take<int32_t>(static_cast<size_t>(L) * (B.z.n_sr + 1));
     d.take<int64_t>(static_cast<size_t>(L) * n_cot * cat);
-    d.take<double>(static_cast<size_t>(B.n_cw) * std::max(nJ, 1) * n_cot * 3);
+    d.take<double>(static_cast<size_t>(B.n_cw / kGradWaves) * std::max(nJ, 1) * n_cot * 3);
     d.take<double>(static_cast<size_t>(L) * B.n_cw * n_cot * 2);
     B.bytes = b + d.bytes();
     return B;
@@ -893,7 +886,7 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     int32_t *hot_ev = c.take<int32_t>(static_cast<size_t>(L) * tables->catalog);
     int32_t *hot_base = c.take<int32_t>(static_cast<size_t>(L) * (B.z.n_sr + 1));
     int64_t *W = c.take<int64_t>(static_cast<size_t>(L) * n_cot * tables->catalog);
-    double *part_elt = c.take<double>(static_cast<size_t>(B.n_cw) * std::max(nJ, 1) * n_cot * 3);
+    double *part_elt = c.take<double>(static_cast<size_t>(B.n_cw / kGradWaves) * std::max(nJ, 1) * n_cot * 3);
     double *part_occ = c.take<double>(static_cast<size_t>(L) * B.n_cw * n_cot * 2);
     int32_t *dev = c.take<int32_t>(static_cast<size_t>(L) * std::max<int64_t>(n, 1));
     HeadImage img(ws);   // clears the error header, the weight scales and the deviating-trial counts
@@ -1015,7 +1008,11 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     Gp.part_occ = part_occ;
     {
         ProfScope prof(ARA_PROF_BWD_RED, st);
-        k_bwd_grad<<<dim3(B.n_cw / kGradWaves, L), kGradThreads, 0, st>>>(Gp);
+        const size_t lds = grad_lds(layers_max_j(layers), n_cot);
+        if (lds > 64 * 1024)
+            ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_bwd_grad),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+        k_bwd_grad<<<dim3(B.n_cw / kGradWaves, L), kGradThreads, lds, st>>>(Gp);
         const int outs = n_cot * tables->n_elts * 3 + n_cot * L * 4;
         k_bwd_final<<<outs, 256, 0, st>>>(d_off, d_ids, L, tables->n_elts, n_cot, B.n_cw, hot_base, B.z.n_sr,
                                           std::max(nJ, 1), nwg_v, part_elt, part_occ, aggpart, grad_elt, grad_layer);
