@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void k_bwd_hot(const OccTables *__restrict__ t
                                                  int32_t *__restrict__ hot_base, int64_t *__restrict__ W) {
     __shared__ int32_t red[4];
     const int s = blockIdx.x, j = blockIdx.y, tid = threadIdx.x;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     int32_t part = 0;
     for (int i = tid; i < s; i += blockDim.x) part += T.count[i];
     for (int o = 32; o > 0; o >>= 1) part += __shfl_down(part, o);
@@ -515,12 +515,41 @@ __global__ __launch_bounds__(256) void k_bwd_wcut(BwdSparse P, int2 cut, int ncu
 
 // (5d) the deviating trials of the range: a wavefront per trial adds
 // v_t - c to W of each hot event of the trial, one integer atomic per
-// (occurrence, row)
-__global__ __launch_bounds__(256) void k_bwd_wsparse(BwdSparse P) {
+// (occurrence, row).  Whether an event is hot is asked of its bit in LDS
+// first, the hot events' bitmap folded onto 2^19 bits by OR: a table word per
+// occurrence is a line from L2 each, 43 of the 70 us that 10,000 trials of
+// 1000 took (2M events, 7% hot); with the filter SPARSETIME us.
+constexpr int kHotFilter = 1 << 14;   // words, 64 KB: two workgroups on a CU
+constexpr int kSparseThreads = 1024;
+
+__global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bwd_wsparse(BwdSparse P) {
+    __shared__ uint32_t filt[kHotFilter];
     const int j = blockIdx.y, lane = threadIdx.x & 63;
-    if (!sparse_chosen(P, j)) return;
+    if (!sparse_chosen(P, j)) return;   // uniform over the workgroup
     const int64_t nwalk = sparse_walk(P, j);
-    const OccTables T = P.tabs[j];
+    if (static_cast<int64_t>(blockIdx.x) * (kSparseThreads >> 6) >= nwalk) return;   // uniform: no trial for it
+    const OccTables T = load_tables(P.tabs + j);
+    const uint4 *bits = reinterpret_cast<const uint4 *>(T.bits);
+    const int n4 = P.n_sr * (kSrWords / 4);
+#pragma unroll
+    for (int k = 0; k < kHotFilter / 4 / kSparseThreads; ++k) {
+        const int f = k * kSparseThreads + static_cast<int>(threadIdx.x);
+        uint4 m = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = f; i < n4; i += 4 * (kHotFilter / 4)) {   // four pieces in flight
+            uint4 b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) b[u] = bits[min(i + u * (kHotFilter / 4), n4 - 1 - (n4 - 1 - f) % (kHotFilter / 4))];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                m.x |= b[u].x;
+                m.y |= b[u].y;
+                m.z |= b[u].z;
+                m.w |= b[u].w;
+            }
+        }
+        reinterpret_cast<uint4 *>(filt)[f] = m;
+    }
+    __syncthreads();
     const int32_t *hb = P.hot_base + static_cast<size_t>(j) * (P.n_sr + 1);
     const int64_t *q = P.vq + static_cast<size_t>(j) * P.n * P.cs;
     int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
@@ -543,11 +572,14 @@ __global__ __launch_bounds__(256) void k_bwd_wsparse(BwdSparse P) {
                 const int64_t k = k0 + v * 64 + lane;
                 e[v] = k < b ? P.t_ids[k] : -1;
             }
+#pragma unroll
+            for (int v = 0; v < kU; ++v)
+                if (e[v] >= 0 && !((filt[(e[v] >> 5) & (kHotFilter - 1)] >> (e[v] & 31)) & 1u)) e[v] = -1;
             uint2 w[kU];
 #pragma unroll
             for (int v = 0; v < kU; ++v) {
-                const int ev = e[v] < 0 ? 0 : e[v];
-                w[v] = T.br[static_cast<size_t>(ev >> kSrBits) * kSrWords + ((ev & (kSr - 1)) >> 5)];
+                w[v] = make_uint2(0u, 0u);
+                if (e[v] >= 0) w[v] = T.br[e[v] >> 5];   // word e / 32 of the table
             }
 #pragma unroll
             for (int v = 0; v < kU; ++v) {
@@ -629,7 +661,7 @@ __global__ __launch_bounds__(kGradThreads) void k_bwd_grad(BwdGrad P) {
     for (int i = tid; i < kGradWaves * J * vals; i += kGradThreads) sums[i] = 0.0;
     __syncthreads();
     const double occL = P.layer_terms[4 * j + 1];
-    const OccTables T = P.tabs[j];
+    const OccTables T = load_tables(P.tabs + j);
 
     // the thread's hot event: weight per row and occurrence-clamp branch.  O =
     // min(max(x - OccR, 0), OccL) is non-zero for these events, and it is
@@ -980,7 +1012,7 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
                 if (wide) k_bwd_wcut<16><<<gc, 256, 0, st>>>(Q, cx, ncut);
                 else k_bwd_wcut<4><<<gc, 256, 0, st>>>(Q, cx, ncut);
             }
-            k_bwd_wsparse<<<dim3(2048, L), 256, 0, st>>>(Q);
+            k_bwd_wsparse<<<dim3(2 * cu, L), kSparseThreads, 0, st>>>(Q);
         }
         if (wide) launch_bwd_w<16>(B.cs, grid, st, S);
         else launch_bwd_w<4>(B.cs, grid, st, S);

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         const int i = (k / P.parts) * kXcds + x;
         part = k % P.parts;
         if (i >= P.n_items) return;   // uniform, before any barrier
-        const FwdItem I = P.items[i];
+        const FwdItem I = load_item(P.items + i);
         b = I.block;
         if (b < 0) return;    // uniform
         tab = I.tab;
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         if (HITS && P.hits) hits = P.hits + static_cast<size_t>(j) * n;
         slot = static_cast<size_t>(j) * P.nb * P.parts + static_cast<size_t>(item);
     }
-    const OccTables T = *tab;
+    const OccTables T = load_tables(tab);
     const EvLayer L = *T.ev;
     const int64_t bt0 = static_cast<int64_t>(b) * P.B.et;
     const int nt = static_cast<int>(min<int64_t>(P.B.et, P.B.n_trials - bt0));
@@ -127,9 +127,11 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     __syncthreads();
 
     const EvRec *rec = reinterpret_cast<const EvRec *>(T.vals);
-    const uint16_t *ent = P.B.ent + P.B.base[b];   // the block's entries: base may be odd
-    const uint16_t *ent2 = reinterpret_cast<const uint16_t *>(reinterpret_cast<uintptr_t>(ent) & ~uintptr_t(3));
-    const uint32_t skew = static_cast<uint32_t>((reinterpret_cast<uintptr_t>(ent) >> 1) & 1u);   // ent = ent2 + skew
+    // the block's entries: base may be odd, and pieces are read from an even place on
+    const int64_t base = P.B.base[b];
+    const uint32_t skew = static_cast<uint32_t>(base & 1);
+    const uint16_t *ent2 = device_ptr(P.B.ent) + (base - skew);
+    const uint16_t *ent = ent2 + skew;
     const uint2 *hdr = DENSE ? nullptr : P.B.hdr + static_cast<size_t>(b) * P.B.ng;
     const uint32_t *start = DENSE ? P.B.start + static_cast<size_t>(b) * (P.B.catalog + 1) : nullptr;
     const int n_units = (L.n_set + kWave - 1) / kWave;
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
     double *ylt, *s_pre;
     int32_t *hits = nullptr;
     if (P.items) {
-        const FwdItem I = P.items[u];
+        const FwdItem I = load_item(P.items + u);
         b = I.block;
         if (b < 0) return;
         t0 = I.t0;
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
         s_pre = P.s_pre ? P.s_pre + static_cast<size_t>(j) * n : nullptr;
         if (HITS && P.hits) hits = P.hits + static_cast<size_t>(j) * n;
     }
-    const EvLayer L = *tab->ev;
+    const EvLayer L = *device_ptr(tab->ev);
     if (!L.mode) return;   // uniform
     const int i = (c * 256 + static_cast<int>(threadIdx.x)) / G, sub = threadIdx.x & (G - 1);
     const int64_t t = static_cast<int64_t>(b) * P.B.et + i;

@@ -42,7 +42,7 @@ struct FwdParams {
 // that stream the same codes run together under one L2 and the codes come
 // from HBM once.  Indexes past the last block give an empty item (block -1).
 __device__ __forceinline__ FwdItem fwd_item(const FwdParams &P, int i) {
-    if (P.items) return P.items[i];
+    if (P.items) return load_item(P.items + i);
     FwdItem it;
     int j = 0, bi = i;
     if (P.reg_nl > 1) {
@@ -166,7 +166,7 @@ __device__ __forceinline__ void fwd_block(const FwdParams &P, const FwdItem &I, 
         acc[i] = V(0);
         if (HITS) hacc[i] = 0;
     }
-    const OccTables T = *I.tab;
+    const OccTables T = load_tables(I.tab);
     // copy range r's table slice into LDS, split over the wavefronts
     auto fetch = [&](int r, RangeInfo ri) {
         const uint32_t dst = bufs_lds;

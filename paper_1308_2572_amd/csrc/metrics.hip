@@ -72,7 +72,17 @@ struct MetCall {
 };
 
 __device__ __forceinline__ MetRow met_row(const MetCall &c, int l) {
-    if (c.rows) return c.rows[l];
+    if (c.rows) {   // pointers from memory
+        MetRow m = c.rows[l];
+        m.ylt = device_ptr(m.ylt);
+        m.out = device_ptr(m.out);
+        m.w = device_ptr(m.w);
+        m.hist = device_ptr(m.hist);
+        m.st = device_ptr(static_cast<char *>(m.st));
+        m.part = device_ptr(static_cast<char *>(m.part));
+        m.cand = device_ptr(m.cand);
+        return m;
+    }
     MetRow m;
     m.ylt = c.ylt + static_cast<size_t>(l) * c.n;
     m.out = c.out + 3 * l;

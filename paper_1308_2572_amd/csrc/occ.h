@@ -17,6 +17,7 @@
 // requested, every event present in at least one of the layer's ELTs.
 #pragma once
 
+#include "wave.h"
 #include "evblk.h"
 
 namespace ara {
@@ -79,6 +80,22 @@ struct OccTables {
     const int64_t *max_len;   // with ev: occurrences of the YET's longest trial
 };
 
+__device__ __forceinline__ OccTables load_tables(const OccTables *p) {
+    OccTables t = *p;
+    t.br = device_ptr(t.br);
+    t.vals = device_ptr(t.vals);
+    t.cnt = device_ptr(t.cnt);
+    t.count = device_ptr(t.count);
+    t.pcount = device_ptr(t.pcount);
+    t.bits = device_ptr(t.bits);
+    t.dense = device_ptr(t.dense);
+    t.dense_nb = device_ptr(t.dense_nb);
+    t.stat = device_ptr(t.stat);
+    t.ev = device_ptr(t.ev);
+    t.max_len = device_ptr(t.max_len);
+    return t;
+}
+
 // min(max(v - R, 0), L), evaluated exactly as the oracle does: a separately
 // rounded subtraction and two selects (no fused operations; the build uses
 // -ffp-contract=off).
@@ -138,6 +155,16 @@ struct FwdItem {
     double *s_pre;             // or null
     int32_t *hits;             // or null
 };
+
+__device__ __forceinline__ FwdItem load_item(const FwdItem *p) {
+    FwdItem it = *p;
+    it.tab = device_ptr(it.tab);
+    it.lterm = device_ptr(it.lterm);
+    it.ylt = device_ptr(it.ylt);
+    it.s_pre = device_ptr(it.s_pre);
+    it.hits = device_ptr(it.hits);
+    return it;
+}
 
 // Enqueue the forward streaming kernel over a device array of items.
 // The regular set of forward items: every layer over the blocks b0 ..

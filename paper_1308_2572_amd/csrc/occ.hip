@@ -84,7 +84,7 @@ __global__ __launch_bounds__(NT) void k_occ_eval(const float *__restrict__ loss,
 
     const int s = blockIdx.x / kPasses, p = blockIdx.x % kPasses, j = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     const int a = elt_off[j];
     const int J = elt_off[j + 1] - a;
     const bool checker = blockIdx.x == 0;
@@ -303,7 +303,7 @@ constexpr int kFormChunks = 2048;
 
 __global__ __launch_bounds__(1024) void k_occ_form(const OccTables *__restrict__ tabs, int n_chunks) {
     __shared__ uint32_t wsum[16];
-    const OccTables T = tabs[blockIdx.x];
+    const OccTables T = load_tables(tabs + blockIdx.x);
     if (!T.ev) return;   // uniform
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t run = 0;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kRankThreads) void k_occ_rank(const OccTables *__re
     __shared__ uint32_t wtot2[2], tot;
     const int s = blockIdx.x / kPasses, p = blockIdx.x % kPasses, j = blockIdx.y;
     const int tid = threadIdx.x;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     const int32_t *pc = T.pcount + static_cast<size_t>(s) * kPasses;
     const uint32_t cnt = static_cast<uint32_t>(pc[p]);
     const size_t w0 = static_cast<size_t>(s) * kSrWords + p * kPassWords;

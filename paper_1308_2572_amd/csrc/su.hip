@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_scan(const OccTables *__restr
                                                         uint32_t *__restrict__ ooff, uint32_t *__restrict__ otot) {
     __shared__ uint32_t wsum[kSuThreads / kWave];
     const int s = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     const int cnt_s = T.count[s];
     const uint8_t *c = T.cnt + static_cast<size_t>(s) * kSr;
     uint32_t *oo = ooff + (static_cast<size_t>(j) * n_sr + s) * kSr;
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_base(const OccTables *__restr
         const double occL = layer_terms[4 * j + 1];
         if (threadIdx.x == 0) bound[j].most = b < occL ? b : occL;
     }
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     uint32_t *ub = ubase + static_cast<size_t>(j) * (n_sr + 1);
     uint32_t *ob = obase + static_cast<size_t>(j) * n_sr;
     const uint32_t n_union = block_exclusive_scan<uint32_t>(reinterpret_cast<const uint32_t *>(T.count), ub, n_sr, wsum);
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
     __shared__ uint32_t n_ev;
     const int s = blockIdx.x / kSuFillChunks, p = blockIdx.x % kSuFillChunks, j = blockIdx.y;
     const int tid = threadIdx.x;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     if (tid < kSuFillWords) lw[tid] = T.br[static_cast<size_t>(s) * kSrWords + p * kSuFillWords + tid];
     const int a = elt_off[j], J = elt_off[j + 1] - a;
     for (int q = tid; q < J; q += blockDim.x) lk[q] = elt_ids[a + q];
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fwd(SuParams P) {
         lr[q] = P.elt_terms[3 * k + 1];
         ll[q] = P.elt_terms[3 * k + 2];
     }
-    const OccTables T = P.tabs[j];
+    const OccTables T = load_tables(P.tabs + j);
     const uint32_t *ub = P.ubase + static_cast<size_t>(j) * (P.n_sr + 1);
     const SuEntry *E = P.ent + P.eregion[j];
     const double occR = P.layer_terms[4 * j + 0], occL = P.layer_terms[4 * j + 1];

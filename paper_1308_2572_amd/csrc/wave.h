@@ -1,5 +1,6 @@
 // Wavefront-wide operations on binary64 values by DPP (data-parallel
-// primitives move values between lanes inside the VALU: no LDS traffic).
+// primitives move values between lanes inside the VALU: no LDS traffic), and
+// pointers' address space.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -7,6 +8,16 @@
 #include <cstdint>
 
 namespace ara {
+
+// A pointer to device memory that was itself loaded from memory.  Without
+// this the compiler takes it for one that may point into LDS, and every
+// access through it for one of both kinds: it waits for all outstanding loads
+// and LDS operations together instead of for its own.
+template <class T>
+__device__ __forceinline__ T *device_ptr(T *p) {
+    // by way of the address: the compiler drops a cast there and back
+    return (T *)(__attribute__((address_space(1))) T *)(reinterpret_cast<uintptr_t>(p));
+}
 
 // Cross-lane move of a binary64 value: CTRL is the DPP control; lanes whose
 // source is outside the pattern (or whose row is masked off) read 0.

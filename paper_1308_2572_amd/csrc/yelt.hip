@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void k_yelt_filter(const OccTables *__restrict
     const int j = blockIdx.y;
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
     if (w >= kFilterWords) return;
-    const OccTables T = tabs[j];
+    const OccTables T = load_tables(tabs + j);
     uint32_t f = 0;
     for (int i = w; i < n_words; i += kFilterWords) f |= T.br[i].x;
     filter[static_cast<size_t>(j) * kFilterWords + w] = f;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kYeltThreads) void k_yelt(YeltParams P) {
     double *st = stage[wv];
     const int64_t gw = static_cast<int64_t>(blockIdx.x) * (kYeltThreads / kWave) + wv;
     const int64_t nw = static_cast<int64_t>(gridDim.x) * (kYeltThreads / kWave);
-    const OccTables T = P.tabs[j];
+    const OccTables T = load_tables(P.tabs + j);
     const gmem<unsigned long long> gbr = (gmem<unsigned long long>)T.br;   // (bits, rank) words, one per 32 events
     const gmem<double> gvals = (gmem<double>)T.vals;
     const gmem<int32_t> gids = (gmem<int32_t>)P.ids;
