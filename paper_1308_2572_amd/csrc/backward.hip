@@ -43,9 +43,17 @@
 // most two) slices it cuts; the second term comes from the trial-major copy
 // of the deviating trials' events.  It is used when the trials to walk are
 // at most a sixteenth of all (each walked trial costs about sixteen times
-// its share of the gather's time); the decision is taken on the device from
-// the counts, so both forms are enqueued and the one not chosen returns at
-// once.
+// its share of the gather's time).
+//
+// A third form serves cotangents of two values, as the metrics' are where
+// many years exceed the aggregate limit (zero there, the AAL's weight on the
+// others): with a the second value,
+//   W(e) = c * (occurrences) + (a - c) * (occurrences in trials of value a)
+//          + sum over t of neither value of (v_t - c) * (occurrences in t),
+// the second count from one bit per trial.
+//
+// The decision is taken on the device from the counts, so all forms are
+// enqueued and those not chosen return at once.
 #include "occ.h"
 #include "wave.h"
 
@@ -214,6 +222,10 @@ __global__ __launch_bounds__(256) void k_bwd_hot(const OccTables *__restrict__ t
     }
 }
 
+__device__ __forceinline__ uint32_t lanes_under(uint64_t m) {   // bits of m below this lane
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
 constexpr int kCand = 8;   // candidates for the common value of a row: 0 and seven sampled trials
 constexpr int kDevChunk = 4096;   // trials per workgroup when counting and listing them
 
@@ -224,9 +236,14 @@ struct BwdSparse {
     int64_t slice_trials;              // trials of one slice of the event-major copy
     const int64_t *tr_off;             // event-major copy: list offsets per (slice, event)
     const uint32_t *tr_ent;            //   and the lists' slice-local trial indices
-    unsigned long long *ndev;          // [n_layers] deviating trials
+    unsigned long long *ndev, *nalt;   // [n_layers] trials of neither value, trials of the second value
     int64_t *common;                   // [n_layers][kMaxCot] the chosen common value
-    int32_t *dev;                      // [n_layers][n] deviating trials (call-relative)
+    int64_t *alt;                      // [n_layers][kMaxCot] the chosen second value (the common one: none)
+    int32_t *dev;                      // [n_layers][n] trials (call-relative) of neither value from the front,
+                                       //   of the second from the back
+    uint2 *abits;                      // [n_layers][aw] bit t: trial t has the second value
+    int64_t aw;                        // 64-bit words of a layer's bits
+    int32_t two, two_bytes;            // whether the third form is available, and its LDS
     const int32_t *t_cnt;              // occurrences of each event
     const int64_t *t_off;              // trial-major copy
     const int32_t *t_ids;
@@ -262,14 +279,16 @@ __device__ __forceinline__ bool slice_cut(const BwdSparse &P, int x) {
     return max(lo, P.t0) < min(hi, P.t0 + P.n) && !slice_inside(P, x);
 }
 
-// Deviating trials the second form walks: those of the range.
-__device__ __forceinline__ int64_t sparse_walk(const BwdSparse &P, int j) { return static_cast<int64_t>(P.ndev[j]); }
-
-// The second form's condition, the same in every kernel that reads it: at
-// most a sixteenth of all the trials to walk.
+// Which form serves layer j, the same in every kernel that asks: the second
+// where the trials to walk are at most a sixteenth of all, the third where
+// those of neither value are a thirty-second (counting the second value takes a
+// third of the gather's time by itself), the first otherwise.
 constexpr int kWalkShare = 16;
-__device__ __forceinline__ bool sparse_chosen(const BwdSparse &P, int j) {
-    return sparse_walk(P, j) * kWalkShare <= P.n_trials;
+enum { kDense = 1, kOneValue = 2, kTwoValues = 3 };
+__device__ __forceinline__ int form_of(const BwdSparse &P, int j) {
+    const int64_t dev = static_cast<int64_t>(P.ndev[j]), alt = static_cast<int64_t>(P.nalt[j]);
+    if ((dev + alt) * kWalkShare <= P.n_trials) return kOneValue;
+    return P.two && 2 * dev * kWalkShare <= P.n_trials ? kTwoValues : kDense;
 }
 
 struct BwdGather {
@@ -299,7 +318,7 @@ template <int CS, int G>
 __global__ __launch_bounds__(256) void k_bwd_w(BwdGather P) {
     constexpr int kU = 2;
     const int x = blockIdx.x % kSlices, wi = blockIdx.x / kSlices, nw = gridDim.x / kSlices, j = blockIdx.y;
-    if (P.use_sp && sparse_chosen(P.sp, j)) return;   // W comes from the deviating trials instead
+    if (P.use_sp && form_of(P.sp, j) != kDense) return;   // W comes from the other forms
     const int64_t tx0 = static_cast<int64_t>(x) * P.slice_trials;
     const int64_t ulo = max<int64_t>(P.t0 - tx0, 0), uhi = min<int64_t>(P.t1 - tx0, P.slice_trials);
     if (uhi <= ulo) return;   // the slice lies outside the call's trials
@@ -361,155 +380,228 @@ static void launch_bwd_w(int cs, dim3 grid, hipStream_t st, const BwdGather &S) 
 
 // (5a) the common value of every row: of 0 and the values at seven sampled
 // trials, the one held by most of 1024 evenly spaced trials (the first on
-// ties).  Any choice gives the same W; a good one keeps the list of
-// deviating trials short.  One workgroup per layer.
+// ties); and the second value, of all rows together: of the same eight, the
+// one held by most of those trials that do not have the common one in every
+// row.  Any choice gives the same W; a good one keeps the list of deviating
+// trials short.  One workgroup per layer.
 constexpr int kPickSamples = 1024;
 
 __global__ __launch_bounds__(kPickSamples) void k_bwd_pick(BwdSparse P) {
-    __shared__ uint32_t cnt[kMaxCot * kCand];
+    __shared__ uint32_t cnt[kMaxCot * kCand], cnt2[kCand];
+    __shared__ int64_t cm[kMaxCot];
     const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     if (tid < kMaxCot * kCand) cnt[tid] = 0;
+    if (tid < kCand) cnt2[tid] = 0;
     __syncthreads();
     const int64_t t = (static_cast<int64_t>(tid) * P.n) / kPickSamples;
     const int64_t *q = P.vq + (static_cast<size_t>(j) * P.n + t) * P.cs;
+    uint32_t same = (1u << kCand) - 1u;   // candidates that the trial equals in every row
     for (int c = 0; c < P.n_cot; ++c) {
         const int64_t v = q[c];
         for (int k = 0; k < kCand; ++k) {
-            const uint64_t m = __ballot(v == cand_value(P, j, c, k));
+            const bool is = v == cand_value(P, j, c, k);
+            const uint64_t m = __ballot(is);
             if (lane == 0 && m) atomicAdd(&cnt[c * kCand + k], static_cast<uint32_t>(__popcll(m)));
+            if (!is) same &= ~(1u << k);
         }
     }
     __syncthreads();
     if (tid < kMaxCot) {
-        int64_t cm = 0;
+        int64_t v = 0;
         if (tid < P.n_cot) {
             int best = 0;
             for (int k = 1; k < kCand; ++k)
                 if (cnt[tid * kCand + k] > cnt[tid * kCand + best]) best = k;
-            cm = cand_value(P, j, tid, best);
+            v = cand_value(P, j, tid, best);
         }
-        P.common[static_cast<size_t>(j) * kMaxCot + tid] = cm;
+        cm[tid] = v;
+        P.common[static_cast<size_t>(j) * kMaxCot + tid] = v;
+    }
+    __syncthreads();
+    bool dev = false;
+    for (int c = 0; c < P.n_cot; ++c) dev = dev || q[c] != cm[c];
+    for (int k = 0; k < kCand; ++k) {
+        const uint64_t m = __ballot(dev && ((same >> k) & 1u));
+        if (lane == 0 && m) atomicAdd(&cnt2[k], static_cast<uint32_t>(__popcll(m)));
+    }
+    __syncthreads();
+    if (tid < kMaxCot) {
+        int best = 0;
+        for (int k = 1; k < kCand; ++k)
+            if (cnt2[k] > cnt2[best]) best = k;
+        P.alt[static_cast<size_t>(j) * kMaxCot + tid] =
+            cnt2[best] == 0 ? cm[tid] : (tid < P.n_cot ? cand_value(P, j, tid, best) : 0);
     }
 }
 
-// (5b) the list of trials where some row differs from its common value.
-// A workgroup gathers the deviating trials of its chunk of kDevChunk trials
-// in LDS and reserves their place in the list with one atomic.
+// (5b) the trials that do not have the common value in every row: those of
+// the second value, as a list and as bits, and the others, as a list.  A
+// workgroup gathers those of its chunk of kDevChunk trials in LDS and reserves
+// their place in each list with one atomic.
 __global__ __launch_bounds__(1024) void k_bwd_dev(BwdSparse P) {
-    __shared__ int32_t buf[kDevChunk];
-    __shared__ uint32_t nbuf;
-    __shared__ unsigned long long base;
+    __shared__ int32_t buf[kDevChunk];   // of neither value from the front, of the second from the back
+    __shared__ uint32_t nbuf, nab;
+    __shared__ unsigned long long base, abase;
     const int j = blockIdx.y, lane = threadIdx.x & 63;
-    int64_t cm[kMaxCot];
+    int64_t cm[kMaxCot], am[kMaxCot];
 #pragma unroll
-    for (int c = 0; c < kMaxCot; ++c) cm[c] = P.common[static_cast<size_t>(j) * kMaxCot + c];
-    if (threadIdx.x == 0) nbuf = 0;
+    for (int c = 0; c < kMaxCot; ++c) {
+        cm[c] = P.common[static_cast<size_t>(j) * kMaxCot + c];
+        am[c] = P.alt[static_cast<size_t>(j) * kMaxCot + c];
+    }
+    if (threadIdx.x == 0) nbuf = nab = 0;
     __syncthreads();
     const int64_t *q = P.vq + static_cast<size_t>(j) * P.n * P.cs;
+    uint2 *ab = P.abits + static_cast<size_t>(j) * P.aw;
     const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kDevChunk;
     const int64_t c1 = min<int64_t>(c0 + kDevChunk, P.n);
     for (int64_t t0 = c0; t0 < c1; t0 += blockDim.x) {   // uniform
         const int64_t t = t0 + threadIdx.x;
-        bool d = false;
+        bool d = false, a = true;
         if (t < c1)
 #pragma unroll
             for (int c = 0; c < kMaxCot; ++c)
-                if (c < P.n_cot) d = d || (q[static_cast<size_t>(t) * P.cs + c] != cm[c]);
-        const uint64_t m = __ballot(d);
+                if (c < P.n_cot) {
+                    const int64_t v = q[static_cast<size_t>(t) * P.cs + c];
+                    d = d || v != cm[c];
+                    a = a && v == am[c];
+                }
+        a = a && d;
+        d = d && !a;
+        const uint64_t m = __ballot(d), ma = __ballot(a);
+        if (lane == 0 && t < c1) ab[t >> 6] = make_uint2(static_cast<uint32_t>(ma), static_cast<uint32_t>(ma >> 32));
         if (m) {
             uint32_t wb = 0;
             if (lane == 0) wb = atomicAdd(&nbuf, static_cast<uint32_t>(__popcll(m)));
             wb = __shfl(wb, 0);
-            if (d) {
-                const uint32_t pos = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
-                buf[wb + pos] = static_cast<int32_t>(t);
-            }
+            if (d) buf[wb + lanes_under(m)] = static_cast<int32_t>(t);
+        }
+        if (ma) {
+            uint32_t wb = 0;
+            if (lane == 0) wb = atomicAdd(&nab, static_cast<uint32_t>(__popcll(ma)));
+            wb = __shfl(wb, 0);
+            if (a) buf[kDevChunk - 1 - (wb + lanes_under(ma))] = static_cast<int32_t>(t);
         }
     }
     __syncthreads();
-    const uint32_t nb = nbuf;
-    if (nb == 0) return;   // uniform
-    if (threadIdx.x == 0) base = atomicAdd(&P.ndev[j], static_cast<unsigned long long>(nb));
+    const uint32_t nb = nbuf, na = nab;
+    if (threadIdx.x == 0 && nb) base = atomicAdd(&P.ndev[j], static_cast<unsigned long long>(nb));
+    if (threadIdx.x == 0 && na) abase = atomicAdd(&P.nalt[j], static_cast<unsigned long long>(na));
     __syncthreads();
-    int32_t *dv = P.dev + static_cast<size_t>(j) * P.n + base;
-    for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) dv[i] = buf[i];
+    int32_t *dv = P.dev + static_cast<size_t>(j) * P.n;
+    for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) dv[base + i] = buf[i];
+    for (uint32_t i = threadIdx.x; i < na; i += blockDim.x) dv[P.n - 1 - static_cast<int64_t>(abase + i)] = buf[kDevChunk - 1 - i];
 }
 
-// (5c) W(e) = c * (occurrences of e in the trial slices the call covers
-// whole; all trials: the per-event totals) for every hot event (when the
-// second form is chosen and c is not zero; the accumulators are zero from
-// step 4 otherwise)
-__global__ __launch_bounds__(256) void k_bwd_winit(BwdSparse P) {
-    const int j = blockIdx.y;
-    if (!sparse_chosen(P, j) || !common_nonzero(P, j)) return;   // c = 0: W starts at zero
+// (5c) the counted part of W(e) for every hot event: c times the occurrences
+// of e in the call's trials and, in the third form, (a - c) times those in
+// trials of the second value a.  (The accumulators are zero from step 4.)
+//
+// The first comes from the event-major offsets: over all trials the
+// per-event totals, over part of them the list lengths of the slices inside
+// the range and, of the slices it cuts (at most two), the list entries in
+// range, counted.  The second counts the entries of every slice whose trial's
+// bit is set, the slice's bits in LDS: a bit from LDS per entry, where the
+// first form gathers each trial's rows from L2 (32 bytes each with three
+// rows, 620 us for half of 1M trials of 1000 and 15 ELTs).  Behind the quote
+// server, three rows over parts of 1M trials of 1000, years above the
+// aggregate limit in a third of the layers: 136 us a quote, where the gather,
+// the counts and the cut slices in kernels of their own took 250.
+//
+// Workgroup i works on slice i mod 8 (second form: on a cut slice, so that all
+// of them have work); G lanes per hot event read its list coalesced; the
+// counts meet W in one integer atomic per row.
+template <int G>
+__global__ __launch_bounds__(256) void k_bwd_count(BwdSparse P, int2 cut, int ncut) {
+    extern __shared__ uint32_t bits[];
+    constexpr int kU = 4;
+    const int j = blockIdx.y, tid = threadIdx.x;
+    const int form = form_of(P, j);
+    if (form == kDense) return;   // uniform
+    int64_t cm[kMaxCot], da[kMaxCot];
+#pragma unroll
+    for (int c = 0; c < kMaxCot; ++c) {
+        cm[c] = P.common[static_cast<size_t>(j) * kMaxCot + c];
+        da[c] = static_cast<int64_t>(static_cast<unsigned long long>(P.alt[static_cast<size_t>(j) * kMaxCot + c]) -
+                                     static_cast<unsigned long long>(cm[c]));
+    }
+    const bool any_c = common_nonzero(P, j);
     const int H = P.hot_base[static_cast<size_t>(j) * (P.n_sr + 1) + P.n_sr];
     const int32_t *hev = P.hot_ev + static_cast<size_t>(j) * P.catalog;
     int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
-    const bool all = P.t0 == 0 && P.n == P.n_trials;   // uniform
-    for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < H; g += gridDim.x * blockDim.x) {
-        const int e = hev[g];
-        int64_t cnt = 0;
-        if (all) {
-            cnt = P.t_cnt[e];
-        } else {
-#pragma unroll
-            for (int x = 0; x < kSlices; ++x)
-                if (slice_inside(P, x)) {
-                    const int64_t *off = P.tr_off + static_cast<int64_t>(x) * P.catalog;
-                    cnt += off[e + 1] - off[e];
-                }
-        }
+    auto add = [&](int g, uint64_t n_c, uint64_t n_a) {   // exact modulo 2^64, like every sum below
 #pragma unroll
         for (int c = 0; c < kMaxCot; ++c)
-            if (c < P.n_cot)
-                Wj[static_cast<size_t>(c) * P.catalog + g] = static_cast<int64_t>(
-                    static_cast<unsigned long long>(P.common[static_cast<size_t>(j) * kMaxCot + c]) *
-                    static_cast<unsigned long long>(cnt));   // exact modulo 2^64, like every sum below
+            if (c < P.n_cot) {
+                const unsigned long long v = static_cast<unsigned long long>(cm[c]) * n_c + static_cast<unsigned long long>(da[c]) * n_a;
+                if (v != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&Wj[static_cast<size_t>(c) * P.catalog + g]), v);
+            }
+    };
+    if (any_c) {
+        const bool all = P.t0 == 0 && P.n == P.n_trials;   // uniform
+        for (int g = blockIdx.x * 256 + tid; g < H; g += gridDim.x * 256) {
+            const int e = hev[g];
+            int64_t cnt = 0;
+            if (all) {
+                cnt = P.t_cnt[e];
+            } else {
+#pragma unroll
+                for (int x = 0; x < kSlices; ++x)
+                    if (slice_inside(P, x)) {
+                        const int64_t *off = P.tr_off + static_cast<int64_t>(x) * P.catalog;
+                        cnt += off[e + 1] - off[e];
+                    }
+            }
+            add(g, static_cast<uint64_t>(cnt), 0);
+        }
     }
-}
-
-// (5c') the slices the call's range cuts (cut[0 .. ncut), at most two): for
-// every hot event, c times the entries of its list in the slice that lie in
-// the range.  Workgroup i works on cut slice i mod ncut, so that every
-// workgroup has work; G lanes per hot event read its list coalesced and
-// count, and the count meets W in one integer atomic per row.
-template <int G>
-__global__ __launch_bounds__(256) void k_bwd_wcut(BwdSparse P, int2 cut, int ncut) {
-    constexpr int kU = 4;
-    const int k = blockIdx.x % ncut, wi = blockIdx.x / ncut, nw = gridDim.x / ncut, j = blockIdx.y;
-    const int x = k == 0 ? cut.x : cut.y;
-    if (!sparse_chosen(P, j) || !common_nonzero(P, j) || !slice_cut(P, x)) return;   // uniform
+    const bool two = form == kTwoValues;
+    if (!two && (ncut == 0 || !any_c)) return;   // uniform
+    const int ns = two ? kSlices : ncut;
+    const int k = blockIdx.x % ns, wi = blockIdx.x / ns, nw = gridDim.x / ns;
+    if (wi >= nw) return;   // uniform
+    const int x = two ? k : (k == 0 ? cut.x : cut.y);
+    const bool is_cut = any_c && slice_cut(P, x);
     const int64_t tx0 = static_cast<int64_t>(x) * P.slice_trials;
     const int64_t ulo = max<int64_t>(P.t0 - tx0, 0), uhi = min<int64_t>(P.t0 + P.n - tx0, P.slice_trials);
+    if (uhi <= ulo || (!two && !is_cut)) return;   // uniform: nothing of the slice is asked for
     const uint32_t u0 = static_cast<uint32_t>(ulo), span = static_cast<uint32_t>(uhi - ulo);
-    const int H = P.hot_base[static_cast<size_t>(j) * (P.n_sr + 1) + P.n_sr];
-    const int32_t *hev = P.hot_ev + static_cast<size_t>(j) * P.catalog;
+    uint32_t first = 0;   // bit of the slice's first trial in range
+    if (two) {
+        const int64_t b0 = tx0 + ulo - P.t0;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(P.abits + static_cast<size_t>(j) * P.aw);
+        first = static_cast<uint32_t>(b0 & 31);
+        const int nwords = static_cast<int>((first + span + 31) / 32);
+        for (int i = tid; i < nwords; i += 256) bits[i] = src[(b0 >> 5) + i];
+        __syncthreads();
+    }
     const int64_t *off = P.tr_off + static_cast<int64_t>(x) * P.catalog;
-    int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
-    const int sub = threadIdx.x & (G - 1);
-    const int ngrp = nw * static_cast<int>(blockDim.x) / G;
-    for (int g = (wi * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x)) / G; g < H; g += ngrp) {
+    const int sub = tid & (G - 1);
+    const int ngrp = nw * 256 / G;
+    for (int g = (wi * 256 + tid) / G; g < H; g += ngrp) {
         const int e = hev[g];
         const int64_t o0 = off[e], o1 = off[e + 1];
-        uint32_t cnt = 0;
+        uint32_t cnt = 0, na = 0;
         for (int64_t i = o0 + sub; i < o1; i += G * kU) {
             uint32_t d[kU];
 #pragma unroll
             for (int v = 0; v < kU; ++v)
                 d[v] = (i + v * G < o1) ? __builtin_nontemporal_load(P.tr_ent + i + v * G) - u0 : span;   // span = skip
 #pragma unroll
-            for (int v = 0; v < kU; ++v) cnt += d[v] < span ? 1u : 0u;
+            for (int v = 0; v < kU; ++v) {
+                const bool in = d[v] < span;
+                cnt += in ? 1u : 0u;
+                if (two) {
+                    const uint32_t b = first + (in ? d[v] : 0u);
+                    na += in ? (bits[b >> 5] >> (b & 31u)) & 1u : 0u;
+                }
+            }
         }
-        for (int s2 = G / 2; s2 > 0; s2 >>= 1) cnt += static_cast<uint32_t>(__shfl_xor(static_cast<int>(cnt), s2, G));
-        if (sub == 0 && cnt != 0) {
-#pragma unroll
-            for (int c = 0; c < kMaxCot; ++c)
-                if (c < P.n_cot)
-                    atomicAdd(reinterpret_cast<unsigned long long *>(&Wj[static_cast<size_t>(c) * P.catalog + g]),
-                              static_cast<unsigned long long>(P.common[static_cast<size_t>(j) * kMaxCot + c]) *
-                                  static_cast<unsigned long long>(cnt));
+        for (int s2 = G / 2; s2 > 0; s2 >>= 1) {
+            cnt += static_cast<uint32_t>(__shfl_xor(static_cast<int>(cnt), s2, G));
+            na += static_cast<uint32_t>(__shfl_xor(static_cast<int>(na), s2, G));
         }
+        if (sub == 0) add(g, is_cut ? cnt : 0u, na);
     }
 }
 
@@ -518,15 +610,17 @@ __global__ __launch_bounds__(256) void k_bwd_wcut(BwdSparse P, int2 cut, int ncu
 // (occurrence, row).  Whether an event is hot is asked of its bit in LDS
 // first, the hot events' bitmap folded onto 2^19 bits by OR: a table word per
 // occurrence is a line from L2 each, 43 of the 70 us that 10,000 trials of
-// 1000 took (2M events, 7% hot); with the filter SPARSETIME us.
+// 1000 took (2M events, 7% hot); with the filter 51 us.
 constexpr int kHotFilter = 1 << 14;   // words, 64 KB: two workgroups on a CU
 constexpr int kSparseThreads = 1024;
 
 __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bwd_wsparse(BwdSparse P) {
     __shared__ uint32_t filt[kHotFilter];
     const int j = blockIdx.y, lane = threadIdx.x & 63;
-    if (!sparse_chosen(P, j)) return;   // uniform over the workgroup
-    const int64_t nwalk = sparse_walk(P, j);
+    const int form = form_of(P, j);
+    if (form == kDense) return;   // uniform over the workgroup
+    const int64_t ndev = static_cast<int64_t>(P.ndev[j]);
+    const int64_t nwalk = ndev + (form == kOneValue ? static_cast<int64_t>(P.nalt[j]) : 0);
     if (static_cast<int64_t>(blockIdx.x) * (kSparseThreads >> 6) >= nwalk) return;   // uniform: no trial for it
     const OccTables T = load_tables(P.tabs + j);
     const uint4 *bits = reinterpret_cast<const uint4 *>(T.bits);
@@ -556,7 +650,7 @@ __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(
     const int waves = gridDim.x * (blockDim.x >> 6);
     for (int64_t i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); i < nwalk; i += waves) {
         unsigned long long dl[kMaxCot];
-        const int32_t u = P.dev[static_cast<size_t>(j) * P.n + i];
+        const int32_t u = P.dev[static_cast<size_t>(j) * P.n + (i < ndev ? i : P.n - 1 - (i - ndev))];
 #pragma unroll
         for (int c = 0; c < kMaxCot; ++c)
             dl[c] = c < P.n_cot ? static_cast<unsigned long long>(q[static_cast<size_t>(u) * P.cs + c]) -
@@ -818,6 +912,8 @@ static int bwd_nwg_v(int64_t n) {   // about two trials per thread, at most 512 
 
 static int64_t dev_blocks(int64_t n) { return std::max<int64_t>(1, (n + kDevChunk - 1) / kDevChunk); }
 
+static int64_t bit_words(int64_t n) { return (std::max<int64_t>(n, 1) + 63) / 64 + 1; }   // one past the last
+
 static int bwd_cs(int n_cot) { return n_cot <= 1 ? 1 : (n_cot <= 2 ? 2 : 4); }
 
 static BwdLayout bwd_layout(const ara_tables *tables, const ara_layers *layers, int n_cot, int64_t n) {
@@ -837,8 +933,9 @@ static BwdLayout bwd_layout(const ara_tables *tables, const ara_layers *layers, 
     size_t b = c.bytes() + static_cast<size_t>(L) * B.z.per_layer;
     Carver d(nullptr);
     d.take<VScale>(static_cast<size_t>(std::max(L * n_cot, 1)));
-    d.take<unsigned long long>(static_cast<size_t>(std::max(L, 1)));
-    d.take<int64_t>(static_cast<size_t>(std::max(L, 1)) * kMaxCot);
+    d.take<unsigned long long>(static_cast<size_t>(std::max(L, 1)) * 2);
+    d.take<int64_t>(static_cast<size_t>(std::max(L, 1)) * kMaxCot * 2);
+    d.take<uint2>(static_cast<size_t>(L) * bit_words(n));
     d.take<int32_t>(static_cast<size_t>(L) * std::max<int64_t>(n, 1));
     d.take<double>(static_cast<size_t>(L) * n_cot * B.nwg_v * 2);
     d.take<int64_t>(static_cast<size_t>(L) * std::max<int64_t>(n, 1) * B.cs);
@@ -909,8 +1006,8 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     int32_t *d_ids = c.take<int32_t>(static_cast<size_t>(std::max(nJ, 1)));
     OccTables *d_tabs = c.take<OccTables>(static_cast<size_t>(L));
     VScale *vs = c.take<VScale>(static_cast<size_t>(L * n_cot));
-    unsigned long long *ndev = c.take<unsigned long long>(static_cast<size_t>(L));
-    int64_t *common = c.take<int64_t>(static_cast<size_t>(L) * kMaxCot);
+    unsigned long long *ndev = c.take<unsigned long long>(static_cast<size_t>(L) * 2);
+    int64_t *common = c.take<int64_t>(static_cast<size_t>(L) * kMaxCot * 2);
     std::vector<OccTables> tabs(static_cast<size_t>(L));
     for (int j = 0; j < L; ++j) tabs[j] = occ_carve(c, B.z, false);
     double *aggpart = c.take<double>(static_cast<size_t>(L) * n_cot * bwd_nwg_v(n) * 2);
@@ -921,11 +1018,13 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     double *part_elt = c.take<double>(static_cast<size_t>(B.n_cw / kGradWaves) * std::max(nJ, 1) * n_cot * 3);
     double *part_occ = c.take<double>(static_cast<size_t>(L) * B.n_cw * n_cot * 2);
     int32_t *dev = c.take<int32_t>(static_cast<size_t>(L) * std::max<int64_t>(n, 1));
+    const int64_t aw = bit_words(n);
+    uint2 *abits = c.take<uint2>(static_cast<size_t>(L) * aw);
     HeadImage img(ws);   // clears the error header, the weight scales and the deviating-trial counts
     img.put(d_off, layers->elt_off, static_cast<size_t>(L + 1));
     img.put(d_ids, layers->elt_ids, static_cast<size_t>(nJ));
     img.put(d_tabs, tabs.data(), tabs.size());
-    img.cover(ndev + L);
+    img.cover(ndev + 2 * L);
     if ((rc = img.send(st))) return rc;
 
     {
@@ -973,7 +1072,15 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     Q.tr_off = yet->tr_off;
     Q.tr_ent = yet->tr_ent;
     Q.ndev = ndev;
+    Q.nalt = ndev + L;
     Q.common = common;
+    Q.alt = common + static_cast<size_t>(L) * kMaxCot;
+    Q.abits = abits;
+    Q.aw = aw;
+    // the third form holds a slice's bits in LDS, a workgroup of four per CU
+    // each: slices of up to 262,144 trials, 2M trials in all
+    Q.two = yet->slice_trials <= 8 * 32 * 1024;
+    Q.two_bytes = Q.two ? static_cast<int32_t>((yet->slice_trials + 31) / 32 + 1) * 4 : 4;
     Q.dev = dev;
     Q.t_cnt = yet->t_cnt;
     Q.t_off = yet->t_off;
@@ -995,8 +1102,6 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
             const unsigned gt = static_cast<unsigned>(dev_blocks(n));
             k_bwd_pick<<<L, kPickSamples, 0, st>>>(Q);
             k_bwd_dev<<<dim3(gt, L), 1024, 0, st>>>(Q);
-            const unsigned gh = static_cast<unsigned>(std::min<int64_t>((tables->catalog + 255) / 256, 1024));
-            k_bwd_winit<<<dim3(gh, L), 256, 0, st>>>(Q);
             // the slices the range cuts: at most its first and its last
             int cut[2], ncut = 0;
             for (int64_t t : {trial_begin, trial_end - 1}) {
@@ -1006,12 +1111,10 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
                 const bool inside = lo >= trial_begin && hi <= trial_end;
                 if (n > 0 && !inside && (ncut == 0 || cut[0] != x)) cut[ncut++] = x;
             }
-            if (ncut > 0) {
-                const dim3 gc(static_cast<unsigned>(ncut * std::max(1, (4 * cu) / ncut)), L);
-                const int2 cx = make_int2(cut[0], ncut > 1 ? cut[1] : cut[0]);
-                if (wide) k_bwd_wcut<16><<<gc, 256, 0, st>>>(Q, cx, ncut);
-                else k_bwd_wcut<4><<<gc, 256, 0, st>>>(Q, cx, ncut);
-            }
+            const int2 cx = make_int2(ncut > 0 ? cut[0] : 0, ncut > 1 ? cut[1] : (ncut > 0 ? cut[0] : 0));
+            const size_t lds = static_cast<size_t>(Q.two_bytes);
+            if (wide) k_bwd_count<16><<<grid, 256, lds, st>>>(Q, cx, ncut);
+            else k_bwd_count<4><<<grid, 256, lds, st>>>(Q, cx, ncut);
             k_bwd_wsparse<<<dim3(2 * cu, L), kSparseThreads, 0, st>>>(Q);
         }
         if (wide) launch_bwd_w<16>(B.cs, grid, st, S);

@@ -345,3 +345,34 @@ def test_deviating_trial_form_full_size_vs_oracle(ara):
     a = sparse(sp, wsub, t0, t1)
     b = dense(sp, wsub, t0, t1)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4])
+@pytest.mark.parametrize("share", [0.1, 0.5, 0.9])
+def test_two_valued_form_is_bitwise_the_gather(ara, rows, share):
+    """Cotangents that take one of two values in all rows together on most
+    trials, and others on a thirty-second of them, one more, or none: over all
+    trials, over part of them cutting two slices, on slice boundaries, inside
+    one slice, and from odd places; the integers are the gather's."""
+    import torch
+    w = synth.config(2, n_trials=24_000)
+    _, s_pre, sparse, dense = _both_forms(ara, w)
+    n, L = w.yet.n_trials, w.layers.n_layers
+    s_pre = s_pre.clamp(min=1.0)
+    g = np.random.default_rng(rows)
+    st = sparse.slice_trials
+    for a0, a1, nd in [(0, n, 0), (0, n, n // 32), (0, n, n // 32 + 1), (5000, 17001, 100), (st, 5 * st, 7), (st + 17, 2 * st - 5, 3),
+                       (3 * st + 1, 3 * st + 3, 0), (33, n - 1, n // 32)]:
+        a1 = min(a1, n)
+        m = a1 - a0
+        c = np.zeros((rows, L, m))
+        c[0] = 1.0 / n
+        second = g.random((L, m)) < share
+        for r in range(rows):
+            c[r][second] = g.choice([0.0, 1.0, -2.5]) / n
+        idx = g.choice(m, size=min(nd, m), replace=False)
+        c[:, :, idx] = g.uniform(-2.0, 2.0, size=(rows, L, len(idx))) / n
+        sp = s_pre[:, a0:a1].contiguous()
+        cot = torch.tensor(c, device="cuda")
+        a, b = sparse(sp, cot, a0, a1), dense(sp, cot, a0, a1)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), (a0, a1, nd)
