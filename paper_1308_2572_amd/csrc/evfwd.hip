@@ -40,6 +40,8 @@ struct EvfParams {
     int64_t t0, t1;
     int32_t b0, nb, nl, parts;
     unsigned char *partial;
+    const uint32_t *share;     // k_ev_share's table, when sweep > 0
+    int32_t sweep;             // workgroups of a block that may walk it together, or 0
     FwdParams fwd;             // for the layers of mode 0
 };
 
@@ -47,6 +49,70 @@ struct EvfParams {
 struct EvPiece {
     uint32_t a[4];
 };
+
+// Several layers of a block read most of its lines each (a line of 128 bytes
+// holds the lists of some 16 events, and a layer with a tenth of the catalogue
+// set touches four lines in five), from HBM unless one of them has just brought
+// them to the XCD's L2.  Layers of one size walk a block side by side by
+// themselves; of uneven ones the smaller run ahead and every layer reads for
+// itself: 6.4 GB at 5.5 TB/s, 1161 us, for four layers of 8 to 20 ELTs over a
+// 1M x 1000 YET's 2.3 GB.  So a block's `sweep` workgroups are dealt to its
+// layers in proportion to their set events, and each walks every parts-th unit
+// of its layer's, from the block's first event to its last: all of them go
+// through the block at one speed.  726 us and 52 for adding 16 parts a block
+// up (8 workgroups 827 + 31, 32 workgroups 785 + 89; 12, 20 and 24 do not
+// divide an XCD's 32 CUs: 819 to 888).
+//
+// It pays where the layers are uneven and read much: this kernel says so
+// (`uneven`) where the largest layer has half as many set events again as the
+// smallest and they hold a fifth of the catalogue or more together (eight
+// equal layers 598 us, so dealt 645; four layers of 3 to 6 ELTs 230 and 263),
+// and the host asks it only for what kSweepLeast and its like describe.
+//
+// share[r]: workgroup r's layer, its part and the layer's parts (8, 8 and 16
+// bits); share[sweep + j]: layer j's first workgroup; share[sweep + nl + 1]:
+// uneven.
+__global__ __launch_bounds__(kWave) void k_ev_share(const OccTables *__restrict__ tabs, int nl, int sweep,
+                                                    int32_t catalog, uint32_t *__restrict__ share) {
+    const int l = threadIdx.x;
+    const bool in = l < nl;
+    float w = 0.0f;
+    bool ok = true;
+    if (in) {
+        const EvLayer L = *device_ptr(tabs[l].ev);
+        w = static_cast<float>(max(L.n_set, 1));
+        ok = L.mode == 1;
+    }
+    float sum = w, most = in ? w : 0.0f, least = in ? w : 3e38f;
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o);
+        most = fmaxf(most, __shfl_xor(most, o));
+        least = fminf(least, __shfl_xor(least, o));
+    }
+    const bool uneven = __all(ok) && most >= 1.5f * least && 5.0f * sum >= static_cast<float>(catalog);
+    // one workgroup each and the proportional share of the others rounded
+    // down; those left over (fewer than the layers) to the layers with the
+    // most events per workgroup
+    int p = in ? 1 + static_cast<int>(static_cast<float>(sweep - nl) * (w / sum)) : 0;
+    int left = p;
+    for (int o = 32; o > 0; o >>= 1) left += __shfl_xor(left, o);
+    for (left = sweep - left; left > 0; --left) {
+        const float load = in ? w / static_cast<float>(p) : -1.0f;
+        float top = load;
+        for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+        if (l == __builtin_ctzll(__ballot(load == top))) ++p;
+    }
+    int first = p;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(first, o);
+        if (l >= o) first += v;
+    }
+    first -= p;
+    if (l <= nl) share[sweep + l] = static_cast<uint32_t>(first);
+    if (l == 0) share[sweep + nl + 1] = uneven ? 1u : 0u;
+    for (int q = 0; q < p && first + q < sweep; ++q)
+        share[first + q] = static_cast<uint32_t>(l) | static_cast<uint32_t>(q) << 8 | static_cast<uint32_t>(p) << 16;
+}
 
 template <bool HITS, bool DENSE>
 __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
@@ -64,8 +130,9 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     double *ylt, *s_pre;
     int32_t *hits = nullptr;
     int64_t t0, t1;
-    int b, part;
+    int b, part, parts = P.parts;
     size_t slot;              // of the partial totals
+    const bool together = P.sweep > 0 && P.share[P.sweep + P.nl + 1] != 0u;   // uniform over the launch
     if (P.items) {            // the item's parts one after another on its XCD
         const int i = (k / P.parts) * kXcds + x;
         part = k % P.parts;
@@ -80,12 +147,25 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         t0 = I.t0;
         t1 = I.t1;
         slot = static_cast<size_t>(i) * P.parts + part;
-    } else {                  // the layers of one (block, part) one after another
-        const int j = k % P.nl;
-        const int item = (k / P.nl) * kXcds + x;
-        const int bi = item / P.parts;
-        part = item - bi * P.parts;
-        if (bi >= P.nb) return;   // uniform
+    } else {
+        int j, bi;
+        if (together) {       // a block's workgroups one after another
+            const int r = k % P.sweep;
+            bi = (k / P.sweep) * kXcds + x;
+            if (bi >= P.nb) return;   // uniform
+            const uint32_t s = P.share[r];
+            j = static_cast<int>(s & 255u);
+            part = static_cast<int>((s >> 8) & 255u);
+            parts = static_cast<int>(s >> 16);
+            slot = static_cast<size_t>(bi) * P.sweep + r;
+        } else {              // the layers of one (block, part) one after another
+            j = k % P.nl;
+            const int item = (k / P.nl) * kXcds + x;
+            bi = item / P.parts;
+            part = item - bi * P.parts;
+            if (bi >= P.nb) return;   // uniform
+            slot = static_cast<size_t>(j) * P.nb * P.parts + static_cast<size_t>(item);
+        }
         b = P.b0 + bi;
         t0 = P.t0;
         t1 = P.t1;
@@ -95,7 +175,6 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         ylt = P.ylt + static_cast<size_t>(j) * n;
         s_pre = P.s_pre ? P.s_pre + static_cast<size_t>(j) * n : nullptr;
         if (HITS && P.hits) hits = P.hits + static_cast<size_t>(j) * n;
-        slot = static_cast<size_t>(j) * P.nb * P.parts + static_cast<size_t>(item);
     }
     const OccTables T = load_tables(tab);
     const EvLayer L = *T.ev;
@@ -112,7 +191,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         I.ylt = ylt + (a - t0);
         I.s_pre = s_pre ? s_pre + (a - t0) : nullptr;
         I.hits = hits ? hits + (a - t0) : nullptr;
-        for (int64_t k2 = a / P.fwd.tb + part; k2 * P.fwd.tb < z; k2 += P.parts) {
+        for (int64_t k2 = a / P.fwd.tb + part; k2 * P.fwd.tb < z; k2 += parts) {
             I.block = static_cast<int32_t>(k2);
             __syncthreads();   // the previous block's totals have been read
             fwd_block<HITS, false, true>(P.fwd, I, smem);
@@ -135,8 +214,11 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     const uint2 *hdr = DENSE ? nullptr : P.B.hdr + static_cast<size_t>(b) * P.B.ng;
     const uint32_t *start = DENSE ? P.B.start + static_cast<size_t>(b) * (P.B.catalog + 1) : nullptr;
     const int n_units = (L.n_set + kWave - 1) / kWave;
-    const int u0 = static_cast<int>(static_cast<int64_t>(n_units) * part / P.parts);
-    const int u1 = static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / P.parts);
+    // a part is a range of the units or, where the block's workgroups walk it
+    // together, every parts-th of them
+    const int u1 = together ? n_units : static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / parts);
+    const int first_u = together ? w * parts + part : static_cast<int>(static_cast<int64_t>(n_units) * part / parts) + w;
+    const int step_u = together ? kEvfWaves * parts : kEvfWaves;
 
     // lane's set event of unit u, its header, its list [s, s + c) of entries
     auto load_rec = [&](int u, EvRec &r, int &nb) {
@@ -202,8 +284,8 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     int n0, n1, n2;
     uint32_t s0, c0, s1, c1;
     EvPiece a0{}, a1{}, e0{}, e1{};   // the first two pieces of a list
-    load_rec(u0 + w, r0, n0);
-    load_rec(u0 + w + kEvfWaves, r1, n1);
+    load_rec(first_u, r0, n0);
+    load_rec(first_u + step_u, r1, n1);
     {
         const uint2 h = load_hdr(r0.ev);
         find(r0.ev, h, s0, c0);
@@ -211,8 +293,8 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     load_piece(s0, c0, 0, a0);
     load_piece(s0, c0, 1, e0);
     uint2 h1 = load_hdr(r1.ev);
-    for (int u = u0 + w; u < u1; u += kEvfWaves) {
-        load_rec(u + 2 * kEvfWaves, r2, n2);
+    for (int u = first_u; u < u1; u += step_u) {
+        load_rec(u + 2 * step_u, r2, n2);
         find(r1.ev, h1, s1, c1);
         load_piece(s1, c1, 0, a1);
         load_piece(s1, c1, 1, e1);
@@ -247,7 +329,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     }
     __syncthreads();
 
-    if (P.parts > 1) {
+    if (parts > 1) {
         unsigned char *p = P.partial + slot * ev_slot_bytes(P.B.et, HITS);
         unsigned long long *ph = reinterpret_cast<unsigned long long *>(p);
         uint32_t *pl = reinterpret_cast<uint32_t *>(p + static_cast<size_t>(P.B.et) * 8);
@@ -311,11 +393,20 @@ __global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
     const int64_t t = static_cast<int64_t>(b) * P.B.et + i;
     if (i >= P.B.et || t < t0 || t >= t1) return;   // all lanes of a trial together
     const size_t slot = ev_slot_bytes(P.B.et, HITS);
-    const unsigned char *p = P.partial + (static_cast<size_t>(u) * P.parts + sub) * slot;
+    int parts = P.parts;
+    size_t slot0 = static_cast<size_t>(u) * P.parts;
+    if (P.sweep > 0 && P.share[P.sweep + P.nl + 1] != 0u) {   // (G is 1: many blocks)
+        const int j = u / P.nb, bi = u - j * P.nb;
+        const uint32_t f = P.share[P.sweep + j];
+        parts = static_cast<int>(P.share[P.sweep + j + 1] - f);
+        slot0 = static_cast<size_t>(bi) * P.sweep + f;
+    }
+    if (parts == 1) return;   // uniform: the results are there
+    const unsigned char *p = P.partial + (slot0 + sub) * slot;
     unsigned long long h = 0, l = 0;
     int32_t k = 0;
 #pragma unroll 4
-    for (int q = sub; q < P.parts; q += G, p += static_cast<size_t>(G) * slot) {
+    for (int q = sub; q < parts; q += G, p += static_cast<size_t>(G) * slot) {
         h += reinterpret_cast<const unsigned long long *>(p)[i];
         l += reinterpret_cast<const uint32_t *>(p + static_cast<size_t>(P.B.et) * 8)[i];
         if (HITS) k += reinterpret_cast<const int32_t *>(p + static_cast<size_t>(P.B.et) * 12)[i];
@@ -341,7 +432,7 @@ static int32_t launch_ev(const EvfParams &P, bool hits, unsigned grid, int n_set
         if (P.B.dense) k_ev_fwd<false, true><<<grid, kEvfThreads, 0, st>>>(P);
         else k_ev_fwd<false, false><<<grid, kEvfThreads, 0, st>>>(P);
     }
-    if (P.parts > 1) {
+    if (P.parts > 1 || P.sweep > 0) {
         int G = 1;   // lanes per trial: while that leaves the device room
         while (2 * G <= std::min(P.parts, kWave) && static_cast<int64_t>(2 * G) * n_sets * P.B.et <= 65536) G *= 2;
         const int per = (P.B.et * G + 255) / 256;
@@ -395,8 +486,14 @@ int32_t launch_ev_forward(const EvBlocks &B, const ara_yet *yet, bool hits, cons
     P.nb = reg.ev_nb;
     P.nl = reg.nl;
     P.partial = reg.partial;
+    if (reg.sweep > 0) {
+        P.sweep = reg.sweep;
+        P.share = reg.share;
+        k_ev_share<<<1, kWave, 0, st>>>(P.tabs, P.nl, P.sweep, B.catalog, reg.share);
+    }
     const int64_t items = (static_cast<int64_t>(reg.ev_nb) * reg.parts + kXcds - 1) / kXcds * kXcds;
-    return launch_ev(P, hits, static_cast<unsigned>(items * reg.nl), reg.nl * reg.ev_nb, st);
+    const int64_t blocks = (static_cast<int64_t>(reg.ev_nb) + kXcds - 1) / kXcds * kXcds;
+    return launch_ev(P, hits, static_cast<unsigned>(std::max(items * reg.nl, blocks * reg.sweep)), reg.nl * reg.ev_nb, st);
 }
 
 int32_t launch_ev_list(const EvBlocks &B, const ara_yet *yet, const FwdItem *d_items, int n_items, int parts,

@@ -102,6 +102,24 @@ int32_t launch_forward(const ara_yet *yet, int n_sr, bool hits, bool f32, const 
     return ARA_OK;
 }
 
+// The workgroups of a block that may walk it together (k_ev_share), or 0.
+// Four layers or more: two share too little for the parts' totals they write
+// (400,000 x 1000, 10 and 15 ELTs: 253 us, dealt 299; three layers 347 and
+// 353).  Blocks of 6M occurrences, 12 MB of lists beside 16 parts' 1.5 MB of
+// totals (1M x 250, four layers: 402 and 486).  And at least eight blocks per
+// XCD, since a block stays on one (150,000 x 1000, 19 blocks: 202 and 237;
+// 1M x 1000, 122 blocks: 1161 and 783).
+constexpr int kSweep = 16;
+constexpr int kSweepLeast = 4, kSweepMost = 16;   // layers
+constexpr int64_t kSweepEntries = 6'000'000;
+constexpr int kShareWords = kSweep + kSweepMost + 2;
+
+static int ev_sweep(int n_layers, const EvBlocks &B, const ara_yet *yet, int64_t blocks) {
+    const bool yes = n_layers >= kSweepLeast && n_layers <= kSweepMost && blocks >= 8 * kXcds &&
+                     yet->nnz / std::max(B.neb, 1) >= kSweepEntries;
+    return yes ? kSweep : 0;
+}
+
 static size_t fwd_workspace(const ara_tables *tables, const ara_layers *layers, bool hits) {
     const OccLayoutSizes z = occ_sizes(tables->catalog, hits);
     const int L = layers->n_layers;
@@ -110,16 +128,20 @@ static size_t fwd_workspace(const ara_tables *tables, const ara_layers *layers, 
     b += align256(static_cast<size_t>(L + 1) * sizeof(int32_t));
     b += align256(static_cast<size_t>(std::max(nJ, 1)) * sizeof(int32_t));
     b += align256(static_cast<size_t>(std::max(L, 1)) * sizeof(OccTables));
+    b += align256(kShareWords * sizeof(uint32_t));
     b += static_cast<size_t>(L) * z.per_layer;
     return b;
 }
 
 // Partial totals a forward workspace has room for: those of two rounds of
-// one workgroup per CU, and of one small block at least.
-static size_t partial_bytes(const ara_yet *yet, bool hits, bool f32) {
+// one workgroup per CU, and of every block's where its workgroups walk it
+// together.
+static size_t partial_bytes(const ara_yet *yet, int n_layers, bool hits, bool f32) {
     EvBlocks B{};
     if (f32 || !ev_blocks(yet, &B)) return 0;
-    return static_cast<size_t>(2 * device_cu_count()) * ev_slot_bytes(B.et, hits);
+    const size_t slots = std::max(static_cast<size_t>(2 * device_cu_count()),
+                                  static_cast<size_t>(ev_sweep(n_layers, B, yet, B.neb)) * static_cast<size_t>(B.neb));
+    return slots * ev_slot_bytes(B.et, hits);
 }
 
 static int32_t check_pair(const ara_tables *tables, const ara_yet *yet) {
@@ -145,7 +167,7 @@ extern "C" int32_t ara_ylt_workspace_bytes(const ara_tables *tables, const ara_y
                            (flags & ARA_F_FP32_ACCUM) != 0, &bb, &cv)))
         return rc;
     *bytes = fwd_workspace(tables, layers, (flags & ARA_F_EMIT_HITS) != 0) +
-             partial_bytes(yet, (flags & ARA_F_EMIT_HITS) != 0, (flags & ARA_F_FP32_ACCUM) != 0);
+             partial_bytes(yet, layers->n_layers, (flags & ARA_F_EMIT_HITS) != 0, (flags & ARA_F_FP32_ACCUM) != 0);
     return ARA_OK;
 }
 
@@ -170,7 +192,7 @@ int32_t forward_args(const ara_tables *tables, const ara_yet *yet, const ara_lay
     if ((rc = fwd_lds_plan(yet->trials_per_block, yet->n_ranges, want_hits, (flags & ARA_F_FP32_ACCUM) != 0, &bb, &cv)))
         return rc;
     *least = fwd_workspace(tables, layers, want_hits);
-    *need = *least + partial_bytes(yet, want_hits, (flags & ARA_F_FP32_ACCUM) != 0);
+    *need = *least + partial_bytes(yet, layers->n_layers, want_hits, (flags & ARA_F_FP32_ACCUM) != 0);
     return ARA_OK;
 }
 
@@ -190,6 +212,7 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
     int32_t *d_off = c.take<int32_t>(static_cast<size_t>(L + 1));
     int32_t *d_ids = c.take<int32_t>(static_cast<size_t>(std::max(nJ, 1)));
     OccTables *d_tabs = c.take<OccTables>(static_cast<size_t>(L));
+    uint32_t *d_share = c.take<uint32_t>(kShareWords);
     const int64_t b_lo = trial_begin / yet->trials_per_block;
     const int64_t b_hi = (trial_end + yet->trials_per_block - 1) / yet->trials_per_block;
     const int nb = static_cast<int>(b_hi - b_lo);
@@ -234,8 +257,11 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
         reg.ev_nb = static_cast<int32_t>((trial_end + B.et - 1) / B.et) - reg.ev_b0;
         const size_t slot = ev_slot_bytes(B.et, want_hits);
         const size_t used = c.bytes();
-        reg.parts = ev_parts(static_cast<int64_t>(L) * reg.ev_nb,
-                             ws_bytes > used ? static_cast<int64_t>((ws_bytes - used) / slot) : 0);
+        const int64_t slots = ws_bytes > used ? static_cast<int64_t>((ws_bytes - used) / slot) : 0;
+        reg.parts = ev_parts(static_cast<int64_t>(L) * reg.ev_nb, slots);
+        reg.sweep = ev_sweep(L, B, yet, reg.ev_nb);
+        if (static_cast<int64_t>(reg.sweep) * reg.ev_nb > slots) reg.sweep = 0;
+        reg.share = d_share;
         reg.partial = reinterpret_cast<unsigned char *>(ws) + used;
         return launch_ev_forward(B, yet, want_hits, reg, st);
     }

@@ -182,6 +182,10 @@ struct FwdRegular {
     // is split over, and the partial totals' room (parts > 1)
     unsigned char *partial;
     int32_t parts, ev_b0, ev_nb, ev_et;
+    // ... or, with sweep > 0 and uneven layers, the workgroups of each block, and
+    // room for the table that deals them to the layers ([sweep + nl + 2])
+    int32_t sweep;
+    uint32_t *share;
 };
 
 // Bytes of one workgroup's partial totals: hi, lo and (with hits) the counts

@@ -168,3 +168,40 @@ def test_many_layers(ara):
     lists = [g.choice(6, size=int(g.integers(0, 5)), replace=False) for _ in range(70)]
     check(ara, workload("layers", 500, 30, 9_000, [300, 900, 100, 700, 50, 2000], lists,
                         [TERMS[k % 3] for k in range(70)], 2))
+
+
+@pytest.mark.parametrize("kind", ["uneven", "even", "few", "five"])
+def test_layers_walking_a_block_together(ara, kind):
+    """Four layers and more over 65 blocks of 6.3M occurrences, where a block's
+    workgroups may be dealt to its layers: every row is, bit for bit, that of
+    its layer alone (the sums are exact), with and without hit counts and over
+    part of the trials."""
+    import torch
+    n, per, C = 530_000, 770, 1_000_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    print(f"[gpu-evfwd] {kind}: {n} x {per}", flush=True)
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda") * per
+    ids = torch.randint(0, C, (n * per,), generator=g, dtype=torch.int32, device="cuda")
+    sizes = {"uneven": [3, 9, 14, 20], "even": [9, 9, 9, 9], "few": [1, 1, 2, 2], "five": [1, 4, 8, 16, 20]}[kind]
+    rec = 12_000
+    K = sum(sizes)
+    ro = torch.arange(K + 1, dtype=torch.int64, device="cuda") * rec
+    ri = torch.cat([torch.randperm(C, generator=g, device="cuda", dtype=torch.int32)[:rec] for _ in range(K)])
+    rl = torch.exp(12.0 + 1.5 * torch.randn(K * rec, generator=g, device="cuda"))
+    tables = ara.EltTables(ro, ri, rl, C)
+    yet = ara.PreparedYet(off, ids, C, transposed=False)
+    del ids
+    eo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    et = torch.tensor([[1.0, 5e4, 5e6]] * K, dtype=torch.float64, device="cuda")
+    lt = torch.tensor([[1e4 * 4 ** j, 1e8, 1e6, 1e9] for j in range(len(sizes))], dtype=torch.float64, device="cuda")
+    layers = ara.Layers(eo, np.arange(K, dtype=np.int32))
+    y, s, _ = ara.ylt_forward(tables, yet, layers, et, lt, check=True)
+    yh, sh, h = ara.ylt_forward(tables, yet, layers, et, lt, want_hits=True, check=True)
+    yr, sr, _ = ara.ylt_forward(tables, yet, layers, et, lt, 1234, n - 777, check=True)
+    assert torch.equal(y, yh) and torch.equal(s, sh)
+    assert torch.equal(yr, y[:, 1234:n - 777]) and torch.equal(sr, s[:, 1234:n - 777])
+    for j, J in enumerate(sizes):
+        one = ara.Layers(np.array([0, J], np.int32), np.arange(eo[j], eo[j + 1], dtype=np.int32))
+        y1, s1, h1 = ara.ylt_forward(tables, yet, one, et, lt[j:j + 1].contiguous(), want_hits=True, check=True)
+        assert torch.equal(y1[0], y[j]) and torch.equal(s1[0], s[j]) and torch.equal(h1[0], h[j]), j
