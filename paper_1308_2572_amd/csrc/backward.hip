@@ -303,7 +303,9 @@ struct BwdGather {
     int64_t *W;                   // [n_layers][n_cot][catalog], by hot index
     BwdSparse sp;                 // the second form's state
     int32_t use_sp;               // 0 when the second form is not available (no trial-major copy)
-    int32_t pad2;
+    int32_t n_layers;
+    EvBlocks B;                   // event-ordered blocks
+    int64_t ev_least;             // hot events, of all layers, from which one row goes through them
 };
 
 // (5) W(e) = sum of v_t over the occurrences (t, e), per hot event, as a
@@ -314,11 +316,11 @@ struct BwdGather {
 // trials' fixed-point weights; the group's sums meet in a lane reduction and
 // the eight slice sums in one integer atomic add per (event, row) -- exact
 // in any order.
-template <int CS, int G>
-__global__ __launch_bounds__(256) void k_bwd_w(BwdGather P) {
-    constexpr int kU = 2;
-    const int x = blockIdx.x % kSlices, wi = blockIdx.x / kSlices, nw = gridDim.x / kSlices, j = blockIdx.y;
-    if (P.use_sp && form_of(P.sp, j) != kDense) return;   // W comes from the other forms
+// Workgroup wi of nw on slice x, `threads` threads; kU entries per lane in
+// flight.
+template <int CS, int G, int kU>
+__device__ __forceinline__ void gather_w(const BwdGather &P, int x, int wi, int nw, int j, int threads) {
+    const int tid = static_cast<int>(threadIdx.x);
     const int64_t tx0 = static_cast<int64_t>(x) * P.slice_trials;
     const int64_t ulo = max<int64_t>(P.t0 - tx0, 0), uhi = min<int64_t>(P.t1 - tx0, P.slice_trials);
     if (uhi <= ulo) return;   // the slice lies outside the call's trials
@@ -328,9 +330,9 @@ __global__ __launch_bounds__(256) void k_bwd_w(BwdGather P) {
     const int32_t *hev = P.hot_ev + static_cast<size_t>(j) * P.catalog;
     const int64_t *off = P.tr_off + static_cast<int64_t>(x) * P.catalog;
     int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
-    const int sub = threadIdx.x & (G - 1);
-    const int ngrp = nw * static_cast<int>(blockDim.x) / G;
-    for (int g = (wi * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x)) / G; g < H; g += ngrp) {
+    const int sub = tid & (G - 1);
+    const int ngrp = nw * threads / G;
+    for (int g = (wi * threads + tid) / G; g < H; g += ngrp) {
         const int e = hev[g];
         const int64_t o0 = off[e], o1 = off[e + 1];
         int64_t acc[CS];
@@ -371,10 +373,179 @@ __global__ __launch_bounds__(256) void k_bwd_w(BwdGather P) {
     }
 }
 
+template <int CS, int G>
+__global__ __launch_bounds__(256) void k_bwd_w(BwdGather P) {
+    const int j = blockIdx.y;
+    if (P.use_sp && form_of(P.sp, j) != kDense) return;   // W comes from the other forms
+    gather_w<CS, G, 2>(P, blockIdx.x % kSlices, blockIdx.x / kSlices, gridDim.x / kSlices, j, 256);
+}
+
+// One row over the event-ordered blocks.  The gather fetches 8 bytes of v per
+// occurrence from L2, a line each, and is bound by the lines (131e9 a second).
+// Here a workgroup keeps its share of the hot events, up to two per thread, and
+// goes through the blocks of trials with a block's v, 64 KB, in LDS: the lists
+// are read once, two bytes an occurrence, W stays in a register and is stored
+// once.  The next block's v, headers and first eight entries are loaded while
+// the present one's are added.  Every workgroup stages all of v, which costs
+// about as much as the lists, so there is one per CU and no more (two, of one
+// event per thread, 209 us where this takes 187; the gather 262: 300,000 x
+// 800, two layers of 10 and 15 ELTs).  The layers' workgroups over one part of
+// the catalogue run on one XCD, block by block together, and share the lists
+// in L2.  Which of the two serves a layer: ev_least.
+constexpr int kBwdEvThreads = 1024;
+constexpr int kEvPer = 2;                // hot events per thread
+constexpr uint32_t kBwdLongList = 256;   // lists beyond this many entries are added by the whole wavefront
+
+struct __attribute__((packed, aligned(2))) EvEight {
+    uint32_t a[4];
+};
+
+// A barrier for LDS alone: the loads in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int G>
+__global__ __launch_bounds__(kBwdEvThreads) void k_bwd_w1(BwdGather P) {
+    __shared__ int64_t v[2][kEvMaxTrials];
+    const int i = blockIdx.x, x = i & (kXcds - 1);
+    const int j = (i / kXcds) % P.n_layers;
+    const int wg = (i / kXcds) / P.n_layers * kXcds + x, n_wg = static_cast<int>(gridDim.x) / P.n_layers;
+    if (P.use_sp && form_of(P.sp, j) != kDense) return;   // uniform: W comes from the other forms
+    const int H = P.hot_base[static_cast<size_t>(j) * (P.n_sr + 1) + P.n_sr];
+    int64_t hot = 0;   // of all layers
+    for (int l = threadIdx.x & 63; l < P.n_layers; l += kWave) hot += P.hot_base[static_cast<size_t>(l) * (P.n_sr + 1) + P.n_sr];
+    for (int o = 32; o > 0; o >>= 1) hot += __shfl_xor(hot, o);
+    if (hot < P.ev_least) {   // uniform, and the same for every layer
+        static_assert(kXcds == kSlices, "a slice per XCD");
+        gather_w<1, G, 4>(P, x, wg / kSlices, n_wg / kSlices, j, kBwdEvThreads);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t *vq = P.vq + static_cast<size_t>(j) * P.n;
+    const int32_t *hev = P.hot_ev + static_cast<size_t>(j) * P.catalog;
+    const EvBlocks &B = P.B;
+    const int b0 = static_cast<int>(P.t0 / B.et), b1 = static_cast<int>((P.t1 + B.et - 1) / B.et);
+    const int g1 = static_cast<int>(static_cast<int64_t>(H) * (wg + 1) / n_wg);
+    // v of the trials k 1024 + tid of block b, 0 outside the call's
+    constexpr int kPer = kEvMaxTrials / kBwdEvThreads;
+    int64_t nv[kPer];
+    auto load_v = [&](int b) {
+        const int64_t base = static_cast<int64_t>(b) * B.et - P.t0;   // the block's trial 0 in the call
+        const int lo = static_cast<int>(max<int64_t>(-base, 0)), hi = static_cast<int>(min<int64_t>(P.n - base, B.et));
+        const char *vb = reinterpret_cast<const char *>(vq + base);
+        uint32_t at = static_cast<uint32_t>(tid) * 8u;
+        asm("" : "+v"(at));   // formed here: eight addresses kept from the loop's start would be spilled
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int t = k * kBwdEvThreads + tid;
+            nv[k] = 0;
+            if (t >= lo && t < hi) nv[k] = *reinterpret_cast<const int64_t *>(vb + k * kBwdEvThreads * 8 + at);
+        }
+    };
+    auto put_v = [&](int b) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) v[b & 1][k * kBwdEvThreads + tid] = nv[k];
+    };
+    for (int gb = static_cast<int>(static_cast<int64_t>(H) * wg / n_wg); gb < g1; gb += kEvPer * kBwdEvThreads) {   // uniform
+        int e[kEvPer];   // the thread's events, -1: none
+        int64_t acc[kEvPer];
+        uint32_t s[kEvPer], c[kEvPer];   // their lists in the present block
+        EvEight d[kEvPer] = {};          // and the first entries
+        uint2 h[kEvPer];                 // the next block's headers
+#pragma unroll
+        for (int q = 0; q < kEvPer; ++q) {
+            const int g = gb + q * kBwdEvThreads + tid;
+            e[q] = g < g1 ? hev[g] : -1;
+            acc[q] = 0;
+        }
+        auto load_hdr = [&](int b, int q) -> uint2 {
+            const int ev = max(e[q], 0);   // event 0's lists (always there) for threads without one
+            if (b >= b1) return make_uint2(0u, 0u);
+            if (B.dense) {
+                const uint32_t *p = B.start + static_cast<size_t>(b) * (B.catalog + 1) + ev;
+                return make_uint2(p[0], p[1]);
+            }
+            return B.hdr[static_cast<size_t>(b) * B.ng + (ev >> 3)];
+        };
+        auto find = [&](int b, int q, uint32_t &s1, uint32_t &c1) {
+            if (B.dense) {
+                s1 = h[q].x;
+                c1 = h[q].y - h[q].x;
+            } else {
+                ev_short_list(h[q], static_cast<uint32_t>(e[q]) & 7u, s1, c1);
+                if (e[q] >= 0 && ev_long(h[q].y)) ev_list(B, b, e[q], s1, c1);
+            }
+            if (e[q] < 0 || b >= b1) c1 = 0;
+        };
+        auto load8 = [&](int b, uint32_t at, EvEight &to) { to = *reinterpret_cast<const EvEight *>(B.ent + B.base[b] + at); };
+        auto add8 = [&](const int64_t *vb, const EvEight &en, uint32_t n, int64_t &to) {
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k)
+                if (k < n) to += vb[((k & 1u) ? en.a[k >> 1] >> 16 : en.a[k >> 1]) & kEvTrialMask];
+        };
+        load_v(b0);
+#pragma unroll
+        for (int q = 0; q < kEvPer; ++q) h[q] = load_hdr(b0, q);
+#pragma unroll
+        for (int q = 0; q < kEvPer; ++q) {
+            find(b0, q, s[q], c[q]);
+            if (c[q] > 0) load8(b0, s[q], d[q]);
+            h[q] = load_hdr(b0 + 1, q);
+        }
+        __syncthreads();   // the last batch's v has been read
+        put_v(b0);
+        __syncthreads();
+        for (int b = b0; b < b1; ++b) {
+            const int64_t *vb = v[b & 1];
+            if (b + 1 < b1) load_v(b + 1);
+            uint32_t s1[kEvPer], c1[kEvPer];
+            EvEight d1[kEvPer] = {};
+#pragma unroll
+            for (int q = 0; q < kEvPer; ++q) {
+                find(b + 1, q, s1[q], c1[q]);
+                if (c1[q] > 0) load8(b + 1, s1[q], d1[q]);
+                h[q] = load_hdr(b + 2, q);
+            }
+#pragma unroll
+            for (int q = 0; q < kEvPer; ++q) {
+                for (uint64_t big = __ballot(c[q] > kBwdLongList); big; big &= big - 1) {
+                    const int l = __builtin_ctzll(big);
+                    const uint32_t sl = __shfl(s[q], l), cl = __shfl(c[q], l);
+                    const uint16_t *ent = B.ent + B.base[b] + sl;
+                    unsigned long long sum = 0;
+                    for (uint32_t k = lane; k < cl; k += kWave) sum += static_cast<unsigned long long>(vb[ent[k] & kEvTrialMask]);
+                    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                    if (lane == l) {
+                        acc[q] = static_cast<int64_t>(static_cast<unsigned long long>(acc[q]) + sum);
+                        c[q] = 0;
+                    }
+                }
+                add8(vb, d[q], c[q], acc[q]);
+                for (uint32_t k = 8; __any(k < c[q]); k += 8)
+                    if (k < c[q]) {
+                        load8(b, s[q] + k, d[q]);
+                        add8(vb, d[q], c[q] - k, acc[q]);
+                    }
+                s[q] = s1[q];
+                c[q] = c1[q];
+                d[q] = d1[q];
+            }
+            // block b + 1's buffer was last read before the barrier that ended block b - 1
+            if (b + 1 < b1) put_v(b + 1);
+            lds_barrier();
+        }
+#pragma unroll
+        for (int q = 0; q < kEvPer; ++q)
+            if (e[q] >= 0) P.W[static_cast<size_t>(j) * P.catalog + gb + q * kBwdEvThreads + tid] = acc[q];
+    }
+}
+
 template <int G>
 static void launch_bwd_w(int cs, dim3 grid, hipStream_t st, const BwdGather &S) {
-    if (cs == 1) k_bwd_w<1, G><<<grid, 256, 0, st>>>(S);
-    else if (cs == 2) k_bwd_w<2, G><<<grid, 256, 0, st>>>(S);
+    if (cs == 1) {
+        // a workgroup per CU over the layers, a multiple of the slices for each
+        const int per = std::max(1, device_cu_count() / (S.n_layers * kXcds));
+        k_bwd_w1<G><<<static_cast<unsigned>(per * kXcds) * static_cast<unsigned>(S.n_layers), kBwdEvThreads, 0, st>>>(S);
+    } else if (cs == 2) k_bwd_w<2, G><<<grid, 256, 0, st>>>(S);
     else k_bwd_w<4, G><<<grid, 256, 0, st>>>(S);
 }
 
@@ -910,6 +1081,21 @@ static int bwd_nwg_v(int64_t n) {   // about two trials per thread, at most 512 
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + 2047) / 2048, 512)));
 }
 
+// Hot events, of all layers, from which k_bwd_w1 goes through the event-ordered
+// blocks.  A block costs every workgroup 2.6 us (its v from L2, latency), and
+// the device 10 ps per hot event, and 5 ps more for each occurrence of its
+// list past the fourth; the gather 280 ps per hot event and 6.5 per
+// occurrence.  From these calls (us: gather, blocks): 1M x 1000, 15 ELTs 574,
+// 608, 6 ELTs 279, 501; 300,000 x 800, two layers 407, 279, with few hot
+// events 157, 205; 100,000 x 1000, 15 ELTs 153, 127, 5 ELTs 81, 99; 400,000 x
+// 1000 over 300,000 events 306, 380; 400,000 x 200 132, 215; 20,000 x 1000
+// 112, 87.  The blocks have to be a tenth the faster.
+static int64_t ev_least(double blocks, double per_event) {
+    const double list = per_event / blocks;
+    const double saved = 280.0 + 6.5 * per_event - blocks * (10.0 + 5.0 * std::max(list - 4.0, 0.0));   // ps per hot event
+    return saved > 0.0 ? static_cast<int64_t>(std::min(1.1 * 2.6e6 * blocks / saved + 1.0, 1e15)) : INT64_MAX;
+}
+
 static int64_t dev_blocks(int64_t n) { return std::max<int64_t>(1, (n + kDevChunk - 1) / kDevChunk); }
 
 static int64_t bit_words(int64_t n) { return (std::max<int64_t>(n, 1) + 63) / 64 + 1; }   // one past the last
@@ -1048,6 +1234,13 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     S.catalog = tables->catalog;
     S.n_sr = B.z.n_sr;
     S.n_cot = n_cot;
+    S.n_layers = L;
+    S.ev_least = INT64_MAX;
+    if (ev_blocks(yet, &S.B) && S.B.et <= kEvMaxTrials && yet->nnz > 0) {
+        const double blocks = static_cast<double>((trial_end + S.B.et - 1) / S.B.et - trial_begin / S.B.et);
+        const double per_event = static_cast<double>(yet->nnz) / tables->catalog * static_cast<double>(n) / yet->n_trials;
+        S.ev_least = ev_least(blocks, per_event);
+    }
     S.slice_trials = yet->slice_trials;
     S.t0 = trial_begin;
     S.t1 = trial_end;

@@ -376,3 +376,36 @@ def test_two_valued_form_is_bitwise_the_gather(ara, rows, share):
         cot = torch.tensor(c, device="cuda")
         a, b = sparse(sp, cot, a0, a1), dense(sp, cot, a0, a1)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), (a0, a1, nd)
+
+
+@pytest.mark.parametrize("trials,mean,catalog,n_elts", [(2000, 400, 60_000, 8), (20_000, 100, 40_000, 12), (9000, 30, 700, 3)])
+def test_one_row_over_blocks_is_bitwise_the_gather(ara, trials, mean, catalog, n_elts):
+    """A dense cotangent of one row over the event-ordered blocks (short lists
+    and long ones, events that occur thousands of times in a block) and, with
+    the mark of those blocks cleared, by the gather: the same integers, over
+    all trials and over parts that start and end inside blocks."""
+    import torch
+    g = np.random.default_rng(trials)
+    lens = g.poisson(mean, size=trials)
+    off = np.zeros(trials + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    elts = synth.lognormal_elts(5, [catalog // 6] * n_elts, catalog, mu=11.0, sigma=1.5)
+    ids[g.random(len(ids)) < 0.02] = elts.rec_ids[0]
+    layers = synth.Layers(np.array([0, n_elts, 2 * n_elts - 1], np.int32),
+                          np.concatenate([np.arange(n_elts), np.arange(1, n_elts)]).astype(np.int32),
+                          np.array([[1e4, 5e6, 1e4, 5e9], [0.0, 1e6, 0.0, 1e9]]))
+    w = synth.Workload("blocks", synth.Yet(catalog, off, ids), elts, layers, 0.9)
+    tables = ara.EltTables.from_numpy(w.elts)
+    lay = ara.Layers(w.layers.elt_off, w.layers.elt_ids)
+    et = torch.tensor(w.elts.terms, dtype=torch.float64, device="cuda")
+    lt = torch.tensor(w.layers.terms, dtype=torch.float64, device="cuda")
+    blocks, gather = (ara.PreparedYet.from_numpy(w.yet, trial_major=False) for _ in range(2))
+    gather.handle.reserved = 0
+    _, s_pre, _ = ara.ylt_forward(tables, blocks, lay, et, lt)
+    cot = torch.tensor(g.uniform(-2.0, 2.0, size=(1, 2, trials)), device="cuda")
+    for t0, t1 in [(0, trials), (1, trials - 1), (trials // 3, trials // 3 + 7), (trials // 2, trials)]:
+        sp, c = s_pre[:, t0:t1].contiguous(), cot[:, :, t0:t1].contiguous()
+        a = ara.ylt_backward(tables, blocks, lay, et, lt, sp, c, t0, t1)
+        b = ara.ylt_backward(tables, gather, lay, et, lt, sp, c, t0, t1)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]), (t0, t1)
