@@ -46,8 +46,11 @@ __global__ void k_tab_scatter(const int64_t *__restrict__ rec_off, const int32_t
 }
 
 // Pass 2: records stored with loss 0 are indistinguishable from absence.
+// Nothing where pass 1 found a fault (its IDs may lie anywhere).
 __global__ void k_tab_clear_zero(const int64_t *__restrict__ rec_off, const int32_t *__restrict__ rec_ids,
-                                 const float *__restrict__ rec_loss, int32_t words, uint32_t *__restrict__ present) {
+                                 const float *__restrict__ rec_loss, int32_t words, uint32_t *__restrict__ present,
+                                 const int32_t *__restrict__ err) {
+    if (*err != 0) return;
     const int k = blockIdx.y;
     const int64_t a = rec_off[k], b = rec_off[k + 1];
     for (int64_t i = a + blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < b;
@@ -86,7 +89,17 @@ extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const i
     int32_t *misc = c.take<int32_t>(64);
     std::vector<int64_t> off(static_cast<size_t>(n_elts) + 1);
     ARA_HIP(hipMemcpyAsync(off.data(), rec_off, off.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    ARA_HIP(hipStreamSynchronize(st));
+    hipEvent_t have = nullptr;   // the offsets have arrived; the tables are cleared meanwhile
+    ARA_HIP(hipEventCreateWithFlags(&have, hipEventDisableTiming));
+    hipError_t e = hipEventRecord(have, st);
+    if (e == hipSuccess) e = hipMemsetAsync(loss, 0, static_cast<size_t>(n_elts) * catalog * sizeof(float), st);
+    if (e == hipSuccess) e = hipMemsetAsync(present, 0, static_cast<size_t>(n_elts) * words * sizeof(uint32_t), st);
+    if (e == hipSuccess) e = hipMemsetAsync(misc, 0, 64 * sizeof(int32_t), st);
+    const hipError_t w = hipEventSynchronize(have);
+    (void)hipEventDestroy(have);
+    if (w != hipSuccess || e != hipSuccess) (void)hipStreamSynchronize(st);   // off is written to until then
+    ARA_HIP(w);
+    ARA_HIP(e);
     int64_t max_rec = 0;
     if (off[0] != 0) return fail(ARA_E_RANGE, "rec_off[0] must be 0");
     for (int32_t k = 0; k < n_elts; ++k) {
@@ -94,21 +107,17 @@ extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const i
         max_rec = std::max<int64_t>(max_rec, off[k + 1] - off[k]);
     }
     if (max_rec > 0 && (!rec_ids || !rec_loss)) return fail(ARA_E_INVAL, "ara_build_elt_tables: null records");
-    ARA_HIP(hipMemsetAsync(loss, 0, static_cast<size_t>(n_elts) * catalog * sizeof(float), st));
-    ARA_HIP(hipMemsetAsync(present, 0, static_cast<size_t>(n_elts) * words * sizeof(uint32_t), st));
-    ARA_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int32_t), st));
     if (n_elts > 0 && max_rec > 0) {
         const unsigned gx = static_cast<unsigned>(std::min<int64_t>((max_rec + 255) / 256, 4096));
         dim3 grid(gx, static_cast<unsigned>(n_elts));
         k_tab_scatter<<<grid, 256, 0, st>>>(rec_off, rec_ids, rec_loss, catalog, words, loss, present, misc);
         ARA_HIP(hipGetLastError());
+        k_tab_clear_zero<<<grid, 256, 0, st>>>(rec_off, rec_ids, rec_loss, words, present, misc);
+        ARA_HIP(hipGetLastError());
         int32_t err = 0;
         ARA_HIP(hipMemcpyAsync(&err, misc, sizeof(err), hipMemcpyDeviceToHost, st));
         ARA_HIP(hipStreamSynchronize(st));
         if (err) return fail(err, std::string("ara_build_elt_tables: ") + ara_status_string(err));
-        k_tab_clear_zero<<<grid, 256, 0, st>>>(rec_off, rec_ids, rec_loss, words, present);
-        ARA_HIP(hipGetLastError());
-        ARA_HIP(hipStreamSynchronize(st));
     }
     ara_tables t{};
     t.n_elts = n_elts;
