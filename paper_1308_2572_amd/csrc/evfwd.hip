@@ -14,7 +14,8 @@
 // bytes: 7872 trials in two parts 302 us, 3936 trials 390 us, 1968 trials 510
 // us, the code stream 560 us (one layer, 1M x 1000, 146,000 of 2,000,000
 // events set).  Layers of one block run together on one XCD and share its
-// lists in L2: four layers 786 us (the code stream grouped by four 1750 us).
+// lists in L2: four uneven layers 778 us (the code stream grouped by four 1750
+// us).
 //
 // The totals are integers (EvLayer): O in fixed point, two words, exact, so
 // the sum does not depend on the order in which wavefronts add, on the parts
