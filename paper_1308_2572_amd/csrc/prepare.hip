@@ -117,10 +117,9 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     if (eg.dense) p.start = c.take<uint32_t>(neb * (static_cast<size_t>(catalog) + 1));
     else p.hdr = c.take<uint2>(neb * static_cast<size_t>(eg.ng));
     p.ev_base = c.take<int64_t>(neb + 1);
-    // the sorted records: in the event-major lists' place when there are any
-    // (those are written last); their positions in the place of the blocks'
-    // entries (written after the codes)
-    p.rec = p.tr_ent ? p.tr_ent : c.take<uint32_t>(occ);
+    // the sorted records; their positions in the place of the blocks' entries
+    // (written after the codes)
+    p.rec = c.take<uint32_t>(occ);
     if (flags & ARA_PREP_POSITIONS) p.rpos = p.ent;
     const size_t chunks = static_cast<size_t>(nnz / kChunk + 2 * n_groups_of(g, n_trials) + 2);
     p.rstart = c.take<uint16_t>(chunks * static_cast<size_t>(g.n_ranges + 1));
