@@ -220,6 +220,9 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
     std::vector<OccTables> tabs(static_cast<size_t>(L));
     for (int j = 0; j < L; ++j) tabs[j] = occ_carve(c, z, want_hits);
     EvBlocks B{};
+    // binary32 totals stay with the code stream although it is slower (100,000
+    // trials of 1000: 212 us where exact sums of the rounded O took 109): they
+    // round at every addition in the trial's order, and those are the results
     const bool ev = !f32 && ev_blocks(yet, &B);
     if (ev)
         for (OccTables &t : tabs) {
