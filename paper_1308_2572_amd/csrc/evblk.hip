@@ -23,10 +23,23 @@ constexpr int kEvThreads = 1024;
 constexpr int kEvWaves = kEvThreads / kWave;
 constexpr int kEvItems = kEvChunk / kEvThreads;      // slices of 64 occurrences per wavefront
 constexpr int kEvWin = 1024;                         // tiles counted at once
-constexpr int kSortItems = 20;                       // records per thread of a tile sorted in registers
-constexpr int kSortCap = kSortItems * kEvThreads;    // 20480
+// Records per thread of a tile sorted in registers, and of the tile: 20480, and
+// one per thread less with positions, whose entries take twice the LDS.
+constexpr int sort_items(bool pos) { return pos ? 19 : 20; }
+constexpr int sort_cap(bool pos) { return sort_items(pos) * kEvThreads; }
 constexpr int kSortRuns = 2048;                      // runs of a tile listed at once
 constexpr int kEvSlotBits = 14;                      // event in the tile, in a record
+constexpr int kEvTileBits = 12;                      // largest tile of a catalogue of up to kEvTileMany of them
+constexpr int64_t kEvTileMany = 4096;
+
+// LDS of k_ev_sort for tiles of 2^te_bits events.
+constexpr size_t sort_lds(int te_bits, bool pos) {
+    return ((size_t(1) << te_bits) + 2 * kSortRuns + 1 + kEvWaves) * sizeof(uint32_t) +
+           (pos ? 2 : 1) * static_cast<size_t>(sort_cap(pos)) * sizeof(uint16_t);
+}
+static_assert(sort_lds(kEvSlotBits, true) <= 160 * 1024 && sort_lds(kEvSlotBits, false) <= 160 * 1024,
+              "the largest tile's workgroup fits a CU's LDS");
+static_assert((int64_t(ARA_MAX_CATALOG) >> kEvSlotBits) <= kEvTileMany, "tiles of the largest catalogue");
 static_assert(kEvWin == kEvThreads, "one counter per thread");
 static_assert(kEvItems * kWave == kEvMark, "a wavefront's share of a chunk starts at a mark");
 
@@ -46,11 +59,11 @@ EvGeometry ev_geometry(int64_t n_trials, int64_t nnz, int32_t catalog) {
     g.dense = mean > 6.0;
     // the largest tile of at most 18,000 records on average, at most 4096
     // events (16 KB of counters) while that gives at most 4096 tiles
-    const int most = static_cast<int64_t>(catalog) > 4096 * int64_t(4096) ? 14 : 12;
+    const int most = static_cast<int64_t>(catalog) > kEvTileMany << kEvTileBits ? kEvSlotBits : kEvTileBits;
     g.te_bits = 3;
     while (g.te_bits < most && mean * (2 << g.te_bits) <= 18000.0) ++g.te_bits;
     if (g.te_bits < most)   // crowded small catalogues: no more tiles than a chunk can count in few windows
-        while ((static_cast<int64_t>(catalog) >> g.te_bits) > 4096) ++g.te_bits;
+        while ((static_cast<int64_t>(catalog) >> g.te_bits) > kEvTileMany) ++g.te_bits;
     g.n_tiles = static_cast<int32_t>((static_cast<int64_t>(catalog) + (int64_t(1) << g.te_bits) - 1) >> g.te_bits);
     g.n_chunks = nnz / kEvChunk + g.neb + 1;
     g.n_marks = nnz / kEvMark + 1;
@@ -268,12 +281,13 @@ __global__ __launch_bounds__(1024) void k_ev_tiles(EvBuild B) {
 
 // One workgroup per (block, tile): the tile's records from the block's runs,
 // ranked by event with LDS counters, the header from the counters' scan, the
-// entries placed in LDS and written out in order.  A tile of at most kSortCap
+// entries placed in LDS and written out in order.  A tile of at most sort_cap
 // records is read once (held in registers between counting and placing); a
 // larger one is read twice and its entries are stored directly.
 template <bool POS>
 __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(POS ? 4 : 8, 8))) void k_ev_sort(EvBuild B) {
     extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int kSortItems = sort_items(POS), kSortCap = sort_cap(POS);
     const int te = 1 << B.g.te_bits;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(smem);                       // [te]
     uint32_t *rcum = cnt + te;                                                // [kSortRuns + 1] records before each run
@@ -480,8 +494,7 @@ int32_t ev_build(const EvBuild &B, hipStream_t st) {
     if (B.pos) k_ev_part<true><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
     else k_ev_part<false><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
     k_ev_tiles<<<static_cast<unsigned>(B.g.neb), 1024, 0, st>>>(B);
-    const size_t lds = ((size_t(1) << B.g.te_bits) + 2 * kSortRuns + 1 + kEvWaves) * sizeof(uint32_t) +
-                       (B.pos ? 2 : 1) * kSortCap * sizeof(uint16_t);
+    const size_t lds = sort_lds(B.g.te_bits, B.pos != nullptr);
     const auto sort = B.pos ? k_ev_sort<true> : k_ev_sort<false>;
     ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sort), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(lds)));

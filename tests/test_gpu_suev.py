@@ -123,3 +123,28 @@ def test_layers_without_events(ara):
     """A layer with an empty ELT beside an ordinary one."""
     s = check(ara, workload("empty", 700, 30, 9_000, [0, 900], [[0], [0, 1], []], TERMS, 3), 3)
     assert np.all(s[0] == 0.0) and np.all(s[2] == 0.0)
+
+
+@pytest.mark.parametrize("catalog", [(1 << 24) + 1, 1 << 26])
+def test_largest_tiles_with_positions(ara, catalog):
+    """Catalogues of more than 2^24 events, whose blocks are sorted by tiles of
+    16,384 events, with positions: one tile of more records than are held in
+    registers (19,456 with positions), the others nearly empty."""
+    g = np.random.default_rng(catalog)
+    lens = g.poisson(100, size=600)
+    off = np.zeros(601, np.int64)
+    np.cumsum(lens, out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int64)
+    u = g.random(ids.shape[0])
+    ids[u < 0.4] = g.integers(3 << 14, 4 << 14, size=int((u < 0.4).sum()))
+    ids[u > 0.98] = catalog - 1
+    assert 19 * 1024 < ((ids >> 14) == 3).sum()
+    ids = ids.astype(np.int32)
+    seen = np.unique(ids)
+    recs = [np.sort(g.choice(seen, size=k, replace=False)) for k in (9000, 4000)]
+    rec_off = np.array([0, 9000, 13_000], np.int64)
+    rec_ids = np.concatenate(recs).astype(np.int32)
+    rec_loss = np.exp(g.normal(11.0, 1.5, size=13_000)).astype(np.float32)
+    elts = synth.Elts(catalog, rec_off, rec_ids, rec_loss, np.array([[1.0, 1e3, 5e6], [1.5, 1e4, 2e6]]))
+    layers = synth.Layers(np.array([0, 2, 3], np.int32), np.array([0, 1, 1], np.int32), np.asarray([TERMS[0], OPEN]))
+    check(ara, synth.Workload("largest tiles", synth.Yet(catalog, off, ids), elts, layers, 0.9), 11)
