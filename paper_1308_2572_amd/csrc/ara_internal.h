@@ -57,6 +57,14 @@ __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_
         if (_e != hipSuccess) return ::ara::hip_fail(_e, #call);   \
     } while (0)
 
+// A grid of at least n workgroups: a launch holds fewer than 2^32 threads in
+// one dimension.  Workgroup grid_index() of it has nothing to do from n on.
+inline dim3 grid_of(int64_t n) {
+    constexpr int64_t kRow = 1 << 20;   // of workgroups of 1024 threads
+    return n <= kRow ? dim3(static_cast<unsigned>(n)) : dim3(static_cast<unsigned>(kRow), static_cast<unsigned>((n + kRow - 1) / kRow));
+}
+__device__ __forceinline__ int64_t grid_index() { return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x; }
+
 // Carve a caller buffer into 256-byte aligned pieces.
 struct Carver {
     char *base;

@@ -299,7 +299,9 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(POS 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = static_cast<int>(uni32(tid >> 6));
     const int nt = B.g.n_tiles;
-    const int b = blockIdx.x / nt, tile = blockIdx.x - b * nt;
+    const int64_t item = grid_index();
+    if (item >= static_cast<int64_t>(B.g.neb) * nt) return;   // uniform, before any barrier
+    const int b = static_cast<int>(item / nt), tile = static_cast<int>(item - static_cast<int64_t>(b) * nt);
     const int64_t c0 = ev_chunk0(B.base, b), c1 = ev_chunk0(B.base, b + 1);
     const int64_t o0 = B.base[b];
     const uint32_t t0 = B.tbase[static_cast<size_t>(b) * (nt + 1) + tile];
@@ -498,7 +500,7 @@ int32_t ev_build(const EvBuild &B, hipStream_t st) {
     const auto sort = B.pos ? k_ev_sort<true> : k_ev_sort<false>;
     ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sort), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(lds)));
-    sort<<<static_cast<unsigned>(B.g.neb) * static_cast<unsigned>(B.g.n_tiles), kEvThreads, lds, st>>>(B);
+    sort<<<grid_of(static_cast<int64_t>(B.g.neb) * B.g.n_tiles), kEvThreads, lds, st>>>(B);
     ARA_HIP(hipGetLastError());
     return ARA_OK;
 }

@@ -504,7 +504,9 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
     const int lane = threadIdx.x & 63;
     const int w = static_cast<int>(uni32(threadIdx.x >> 6));
     const int nr = P.part.n_ranges;
-    if (blockIdx.x == gridDim.x - 1) {
+    const int64_t wg = grid_index(), last_wg = (static_cast<int64_t>(P.n_groups) * nr + kEmitWaves - 1) / kEmitWaves;
+    if (wg > last_wg) return;
+    if (wg == last_wg) {
         const int64_t total = P.part.misc[kMiscCodes];
         for (int i = threadIdx.x; i < kPadCodes; i += kEmitThreads) {
             P.code[total + i] = kSkip;
@@ -512,7 +514,7 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
         }
         return;
     }
-    const int64_t idx = blockIdx.x * static_cast<int64_t>(kEmitWaves) + w;
+    const int64_t idx = wg * kEmitWaves + w;
     if (idx >= static_cast<int64_t>(P.n_groups) * nr) return;   // no barriers below
     const int64_t g = idx / nr;
     const int r = static_cast<int>(idx - g * nr);
@@ -812,7 +814,7 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     // CU and holds the segments of up to 40 codes per lane on average; 128
     // (16 KB a wavefront) those of the densest groups
     const bool small = static_cast<double>(nnz) <= 40.0 * kWave * static_cast<double>(ng) * g.n_ranges;
-    const unsigned ge = static_cast<unsigned>((n_segs + kEmitWaves - 1) / kEmitWaves + 1);
+    const dim3 ge = grid_of((n_segs + kEmitWaves - 1) / kEmitWaves + 1);
     if (positions) {
         if (small) k_prep_emit<48, true><<<ge, kEmitThreads, 0, st>>>(M);
         else k_prep_emit<128, true><<<ge, kEmitThreads, 0, st>>>(M);

@@ -250,3 +250,29 @@ def test_event_blocks(ara, n, mean, catalog):
     ids[g.random(ids.shape[0]) < 0.02] = catalog - 1       # a long list in the last group
     ids[g.random(ids.shape[0]) < 0.01] = catalog // 2
     check(ara, synth.Yet(catalog, off, ids))
+
+
+def test_more_sorted_tiles_than_one_grid_row(ara):
+    """9 million trials, all but a few empty, over 2^24 events: 1099 blocks of
+    4096 tiles, 4.6e9 threads of the sort, more than a launch holds in one
+    dimension.  Year losses of the trials that have occurrences."""
+    import torch
+    n, catalog = 9_000_000, 1 << 24
+    g = np.random.default_rng(2)
+    trials = np.sort(g.choice(n, size=4000, replace=False))
+    trials[0], trials[-1] = 0, n - 1
+    lens = np.zeros(n, np.int64)
+    lens[trials] = g.integers(1, 20, size=4000)
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    rec = np.sort(g.choice(catalog, size=50_000, replace=False)).astype(np.int32)
+    rec[-1] = catalog - 1
+    ids = rec[g.integers(0, 50_000, size=int(off[-1]))]
+    loss = np.round(np.exp(g.normal(8.0, 1.0, size=50_000))).astype(np.float32)   # whole numbers: exact sums
+    _say(f"trials {n} catalog {catalog}")
+    yet = ara.PreparedYet.from_numpy(synth.Yet(catalog, off, ids), "cuda", transposed=False)
+    tables = ara.EltTables.from_numpy(synth.Elts(catalog, np.array([0, 50_000], np.int64), rec, loss, None))
+    terms = [torch.tensor([x], dtype=torch.float64, device="cuda") for x in ([1.0, 0.0, np.inf], [0.0, np.inf, 0.0, np.inf])]
+    y, _, _ = ara.ylt_forward(tables, yet, ara.Layers([0, 1], [0]), *terms, check=True)
+    want = np.bincount(np.repeat(np.arange(n), lens), weights=loss.astype(np.float64)[np.searchsorted(rec, ids)], minlength=n)
+    assert np.array_equal(y[0].cpu().numpy(), want)
