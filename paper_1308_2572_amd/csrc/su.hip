@@ -135,16 +135,23 @@ __device__ T block_exclusive_scan(const T *in, T *out, int n, T *wsum) {
 // ELT limits) <= 2^e, so in units of 2^(e - 46) a trial's (at most 65536)
 // add up to less than 2^62, and the 48 bits below the unit of each to less
 // than 2^64: two integers per trial, and a total that does not depend on the
-// order.  What a loss holds below 2^(e - 94) is rounded away: less than 2^-54
-// of every loss of at least 2^-16 of the smallest (scaled) mean, which a
-// layer has to have above 2^(e - 24).  gexp is e - 46; mode 0: some layer's
-// terms or means do not fit this (no finite limit, for one), and the stream
-// of the codes serves it.
+// order.  No draw lies below exp(m - kZMost s), so where that, scaled, and
+// every ELT limit is at least 2^(e - 41) no loss has a bit below 2^(e - 94):
+// the sums are exact, and the total is rounded once.  gexp is e - 46; mode 0:
+// some layer's terms or draws do not fit this (no finite limit, for one), and
+// the stream of the codes serves it.
 struct SuBound {
     double most;      // B
-    uint32_t least;   // bitwise complement of the smallest positive scaled mean, a binary32 value rounded down (0: none)
+    uint32_t least;   // bitwise complement of the smallest of these draws and limits, binary32, rounded down
     uint32_t pad;
 };
+// Largest |z| of a draw: sqrt(-2 ln u), u >= 2^-53, is 8.572.
+constexpr double kZMost = 8.58;
+constexpr int kSuLeastBits = 41;
+
+// The complement of a binary32 value at most v (0 for what is not positive):
+// the smallest of several is the largest of these.
+__device__ __forceinline__ uint32_t su_least(double v) { return ~__float_as_uint(v > 0.0 ? __double2float_rd(v) : 0.0f); }
 
 __device__ __forceinline__ EvLayer su_form(const SuBound &b) {
     EvLayer f{};
@@ -153,8 +160,8 @@ __device__ __forceinline__ EvLayer su_form(const SuBound &b) {
     frexp(b.most, &e);
     f.gexp = e - 46;
     f.frac = 48;
-    const double low = static_cast<double>(__uint_as_float(~b.least));   // NaN without a positive mean
-    f.mode = e > -800 && !(low < ldexp(1.0, e - 24));
+    const double low = static_cast<double>(__uint_as_float(~b.least));   // NaN without ELTs
+    f.mode = e > -800 && !(low < ldexp(1.0, e - kSuLeastBits));
     return f;
 }
 
@@ -175,10 +182,21 @@ __global__ __launch_bounds__(kSuThreads) void k_su_base(const OccTables *__restr
     const int j = blockIdx.x;
     if (threadIdx.x < kWave) {
         double b = 0.0;
-        for (int q = elt_off[j] + threadIdx.x; q < elt_off[j + 1]; q += kWave) b += elt_terms[3 * elt_ids[q] + 2];
-        for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o);
+        uint32_t low = 0;
+        for (int q = elt_off[j] + threadIdx.x; q < elt_off[j + 1]; q += kWave) {
+            const double lim = elt_terms[3 * elt_ids[q] + 2];
+            b += lim;
+            low = max(low, su_least(lim));
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            b += __shfl_xor(b, o);
+            low = max(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), o)));
+        }
         const double occL = layer_terms[4 * j + 1];
-        if (threadIdx.x == 0) bound[j].most = b < occL ? b : occL;
+        if (threadIdx.x == 0) {
+            bound[j].most = b < occL ? b : occL;
+            bound[j].least = low;
+        }
     }
     const OccTables T = load_tables(tabs + j);
     uint32_t *ub = ubase + static_cast<size_t>(j) * (n_sr + 1);
@@ -299,7 +317,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
 // Per layer: each entry's lognormal parameters from its mean and deviation,
 // s^2 = ln(1 + sigma^2/mu^2), m = ln mu - s^2/2 (0, 0 for an exact entry), one
 // thread per entry so that the binary64 logarithms run on full wavefronts.
-// Also the smallest positive scaled mean of the layer's records.
+// Also the smallest scaled draw that they allow.
 __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ eregion,
                                                    const uint64_t *__restrict__ ecap,
                                                    const uint64_t *__restrict__ eused, SuEntry *__restrict__ ent,
@@ -312,14 +330,16 @@ __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ 
     for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < used;
          i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
         SuEntry &e = E[i];
-        const double sm = elt_terms[3 * e.k] * static_cast<double>(e.mu);
-        if (sm > 0.0) low = max(low, ~__float_as_uint(__double2float_rd(sm)));
-        if (e.exact) continue;
-        const double mu = static_cast<double>(e.mu);
+        const double mu = static_cast<double>(e.mu), scale = elt_terms[3 * e.k];
+        if (e.exact) {
+            if (mu > 0.0) low = max(low, su_least(scale * mu));
+            continue;
+        }
         const double rr = e.s / mu;
         const double s2 = log1p(rr * rr);
         e.m = log(mu) - 0.5 * s2;
         e.s = sqrt(s2);
+        low = max(low, su_least(scale * exp(e.m - kZMost * e.s)));
     }
     for (int o = 32; o > 0; o >>= 1) low = max(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), o)));
     __shared__ uint32_t most;   // one atomic per workgroup, and few of those: most workgroups' is no news

@@ -148,3 +148,30 @@ def test_largest_tiles_with_positions(ara, catalog):
     elts = synth.Elts(catalog, rec_off, rec_ids, rec_loss, np.array([[1.0, 1e3, 5e6], [1.5, 1e4, 2e6]]))
     layers = synth.Layers(np.array([0, 2, 3], np.int32), np.array([0, 1, 1], np.int32), np.asarray([TERMS[0], OPEN]))
     check(ara, synth.Workload("largest tiles", synth.Yet(catalog, off, ids), elts, layers, 0.9), 11)
+
+
+@pytest.mark.parametrize("kind", ["wide", "narrow", "limit"])
+def test_small_totals_keep_their_bits(ara, kind):
+    """Years of an occurrence or two whose losses lie far below the limits:
+    coefficients of variation of a hundred (draws 2^-40 below their mean and
+    less) under a limit 2^23 above the mean, of one under a limit 2^21 above,
+    and an ELT whose limit is 2^-60 of another's.  The totals of both paths
+    differ by their own roundings alone, relative to the total itself."""
+    import torch
+    w = workload(kind, 20_000, 1, 4_000, [1500, 1500], [[0], [0, 1], [1]], [OPEN] * 3, 21)
+    w.elts.rec_loss[:] = np.exp(np.random.default_rng(3).normal(11.0, 0.1, 3000)).astype(np.float32)
+    most = 2.0 ** {"wide": 23, "narrow": 21, "limit": 10}[kind] * 6e4
+    w.elts.terms = np.array([[1.0, 0.0, most], [1.0, 0.0, most * 2.0 ** -60 / 3 if kind == "limit" else most]])
+    sg = (w.elts.rec_loss * {"wide": 100.0, "narrow": 1.0, "limit": 0.5}[kind]).astype(np.float32)
+    print(f"[gpu-suev] small totals, {kind}", flush=True)
+    tables = ara.EltTables.from_numpy(w.elts)
+    sigma = ara.SigmaTables.from_numpy(tables, sg)
+    layers = ara.Layers(w.layers.elt_off, w.layers.elt_ids)
+    yet, stream = (ara.PreparedYet.from_numpy(w.yet, transposed=False, positions=True) for _ in range(2))
+    stream.handle.reserved = 0
+    et = torch.tensor(w.elts.terms, dtype=torch.float64, device="cuda")
+    lt = torch.tensor(w.layers.terms, dtype=torch.float64, device="cuda")
+    s, ss = (ara.ylt_forward_su(tables, sigma, y, layers, et, lt, 77, check=True)[1].cpu().numpy() for y in (yet, stream))
+    n = int(np.diff(w.yet.offsets).max())
+    assert ss[ss > 0].min() < 2.0 ** -15 * np.median(ss[ss > 0]) or kind == "narrow"
+    assert np.all(np.abs(s - ss) <= (2 * n + 1) * 2.0 ** -53 * ss)
