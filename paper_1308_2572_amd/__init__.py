@@ -217,13 +217,15 @@ class EltTables:
         # the CSR is kept for the standard-deviation tables of secondary uncertainty
         self.rec_off = rec_off
         self.rec_ids = rec_ids
+        # the offsets as the tables were built from them: the caller may use its tensor again
+        self._built_off = rec_off.clone()
         self._records: Optional[np.ndarray] = None
 
     @property
     def records(self) -> np.ndarray:
         """Records per ELT, fetched when first asked for (secondary uncertainty)."""
         if self._records is None:
-            off_h = self.rec_off.cpu().numpy().astype(np.int64)
+            off_h = self._built_off.cpu().numpy().astype(np.int64)
             self._records = np.ascontiguousarray(off_h[1:] - off_h[:-1], dtype=np.int64)
         return self._records
 

@@ -234,3 +234,25 @@ def test_errors(ara):
     y, s = ara.ylt_forward_su(e.tables, e.sigma, e.yet, e.layers, e.et, e.lt, 1, 5, 5)
     assert y.shape == (1, 0)
     torch.cuda.synchronize()
+
+
+def test_record_counts_are_those_the_tables_were_built_from(ara):
+    """The caller writes other offsets into its tensor once the tables and the
+    deviations are built: the calls after that are the same."""
+    import torch
+    w = synth.tiny_random(2)
+    off = torch.from_numpy(np.ascontiguousarray(w.elts.rec_off, np.int64)).cuda()
+    recs = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (w.elts.rec_ids, w.elts.rec_loss)]
+    counts = np.diff(w.elts.rec_off)
+    tables = ara.EltTables(off, *recs, int(w.elts.catalog))
+    sigma = ara.SigmaTables.from_numpy(tables, synth.record_sigmas(2, w.elts, zero_frac=0.2))
+    off.zero_()
+    assert np.array_equal(tables.records, counts) and np.array_equal(tables.records, counts)
+    yet = ara.PreparedYet.from_numpy(w.yet, transposed=False, positions=True)
+    et = torch.tensor(w.elts.terms, dtype=torch.float64, device="cuda")
+    lt = torch.tensor(w.layers.terms, dtype=torch.float64, device="cuda")
+    layers = ara.Layers(w.layers.elt_off, w.layers.elt_ids)
+    got = ara.ylt_forward_su(tables, sigma, yet, layers, et, lt, 5, check=True)
+    again = ara.EltTables.from_numpy(w.elts)
+    want = ara.ylt_forward_su(again, sigma, yet, layers, et, lt, 5, check=True)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
