@@ -149,7 +149,10 @@ typedef struct ara_yet {
                                     are keyed by the trial-major occurrence index; every trial must then
                                     hold at most 65536 occurrences (ARA_E_LIMIT otherwise) */
 
-/* Upper bound of the device buffer ara_yet_prepare needs for these flags. */
+/* Upper bound of the device buffer ara_yet_prepare needs for these flags.  At a million trials of 1000
+ * occurrences over two million events: 8.9 GB (4.8 without the preparation's scratch, see
+ * ara_yet_prepare_split), 13.0 (8.9) with ARA_PREP_TRANSPOSED, 17.1 (12.9) with ARA_PREP_TRIAL_MAJOR too,
+ * 15.4 (9.3) with ARA_PREP_POSITIONS alone. */
 int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags, size_t *bytes);
 
 /*
@@ -169,6 +172,20 @@ int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, ui
 int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, int64_t n_trials,
                         int32_t catalog, uint32_t flags, void *buf, size_t buf_bytes,
                         void *stream, ara_yet *out);
+
+/*
+ * The same with the preparation's scratch in a buffer of its own, so that
+ * only what the prepared YET needs stays with it: buf of at least *keep bytes,
+ * which must outlive every use of *out, and scratch of at least *scratch
+ * bytes, which may be used otherwise once the call has returned (it
+ * synchronises the stream).  With ARA_PREP_TRANSPOSED the scratch is small: the
+ * event-major copy's place serves first.  Both buffers 256-byte aligned.
+ */
+int32_t ara_yet_prepare_split_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags,
+                                    size_t *keep, size_t *scratch);
+int32_t ara_yet_prepare_split(const int64_t *offsets, const int32_t *ids, int64_t n_trials,
+                              int32_t catalog, uint32_t flags, void *buf, size_t buf_bytes,
+                              void *scratch, size_t scratch_bytes, void *stream, ara_yet *out);
 
 /* ------------------------------------------------------------------------ */
 /* ELTs: the second input (Section II) -- event -> loss dictionaries, held as */

@@ -76,6 +76,8 @@ _SIGNATURES = {
     "ara_check_device_error": (_c_i32, [_c_p, _c_p]),
     "ara_yet_prepare_bytes": (_c_i32, [_c_i64, _c_i64, _c_i32, _c_u32, _P(_c_sz)]),
     "ara_yet_prepare": (_c_i32, [_c_p, _c_p, _c_i64, _c_i32, _c_u32, _c_p, _c_sz, _c_p, _P(ara_yet)]),
+    "ara_yet_prepare_split_bytes": (_c_i32, [_c_i64, _c_i64, _c_i32, _c_u32, _P(_c_sz), _P(_c_sz)]),
+    "ara_yet_prepare_split": (_c_i32, [_c_p, _c_p, _c_i64, _c_i32, _c_u32, _c_p, _c_sz, _c_p, _c_sz, _c_p, _P(ara_yet)]),
     "ara_build_elt_tables_bytes": (_c_i32, [_c_i32, _c_i32, _P(_c_sz)]),
     "ara_build_elt_tables": (_c_i32, [_c_i32, _c_i32, _c_p, _c_p, _c_p, _c_p, _c_sz, _c_p, _P(ara_tables)]),
     "ara_ylt_workspace_bytes": (_c_i32, [_P(ara_tables), _P(ara_yet), _P(ara_layers), _c_u32, _P(_c_sz)]),
@@ -177,13 +179,16 @@ class PreparedYet:
         trial_major = transposed if trial_major is None else trial_major
         flags = ((PREP_TRANSPOSED if transposed else 0) | (PREP_TRIAL_MAJOR if trial_major else 0)
                  | (PREP_POSITIONS if positions else 0))
-        nb = _c_sz()
-        _check(lib.ara_yet_prepare_bytes(n_trials, nnz, catalog, flags, ctypes.byref(nb)), "ara_yet_prepare_bytes")
+        keep, scr = _c_sz(), _c_sz()
+        _check(lib.ara_yet_prepare_split_bytes(n_trials, nnz, catalog, flags, ctypes.byref(keep), ctypes.byref(scr)),
+               "ara_yet_prepare_bytes")
         self.device = offsets.device
-        self.buf = _workspace(nb.value, self.device)
+        self.buf = _workspace(keep.value, self.device)
+        scratch = _workspace(scr.value, self.device)
         self.handle = ara_yet()
-        _check(lib.ara_yet_prepare(_dptr(offsets), _dptr(ids), n_trials, catalog, flags, _dptr(self.buf),
-                                   self.buf.numel(), _stream(), ctypes.byref(self.handle)), "ara_yet_prepare")
+        _check(lib.ara_yet_prepare_split(_dptr(offsets), _dptr(ids), n_trials, catalog, flags, _dptr(self.buf),
+                                         self.buf.numel(), _dptr(scratch), scratch.numel(), _stream(),
+                                         ctypes.byref(self.handle)), "ara_yet_prepare")
         self.n_trials = n_trials
         self.catalog = catalog
         self.transposed = transposed

@@ -25,6 +25,7 @@
 #include "evblk.h"
 
 #include <algorithm>
+#include <string>
 
 namespace ara {
 
@@ -89,6 +90,7 @@ struct Prepared {
 
 static int64_t n_groups_of(const Geometry &g, int64_t n_trials) { return (n_trials + g.tg - 1) / g.tg; }
 
+// What stays with the prepared YET.
 static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
     Prepared p{};
     const size_t occ = static_cast<size_t>(std::max<int64_t>(nnz, 1));
@@ -100,7 +102,6 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     if (flags & ARA_PREP_TRANSPOSED) {
         p.tr_off = c.take<int64_t>(static_cast<size_t>(kSlices) * catalog + 1);
         p.tr_ent = c.take<uint32_t>(occ);
-        p.ssum = c.take<int64_t>(ev_major_sums(catalog));
     }
     if (flags & ARA_PREP_TRIAL_MAJOR) {
         p.t_off = c.take<int64_t>(static_cast<size_t>(n_trials) + 1);
@@ -117,10 +118,26 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     if (eg.dense) p.start = c.take<uint32_t>(neb * (static_cast<size_t>(catalog) + 1));
     else p.hdr = c.take<uint2>(neb * static_cast<size_t>(eg.ng));
     p.ev_base = c.take<int64_t>(neb + 1);
-    // the sorted records; their positions in the place of the blocks' entries
-    // (written after the codes)
-    p.rec = c.take<uint32_t>(occ);
-    if (flags & ARA_PREP_POSITIONS) p.rpos = p.ent;
+    if (flags & ARA_PREP_POSITIONS) p.ev_pos = c.take<uint16_t>(occ + kEvPad);
+    return p;
+}
+
+// What only the preparation needs: 4 bytes per occurrence for the sorted
+// records (in the event-major lists' place, written last, where the caller
+// gives the scratch by itself: lend), two more with positions, and the runs'
+// bounds.  The records' positions of the first sort lie in the place of the
+// blocks' entries, which are written after the codes.
+static void carve_scratch(Carver &c, Prepared &p, const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog,
+                          uint32_t flags, bool lend) {
+    const size_t occ = static_cast<size_t>(std::max<int64_t>(nnz, 1));
+    const EvGeometry eg = ev_geometry(n_trials, nnz, catalog);
+    const size_t neb = static_cast<size_t>(eg.neb);
+    p.rec = lend && (flags & ARA_PREP_TRANSPOSED) ? p.tr_ent : c.take<uint32_t>(occ);
+    if (flags & ARA_PREP_TRANSPOSED) p.ssum = c.take<int64_t>(ev_major_sums(catalog));
+    if (flags & ARA_PREP_POSITIONS) {
+        p.rpos = p.ent;
+        p.ev_rpos = c.take<uint16_t>(occ);
+    }
     const size_t chunks = static_cast<size_t>(nnz / kChunk + 2 * n_groups_of(g, n_trials) + 2);
     p.rstart = c.take<uint16_t>(chunks * static_cast<size_t>(g.n_ranges + 1));
     p.rsum = c.take<uint32_t>(chunks * static_cast<size_t>(g.n_ranges));
@@ -128,17 +145,17 @@ static Prepared carve(Carver &c, const Geometry &g, int64_t n_trials, int64_t nn
     p.tstart = c.take<uint16_t>(static_cast<size_t>(eg.n_chunks) * static_cast<size_t>(eg.n_tiles + 1));
     p.tbase = c.take<uint32_t>(neb * static_cast<size_t>(eg.n_tiles + 1));
     p.mark = c.take<uint32_t>(static_cast<size_t>(eg.n_marks));
-    if (flags & ARA_PREP_POSITIONS) {
-        p.ev_pos = c.take<uint16_t>(occ + kEvPad);
-        p.ev_rpos = c.take<uint16_t>(occ);
-    }
-    return p;
 }
 
-static size_t prepare_bytes(const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
-    Carver c(nullptr);
-    carve(c, g, n_trials, nnz, catalog, flags);
-    return c.bytes();
+struct PrepareBytes {
+    size_t keep, scratch;
+};
+
+static PrepareBytes prepare_bytes(const Geometry &g, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags, bool lend) {
+    Carver c(nullptr), s(nullptr);
+    Prepared p = carve(c, g, n_trials, nnz, catalog, flags);
+    carve_scratch(s, p, g, n_trials, nnz, catalog, flags, lend);
+    return {c.bytes(), s.bytes()};
 }
 
 // How the codes are made: a scattered store per code leaves every segment's
@@ -696,22 +713,44 @@ bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
 
 using namespace ara;
 
-extern "C" int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags,
-                                         size_t *bytes) {
-    if (!bytes) return fail(ARA_E_INVAL, "ara_yet_prepare_bytes: null output");
-    if (n_trials < 0 || nnz < 0 || catalog <= 0) return fail(ARA_E_INVAL, "ara_yet_prepare_bytes: negative size");
+static int32_t check_sizes(const char *what, int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags) {
+    const std::string at = std::string(what) + ": ";
+    if (n_trials < 0 || nnz < 0 || catalog <= 0) return fail(ARA_E_INVAL, at + "negative size");
     if (catalog > ARA_MAX_CATALOG) return fail(ARA_E_LIMIT, "catalog exceeds ARA_MAX_CATALOG");
-    if (flags & ~kPrepFlags) return fail(ARA_E_INVAL, "ara_yet_prepare_bytes: unknown flag");
-    *bytes = prepare_bytes(geometry(n_trials, catalog), n_trials, nnz, catalog, flags);
+    if (flags & ~kPrepFlags) return fail(ARA_E_INVAL, at + "unknown flag");
     return ARA_OK;
 }
 
-extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, int64_t n_trials, int32_t catalog,
-                                   uint32_t flags, void *buf, size_t buf_bytes, void *stream, ara_yet *out) {
-    if (!offsets || !buf || !out) return fail(ARA_E_INVAL, "ara_yet_prepare: null pointer");
-    if (n_trials < 0 || catalog <= 0) return fail(ARA_E_INVAL, "ara_yet_prepare: bad size");
+extern "C" int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags,
+                                         size_t *bytes) {
+    if (!bytes) return fail(ARA_E_INVAL, "ara_yet_prepare_bytes: null output");
+    const int32_t rc = check_sizes("ara_yet_prepare_bytes", n_trials, nnz, catalog, flags);
+    if (rc) return rc;
+    const PrepareBytes b = prepare_bytes(geometry(n_trials, catalog), n_trials, nnz, catalog, flags, false);
+    *bytes = b.keep + b.scratch;
+    return ARA_OK;
+}
+
+extern "C" int32_t ara_yet_prepare_split_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, uint32_t flags,
+                                               size_t *keep, size_t *scratch) {
+    if (!keep || !scratch) return fail(ARA_E_INVAL, "ara_yet_prepare_split_bytes: null output");
+    const int32_t rc = check_sizes("ara_yet_prepare_split_bytes", n_trials, nnz, catalog, flags);
+    if (rc) return rc;
+    const PrepareBytes b = prepare_bytes(geometry(n_trials, catalog), n_trials, nnz, catalog, flags, true);
+    *keep = b.keep;
+    *scratch = b.scratch;
+    return ARA_OK;
+}
+
+// scratch null: it follows what stays in buf, without lent places.
+static int32_t prepare(const char *what, const int64_t *offsets, const int32_t *ids, int64_t n_trials, int32_t catalog,
+                       uint32_t flags, void *buf, size_t buf_bytes, void *scratch, size_t scratch_bytes, void *stream,
+                       ara_yet *out) {
+    const std::string at = std::string(what) + ": ";
+    if (!offsets || !buf || !out) return fail(ARA_E_INVAL, at + "null pointer");
+    if (n_trials < 0 || catalog <= 0) return fail(ARA_E_INVAL, at + "bad size");
     if (catalog > ARA_MAX_CATALOG) return fail(ARA_E_LIMIT, "catalog exceeds ARA_MAX_CATALOG");
-    if (flags & ~kPrepFlags) return fail(ARA_E_INVAL, "ara_yet_prepare: unknown flag");
+    if (flags & ~kPrepFlags) return fail(ARA_E_INVAL, at + "unknown flag");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Geometry g = geometry(n_trials, catalog);
     int64_t ends[2] = {0, 0};
@@ -720,12 +759,15 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     ARA_HIP(hipStreamSynchronize(st));
     if (ends[0] != 0 || ends[1] < 0) return fail(ARA_E_RANGE, "offsets[0] must be 0 and offsets[n] >= 0");
     const int64_t nnz = ends[1];
-    if (nnz > 0 && !ids) return fail(ARA_E_INVAL, "ara_yet_prepare: null ids");
-    if (buf_bytes < prepare_bytes(g, n_trials, nnz, catalog, flags)) return fail(ARA_E_NOSPACE, "ara_yet_prepare: buffer too small");
+    if (nnz > 0 && !ids) return fail(ARA_E_INVAL, at + "null ids");
+    const PrepareBytes need = prepare_bytes(g, n_trials, nnz, catalog, flags, scratch != nullptr);
+    if (buf_bytes < need.keep + (scratch ? 0 : need.scratch)) return fail(ARA_E_NOSPACE, at + "buffer too small");
+    if (scratch && scratch_bytes < need.scratch) return fail(ARA_E_NOSPACE, at + "scratch too small");
 
     Carver c(buf);
-    const Prepared p = carve(c, g, n_trials, nnz, catalog, flags);
-    int32_t *max_occ = reinterpret_cast<int32_t *>(p.misc + kMiscMaxOcc);
+    Prepared p = carve(c, g, n_trials, nnz, catalog, flags);
+    Carver s(scratch ? scratch : static_cast<char *>(buf) + need.keep);
+    carve_scratch(s, p, g, n_trials, nnz, catalog, flags, scratch != nullptr);
     const bool transposed = (flags & ARA_PREP_TRANSPOSED) != 0, positions = (flags & ARA_PREP_POSITIONS) != 0;
     if (flags & ARA_PREP_TRIAL_MAJOR) {
         ARA_HIP(hipMemsetAsync(p.t_cnt, 0, static_cast<size_t>(catalog) * sizeof(int32_t), st));
@@ -857,4 +899,17 @@ extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, i
     y.max_occ = static_cast<int32_t>(head[kMiscMaxOcc] & 0xffffffff);
     *out = y;
     return ARA_OK;
+}
+
+extern "C" int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, int64_t n_trials, int32_t catalog,
+                                   uint32_t flags, void *buf, size_t buf_bytes, void *stream, ara_yet *out) {
+    return prepare("ara_yet_prepare", offsets, ids, n_trials, catalog, flags, buf, buf_bytes, nullptr, 0, stream, out);
+}
+
+extern "C" int32_t ara_yet_prepare_split(const int64_t *offsets, const int32_t *ids, int64_t n_trials, int32_t catalog,
+                                         uint32_t flags, void *buf, size_t buf_bytes, void *scratch,
+                                         size_t scratch_bytes, void *stream, ara_yet *out) {
+    if (!scratch) return fail(ARA_E_INVAL, "ara_yet_prepare_split: null pointer");
+    return prepare("ara_yet_prepare_split", offsets, ids, n_trials, catalog, flags, buf, buf_bytes, scratch,
+                   scratch_bytes, stream, out);
 }

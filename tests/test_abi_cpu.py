@@ -86,6 +86,34 @@ def test_size_queries(ara):
     assert lib.ara_yet_prepare_bytes(-1, 10, 100, 0, ctypes.byref(nb)) == 1
 
 
+@pytest.mark.parametrize("n,nnz,catalog", [(1_000_000, 1_000_000_000, 2_000_000), (1000, 1_000_000, 200_000), (0, 0, 5)])
+def test_prepared_yet_keeps_no_scratch(ara, n, nnz, catalog):
+    """What a prepared YET keeps: the codes (at most 768 of padding and gaps
+    per segment), the event-ordered blocks (two bytes an occurrence, at most
+    nine per event and block of trials), and what the flags add; the records
+    of the sorts (four bytes an occurrence, six with positions) are scratch,
+    and lie in the event-major lists' place where there is one."""
+    lib = ara.library()
+    nb, keep, scratch = (ctypes.c_size_t() for _ in range(3))
+    tg = min(max(1, -(-n // (2 * 16 * 256))), 256)
+    segs = -(-n // (16 * tg)) * -(-catalog // 32768) * 16
+    blocks = -(-n // 8192)
+    base = 2 * nnz + segs * (2 * 768 + 76) + 2 * nnz + 9 * blocks * (catalog + 16) + 4096
+    for flags, more in ((0, 0), (ara.PREP_TRANSPOSED, 4 * nnz + 64 * (catalog + 1)),
+                        (ara.PREP_TRANSPOSED | ara.PREP_TRIAL_MAJOR, 8 * nnz + 68 * (catalog + 1) + 8 * (n + 1)),
+                        (ara.PREP_POSITIONS, 4 * nnz + segs * 2 * 768 + 8 * (n + 1))):
+        assert lib.ara_yet_prepare_split_bytes(n, nnz, catalog, flags, ctypes.byref(keep), ctypes.byref(scratch)) == 0
+        assert lib.ara_yet_prepare_bytes(n, nnz, catalog, flags, ctypes.byref(nb)) == 0
+        assert keep.value <= base + more + 4096
+        assert nb.value >= keep.value + scratch.value
+        per = 0 if flags & ara.PREP_TRANSPOSED else 6 if flags & ara.PREP_POSITIONS else 4
+        assert scratch.value <= (per + 0.6) * nnz + 64 * (catalog + blocks) + 70_000 + 12 * segs
+    assert lib.ara_yet_prepare_split_bytes(n, nnz, catalog, 8, ctypes.byref(keep), ctypes.byref(scratch)) == 1
+    assert lib.ara_yet_prepare_split_bytes(n, nnz, 1 << 27, 0, ctypes.byref(keep), ctypes.byref(scratch)) == 6
+    assert lib.ara_yet_prepare_split_bytes(n, nnz, catalog, 0, None, ctypes.byref(scratch)) == 1
+    assert lib.ara_yet_prepare_split(1, 1, n, catalog, 0, 1, 1 << 40, None, 0, None, ctypes.byref(ara.ara_yet())) == 1
+
+
 def test_argument_validation_before_device_work(ara):
     lib = ara.library()
     # p outside (0, 1)

@@ -276,3 +276,50 @@ def test_more_sorted_tiles_than_one_grid_row(ara):
     y, _, _ = ara.ylt_forward(tables, yet, ara.Layers([0, 1], [0]), *terms, check=True)
     want = np.bincount(np.repeat(np.arange(n), lens), weights=loss.astype(np.float64)[np.searchsorted(rec, ids)], minlength=n)
     assert np.array_equal(y[0].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("flags", [0, 3, 4, 7])
+def test_scratch_is_free_after_the_call(ara, flags):
+    """One buffer and two give the same prepared YET, and what lies behind its
+    kept bytes, or in the scratch, may be written over afterwards."""
+    import ctypes
+    import torch
+    w = synth.config(0, n_trials=3000)
+    off = torch.from_numpy(w.yet.offsets).cuda()
+    ids = torch.from_numpy(w.yet.ids).cuda()
+    n, nnz, catalog = w.yet.n_trials, w.yet.nnz, int(w.yet.catalog)
+    lib = ara.library()
+    nb, keep, scr = (ctypes.c_size_t() for _ in range(3))
+    assert lib.ara_yet_prepare_bytes(n, nnz, catalog, flags, ctypes.byref(nb)) == 0
+    assert lib.ara_yet_prepare_split_bytes(n, nnz, catalog, flags, ctypes.byref(keep), ctypes.byref(scr)) == 0
+    _say(f"flags {flags}: {nb.value} bytes, {keep.value} kept")
+    one = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+    two, scratch = (torch.empty(b.value, dtype=torch.uint8, device="cuda") for b in (keep, scr))
+    yets = []
+    for buf, s in ((one, None), (two, scratch)):
+        y = object.__new__(ara.PreparedYet)
+        y.handle, y.buf, y.device, y.n_trials, y.catalog = ara.ara_yet(), buf, buf.device, n, catalog
+        args = (off.data_ptr(), ids.data_ptr(), n, catalog, flags, buf.data_ptr(), buf.numel())
+        if s is None:
+            assert lib.ara_yet_prepare(*args, None, ctypes.byref(y.handle)) == 0
+        else:
+            assert lib.ara_yet_prepare_split(*args, s.data_ptr(), scr.value - 1, None, ctypes.byref(y.handle)) == 4
+            assert lib.ara_yet_prepare_split(*args, s.data_ptr(), s.numel(), None, ctypes.byref(y.handle)) == 0
+        yets.append(y)
+    one[keep.value:] = 0xA5
+    scratch[:] = 0x5A
+    check_codes(yets[1], w.yet)
+    tables = ara.EltTables.from_numpy(w.elts)
+    layers = ara.Layers(w.layers.elt_off, w.layers.elt_ids)
+    et = torch.tensor(w.elts.terms, dtype=torch.float64, device="cuda")
+    lt = torch.tensor(w.layers.terms, dtype=torch.float64, device="cuda")
+    out = [ara.ylt_forward(tables, y, layers, et, lt, want_hits=True, check=True) for y in yets]
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    if flags & ara.PREP_TRANSPOSED:
+        cot = torch.rand((1,) + tuple(out[0][0].shape), dtype=torch.float64, device="cuda")
+        g = [ara.ylt_backward(tables, y, layers, et, lt, out[0][1], cot) for y in yets]
+        assert all(torch.equal(a, b) for a, b in zip(*g))
+    if flags & ara.PREP_POSITIONS:
+        sigma = ara.SigmaTables.from_numpy(tables, synth.record_sigmas(1, w.elts))
+        s = [ara.ylt_forward_su(tables, sigma, y, layers, et, lt, 9, check=True) for y in yets]
+        assert all(torch.equal(a, b) for a, b in zip(*s))
