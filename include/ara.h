@@ -212,6 +212,12 @@ int32_t ara_build_elt_tables_bytes(int32_t n_elts, int32_t catalog, size_t *byte
 int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const int64_t *rec_off,
                              const int32_t *rec_ids, const float *rec_loss,
                              void *buf, size_t buf_bytes, void *stream, ara_tables *out);
+/* The same, and the records of each ELT into the host array records[n_elts] (what ara_su_workspace_bytes asks
+ * for), from the offsets that the call reads anyway. */
+int32_t ara_build_elt_tables_counted(int32_t n_elts, int32_t catalog, const int64_t *rec_off,
+                                     const int32_t *rec_ids, const float *rec_loss,
+                                     void *buf, size_t buf_bytes, void *stream, ara_tables *out,
+                                     int64_t *records);
 
 /* ------------------------------------------------------------------------ */
 /* Layers: the third input (Section II) -- ELT lists plus layer terms.       */

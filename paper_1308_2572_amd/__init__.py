@@ -80,6 +80,7 @@ _SIGNATURES = {
     "ara_yet_prepare_split": (_c_i32, [_c_p, _c_p, _c_i64, _c_i32, _c_u32, _c_p, _c_sz, _c_p, _c_sz, _c_p, _P(ara_yet)]),
     "ara_build_elt_tables_bytes": (_c_i32, [_c_i32, _c_i32, _P(_c_sz)]),
     "ara_build_elt_tables": (_c_i32, [_c_i32, _c_i32, _c_p, _c_p, _c_p, _c_p, _c_sz, _c_p, _P(ara_tables)]),
+    "ara_build_elt_tables_counted": (_c_i32, [_c_i32, _c_i32, _c_p, _c_p, _c_p, _c_p, _c_sz, _c_p, _P(ara_tables), _c_p]),
     "ara_ylt_workspace_bytes": (_c_i32, [_P(ara_tables), _P(ara_yet), _P(ara_layers), _c_u32, _P(_c_sz)]),
     "ara_ylt_forward": (_c_i32, [_P(ara_tables), _P(ara_yet), _P(ara_layers), _c_p, _c_p, _c_i64, _c_i64, _c_u32,
                                  _c_p, _c_p, _c_p, _c_p, _c_sz, _c_p]),
@@ -214,25 +215,16 @@ class EltTables:
         self.device = rec_off.device
         self.buf = _workspace(nb.value, self.device)
         self.handle = ara_tables()
-        _check(lib.ara_build_elt_tables(n_elts, catalog, _dptr(rec_off), _dptr(rec_ids), _dptr(rec_loss),
-                                        _dptr(self.buf), self.buf.numel(), _stream(), ctypes.byref(self.handle)),
+        self.records = np.zeros(max(n_elts, 0), np.int64)   # of each ELT, as the tables were built
+        _check(lib.ara_build_elt_tables_counted(n_elts, catalog, _dptr(rec_off), _dptr(rec_ids), _dptr(rec_loss),
+                                                _dptr(self.buf), self.buf.numel(), _stream(),
+                                                ctypes.byref(self.handle), self.records.ctypes.data_as(_c_p)),
                "ara_build_elt_tables")
         self.n_elts = n_elts
         self.catalog = catalog
         # the CSR is kept for the standard-deviation tables of secondary uncertainty
         self.rec_off = rec_off
         self.rec_ids = rec_ids
-        # the offsets as the tables were built from them: the caller may use its tensor again
-        self._built_off = rec_off.clone()
-        self._records: Optional[np.ndarray] = None
-
-    @property
-    def records(self) -> np.ndarray:
-        """Records per ELT, fetched when first asked for (secondary uncertainty)."""
-        if self._records is None:
-            off_h = self._built_off.cpu().numpy().astype(np.int64)
-            self._records = np.ascontiguousarray(off_h[1:] - off_h[:-1], dtype=np.int64)
-        return self._records
 
     @classmethod
     def from_numpy(cls, elts, device="cuda"):

@@ -74,9 +74,9 @@ extern "C" int32_t ara_build_elt_tables_bytes(int32_t n_elts, int32_t catalog, s
     return ARA_OK;
 }
 
-extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const int64_t *rec_off,
-                                        const int32_t *rec_ids, const float *rec_loss, void *buf, size_t buf_bytes,
-                                        void *stream, ara_tables *out) {
+extern "C" int32_t ara_build_elt_tables_counted(int32_t n_elts, int32_t catalog, const int64_t *rec_off,
+                                                const int32_t *rec_ids, const float *rec_loss, void *buf,
+                                                size_t buf_bytes, void *stream, ara_tables *out, int64_t *records) {
     if (!rec_off || !buf || !out) return fail(ARA_E_INVAL, "ara_build_elt_tables: null pointer");
     if (n_elts < 0 || catalog <= 0) return fail(ARA_E_INVAL, "ara_build_elt_tables: bad size");
     if (catalog > ARA_MAX_CATALOG) return fail(ARA_E_LIMIT, "catalog exceeds ARA_MAX_CATALOG");
@@ -105,6 +105,7 @@ extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const i
     for (int32_t k = 0; k < n_elts; ++k) {
         if (off[k + 1] < off[k]) return fail(ARA_E_RANGE, "rec_off must be non-decreasing");
         max_rec = std::max<int64_t>(max_rec, off[k + 1] - off[k]);
+        if (records) records[k] = off[k + 1] - off[k];
     }
     if (max_rec > 0 && (!rec_ids || !rec_loss)) return fail(ARA_E_INVAL, "ara_build_elt_tables: null records");
     if (n_elts > 0 && max_rec > 0) {
@@ -127,4 +128,10 @@ extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const i
     t.present = present;
     *out = t;
     return ARA_OK;
+}
+
+extern "C" int32_t ara_build_elt_tables(int32_t n_elts, int32_t catalog, const int64_t *rec_off,
+                                        const int32_t *rec_ids, const float *rec_loss, void *buf, size_t buf_bytes,
+                                        void *stream, ara_tables *out) {
+    return ara_build_elt_tables_counted(n_elts, catalog, rec_off, rec_ids, rec_loss, buf, buf_bytes, stream, out, nullptr);
 }
