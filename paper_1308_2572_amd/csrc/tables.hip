@@ -88,10 +88,10 @@ extern "C" int32_t ara_build_elt_tables_counted(int32_t n_elts, int32_t catalog,
     uint32_t *present = c.take<uint32_t>(static_cast<size_t>(n_elts) * words);
     int32_t *misc = c.take<int32_t>(64);
     std::vector<int64_t> off(static_cast<size_t>(n_elts) + 1);
-    ARA_HIP(hipMemcpyAsync(off.data(), rec_off, off.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     hipEvent_t have = nullptr;   // the offsets have arrived; the tables are cleared meanwhile
     ARA_HIP(hipEventCreateWithFlags(&have, hipEventDisableTiming));
-    hipError_t e = hipEventRecord(have, st);
+    hipError_t e = hipMemcpyAsync(off.data(), rec_off, off.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipEventRecord(have, st);
     if (e == hipSuccess) e = hipMemsetAsync(loss, 0, static_cast<size_t>(n_elts) * catalog * sizeof(float), st);
     if (e == hipSuccess) e = hipMemsetAsync(present, 0, static_cast<size_t>(n_elts) * words * sizeof(uint32_t), st);
     if (e == hipSuccess) e = hipMemsetAsync(misc, 0, 64 * sizeof(int32_t), st);
@@ -101,13 +101,18 @@ extern "C" int32_t ara_build_elt_tables_counted(int32_t n_elts, int32_t catalog,
     ARA_HIP(w);
     ARA_HIP(e);
     int64_t max_rec = 0;
-    if (off[0] != 0) return fail(ARA_E_RANGE, "rec_off[0] must be 0");
+    // a refusal leaves nothing running on the caller's buffer
+    auto refuse = [&](int32_t rc, const char *msg) {
+        (void)hipStreamSynchronize(st);
+        return fail(rc, msg);
+    };
+    if (off[0] != 0) return refuse(ARA_E_RANGE, "rec_off[0] must be 0");
     for (int32_t k = 0; k < n_elts; ++k) {
-        if (off[k + 1] < off[k]) return fail(ARA_E_RANGE, "rec_off must be non-decreasing");
+        if (off[k + 1] < off[k]) return refuse(ARA_E_RANGE, "rec_off must be non-decreasing");
         max_rec = std::max<int64_t>(max_rec, off[k + 1] - off[k]);
         if (records) records[k] = off[k + 1] - off[k];
     }
-    if (max_rec > 0 && (!rec_ids || !rec_loss)) return fail(ARA_E_INVAL, "ara_build_elt_tables: null records");
+    if (max_rec > 0 && (!rec_ids || !rec_loss)) return refuse(ARA_E_INVAL, "ara_build_elt_tables: null records");
     if (n_elts > 0 && max_rec > 0) {
         const unsigned gx = static_cast<unsigned>(std::min<int64_t>((max_rec + 255) / 256, 4096));
         dim3 grid(gx, static_cast<unsigned>(n_elts));
