@@ -166,7 +166,7 @@ int32_t ara_yet_prepare_bytes(int64_t n_trials, int64_t nnz, int32_t catalog, ui
  * Validates every ID (ARA_E_RANGE) and every offset.  SYNCHRONISES `stream`
  * (it sizes the layout from device-side counts); one-time cost.
  * ARA_E_LIMIT if one (slice, catalogue range) of the event-major copy, or
- * 8192 consecutive trials, would hold 2^32 occurrences or more, or with
+ * 8128 consecutive trials, would hold 2^32 occurrences or more, or with
  * ARA_PREP_POSITIONS if a trial holds more than 65536 occurrences.
  */
 int32_t ara_yet_prepare(const int64_t *offsets, const int32_t *ids, int64_t n_trials,

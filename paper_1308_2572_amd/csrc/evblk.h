@@ -1,6 +1,6 @@
 // Event-ordered blocks: the prepared YET's second layout.
 //
-// The trials are cut into blocks of `et` <= 8192 consecutive trials.  A
+// The trials are cut into blocks of `et` <= 8128 consecutive trials.  A
 // block's occurrences are stored by event: event e's occurrences are the
 // entries [start, start + n) of the block, one 16-bit word each,
 //     bits 0..12   the trial in the block
@@ -23,7 +23,8 @@
 
 namespace ara {
 
-constexpr int kEvMaxTrials = 8192;
+constexpr int kEvMaxTrials = 8192;     // that an entry can name
+constexpr int kEvBlockTrials = 8128;   // of a block: the forward keeps other things in the last places of its LDS
 constexpr int kEvTrialBits = 13;
 constexpr uint32_t kEvTrialMask = (1u << kEvTrialBits) - 1u;
 // Entries readable past the last one (lists are read in 16-byte pieces).

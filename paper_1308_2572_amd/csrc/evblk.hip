@@ -45,11 +45,11 @@ static_assert(kEvItems * kWave == kEvMark, "a wavefront's share of a chunk start
 
 EvGeometry ev_geometry(int64_t n_trials, int64_t nnz, int32_t catalog) {
     EvGeometry g{};
-    // blocks of equal size, as few as 8192 trials allow (longer lists per
+    // blocks of equal size, as few as 8128 trials allow (longer lists per
     // event: at 1M x 1000 and 7% of the events read, blocks of 7872 trials
     // took 302 us where 3936 took 390 and 1968 took 510), and of less than
     // 2^31 entries on average
-    const int64_t neb = std::max<int64_t>({1, (n_trials + kEvMaxTrials - 1) / kEvMaxTrials, nnz >> 31});
+    const int64_t neb = std::max<int64_t>({1, (n_trials + kEvBlockTrials - 1) / kEvBlockTrials, nnz >> 31});
     g.et = static_cast<int32_t>(std::max<int64_t>(1, (n_trials + neb - 1) / neb));
     g.neb = static_cast<int32_t>((n_trials + g.et - 1) / g.et);
     g.ng = (catalog + 7) / 8 + 1;

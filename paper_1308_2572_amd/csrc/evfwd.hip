@@ -28,7 +28,14 @@ namespace ara {
 
 constexpr int kEvfThreads = 1024;
 constexpr int kEvfWaves = kEvfThreads / kWave;
-constexpr uint32_t kLongList = 512;   // lists beyond this many entries are added by the whole wavefront
+constexpr int kRunUnits = 4;
+// Lists of more than kLong entries, or kLonger, or kLongest, are added by a whole
+// wavefront instead of their lanes (long_lists).
+constexpr uint32_t kLong = 48, kLonger = 128, kLongest = 1024;
+constexpr uint32_t kTaskList = 2048;  // beyond this many, by the workgroup's wavefronts together
+constexpr int kTasks = 60;            // pieces of those that wait for them
+static_assert(kEvMaxTrials - kEvBlockTrials >= kTasks + 1, "the last trials' places hold the pieces");
+static_assert(kEvfWaves % kRunUnits == 0, "runs to wavefronts");
 
 struct EvfParams {
     EvBlocks B;
@@ -43,13 +50,34 @@ struct EvfParams {
     unsigned char *partial;
     const uint32_t *share;     // k_ev_share's table, when sweep > 0
     int32_t sweep;             // workgroups of a block that may walk it together, or 0
-    FwdParams fwd;             // for the layers of mode 0
+    int32_t spread;            // the parts take runs of units in turn
+    FwdParams fwd;             // for the layers of mode 0 
 };
 
-// Sixteen bytes of a list, from an even entry on.
-struct EvPiece {
-    uint32_t a[4];
-};
+// Sixteen bytes of a list, from an even entry on.  (A vector: of a struct the
+// compiler copies the words one by one behind each conditional load, and so
+// waits for it there.)
+typedef uint32_t EvPiece __attribute__((ext_vector_type(4), aligned(4)));
+
+// Waits for this wavefront's loads: behind a loop that loads one step too far,
+// so that the compiler does not wait for those, and with them for all others,
+// where it next uses their registers, on the path that had no such loop too.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// The lanes whose lists of c entries the wavefront adds together.  The lanes by
+// themselves take as many steps of 16 entries as the longest list needs, the
+// wavefront the time of some four for each list: so the few above a length, if
+// one of them is longer by 64 entries for each of them, and any of many entries.
+__device__ __forceinline__ uint64_t long_lists(uint32_t c) {
+    uint64_t m = __ballot(c > kLong);
+    if (!m) return m;
+    uint32_t n = static_cast<uint32_t>(__popcll(m));
+    if (n <= 12u && __any(c > kLong + 64u * n)) return m;
+    m = __ballot(c > kLonger);
+    n = static_cast<uint32_t>(__popcll(m));
+    if (n <= 24u && __any(c > kLonger + 64u * n)) return m;
+    return __ballot(c > kLongest);
+}
 
 // Several layers of a block read most of its lines each (a line of 128 bytes
 // holds the lists of some 16 events, and a layer with a tenth of the catalogue
@@ -122,6 +150,10 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     unsigned long long *hi = reinterpret_cast<unsigned long long *>(smem);
     uint32_t *lo = reinterpret_cast<uint32_t *>(smem + kEvMaxTrials * 8);
     int32_t *hc = reinterpret_cast<int32_t *>(smem + kEvMaxTrials * 12);   // with hits
+    // in the places of the trials from kEvBlockTrials on, which no block has
+    uint2 *task_range = reinterpret_cast<uint2 *>(hi + kEvBlockTrials);    // [kTasks] entries of ent2
+    uint32_t *n_task = lo + kEvBlockTrials;
+    uint32_t *task_rec = n_task + 1;                                       // [kTasks] of set event
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroup 8k + x is the k-th on XCD x
@@ -204,6 +236,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
         lo[i] = 0u;
         if (HITS) hc[i] = 0;
     }
+    if (tid == 0) *n_task = 0u;
     __syncthreads();
 
     const EvRec *rec = reinterpret_cast<const EvRec *>(T.vals);
@@ -214,28 +247,31 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     const uint16_t *ent = ent2 + skew;
     const uint2 *hdr = DENSE ? nullptr : P.B.hdr + static_cast<size_t>(b) * P.B.ng;
     const uint32_t *start = DENSE ? P.B.start + static_cast<size_t>(b) * (P.B.catalog + 1) : nullptr;
+    // A part is a range of the units; where some events are far more frequent
+    // than most (P.spread), every parts-th run of kRunUnits units, since the
+    // range with those would have most of the work; or, where the block's
+    // workgroups walk it together, every parts-th unit.
     const int n_units = (L.n_set + kWave - 1) / kWave;
-    // a part is a range of the units or, where the block's workgroups walk it
-    // together, every parts-th of them
-    const int u1 = together ? n_units : static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / parts);
-    const int first_u = together ? w * parts + part : static_cast<int>(static_cast<int64_t>(n_units) * part / parts) + w;
-    const int step_u = together ? kEvfWaves * parts : kEvfWaves;
+    const int run = together ? 1 : (P.spread ? kRunUnits : 0);   // uniform
+    const int u1 = run ? n_units : static_cast<int>(static_cast<int64_t>(n_units) * (part + 1) / parts);
+    const int first_u = run ? ((w / run) * parts + part) * run + w % run : static_cast<int>(static_cast<int64_t>(n_units) * part / parts) + w;
+    const int step_u = run ? kEvfWaves * parts : kEvfWaves;
+    const int n_set = min(L.n_set, u1 * kWave);   // set events before the part's end
 
-    // lane's set event of unit u, its header, its list [s, s + c) of entries
-    auto load_rec = [&](int u, EvRec &r, int &nb) {
+    // set event i, its header, its list [s, s + c) of entries
+    auto load_rec = [&](int i, EvRec &r, int &nb) {
         r = EvRec{0, 0, ~0u};
         nb = 0;
-        const int i = u * kWave + lane;
         if (L.mode == 2) {   // uniform
             constexpr int kChunk = kOccChunkWords * 32;
-            if (u < u1 && i % kChunk < T.pcount[i / kChunk]) {
+            if (i < n_set && i % kChunk < T.pcount[i / kChunk]) {
                 const uint2 v = reinterpret_cast<const uint2 *>(T.dense)[i];
                 r.hi = reinterpret_cast<const unsigned long long *>(T.vals)[i];
                 r.lo = v.x;
                 r.ev = v.y;
                 if (HITS) nb = T.cnt[i];
             }
-        } else if (u < u1 && i < L.n_set) {
+        } else if (i < n_set) {
             const uint4 v = *reinterpret_cast<const uint4 *>(rec + i);
             r.hi = static_cast<unsigned long long>(v.x) | (static_cast<unsigned long long>(v.y) << 32);
             r.lo = v.z;
@@ -269,66 +305,149 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     auto load_piece = [&](uint32_t s, uint32_t c, uint32_t p, EvPiece &d) {
         if (8u * p < (s & 1u) + c) d = *reinterpret_cast<const EvPiece *>(ent2 + (s & ~1u) + static_cast<size_t>(8u * p));
     };
-    auto add = [&](uint32_t t, const EvRec &r, int nb) {
-        atomicAdd(&hi[t], r.hi);
-        atomicAdd(&lo[t], r.lo);
-        if (HITS) atomicAdd(&hc[t], nb);
+    // r added to the trials of the entries i of piece d that in(i) names
+    auto add = [&](const EvPiece &d, auto in, const EvRec &r, int nb) {
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            if (in(i)) {
+                const uint32_t t = ((i & 1u) ? d[i >> 1] >> 16 : d[i >> 1]) & kEvTrialMask;
+                atomicAdd(&hi[t], r.hi);
+                atomicAdd(&lo[t], r.lo);
+                if (HITS) atomicAdd(&hc[t], nb);
+            }
     };
     auto add_piece = [&](uint32_t s, uint32_t c, uint32_t p, const EvPiece &d, const EvRec &r, int nb) {
         const uint32_t first = 8u * p - (s & 1u);   // entry 0 of the piece in the list (wraps below 0)
-#pragma unroll
-        for (uint32_t i = 0; i < 8; ++i)
-            if (first + i < c) add(((i & 1u) ? d.a[i >> 1] >> 16 : d.a[i >> 1]) & kEvTrialMask, r, nb);
+        add(d, [&](uint32_t i) { return first + i < c; }, r, nb);
+    };
+    // the entries [a, z) of ent2, none before place s, added by a wavefront,
+    // eight a lane and two loads in flight
+    auto add_wide = [&](uint32_t s, uint32_t a, uint32_t z, const EvRec &r, int nb) {
+        a &= ~1u;
+        EvPiece d, d2;
+        const uint32_t a0 = a;
+        auto load = [&](uint32_t at, EvPiece &to) {
+            const uint32_t k = at + 8u * lane;
+            to = *reinterpret_cast<const EvPiece *>(ent2 + (k < z ? k : a0));
+        };
+        auto put = [&](uint32_t at, const EvPiece &from) {
+            const uint32_t k = at + 8u * lane;
+            add(from, [&](uint32_t i) { return k + i >= s && k + i < z; }, r, nb);
+        };
+        load(a, d);
+        for (; a < z; a += 1024u) {   // uniform
+            load(a + 512u, d2);
+            put(a, d);
+            load(a + 1024u, d);
+            put(a + 512u, d2);
+        }
+        wait_loads();
     };
 
     EvRec r0, r1, r2;
     int n0, n1, n2;
     uint32_t s0, c0, s1, c1;
-    EvPiece a0{}, a1{}, e0{}, e1{};   // the first two pieces of a list
-    load_rec(first_u, r0, n0);
-    load_rec(first_u + step_u, r1, n1);
+    EvPiece a1{}, e1{};   // the first two pieces of the next lists to be added
+    load_rec(first_u * kWave + lane, r0, n0);
+    load_rec((first_u + step_u) * kWave + lane, r1, n1);
     {
         const uint2 h = load_hdr(r0.ev);
         find(r0.ev, h, s0, c0);
     }
-    load_piece(s0, c0, 0, a0);
-    load_piece(s0, c0, 1, e0);
+    load_piece(s0, c0, 0, a1);
+    load_piece(s0, c0, 1, e1);
     uint2 h1 = load_hdr(r1.ev);
     for (int u = first_u; u < u1; u += step_u) {
-        load_rec(u + 2 * step_u, r2, n2);
+        load_rec((u + 2 * step_u) * kWave + lane, r2, n2);
         find(r1.ev, h1, s1, c1);
+        // the pieces have come with the headers, which were loaded after them;
+        // taken over any earlier they would be waited for by themselves (left
+        // to itself the compiler may do so right behind their loads)
+        EvPiece a0 = a1;
+        const EvPiece e0 = e1;
         load_piece(s1, c1, 0, a1);
         load_piece(s1, c1, 1, e1);
         h1 = load_hdr(r2.ev);
-        // a list of many entries: the wavefront's lanes take them together
-        for (uint64_t big = __ballot(c0 > kLongList); big; big &= big - 1) {
+        // a list of many entries: the wavefront's lanes take them together, and
+        // one of very many is left, in up to as many pieces as there are
+        // wavefronts, to all of them after the others (where there is room)
+        uint64_t big = long_lists(c0);
+        for (; big; big &= big - 1) {
             const int l = __builtin_ctzll(big);
+            const uint32_t s = __builtin_amdgcn_readlane(s0, l), c = __builtin_amdgcn_readlane(c0, l);
+            if (lane == l) c0 = 0;
+            if (c > kTaskList) {
+                const uint32_t per = max((c / kEvfWaves + 1024u) & ~1023u, kTaskList);   // entries of a piece
+                const uint32_t n = (c + per - 1u) / per;
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(n_task, n);
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (at + n <= static_cast<uint32_t>(kTasks)) {
+                    if (static_cast<uint32_t>(lane) < n) {
+                        task_range[at + lane] = make_uint2(s + lane * per, s + min(c, (lane + 1u) * per));
+                        task_rec[at + lane] = static_cast<uint32_t>(u * kWave + l);
+                    }
+                    continue;
+                }
+                if (static_cast<uint32_t>(lane) < n && at + lane < static_cast<uint32_t>(kTasks))
+                    task_range[at + lane] = make_uint2(0u, 0u);   // reserved, but not for this list
+            }
             EvRec r;
             r.hi = __shfl(r0.hi, l);
-            r.lo = __shfl(r0.lo, l);
-            const int nb = HITS ? __shfl(n0, l) : 0;
-            const uint32_t s = __shfl(s0, l), c = __shfl(c0, l);
-            for (uint32_t i = lane; i < c; i += kWave) add(ent2[static_cast<size_t>(s) + i] & kEvTrialMask, r, nb);
-            if (lane == l) c0 = 0;
+            r.lo = __builtin_amdgcn_readlane(r0.lo, l);
+            add_wide(s, s, s + c, r, HITS ? __builtin_amdgcn_readlane(n0, l) : 0);
         }
         add_piece(s0, c0, 0, a0, r0, n0);
         if (__any((s0 & 1u) + c0 > 8u)) {
             add_piece(s0, c0, 1, e0, r0, n0);
-            for (uint32_t p = 2; __any((s0 & 1u) + c0 > 8u * p); ++p) {
-                load_piece(s0, c0, p, a0);
-                add_piece(s0, c0, p, a0, r0, n0);
+            if (!__any((s0 & 1u) + c0 > 32u)) {
+                for (uint32_t p = 2; __any((s0 & 1u) + c0 > 8u * p); ++p) {
+                    load_piece(s0, c0, p, a0);
+                    add_piece(s0, c0, p, a0, r0, n0);
+                }
+            } else {   // two more pieces in flight while two are added
+                // (from the block's first entries for the lanes without: a
+                // branch around a load makes the compiler wait for all of them)
+                EvPiece x, y, x2, y2;
+                auto load_any = [&](uint32_t p, EvPiece &d) {
+                    const uint32_t at = 8u * p < (s0 & 1u) + c0 ? (s0 & ~1u) + 8u * p : 0u;
+                    d = *reinterpret_cast<const EvPiece *>(ent2 + at);
+                };
+                load_any(2, x);
+                load_any(3, y);
+                for (uint32_t p = 2; __any((s0 & 1u) + c0 > 8u * p); p += 4) {
+                    load_any(p + 2, x2);
+                    load_any(p + 3, y2);
+                    add_piece(s0, c0, p, x, r0, n0);
+                    add_piece(s0, c0, p + 1, y, r0, n0);
+                    load_any(p + 4, x);
+                    load_any(p + 5, y);
+                    add_piece(s0, c0, p + 2, x2, r0, n0);
+                    add_piece(s0, c0, p + 3, y2, r0, n0);
+                }
+                wait_loads();
             }
         }
         r0 = r1;
         n0 = n1;
         s0 = s1;
         c0 = c1;
-        a0 = a1;
-        e0 = e1;
         r1 = r2;
         n1 = n2;
     }
     __syncthreads();
+    // the pieces left over
+    const int nt_left = min(static_cast<int>(*n_task), kTasks);   // uniform
+    for (int q = w; q < nt_left; q += kEvfWaves) {
+        const uint2 range = task_range[q];
+        const uint32_t a = __builtin_amdgcn_readfirstlane(range.x), z = __builtin_amdgcn_readfirstlane(range.y);
+        if (a >= z) continue;
+        EvRec r;
+        int nb;
+        load_rec(static_cast<int>(__builtin_amdgcn_readfirstlane(task_rec[q])), r, nb);
+        add_wide(a, a, z, r, nb);
+    }
+    if (nt_left > 0) __syncthreads();
 
     if (parts > 1) {
         unsigned char *p = P.partial + slot * ev_slot_bytes(P.B.et, HITS);
@@ -464,10 +583,12 @@ int ev_parts(int64_t n_items, int64_t slots) {
 }
 
 static int32_t ev_params(const EvBlocks &B, const ara_yet *yet, bool hits, int parts, EvfParams &P) {
-    if (B.et < 1 || B.et > kEvMaxTrials || parts < 1)
+    if (B.et < 1 || B.et > kEvBlockTrials || parts < 1)
         return fail(ARA_E_INVAL, "event-ordered forward: blocks not prepared by this library");
     P.B = B;
     P.parts = parts;
+    const double blocks = std::max(B.neb, 1);   // entries of the longest list, and of one on average
+    P.spread = yet->max_occ / blocks > 64.0 + 8.0 * static_cast<double>(yet->nnz) / (blocks * std::max(B.catalog, 1));
     return fwd_params(yet, hits, false, P.fwd);
 }
 

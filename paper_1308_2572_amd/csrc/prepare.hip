@@ -895,7 +895,7 @@ static int32_t prepare(const char *what, const int64_t *offsets, const int32_t *
     ARA_HIP(hipMemcpyAsync(head, p.misc, sizeof(head), hipMemcpyDeviceToHost, st));
     ARA_HIP(hipStreamSynchronize(st));
     if ((head[kMiscErr] & 0xffffffff) != 0)
-        return fail(ARA_E_LIMIT, "ara_yet_prepare: 2^32 or more occurrences in one (slice, range) or one block of 8192 trials");
+        return fail(ARA_E_LIMIT, "ara_yet_prepare: 2^32 or more occurrences in one (slice, range) or one block of 8128 trials");
     y.max_occ = static_cast<int32_t>(head[kMiscMaxOcc] & 0xffffffff);
     *out = y;
     return ARA_OK;

@@ -205,3 +205,32 @@ def test_layers_walking_a_block_together(ara, kind):
         one = ara.Layers(np.array([0, J], np.int32), np.arange(eo[j], eo[j + 1], dtype=np.int32))
         y1, s1, h1 = ara.ylt_forward(tables, yet, one, et, lt[j:j + 1].contiguous(), want_hits=True, check=True)
         assert torch.equal(y1[0], y[j]) and torch.equal(s1[0], s[j]) and torch.equal(h1[0], h[j]), j
+
+
+def frequent(n, mean, catalog, freq, seed):
+    """A workload whose YET has events of the given numbers of occurrences
+    (all held by both ELTs) among ordinary ones."""
+    w = workload("frequent", n, mean, catalog, [catalog // 8, catalog // 5], [[0, 1], [1]], TERMS[:2], seed)
+    g = np.random.default_rng(seed)
+    hot = np.intersect1d(w.elts.rec_ids[:catalog // 8], w.elts.rec_ids[catalog // 8:])[:len(freq)]
+    assert len(hot) == len(freq) and sum(freq) < 0.7 * w.yet.nnz
+    at = g.permutation(w.yet.nnz)[:sum(freq)]
+    w.yet.ids[at] = np.repeat(hot, freq)
+    return w
+
+
+FREQUENCIES = [
+    [47, 48, 49, 50, 127, 128, 129, 130, 1023, 1024, 1025, 2047, 2048, 2049, 2050, 16_383, 16_384, 16_385],
+    [60] * 40 + [140] * 30,                   # more than a few lanes with lists of either length
+    [1100] * 50,
+    [2100] * 100,                             # more pieces than wait for the workgroup
+    [100_000, 40_000, 3000, 3000],
+]
+
+
+@pytest.mark.parametrize("catalog", [40_000, 10_000])
+@pytest.mark.parametrize("freq", FREQUENCIES)
+def test_lists_of_frequent_events(ara, catalog, freq):
+    """Lists around the lengths from which a wavefront, or the workgroup, adds
+    them together, few and many to a unit, in both header forms."""
+    check(ara, frequent(7000, 60, catalog, freq, 7 + catalog))
