@@ -46,6 +46,8 @@ struct EvBlocks {
 
 // The event-ordered blocks of a prepared YET (false: it has none).
 bool ev_blocks(const ara_yet *yet, EvBlocks *out);
+// The same, for the binary64 forward (false: it takes the code stream).
+bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out);
 
 // Whether one of the eight lengths of a sparse header is 15.
 __device__ __forceinline__ bool ev_long(uint32_t nib) {

@@ -138,7 +138,7 @@ static size_t fwd_workspace(const ara_tables *tables, const ara_layers *layers, 
 // together.
 static size_t partial_bytes(const ara_yet *yet, int n_layers, bool hits, bool f32) {
     EvBlocks B{};
-    if (f32 || !ev_blocks(yet, &B)) return 0;
+    if (f32 || !ev_forward_blocks(yet, &B)) return 0;
     const size_t slots = std::max(static_cast<size_t>(2 * device_cu_count()),
                                   static_cast<size_t>(ev_sweep(n_layers, B, yet, B.neb)) * static_cast<size_t>(B.neb));
     return slots * ev_slot_bytes(B.et, hits);
@@ -223,7 +223,7 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
     // binary32 totals stay with the code stream although it is slower (100,000
     // trials of 1000: 212 us where exact sums of the rounded O took 109): they
     // round at every addition in the trial's order, and those are the results
-    const bool ev = !f32 && ev_blocks(yet, &B);
+    const bool ev = !f32 && ev_forward_blocks(yet, &B);
     if (ev)
         for (OccTables &t : tabs) {
             t.ev = t.ev_space;

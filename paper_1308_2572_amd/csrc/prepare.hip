@@ -681,9 +681,36 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
 // flags it was prepared with: the pieces' places follow from the sizes and
 // those flags.
 constexpr int32_t kHasEvBlocks = 0x100;
+// ... and one whose binary64 forward takes them.
+constexpr int32_t kEvForward = 0x200;
+
+// Whether the forward of a YET takes its event-ordered blocks.  It depends on
+// the YET alone, so that a layer's results are the same in every call.  The
+// blocks are the faster of the two but for (us of one layer's call over
+// uniform event frequencies: blocks, stream):
+//   * events in most years, whose lists a few workgroups have to themselves:
+//     on average 3200 entries a list 274, 255 (400,000 x 1000), 2670 entries
+//     236, 255; one event's 11,000, all of the 64 most frequent held by the
+//     layer 146, 139 (100,000 x 1000), 3400 entries 118, 140;
+//   * few ranges and few occurrences, where the stream is as short as the
+//     blocks' chain of launches: 20,000 x 1000 over 10,000 events 80, 53,
+//     30,000 61, 55, 60,000 62, 57, 100,000 57, 62; over 10,000 events 50,000 x
+//     1000 88, 71 and 100,000 x 1000 90, 94;
+//   * many short years, whose blocks are walked for a few entries: 3M x 60 over
+//     2M events (0.24 a list) 458, 352, 3M x 150 (0.61) 496, 491, 10M x 10 over
+//     300,000 (0.27) 257, 213, x 60 (1.6) 380, 432; with no more blocks than
+//     workgroups run at once the blocks win (1M x 10 over 2M 161, 242).
+static bool ev_pays(const EvGeometry &g, int64_t nnz, int32_t catalog, int32_t max_occ) {
+    const double mean = static_cast<double>(nnz) / (static_cast<double>(catalog) * g.neb);
+    if (mean > 3000.0 || static_cast<double>(max_occ) > 10000.0 * g.neb) return false;
+    if (catalog <= 3 * kRange && static_cast<double>(nnz) * catalog < 1.3e12) return false;
+    return g.neb <= 150 || mean >= 0.85;
+}
+
+bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out) { return (yet->reserved & kEvForward) != 0 && ev_blocks(yet, out); }
 
 bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
-    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags)) != kHasEvBlocks || yet->n_blocks == 0) return false;
+    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags | kEvForward)) != kHasEvBlocks || yet->n_blocks == 0) return false;
     const uint32_t flags = static_cast<uint32_t>(yet->reserved) & kPrepFlags;
     Geometry g{};
     g.tg = yet->trials_per_group;
@@ -897,6 +924,7 @@ static int32_t prepare(const char *what, const int64_t *offsets, const int32_t *
     if ((head[kMiscErr] & 0xffffffff) != 0)
         return fail(ARA_E_LIMIT, "ara_yet_prepare: 2^32 or more occurrences in one (slice, range) or one block of 8128 trials");
     y.max_occ = static_cast<int32_t>(head[kMiscMaxOcc] & 0xffffffff);
+    if (ev_pays(E.g, nnz, catalog, y.max_occ)) y.reserved |= kEvForward;
     *out = y;
     return ARA_OK;
 }

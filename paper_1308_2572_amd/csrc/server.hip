@@ -401,7 +401,7 @@ extern "C" int32_t ara_server_create(const ara_tables *tables, const ara_yet *ye
     X.tables = *tables;
     X.yet = *yet;
     X.elt_terms = elt_terms;
-    X.use_ev = ev_blocks(yet, &X.ev);
+    X.use_ev = ev_forward_blocks(yet, &X.ev);
     X.z = occ_sizes(tables->catalog, false);
     X.res_doubles = 3 + 12 + static_cast<size_t>(3) * tables->n_elts * 3;
     X.stage_bytes = HipExecutor::kResOff + X.res_doubles * sizeof(double);
