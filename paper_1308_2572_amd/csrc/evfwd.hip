@@ -51,7 +51,7 @@ struct EvfParams {
     const uint32_t *share;     // k_ev_share's table, when sweep > 0
     int32_t sweep;             // workgroups of a block that may walk it together, or 0
     int32_t spread;            // the parts take runs of units in turn
-    FwdParams fwd;             // for the layers of mode 0 
+    FwdParams fwd;             // for the layers of mode 0 (k_ev_rest)
 };
 
 // Sixteen bytes of a list, from an even entry on.  (A vector: of a struct the
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kWave) void k_ev_share(const OccTables *__restrict_
     if (in) {
         const EvLayer L = *device_ptr(tabs[l].ev);
         w = static_cast<float>(max(L.n_set, 1));
-        ok = L.mode == 1;
+        ok = (L.mode & kEvLayout) == 1;
     }
     float sum = w, most = in ? w : 0.0f, least = in ? w : 3e38f;
     for (int o = 32; o > 0; o >>= 1) {
@@ -146,7 +146,6 @@ __global__ __launch_bounds__(kWave) void k_ev_share(const OccTables *__restrict_
 template <bool HITS, bool DENSE>
 __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     __shared__ __align__(16) unsigned char smem[kEvMaxTrials * (HITS ? 16 : 12)];
-    static_assert(sizeof(smem) >= kLdsBytes, "the stream's LDS");
     unsigned long long *hi = reinterpret_cast<unsigned long long *>(smem);
     uint32_t *lo = reinterpret_cast<uint32_t *>(smem + kEvMaxTrials * 8);
     int32_t *hc = reinterpret_cast<int32_t *>(smem + kEvMaxTrials * 12);   // with hits
@@ -213,24 +212,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     const EvLayer L = *T.ev;
     const int64_t bt0 = static_cast<int64_t>(b) * P.B.et;
     const int nt = static_cast<int>(min<int64_t>(P.B.et, P.B.n_trials - bt0));
-    if (!L.mode) {   // uniform: the stream's blocks that meet this one, its parts in turn
-        const int64_t a = max(t0, bt0), z = min(t1, bt0 + nt);
-        FwdItem I;
-        I.tab = tab;
-        I.lterm = lterm;
-        I.pad = 0;
-        I.t0 = a;
-        I.t1 = z;
-        I.ylt = ylt + (a - t0);
-        I.s_pre = s_pre ? s_pre + (a - t0) : nullptr;
-        I.hits = hits ? hits + (a - t0) : nullptr;
-        for (int64_t k2 = a / P.fwd.tb + part; k2 * P.fwd.tb < z; k2 += parts) {
-            I.block = static_cast<int32_t>(k2);
-            __syncthreads();   // the previous block's totals have been read
-            fwd_block<HITS, false, true>(P.fwd, I, smem);
-        }
-        return;
-    }
+    if (!L.mode) return;   // uniform: the stream's (k_ev_rest)
     for (int i = tid; i < nt; i += kEvfThreads) {
         hi[i] = 0ull;
         lo[i] = 0u;
@@ -262,7 +244,7 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     auto load_rec = [&](int i, EvRec &r, int &nb) {
         r = EvRec{0, 0, ~0u};
         nb = 0;
-        if (L.mode == 2) {   // uniform
+        if ((L.mode & kEvLayout) == 2) {   // uniform
             constexpr int kChunk = kOccChunkWords * 32;
             if (i < n_set && i % kChunk < T.pcount[i / kChunk]) {
                 const uint2 v = reinterpret_cast<const uint2 *>(T.dense)[i];
@@ -305,16 +287,34 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
     auto load_piece = [&](uint32_t s, uint32_t c, uint32_t p, EvPiece &d) {
         if (8u * p < (s & 1u) + c) d = *reinterpret_cast<const EvPiece *>(ent2 + (s & ~1u) + static_cast<size_t>(8u * p));
     };
-    // r added to the trials of the entries i of piece d that in(i) names
+    // r added to the trials of the entries i of piece d that in(i) names.  With
+    // carry lo takes all of its 32 bits, and an addition that wraps it adds one
+    // to hi.
+    const bool carry = (L.mode & kEvCarry) != 0;   // uniform
     auto add = [&](const EvPiece &d, auto in, const EvRec &r, int nb) {
+        auto trial = [&](uint32_t i) { return ((i & 1u) ? d[i >> 1] >> 16 : d[i >> 1]) & kEvTrialMask; };
+        if (!carry) {
 #pragma unroll
-        for (uint32_t i = 0; i < 8; ++i)
-            if (in(i)) {
-                const uint32_t t = ((i & 1u) ? d[i >> 1] >> 16 : d[i >> 1]) & kEvTrialMask;
-                atomicAdd(&hi[t], r.hi);
-                atomicAdd(&lo[t], r.lo);
-                if (HITS) atomicAdd(&hc[t], nb);
-            }
+            for (uint32_t i = 0; i < 8; ++i)
+                if (in(i)) {
+                    const uint32_t t = trial(i);
+                    atomicAdd(&hi[t], r.hi);
+                    atomicAdd(&lo[t], r.lo);
+                    if (HITS) atomicAdd(&hc[t], nb);
+                }
+        } else {
+            uint32_t old[8];
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                if (in(i)) old[i] = atomicAdd(&lo[trial(i)], r.lo);
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                if (in(i)) {
+                    const uint32_t t = trial(i);
+                    atomicAdd(&hi[t], r.hi + (old[i] + r.lo < old[i] ? 1ull : 0ull));
+                    if (HITS) atomicAdd(&hc[t], nb);
+                }
+        }
     };
     auto add_piece = [&](uint32_t s, uint32_t c, uint32_t p, const EvPiece &d, const EvRec &r, int nb) {
         const uint32_t first = 8u * p - (s & 1u);   // entry 0 of the piece in the list (wraps below 0)
@@ -473,12 +473,16 @@ __global__ __launch_bounds__(kEvfThreads) void k_ev_fwd(EvfParams P) {
 }
 
 // The results of a split launch's trials from the parts' totals (integers: in
-// any order).  Regular set: one run of 256 / G trials of a (layer, block) per
+// any order).  Regular set: one run of NT / G trials of a (layer, block) per
 // workgroup, G lanes per trial where there are few, so that its parts' loads
 // overlap.  List: the same of an item.
-template <bool HITS>
-__global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
+constexpr int kRestThreads = 1024;
+constexpr int kAddThreads = 256;
+
+template <bool HITS, int NT>
+__device__ __forceinline__ void ev_add(const EvfParams &P, int G, int per) {
     const int u = blockIdx.x / per, c = blockIdx.x - u * per;
+    if (u >= (P.items ? P.n_items : P.nl * P.nb)) return;
     int b;
     int64_t t0, t1;
     const OccTables *tab;
@@ -509,7 +513,7 @@ __global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
     }
     const EvLayer L = *device_ptr(tab->ev);
     if (!L.mode) return;   // uniform
-    const int i = (c * 256 + static_cast<int>(threadIdx.x)) / G, sub = threadIdx.x & (G - 1);
+    const int i = (c * NT + static_cast<int>(threadIdx.x)) / G, sub = threadIdx.x & (G - 1);
     const int64_t t = static_cast<int64_t>(b) * P.B.et + i;
     if (i >= P.B.et || t < t0 || t >= t1) return;   // all lanes of a trial together
     const size_t slot = ev_slot_bytes(P.B.et, HITS);
@@ -544,6 +548,56 @@ __global__ __launch_bounds__(256) void k_ev_add(EvfParams P, int G, int per) {
     if (HITS && hits) hits[o] = k;
 }
 
+// By itself, of a block's workgroups that walked it together: 16 parts of every
+// trial, four layers over 1M trials 51 us, as a part of k_ev_rest 65.
+template <bool HITS>
+__global__ __launch_bounds__(kAddThreads) void k_ev_add(EvfParams P, int per) {
+    ev_add<HITS, kAddThreads>(P, 1, per);
+}
+
+// What is left behind k_ev_fwd: the first n_add workgroups add the parts up,
+// the others stream the layers that its integers do not fit, as k_fwd would
+// (two workgroups on a CU, where k_ev_fwd has one).  In one launch, since such
+// layers are rare and only the device knows of them: the workgroups find none
+// and end.
+template <bool HITS, bool SHARED, bool LIST>
+__global__ __launch_bounds__(kRestThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ev_rest(EvfParams P, int G, int per,
+                                                                                                  int n_add) {
+    __shared__ __align__(16) unsigned char smem[kLdsBytes];
+    if (static_cast<int>(blockIdx.x) < n_add) {
+        ev_add<HITS, kRestThreads>(P, G, per);
+        return;
+    }
+    const int first = static_cast<int>(blockIdx.x) - n_add, step = static_cast<int>(gridDim.x) - n_add;
+    int n = P.n_items;
+    if (!LIST) {
+        bool any = false;
+        for (int j = threadIdx.x & 63; j < P.nl; j += kWave) any = any || device_ptr(P.tabs[j].ev)->mode == 0;
+        if (!__any(any)) return;   // uniform
+        n = P.nl <= 1 ? P.fwd.reg_nb : P.nl * kXcds * ((P.fwd.reg_nb + kXcds - 1) / kXcds);   // fwd_regular_items
+    }
+    for (int i = first; i < n; i += step) {
+        FwdItem I = fwd_item(P.fwd, i);
+        if (I.block < 0 || device_ptr(I.tab->ev)->mode) continue;   // uniform
+        int k = I.block, k1 = k + 1;
+        if (LIST) {   // the stream's blocks that meet the item's
+            const int64_t bt0 = static_cast<int64_t>(I.block) * P.B.et;
+            const int64_t a = max(I.t0, bt0), z = min(I.t1, min(bt0 + P.B.et, P.B.n_trials));
+            I.ylt += a - I.t0;
+            if (I.s_pre) I.s_pre += a - I.t0;
+            I.t0 = a;
+            I.t1 = z;
+            k = static_cast<int>(a / P.fwd.tb);
+            k1 = static_cast<int>((z + P.fwd.tb - 1) / P.fwd.tb);
+        }
+        for (; k < k1; ++k) {
+            I.block = k;
+            __syncthreads();   // the previous block's totals have been read
+            fwd_block<HITS, false, SHARED, true>(P.fwd, I, smem);
+        }
+    }
+}
+
 static int32_t launch_ev(const EvfParams &P, bool hits, unsigned grid, int n_sets, hipStream_t st) {
     if (hits) {
         if (P.B.dense) k_ev_fwd<true, true><<<grid, kEvfThreads, 0, st>>>(P);
@@ -552,14 +606,29 @@ static int32_t launch_ev(const EvfParams &P, bool hits, unsigned grid, int n_set
         if (P.B.dense) k_ev_fwd<false, true><<<grid, kEvfThreads, 0, st>>>(P);
         else k_ev_fwd<false, false><<<grid, kEvfThreads, 0, st>>>(P);
     }
-    if (P.parts > 1 || P.sweep > 0) {
-        int G = 1;   // lanes per trial: while that leaves the device room
+    int G = 1, per = 0;
+    if (P.sweep > 0) {
+        const int pa = (P.B.et + kAddThreads - 1) / kAddThreads;
+        const unsigned g = static_cast<unsigned>(n_sets) * static_cast<unsigned>(pa);
+        if (hits) k_ev_add<true><<<g, kAddThreads, 0, st>>>(P, pa);
+        else k_ev_add<false><<<g, kAddThreads, 0, st>>>(P, pa);
+    } else if (P.parts > 1) {   // lanes per trial: while that leaves the device room
         while (2 * G <= std::min(P.parts, kWave) && static_cast<int64_t>(2 * G) * n_sets * P.B.et <= 65536) G *= 2;
-        const int per = (P.B.et * G + 255) / 256;
-        const unsigned ga = static_cast<unsigned>(n_sets) * static_cast<unsigned>(per);
-        if (hits) k_ev_add<true><<<ga, 256, 0, st>>>(P, G, per);
-        else k_ev_add<false><<<ga, 256, 0, st>>>(P, G, per);
+        per = (P.B.et * G + kRestThreads - 1) / kRestThreads;
     }
+    // (a multiple of the XCDs, so that what follows goes to them in turn)
+    const int n_add = (n_sets * per + kXcds - 1) / kXcds * kXcds;
+    // the stream's two workgroups on each CU, a multiple of the XCDs
+    const int n_rest = std::min(P.items ? P.n_items : fwd_regular_items(P.nl, P.fwd.reg_nb), 2 * device_cu_count());
+    const unsigned ga = static_cast<unsigned>(n_add + (n_rest + kXcds - 1) / kXcds * kXcds);
+    per = std::max(per, 1);
+#define ARA_REST_LAUNCH(H, S, L) k_ev_rest<H, S, L><<<ga, kRestThreads, 0, st>>>(P, G, per, n_add)
+    if (P.items) ARA_REST_LAUNCH(false, true, true);
+    else if (hits && P.nl > 1) ARA_REST_LAUNCH(true, true, false);
+    else if (hits) ARA_REST_LAUNCH(true, false, false);
+    else if (P.nl > 1) ARA_REST_LAUNCH(false, true, false);
+    else ARA_REST_LAUNCH(false, false, false);
+#undef ARA_REST_LAUNCH
     ARA_HIP(hipGetLastError());
     return ARA_OK;
 }
@@ -608,6 +677,16 @@ int32_t launch_ev_forward(const EvBlocks &B, const ara_yet *yet, bool hits, cons
     P.nb = reg.ev_nb;
     P.nl = reg.nl;
     P.partial = reg.partial;
+    P.fwd.reg_tabs = reg.tabs;
+    P.fwd.reg_lterm = reg.lterm;
+    P.fwd.reg_ylt = reg.ylt;
+    P.fwd.reg_s_pre = reg.s_pre;
+    P.fwd.reg_hits = reg.hits;
+    P.fwd.reg_t0 = reg.t0;
+    P.fwd.reg_t1 = reg.t1;
+    P.fwd.reg_b0 = reg.b0;
+    P.fwd.reg_nb = reg.nb;
+    P.fwd.reg_nl = reg.nl;
     if (reg.sweep > 0) {
         P.sweep = reg.sweep;
         P.share = reg.share;
@@ -624,7 +703,7 @@ int32_t launch_ev_list(const EvBlocks &B, const ara_yet *yet, const FwdItem *d_i
     EvfParams P{};
     const int32_t rc = ev_params(B, yet, false, parts, P);
     if (rc) return rc;
-    P.items = d_items;
+    P.items = P.fwd.items = d_items;
     P.n_items = n_items;
     P.nl = 1;
     P.partial = partial;

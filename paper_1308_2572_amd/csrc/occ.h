@@ -37,10 +37,17 @@ struct OccChunkStat {
 };
 
 // How the event-ordered forward serves a layer.  Its totals are integers:
-// O = (hi * 2^frac + lo) * 2^(gexp - frac) exactly, lo < 2^frac, with hi's
-// sum over any trial below 2^62 and lo's below 2^32.  mode 0: some O does not
-// fit (values more than 2^62 apart, an infinity) or the events held exceed
-// half the table's room, and the one-layer stream serves the layer.
+// O = (hi * 2^frac + lo) * 2^(gexp - frac) exactly, lo < 2^frac, with hi's sum
+// over any trial below 2^64.  In the plain form lo's sum stays below 2^32 by
+// itself (frac = 32 - b, where 2^b occurrences are no fewer than the longest
+// trial's) and no O may have a bit 94 - 2b places or more below the largest
+// O's power of two; for values of 53 bits a ratio of 2^21 with b = 10, 2^9 with
+// b = 16.  With kEvCarry lo uses its 32 bits and what wraps goes to hi: 96 - b
+// places, 2^33 and 2^27.  Of mode 0 is what neither holds, or an infinity: the
+// code stream serves the layer.
+constexpr int kEvLayout = 3;   // 1: records in event order over the whole catalogue;
+                               // 2: the chunks' own places (the events held exceed half the table's room)
+constexpr int kEvCarry = 4;
 struct EvLayer {
     int32_t mode, n_set, gexp, frac;
 };

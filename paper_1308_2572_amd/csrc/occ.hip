@@ -286,10 +286,17 @@ __device__ EvLayer occ_layer_form(const OccTables &T, int n_chunks, int before, 
     const int top = (ex ? ex - 1022 : -1021) + lbits;   // every total < 2^top
     L.gexp = top - 62;
     L.frac = 32 - lbits;
-    if (low < L.gexp - L.frac) return L;
+    int carry = 0;
+    if (low < L.gexp - L.frac) {
+        carry = kEvCarry;
+        L.gexp = top - 64;
+        L.frac = 32;
+        if (low < L.gexp - L.frac) return L;
+    }
     const int slots = n_chunks * (kOccChunkWords * 32);
-    L.mode = 2ull * un <= static_cast<unsigned long long>(slots) ? 1 : 2;
-    if (L.mode == 2) L.n_set = slots;
+    const int layout = 2ull * un <= static_cast<unsigned long long>(slots) ? 1 : 2;
+    L.mode = layout | carry;
+    if (layout == 2) L.n_set = slots;
     return L;
 }
 
@@ -366,7 +373,8 @@ __global__ __launch_bounds__(kRankThreads) void k_occ_rank(const OccTables *__re
             }
             __syncthreads();
             EvRec *rec = reinterpret_cast<EvRec *>(T.vals) + gbase;
-            const size_t cdst = L.mode == 1 ? gbase : src;
+            const bool compact = (L.mode & kEvLayout) == 1;
+            const size_t cdst = compact ? gbase : src;
             for (uint32_t i = tid; i < cnt; i += kRankThreads) {
                 const unsigned long long ob = static_cast<unsigned long long>(__double_as_longlong(T.dense[src + i]));
                 EvRec v{0, 0, static_cast<uint32_t>(src) + list[i]};
@@ -378,12 +386,12 @@ __global__ __launch_bounds__(kRankThreads) void k_occ_rank(const OccTables *__re
                         m >>= -sh;
                         sh = 0;
                     }
-                    // sh <= 42: the value is below 2^(62 + frac), m at least 2^52 (or, of a subnormal, the
+                    // sh <= 43: the value is below 2^(64 + frac), m at least 2^52 (or, of a subnormal, the
                     // exponent at its lowest)
                     v.hi = sh >= L.frac ? m << (sh - L.frac) : m >> (L.frac - sh);
                     v.lo = static_cast<uint32_t>((m << sh) & ((1ull << L.frac) - 1ull));
                 }
-                if (L.mode == 1) {
+                if (compact) {
                     rec[i] = v;
                 } else {   // dense[src + i] has just been read by this thread, and by no other
                     reinterpret_cast<unsigned long long *>(T.vals)[src + i] = v.hi;
