@@ -332,7 +332,10 @@ __device__ __forceinline__ void gather_w(const BwdGather &P, int x, int wi, int 
     int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
     const int sub = tid & (G - 1);
     const int ngrp = nw * threads / G;
-    for (int g = (wi * threads + tid) / G; g < H; g += ngrp) {
+    // wavefronts to the workgroups in turn: a few hundred events, of long lists,
+    // are then walked on all CUs (1000 events, 400,000 x 1000: 1561 us in
+    // workgroups of 256 threads, in these 2516 when the first ones took them all)
+    for (int g = ((tid / kWave * nw + wi) * kWave + tid % kWave) / G; g < H; g += ngrp) {
         const int e = hev[g];
         const int64_t o0 = off[e], o1 = off[e + 1];
         int64_t acc[CS];
@@ -545,8 +548,17 @@ __global__ __launch_bounds__(kBwdEvThreads) void k_bwd_w1(BwdGather P) {
 }
 
 template <int G>
-static void launch_bwd_w(int cs, dim3 grid, hipStream_t st, const BwdGather &S) {
-    if (cs == 1) {
+static void launch_bwd_w(int cs, dim3 grid, hipStream_t st, const BwdGather &S, double mean_list) {
+    if (cs == 1 && S.ev_least == INT64_MAX && mean_list >= 4096.0) {
+        // lists so long that a wavefront takes each: of a few events, a group of
+        // 16 lanes walks its list alone (20 events of 62,500 a list 0.9 to 1.8 ms)
+        k_bwd_w<1, kWave><<<grid, 256, 0, st>>>(S);
+    } else if (cs == 1 && S.ev_least == INT64_MAX) {
+        // the gather for sure: in workgroups of 256 (frequencies as u^6, one event
+        // in a tenth of the occurrences, 7.6 ms; in those of k_bwd_w1 9.1; 20
+        // events 0.93 and 1.6)
+        k_bwd_w<1, G><<<grid, 256, 0, st>>>(S);
+    } else if (cs == 1) {
         // a workgroup per CU over the layers, a multiple of the slices for each
         const int per = std::max(1, device_cu_count() / (S.n_layers * kXcds));
         k_bwd_w1<G><<<static_cast<unsigned>(per * kXcds) * static_cast<unsigned>(S.n_layers), kBwdEvThreads, 0, st>>>(S);
@@ -1087,18 +1099,26 @@ static int bwd_nwg_v(int64_t n) {   // about two trials per thread, at most 512 
 }
 
 // Hot events, of all layers, from which k_bwd_w1 goes through the event-ordered
-// blocks.  A block costs every workgroup 2.6 us (its v from L2, latency), and
-// the device 10 ps per hot event, and 5 ps more for each occurrence of its
-// list past the fourth; the gather 280 ps per hot event and 6.5 per
-// occurrence.  From these calls (us: gather, blocks): 1M x 1000, 15 ELTs 574,
-// 608, 6 ELTs 279, 501; 300,000 x 800, two layers 407, 279, with few hot
-// events 157, 205; 100,000 x 1000, 15 ELTs 153, 127, 5 ELTs 81, 99; 400,000 x
-// 1000 over 300,000 events 306, 380; 400,000 x 200 132, 215; 20,000 x 1000
-// 112, 87.  The blocks have to be a tenth the faster.
-static int64_t ev_least(double blocks, double per_event) {
+// blocks.  A block costs every workgroup 2.6 us (its v from L2, latency) and 80
+// ns for each entry of the longest list past the eighth, which all wait for, and
+// the device 10 ps per hot event and 2.5 ps for each occurrence of its list past
+// the fourth; the gather 280 ps per hot event and 6.5 per occurrence.  Where an
+// event's lists have more than kBwdLongList entries on average the gather serves
+// (400,000 x 1000 over 10,000 events 340 us, blocks 1430).  From these calls (us:
+// gather, blocks): 1M x 1000 over 2M events, 15 ELTs 574, 608, 6 ELTs 279, 501;
+// 300,000 x 800, two layers 407, 279, with few hot events 157, 205; 400,000 x
+// 1000 over 3M, 1M, 400,000, 200,000, 120,000 and 50,000 events, a sixth of them
+// hot, 646, 389; 493, 353; 462, 406; 446, 512; 430, 658; 397, 1097; a fortieth of
+// 1M 155, 253; two layers over 200,000 799, 580; 100,000 x 1000 over 3M, 400,000
+// and 120,000 290, 183; 196, 160; 166, 217; 100,000 x 200 over 1M 138, 134;
+// frequencies as u^1.3, longest list 333, 626, 1063.  The blocks have to be a
+// tenth the faster.
+static int64_t ev_least(double blocks, double per_event, double longest) {
+    if (longest > kBwdLongList) return INT64_MAX;
     const double list = per_event / blocks;
-    const double saved = 280.0 + 6.5 * per_event - blocks * (10.0 + 5.0 * std::max(list - 4.0, 0.0));   // ps per hot event
-    return saved > 0.0 ? static_cast<int64_t>(std::min(1.1 * 2.6e6 * blocks / saved + 1.0, 1e15)) : INT64_MAX;
+    const double fixed = blocks * (2.6e6 + 8e4 * std::max(longest - 8.0, 0.0));                                   // ps
+    const double saved = 280.0 + 6.5 * per_event - blocks * (10.0 + 2.5 * std::max(list - 4.0, 0.0));   // per hot event
+    return saved > 0.0 ? static_cast<int64_t>(std::min(1.1 * fixed / saved + 1.0, 1e15)) : INT64_MAX;
 }
 
 static int64_t dev_blocks(int64_t n) { return std::max<int64_t>(1, (n + kDevChunk - 1) / kDevChunk); }
@@ -1244,7 +1264,8 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     if (ev_blocks(yet, &S.B) && S.B.et <= kEvMaxTrials && yet->nnz > 0) {
         const double blocks = static_cast<double>((trial_end + S.B.et - 1) / S.B.et - trial_begin / S.B.et);
         const double per_event = static_cast<double>(yet->nnz) / tables->catalog * static_cast<double>(n) / yet->n_trials;
-        S.ev_least = ev_least(blocks, per_event);
+        const double longest = static_cast<double>(yet->max_occ) / S.B.neb;   // mean list of the most frequent event
+        S.ev_least = ev_always_backward(yet) ? 0 : ev_least(blocks, per_event, longest);
     }
     S.slice_trials = yet->slice_trials;
     S.t0 = trial_begin;
@@ -1315,8 +1336,8 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
             else k_bwd_count<4><<<grid, 256, lds, st>>>(Q, cx, ncut);
             k_bwd_wsparse<<<dim3(2 * cu, L), kSparseThreads, 0, st>>>(Q);
         }
-        if (wide) launch_bwd_w<16>(B.cs, grid, st, S);
-        else launch_bwd_w<4>(B.cs, grid, st, S);
+        if (wide) launch_bwd_w<16>(B.cs, grid, st, S, mean_list);
+        else launch_bwd_w<4>(B.cs, grid, st, S, mean_list);
         ARA_HIP(hipGetLastError());
     }
     BwdGrad Gp{};

@@ -48,6 +48,10 @@ struct EvBlocks {
 bool ev_blocks(const ara_yet *yet, EvBlocks *out);
 // The same, for the binary64 forward (false: it takes the code stream).
 bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out);
+// A mark set by hand on a YET that has blocks: the one-row backward goes through
+// them whatever its rule says (tests compare the ways at sizes where it would
+// not; both give the same integers).
+bool ev_always_backward(const ara_yet *yet);
 
 // Whether one of the eight lengths of a sparse header is 15.
 __device__ __forceinline__ bool ev_long(uint32_t nib) {

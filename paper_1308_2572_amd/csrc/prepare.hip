@@ -683,6 +683,7 @@ __global__ __launch_bounds__(kEmitThreads) void k_prep_emit(EmitParams P) {
 constexpr int32_t kHasEvBlocks = 0x100;
 // ... and one whose binary64 forward takes them.
 constexpr int32_t kEvForward = 0x200;
+constexpr int32_t kEvAlwaysBackward = 0x400;   // (ev_always_backward)
 
 // Whether the forward of a YET takes its event-ordered blocks.  It depends on
 // the YET alone, so that a layer's results are the same in every call.  The
@@ -709,8 +710,10 @@ static bool ev_pays(const EvGeometry &g, int64_t nnz, int32_t catalog, int32_t m
 
 bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out) { return (yet->reserved & kEvForward) != 0 && ev_blocks(yet, out); }
 
+bool ev_always_backward(const ara_yet *yet) { return (yet->reserved & kEvAlwaysBackward) != 0; }
+
 bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
-    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags | kEvForward)) != kHasEvBlocks || yet->n_blocks == 0) return false;
+    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags | kEvForward | kEvAlwaysBackward)) != kHasEvBlocks || yet->n_blocks == 0) return false;
     const uint32_t flags = static_cast<uint32_t>(yet->reserved) & kPrepFlags;
     Geometry g{};
     g.tg = yet->trials_per_group;

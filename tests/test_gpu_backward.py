@@ -409,3 +409,60 @@ def test_one_row_over_blocks_is_bitwise_the_gather(ara, trials, mean, catalog, n
         a = ara.ylt_backward(tables, blocks, lay, et, lt, sp, c, t0, t1)
         b = ara.ylt_backward(tables, gather, lay, et, lt, sp, c, t0, t1)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]), (t0, t1)
+
+
+@pytest.mark.parametrize("trials,mean,catalog,n_elts", [(2000, 400, 60_000, 8), (20_000, 100, 40_000, 12), (9000, 30, 700, 3)])
+def test_one_row_over_blocks_where_the_gather_would_serve(ara, trials, mean, catalog, n_elts, monkeypatch):
+    """The same with lists too long, or events too few, for the rule that
+    chooses the blocks, by the mark that overrules it."""
+    prepared = ara.PreparedYet.from_numpy.__func__
+
+    def marked(cls, *args, **kw):
+        yet = prepared(cls, *args, **kw)
+        yet.handle.reserved |= 0x400
+        return yet
+
+    monkeypatch.setattr(ara.PreparedYet, "from_numpy", classmethod(marked))
+    test_one_row_over_blocks_is_bitwise_the_gather(ara, trials, mean, catalog, n_elts)
+
+
+@pytest.mark.parametrize("catalog,power", [(10_000, 1.0), (50_000, 1.0), (500_000, 2.0), (100, 1.0)])
+def test_long_lists_cost_no_more_than_the_gather(ara, catalog, power):
+    """One dense row of 100,000 x 500 over small catalogues, and over events of
+    very unequal frequency: the call takes the time of the gather, and of few
+    events the gather keeps all of the device busy.  The blocks took 1.6 to 6.7
+    times as long."""
+    import time
+    import torch
+    n, per = 100_000, 500
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda") * per
+    ids = (torch.rand(n * per, generator=g, device="cuda", dtype=torch.float64) ** power * catalog).to(torch.int32)
+    ids.clamp_(0, catalog - 1)
+    K, rec = 10, max(3, catalog // 60)
+    ri = torch.cat([torch.randperm(catalog, generator=g, device="cuda", dtype=torch.int32)[:rec] for _ in range(K)])
+    rl = torch.exp(12.0 + 1.5 * torch.randn(K * rec, generator=g, device="cuda"))
+    tables = ara.EltTables(torch.arange(K + 1, dtype=torch.int64, device="cuda") * rec, ri, rl, catalog)
+    yet = ara.PreparedYet(off, ids, catalog)
+    lay = ara.Layers(np.array([0, K], np.int32), np.arange(K, dtype=np.int32))
+    et = torch.tensor([[1.0, 0.0, 5e6]] * K, dtype=torch.float64, device="cuda")
+    lt = torch.tensor([[0.0, 1e7, 1e6, 1e12]], dtype=torch.float64, device="cuda")
+    _, s_pre, _ = ara.ylt_forward(tables, yet, lay, et, lt)
+    cot = torch.rand((1, 1, n), generator=g, dtype=torch.float64, device="cuda") / n
+
+    def best(reserved):
+        yet.handle.reserved = reserved
+        t = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            ara.ylt_backward(tables, yet, lay, et, lt, s_pre, cot)
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        return min(t)
+
+    auto = best(yet.handle.reserved)
+    gather = best(0)
+    print(f"[gpu-backward] {catalog} events, u^{power}: {auto * 1e6:.0f} us, gather {gather * 1e6:.0f} us", flush=True)
+    assert auto < 1.15 * gather
