@@ -244,6 +244,7 @@ struct BwdSparse {
     uint2 *abits;                      // [n_layers][aw] bit t: trial t has the second value
     int64_t aw;                        // 64-bit words of a layer's bits
     int32_t two, two_bytes;            // whether the third form is available, and its LDS
+    int32_t segs;                      // wavefronts for each trial that is walked
     const int32_t *t_cnt;              // occurrences of each event
     const int64_t *t_off;              // trial-major copy
     const int32_t *t_ids;
@@ -793,7 +794,8 @@ __global__ __launch_bounds__(256) void k_bwd_count(BwdSparse P, int2 cut, int nc
     }
 }
 
-// (5d) the deviating trials of the range: a wavefront per trial adds
+// (5d) the deviating trials of the range: a wavefront per trial, or P.segs of
+// them where trials have more events than a wavefront takes in one round, adds
 // v_t - c to W of each hot event of the trial, one integer atomic per
 // (occurrence, row).  Whether an event is hot is asked of its bit in LDS
 // first, the hot events' bitmap folded onto 2^19 bits by OR: a table word per
@@ -801,6 +803,7 @@ __global__ __launch_bounds__(256) void k_bwd_count(BwdSparse P, int2 cut, int nc
 // 1000 took (2M events, 7% hot); with the filter 51 us.
 constexpr int kHotFilter = 1 << 14;   // words, 64 KB: two workgroups on a CU
 constexpr int kSparseThreads = 1024;
+constexpr int kSparseRound = 1024;      // events of a trial in flight
 
 __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bwd_wsparse(BwdSparse P) {
     __shared__ uint32_t filt[kHotFilter];
@@ -809,7 +812,7 @@ __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(
     if (form == kDense) return;   // uniform over the workgroup
     const int64_t ndev = static_cast<int64_t>(P.ndev[j]);
     const int64_t nwalk = ndev + (form == kOneValue ? static_cast<int64_t>(P.nalt[j]) : 0);
-    if (static_cast<int64_t>(blockIdx.x) * (kSparseThreads >> 6) >= nwalk) return;   // uniform: no trial for it
+    if (static_cast<int64_t>(blockIdx.x) * (kSparseThreads >> 6) >= nwalk * P.segs) return;   // uniform: no trial for it
     const OccTables T = load_tables(P.tabs + j);
     const uint4 *bits = reinterpret_cast<const uint4 *>(T.bits);
     const int n4 = P.n_sr * (kSrWords / 4);
@@ -836,8 +839,10 @@ __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(
     const int64_t *q = P.vq + static_cast<size_t>(j) * P.n * P.cs;
     int64_t *Wj = P.W + static_cast<size_t>(j) * P.n_cot * P.catalog;
     const int waves = gridDim.x * (blockDim.x >> 6);
-    for (int64_t i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); i < nwalk; i += waves) {
+    for (int64_t is = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); is < nwalk * P.segs; is += waves) {
         unsigned long long dl[kMaxCot];
+        const int64_t i = is / P.segs;
+        const int seg = static_cast<int>(is - i * P.segs);
         const int32_t u = P.dev[static_cast<size_t>(j) * P.n + (i < ndev ? i : P.n - 1 - (i - ndev))];
 #pragma unroll
         for (int c = 0; c < kMaxCot; ++c)
@@ -846,8 +851,8 @@ __global__ __launch_bounds__(kSparseThreads) __attribute__((amdgpu_waves_per_eu(
                                 : 0ull;
         const int64_t t = P.t0 + u;
         const int64_t a = P.t_off[t], b = P.t_off[t + 1];
-        constexpr int kU = 16;   // events per lane in flight: a 1000-event trial in one round
-        for (int64_t k0 = a; k0 < b; k0 += 64 * kU) {
+        constexpr int kU = kSparseRound / kWave;   // events per lane in flight
+        for (int64_t k0 = a + static_cast<int64_t>(seg) * kSparseRound; k0 < b; k0 += static_cast<int64_t>(P.segs) * kSparseRound) {
             int e[kU];
 #pragma unroll
             for (int v = 0; v < kU; ++v) {
@@ -1300,6 +1305,8 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
     // each: slices of up to 262,144 trials, 2M trials in all
     Q.two = yet->slice_trials <= 8 * 32 * 1024;
     Q.two_bytes = Q.two ? static_cast<int32_t>((yet->slice_trials + 31) / 32 + 1) * 4 : 4;
+    // (2000 x 60,000, three rows, 20 trials walked: 1023 us with one)
+    Q.segs = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(yet->nnz / yet->n_trials / kSparseRound, 1), 1024));
     Q.dev = dev;
     Q.t_cnt = yet->t_cnt;
     Q.t_off = yet->t_off;

@@ -466,3 +466,31 @@ def test_long_lists_cost_no_more_than_the_gather(ara, catalog, power):
     gather = best(0)
     print(f"[gpu-backward] {catalog} events, u^{power}: {auto * 1e6:.0f} us, gather {gather * 1e6:.0f} us", flush=True)
     assert auto < 1.15 * gather
+
+
+@pytest.mark.parametrize("mean", [1000, 2047, 2049, 9000])
+def test_deviating_trials_of_several_wavefronts(ara, mean):
+    """Trials of more events than one wavefront takes in a round, ragged, empty
+    and several times as long among them: W from the trials that deviate is the
+    gather's, bit for bit."""
+    import torch
+    n, catalog = 400, 30_000
+    g = np.random.default_rng(mean)
+    lens = g.integers(0, 2 * mean + 1, size=n)
+    lens[::9] = 0
+    lens[7] = 5 * mean
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    elts = synth.lognormal_elts(3, [4000] * 4, catalog, mu=11.0, sigma=1.5)
+    layers = synth.Layers(np.array([0, 4, 6], np.int32), np.array([0, 1, 2, 3, 1, 2], np.int32),
+                          np.array([[1e4, 5e6, 1e4, 5e11], [0.0, 1e6, 0.0, 1e12]]))
+    w = synth.Workload("long years", synth.Yet(catalog, off, g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)), elts,
+                       layers, 0.9)
+    _, s_pre, sparse, dense = _both_forms(ara, w)
+    _say(f"long years: {n} x {mean}")
+    cot = torch.full((3, 2, n), 1.0 / n, dtype=torch.float64, device="cuda")
+    cot[1] = 0.0
+    cot[:, :, 7] = 0.25
+    cot[2, :, torch.as_tensor(g.choice(n, size=20, replace=False), device="cuda")] = -0.5
+    a, b = sparse(s_pre, cot), dense(s_pre, cot)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
