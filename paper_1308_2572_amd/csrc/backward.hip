@@ -400,10 +400,6 @@ constexpr int kBwdEvThreads = 1024;
 constexpr int kEvPer = 2;                // hot events per thread
 constexpr uint32_t kBwdLongList = 256;   // lists beyond this many entries are added by the whole wavefront
 
-struct __attribute__((packed, aligned(2))) EvEight {
-    uint32_t a[4];
-};
-
 // A barrier for LDS alone: the loads in flight stay in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 

@@ -53,6 +53,12 @@ bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out);
 // not; both give the same integers).
 bool ev_always_backward(const ara_yet *yet);
 
+// Eight entries, from any place on.
+struct __attribute__((packed, aligned(2))) EvEight {
+    uint32_t a[4];
+    __device__ __forceinline__ uint32_t operator[](uint32_t k) const { return (k & 1u) ? a[k >> 1] >> 16 : a[k >> 1] & 0xFFFFu; }
+};
+
 // Whether one of the eight lengths of a sparse header is 15.
 __device__ __forceinline__ bool ev_long(uint32_t nib) {
     uint32_t t = nib & (nib >> 1);

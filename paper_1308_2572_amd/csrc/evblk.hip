@@ -567,6 +567,8 @@ constexpr int kMajorEvents = 256;
 constexpr int kMajorCap = 18432;   // entries of a (slice, 256 events) staged in LDS: 72 KB, two workgroups per CU
 constexpr int kMajorParts = 4;     // threads per event
 constexpr int kMajorBatch = 2;     // blocks whose lists a thread has in flight
+constexpr uint32_t kMajorFar = 24;     // entries from which a list is left to the second loop
+constexpr uint32_t kMajorWide = 256;   // ... and a wavefront takes a list, or a group's, together
 
 struct EvMajor {
     EvBlocks B;
@@ -606,12 +608,17 @@ __global__ __launch_bounds__(256) void k_ev_major_count(EvMajor M) {
     if (gr < M.B.ng - 1) {
 #pragma unroll 4
         for (int b = S.b0; b < S.b1; ++b) {
-            if (block_inside(M, S, b)) {
-                ev_group_counts(M.B, b, gr, c);
-                continue;
-            }
-            // a block the slice cuts: count the group's entries inside it
-            uint32_t s0, s1;
+            if (block_inside(M, S, b)) ev_group_counts(M.B, b, gr, c);
+        }
+    }
+    // the blocks that the slice cuts: the group's entries inside it, counted by
+    // the lane, or by the wavefront where there are many (frequent events:
+    // 185 ms when lanes counted them, frequencies as u^6 over 2M events, 400,000
+    // x 1000)
+    for (int b = S.b0; b < S.b1; ++b) {   // uniform
+        if (block_inside(M, S, b)) continue;
+        uint32_t s0 = 0, s1 = 0;
+        if (gr < M.B.ng - 1) {
             if (M.B.dense) {
                 const uint32_t *p = M.B.start + static_cast<size_t>(b) * (M.B.catalog + 1);
                 s0 = p[8 * gr];
@@ -621,25 +628,54 @@ __global__ __launch_bounds__(256) void k_ev_major_count(EvMajor M) {
                 s0 = p[0].x;
                 s1 = p[1].x;
             }
-            const uint16_t *p = M.B.ent + M.B.base[b];
-            const uint32_t shift = static_cast<uint32_t>(static_cast<int64_t>(b) * M.B.et - S.lo);
-            const uint32_t span = static_cast<uint32_t>(S.hi - S.lo);
-            uint64_t some = 0;   // eight counts of one byte
-            uint32_t n = 0;
-            auto flush = [&]() {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) c[k] += (some >> (8 * k)) & 255u;
-                some = 0;
-                n = 0;
-            };
-#pragma unroll 4
-            for (uint32_t i = s0; i < s1; ++i) {
-                const uint32_t v = p[i];
-                if (shift + (v & kEvTrialMask) < span) some += 1ull << (8 * (v >> kEvTrialBits));
-                if (++n == 255u) flush();
-            }
-            flush();
         }
+        const int64_t base = M.B.base[b];
+        const uint16_t *p = M.B.ent + base;
+        const uint32_t shift = static_cast<uint32_t>(static_cast<int64_t>(b) * M.B.et - S.lo);
+        const uint32_t span = static_cast<uint32_t>(S.hi - S.lo);
+        uint64_t some = 0;   // eight counts of one byte
+        uint32_t n = 0;
+        auto flush = [&](uint64_t (&to)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) to[k] += (some >> (8 * k)) & 255u;
+            some = 0;
+            n = 0;
+        };
+        auto count = [&](uint32_t v) {
+            if (shift + (v & kEvTrialMask) < span) some += 1ull << (8 * (v >> kEvTrialBits));
+        };
+        for (uint64_t big = __ballot(s1 - s0 > kMajorWide); big; big &= big - 1) {
+            const int l = __builtin_ctzll(big);
+            const uint32_t a = __builtin_amdgcn_readlane(s0, l), z = __builtin_amdgcn_readlane(s1, l);
+            uint64_t part[8] = {};
+            const int64_t step = 8 * kWave;
+            int64_t i = static_cast<int64_t>(a) + 8 * (threadIdx.x & 63);
+            EvEight d{}, next{};
+            if (i < z) d = *reinterpret_cast<const EvEight *>(p + i);
+            for (; i < z; i += step) {
+                if (i + step < z) next = *reinterpret_cast<const EvEight *>(p + i + step);
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k)
+                    if (i + k < z) count(d[k]);
+                if ((n += 8u) > 240u) flush(part);
+                d = next;
+            }
+            flush(part);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                for (int o = 32; o > 0; o >>= 1) part[k] += __shfl_xor(part[k], o);
+                if (static_cast<int>(threadIdx.x & 63) == l) c[k] += part[k];
+            }
+            if (static_cast<int>(threadIdx.x & 63) == l) s1 = s0;
+        }
+#pragma unroll 4
+        for (uint32_t i = s0; i < s1; ++i) {
+            count(p[i]);
+            if (++n == 255u) flush(c);
+        }
+        flush(c);
+    }
+    if (gr < M.B.ng - 1) {
         int64_t *off = M.tr_off + static_cast<int64_t>(x) * M.B.catalog + 8 * static_cast<int64_t>(gr);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -744,6 +780,7 @@ __global__ __launch_bounds__(kMajorEvents * kMajorParts) __attribute__((amdgpu_w
     if (total == 0) return;   // uniform
     const bool staged = total <= kMajorCap;   // uniform
     uint32_t *dst = M.tr_ent + s0;
+    bool far = false;   // one of the thread's lists is long
     if (in) {
         for (int b0 = S.b0 + part * kMajorBatch; b0 < S.b1; b0 += kMajorBatch * kMajorParts) {
             uint32_t s[kMajorBatch], n[kMajorBatch];
@@ -787,6 +824,10 @@ __global__ __launch_bounds__(kMajorEvents * kMajorParts) __attribute__((amdgpu_w
                         else dst[at] = t[i];
                         ++at;
                     }
+                if (n[u] > kMajorFar) {
+                    far = true;
+                    continue;
+                }
                 for (uint32_t i = 7; i < n[u]; ++i) {
                     const uint32_t tt = static_cast<uint32_t>(shift) + (M.B.ent[first + i] & kEvTrialMask);
                     if (tt >= span) continue;
@@ -796,6 +837,73 @@ __global__ __launch_bounds__(kMajorEvents * kMajorParts) __attribute__((amdgpu_w
                 }
             }
         }
+    }
+    // The long lists' entries from the eighth on, eight at a time, and by the
+    // wavefront together where there are many (frequent events: 279 ms when each
+    // lane took its own entry by entry, frequencies as u^6 over 2M events, 400,000
+    // x 1000; 10 ms).  The lists are found again, so that the loop above has
+    // nothing more to hold.
+    if (__any(far)) {
+        for (int b0 = S.b0 + part * kMajorBatch; b0 < S.b1; b0 += kMajorBatch * kMajorParts)   // uniform over the wavefront
+            for (int b = b0; b < min(b0 + kMajorBatch, S.b1); ++b) {
+                uint32_t s = 0, n = 0;
+                if (in) ev_list(M.B, b, static_cast<int>(e), s, n);
+                const uint32_t shift = static_cast<uint32_t>(static_cast<int64_t>(b) * M.B.et - S.lo);
+                const uint32_t span = static_cast<uint32_t>(S.hi - S.lo);
+                const uint16_t *ent = M.B.ent + M.B.base[b];
+                // of the entries i .. i + 7 of a list of nl, those in the slice
+                auto inside = [&](const EvEight &d, int64_t i, int64_t nl) {
+                    uint32_t ok = 0;
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; ++k) ok |= i + k < nl && shift + (d[k] & kEvTrialMask) < span ? 1u << k : 0u;
+                    return ok;
+                };
+                auto put = [&](const EvEight &d, uint32_t ok, unsigned long long at) {
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; ++k)
+                        if ((ok >> k) & 1u) {
+                            const uint32_t t = shift + (d[k] & kEvTrialMask);
+                            if (staged) stage[at] = t;
+                            else dst[at] = t;
+                            ++at;
+                        }
+                };
+                for (uint64_t big = __ballot(n > kMajorWide); big; big &= big - 1) {
+                    const int l = __builtin_ctzll(big);
+                    const int64_t nl = __builtin_amdgcn_readlane(n, l);
+                    const uint16_t *p = ent + __builtin_amdgcn_readlane(s, l);
+                    unsigned long long *c = &cur[le - lane + l];
+                    constexpr int64_t kStep = 8 * kWave;
+                    int64_t i = 7 + 8 * lane;
+                    EvEight d{}, next{};
+                    if (i < nl) d = *reinterpret_cast<const EvEight *>(p + i);
+                    for (int64_t i0 = 7; i0 < nl; i0 += kStep, i += kStep) {   // uniform
+                        if (i + kStep < nl) next = *reinterpret_cast<const EvEight *>(p + i + kStep);
+                        const uint32_t ok = inside(d, i, nl);
+                        uint32_t incl = static_cast<uint32_t>(__popc(ok));
+                        for (int o = 1; o < kWave; o <<= 1) {
+                            const uint32_t x2 = __shfl_up(incl, o);
+                            if (lane >= o) incl += x2;
+                        }
+                        const uint32_t all = __builtin_amdgcn_readlane(incl, kWave - 1);
+                        unsigned long long at = 0;
+                        if (lane == 0 && all) at = atomicAdd(c, static_cast<unsigned long long>(all));
+                        put(d, ok, __shfl(at, 0) + incl - static_cast<uint32_t>(__popc(ok)));
+                        d = next;
+                    }
+                    if (lane == l) n = 0;
+                }
+                if (n > kMajorFar) {
+                    const uint16_t *p = ent + s;
+                    EvEight d = *reinterpret_cast<const EvEight *>(p + 7), next{};
+                    for (uint32_t i = 7; i < n; i += 8) {
+                        if (i + 8 < n) next = *reinterpret_cast<const EvEight *>(p + i + 8);
+                        const uint32_t ok = inside(d, i, n);
+                        if (ok) put(d, ok, atomicAdd(&cur[le], static_cast<unsigned long long>(__popc(ok))));
+                        d = next;
+                    }
+                }
+            }
     }
     if (!staged) return;
     __syncthreads();

@@ -323,3 +323,50 @@ def test_scratch_is_free_after_the_call(ara, flags):
         sigma = ara.SigmaTables.from_numpy(tables, synth.record_sigmas(1, w.elts))
         s = [ara.ylt_forward_su(tables, sigma, y, layers, et, lt, 9, check=True) for y in yets]
         assert all(torch.equal(a, b) for a, b in zip(*s))
+
+
+@pytest.mark.parametrize("n,mean,catalog,freq", [
+    (9000, 60, 30_000, [7, 8, 9, 126, 127, 128, 129, 130, 135, 136, 137, 519, 520, 521, 5000, 60_000]),   # blocks the slices cut
+    (70_000, 10, 3_000, [200, 40_000, 200_000]),          # blocks inside slices too
+    (500, 300, 12, []),                                    # nothing but long lists, one block in eight slices
+    (40, 3000, 70, [20_000]),
+])
+def test_event_major_lists_of_frequent_events(ara, n, mean, catalog, freq):
+    """Lists, and groups of eight events' entries, around and far beyond those
+    that a wavefront takes together."""
+    g = np.random.default_rng(catalog)
+    lens = g.poisson(mean, size=n)
+    lens[::17] = 0
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    at = g.permutation(len(ids))[:sum(freq)]
+    ids[at] = np.repeat(g.choice(catalog, size=len(freq), replace=False), freq) if freq else 0
+    check(ara, synth.Yet(catalog, off, ids))
+
+
+@pytest.mark.parametrize("n,per,catalog,power", [(100_000, 500, 500_000, 6.0), (100_000, 500, 500_000, 3.0), (100_000, 500, 200, 1.0)])
+def test_frequent_events_are_laid_out_in_time(ara, n, per, catalog, power):
+    """The event-major copy of events of very unequal frequency, and of a small
+    catalogue, in at most fifteen times the time of a YET as large with uniform
+    frequencies over 500,000 events: one CU lays the most frequent event's lists
+    of a slice out, a lane took over a hundred times as long."""
+    import time
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda") * per
+    u = torch.rand(n * per, generator=g, device="cuda", dtype=torch.float64)
+    times = []
+    for c, p in ((500_000, 1.0), (catalog, power)):
+        ids = (u ** p * c).to(torch.int32).clamp_(0, c - 1)
+        t = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            ara.PreparedYet(off, ids, c)
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        times.append(min(t))
+    _say(f"{n} x {per} over {catalog}, u^{power}: {times[1] * 1e3:.2f} ms, uniform over 500,000 {times[0] * 1e3:.2f} ms")
+    assert times[1] < 15.0 * times[0]
