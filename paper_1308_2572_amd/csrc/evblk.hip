@@ -244,7 +244,33 @@ __global__ __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(POS 
     }
 }
 
+// Where a block has many chunks and tiles (few blocks, long trials): their sums
+// beforehand, over shares of the block's chunks, into tbase, which is zero.
+constexpr int kTileShare = 256;   // chunks of a workgroup
+
+__global__ __launch_bounds__(256) void k_ev_tile_zero(EvBuild B) {
+    const size_t n = static_cast<size_t>(B.g.neb) * (B.g.n_tiles + 1);
+    for (size_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += static_cast<size_t>(gridDim.x) * 256) B.tbase[i] = 0u;
+}
+
+__global__ __launch_bounds__(256) void k_ev_tile_sums(EvBuild B) {
+    if (ev_failed(B.misc)) return;
+    const int b = blockIdx.z, t = blockIdx.x * 256 + threadIdx.x, nt = B.g.n_tiles;
+    const int64_t end = ev_chunk0(B.base, b + 1);
+    if (t >= nt) return;
+    uint32_t v = 0;
+    for (int64_t c0 = ev_chunk0(B.base, b) + static_cast<int64_t>(blockIdx.y) * kTileShare; c0 < end;
+         c0 += static_cast<int64_t>(gridDim.y) * kTileShare) {
+        const uint16_t *p = B.tstart + c0 * (nt + 1) + t;
+        const int64_t c1 = min(end, c0 + kTileShare);
+#pragma unroll 8
+        for (int64_t c = c0; c < c1; ++c, p += nt + 1) v += static_cast<uint32_t>(p[1]) - static_cast<uint32_t>(p[0]);
+    }
+    if (v) atomicAdd(&B.tbase[static_cast<size_t>(b) * (nt + 1) + t], v);
+}
+
 // Each block's first entry of every tile (relative to the block).
+template <bool SUMS>
 __global__ __launch_bounds__(1024) void k_ev_tiles(EvBuild B) {
     __shared__ uint32_t wsum[16];
     if (ev_failed(B.misc)) return;
@@ -255,7 +281,9 @@ __global__ __launch_bounds__(1024) void k_ev_tiles(EvBuild B) {
     for (int t0 = 0; t0 < nt; t0 += 1024) {
         const int t = t0 + tid;
         uint32_t v = 0;
-        if (t < nt) {
+        if (SUMS) {
+            if (t < nt) v = B.tbase[static_cast<size_t>(b) * (nt + 1) + t];
+        } else if (t < nt) {
             const uint16_t *p = B.tstart + c0 * (nt + 1) + t;
 #pragma unroll 8
             for (int64_t c = c0; c < c1; ++c, p += nt + 1) v += static_cast<uint32_t>(p[1]) - static_cast<uint32_t>(p[0]);
@@ -495,7 +523,17 @@ int32_t ev_build(const EvBuild &B, hipStream_t st) {
     k_ev_marks<<<gm, 256, 0, st>>>(B);
     if (B.pos) k_ev_part<true><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
     else k_ev_part<false><<<static_cast<unsigned>(B.g.n_chunks), kEvThreads, 0, st>>>(B);
-    k_ev_tiles<<<static_cast<unsigned>(B.g.neb), 1024, 0, st>>>(B);
+    // (2000 x 60,000, one block of 7324 chunks and 7813 tiles: 4.6 ms by itself)
+    const int64_t per_block = B.nnz / kEvChunk / B.g.neb + 2;   // chunks
+    const int64_t steps = per_block * ((B.g.n_tiles + 1023) / 1024);   // of one workgroup in k_ev_tiles, 0.6 us for eight
+    if (steps > 2048 && B.g.neb <= 65535) {
+        const unsigned shares = static_cast<unsigned>(std::min<int64_t>((per_block + kTileShare - 1) / kTileShare, 1024));
+        k_ev_tile_zero<<<1024, 256, 0, st>>>(B);
+        k_ev_tile_sums<<<dim3(static_cast<unsigned>((B.g.n_tiles + 255) / 256), shares, static_cast<unsigned>(B.g.neb)), 256, 0, st>>>(B);
+        k_ev_tiles<true><<<static_cast<unsigned>(B.g.neb), 1024, 0, st>>>(B);
+    } else {
+        k_ev_tiles<false><<<static_cast<unsigned>(B.g.neb), 1024, 0, st>>>(B);
+    }
     const size_t lds = sort_lds(B.g.te_bits, B.pos != nullptr);
     const auto sort = B.pos ? k_ev_sort<true> : k_ev_sort<false>;
     ARA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sort), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -370,3 +370,28 @@ def test_frequent_events_are_laid_out_in_time(ara, n, per, catalog, power):
         times.append(min(t))
     _say(f"{n} x {per} over {catalog}, u^{power}: {times[1] * 1e3:.2f} ms, uniform over 500,000 {times[0] * 1e3:.2f} ms")
     assert times[1] < 15.0 * times[0]
+
+
+@pytest.mark.parametrize("n,mean,catalog", [(30, 1_500_000, 300_000), (9000, 9000, 40_000)])
+def test_blocks_of_many_chunks_and_tiles(ara, n, mean, catalog):
+    """Thousands of chunks of a block, over thousands of tiles: their sums are
+    made by several workgroups.  The blocks through the year losses."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    lens = torch.randint(0, 2 * mean + 1, (n,), generator=g, device="cuda")
+    off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=off[1:])
+    ids = torch.randint(0, catalog, (int(off[-1]),), generator=g, dtype=torch.int32, device="cuda")
+    rec = torch.randperm(catalog, generator=g, device="cuda", dtype=torch.int32)[:catalog // 3].contiguous()
+    loss = torch.randint(1, 1000, (rec.numel(),), generator=g, device="cuda").float()   # whole numbers: exact sums
+    _say(f"{n} x {mean} over {catalog}: {ids.numel()} occurrences")
+    yet = ara.PreparedYet(off, ids, catalog, transposed=False)
+    yet.handle.reserved |= 0x200   # the forward takes the blocks
+    tables = ara.EltTables(torch.tensor([0, rec.numel()], device="cuda"), rec, loss, catalog)
+    terms = [torch.tensor([x], dtype=torch.float64, device="cuda") for x in ([1.0, 0.0, np.inf], [0.0, np.inf, 0.0, np.inf])]
+    y, _, _ = ara.ylt_forward(tables, yet, ara.Layers([0, 1], [0]), *terms, check=True)
+    by_event = torch.zeros(catalog, dtype=torch.float64, device="cuda")
+    by_event[rec.long()] = loss.double()
+    want = torch.segment_reduce(by_event[ids.long()], "sum", offsets=off, initial=0.0)
+    assert torch.equal(y[0], want)
