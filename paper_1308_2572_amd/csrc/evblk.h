@@ -52,6 +52,8 @@ bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out);
 // them whatever its rule says (tests compare the ways at sizes where it would
 // not; both give the same integers).
 bool ev_always_backward(const ara_yet *yet);
+// The same for secondary uncertainty, of the YET's rule and of the layers'.
+bool ev_always_uncertain(const ara_yet *yet);
 
 // Eight entries, from any place on.
 struct __attribute__((packed, aligned(2))) EvEight {

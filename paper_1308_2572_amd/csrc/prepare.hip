@@ -684,6 +684,8 @@ constexpr int32_t kHasEvBlocks = 0x100;
 // ... and one whose binary64 forward takes them.
 constexpr int32_t kEvForward = 0x200;
 constexpr int32_t kEvAlwaysBackward = 0x400;   // (ev_always_backward)
+constexpr int32_t kEvAlwaysUncertain = 0x800;  // (ev_always_uncertain)
+constexpr int32_t kEvMarks = kEvForward | kEvAlwaysBackward | kEvAlwaysUncertain;
 
 // Whether the forward of a YET takes its event-ordered blocks.  It depends on
 // the YET alone, so that a layer's results are the same in every call.  The
@@ -712,8 +714,10 @@ bool ev_forward_blocks(const ara_yet *yet, EvBlocks *out) { return (yet->reserve
 
 bool ev_always_backward(const ara_yet *yet) { return (yet->reserved & kEvAlwaysBackward) != 0; }
 
+bool ev_always_uncertain(const ara_yet *yet) { return (yet->reserved & kEvAlwaysUncertain) != 0; }
+
 bool ev_blocks(const ara_yet *yet, EvBlocks *out) {
-    if ((yet->reserved & ~static_cast<int32_t>(kPrepFlags | kEvForward | kEvAlwaysBackward)) != kHasEvBlocks || yet->n_blocks == 0) return false;
+    if ((yet->reserved & ~(static_cast<int32_t>(kPrepFlags) | kEvMarks)) != kHasEvBlocks || yet->n_blocks == 0) return false;
     const uint32_t flags = static_cast<uint32_t>(yet->reserved) & kPrepFlags;
     Geometry g{};
     g.tg = yet->trials_per_group;

@@ -138,12 +138,12 @@ __device__ T block_exclusive_scan(const T *in, T *out, int n, T *wsum) {
 // order.  No draw lies below exp(m - kZMost s), so where that, scaled, and
 // every ELT limit is at least 2^(e - 41) no loss has a bit below 2^(e - 94):
 // the sums are exact, and the total is rounded once.  gexp is e - 46; mode 0:
-// some layer's terms or draws do not fit this (no finite limit, for one), and
-// the stream of the codes serves it.
+// some layer's terms or draws do not fit this (no finite limit, for one), or
+// su_streams puts it so, and the stream of the codes serves it.
 struct SuBound {
     double most;      // B
     uint32_t least;   // bitwise complement of the smallest of these draws and limits, binary32, rounded down
-    uint32_t pad;
+    uint32_t stream;  // the layer takes the stream
 };
 // Largest |z| of a draw: sqrt(-2 ln u), u >= 2^-53, is 8.572.
 constexpr double kZMost = 8.58;
@@ -155,7 +155,7 @@ __device__ __forceinline__ uint32_t su_least(double v) { return ~__float_as_uint
 
 __device__ __forceinline__ EvLayer su_form(const SuBound &b) {
     EvLayer f{};
-    if (!(b.most >= 0.0) || !(b.most < 0x1p900)) return f;
+    if (b.stream || !(b.most >= 0.0) || !(b.most < 0x1p900)) return f;
     int e = 0;
     frexp(b.most, &e);
     f.gexp = e - 46;
@@ -960,6 +960,40 @@ struct SuLayout {
     uint64_t n_ent = 0;
 };
 
+// Whether secondary uncertainty over a YET takes its event-ordered blocks.  It
+// depends on the YET alone, and su_streams on the layer's records, so that a
+// layer's results are the same in every call.  Every event is drawn for by the
+// lanes that own it, so the blocks lose to the stream (us of one layer of 10
+// ELTs, 5% to 15% of the catalogue; blocks, stream):
+//   * where single lists are long: 100,000 x 500 over 500,000 events, the
+//     longest list of a block on average 42 entries 259, 294, 157 entries 308,
+//     291, 621 entries 376, 293, 5451 entries 617, 293; uniform events of 71
+//     entries a list (50,000 x 500 over 50,000, four layers) 281, 329, of 357
+//     663, 309;
+//   * over a few ranges, with few occurrences, where the stream is short: 5000
+//     x 500 over 200,000 events 1.03 to 1.15 of the stream's time, over 500,000
+//     0.76 to 0.88; 50,000 x 500 over 100,000 1.08 to 1.19, over 200,000 0.85
+//     to 0.94; 200,000 x 500 over 50,000 0.94 to 0.97;
+//   * for many short years, walked for a few entries a block: 5M x 20 over
+//     300,000 events (0.54 a list) 573, 480, 2M x 10 over 2M (0.04) 511, 483;
+//     with no more blocks than run at once they win (1M x 20 over 2M 353, 481).
+static bool su_blocks_pay(const EvBlocks &B, const ara_yet *yet) {
+    const double nnz = static_cast<double>(yet->nnz), C = static_cast<double>(yet->catalog);
+    if (static_cast<double>(yet->max_occ) > 100.0 * B.neb) return false;
+    if (C < 400e3 && nnz * C < 4e12) return false;
+    return B.neb <= 150 || nnz >= 0.85 * C * B.neb;
+}
+
+// Whether a layer of `records` ELT records is streamed all the same.  Of dense
+// layers the stream's queue keeps every lane drawing, the blocks' lanes wait
+// for the longest of their lists: records of 0.15 of the catalogue 290 us
+// against the stream's 345, of 0.6 875 against 798, of 5 1475 against 1109
+// (200,000 x 500, 200,000 x 500 and 50,000 x 300 over 200,000 events), over
+// 500,000 events 321 against 404 and 895 against 846.
+static bool su_streams(uint64_t records, int32_t catalog) {
+    return static_cast<double>(records) > 0.4 * static_cast<double>(catalog);
+}
+
 static int32_t su_layout(const ara_tables *tables, const ara_layers *layers, const int64_t *elt_records, SuLayout &S) {
     S.z = occ_sizes(tables->catalog, true);
     const int L = layers->n_layers;
@@ -1102,6 +1136,18 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     uint32_t *obase = c.take<uint32_t>(static_cast<size_t>(L) * n_sr);
     SuEntry *ent = c.take<SuEntry>(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)));
     int32_t *uev = c.take<int32_t>(static_cast<size_t>(std::max<uint64_t>(S.n_ent, 1)));
+    // which layers take the event-ordered blocks, if their terms fit (su_form)
+    SuEvParams Q{};
+    bool ev = ev_blocks(yet, &Q.B) && Q.B.pos && Q.B.et >= 1 && Q.B.et <= kEvMaxTrials;
+    std::vector<SuBound> how(static_cast<size_t>(L), SuBound{});
+    if (ev && !ev_always_uncertain(yet)) {
+        ev = false;
+        const bool pays = su_blocks_pay(Q.B, yet);
+        for (int j = 0; j < L; ++j) {
+            how[j].stream = !pays || su_streams(S.cap[j], tables->catalog);
+            ev = ev || !how[j].stream;
+        }
+    }
     HeadImage img(ws);
     img.cover(d_err + kWsHeaderBytes / sizeof(int32_t));
     img.put(d_off, layers->elt_off, static_cast<size_t>(L + 1));
@@ -1109,7 +1155,7 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     img.put(d_tabs, tabs.data(), tabs.size());
     img.put(d_cap, S.cap.data(), S.cap.size());
     img.put(d_region, S.region.data(), S.region.size());
-    img.cover(bound + L);
+    img.put(bound, how.data(), how.size());
     if ((rc = img.send(st))) return rc;
 
     {
@@ -1166,8 +1212,6 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
     P.s_pre = s_pre;
     const int64_t groups = L == 1 ? P.nb : static_cast<int64_t>(kXcds) * ((P.nb + kXcds - 1) / kXcds) * L;
     if (groups > 0x7FFFFFFF) return fail(ARA_E_LIMIT, "too many workgroups");
-    SuEvParams Q{};
-    const bool ev = ev_blocks(yet, &Q.B) && Q.B.pos && Q.B.et >= 1 && Q.B.et <= kEvMaxTrials;
     if (ev) P.bound = bound;
     ProfScope prof(ARA_PROF_SU, st);
     if (ev) {
