@@ -217,10 +217,14 @@ __global__ __launch_bounds__(kSuThreads) void k_su_base(const OccTables *__restr
 // losses), so what counts is the rounds of workgroups: with one event of the
 // catalogue per thread, where 14% are in the union, 2M events took 1953
 // workgroups in four rounds, 55 us; these are 489 in one, 26 us.
+// Where most events are in the union, or small chunks fit one round anyway,
+// chunks of 1024 have a thread for every event: 200,000 events, all of them in
+// the union with 5 ELTs each, 28 us against 71 in chunks of 4096.
 constexpr int kSuFillWords = 128;                  // 4096 events per workgroup
-constexpr int kSuFillChunks = kSrWords / kSuFillWords;
+constexpr int kSuFillFew = kSuThreads / 32;        // 1024
 constexpr int kSuFillBatch = 8;                    // ELTs whose loads are in flight together
 
+template <int WORDS>
 __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict__ loss, const float *__restrict__ sigma,
                                                         const uint32_t *__restrict__ present, int32_t catalog,
                                                         int32_t words, const int32_t *__restrict__ elt_off,
@@ -233,25 +237,25 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
                                                         const uint64_t *__restrict__ eregion,
                                                         SuEntry *__restrict__ ent, int32_t *__restrict__ uev) {
     __shared__ int32_t lk[kSuMaxJ];
-    __shared__ uint2 lw[kSuFillWords];               // the chunk's bitmap words with ranks
-    __shared__ uint16_t lev[kSuFillWords * 32];      // its union events
+    __shared__ uint2 lw[WORDS];               // the chunk's bitmap words with ranks
+    __shared__ uint16_t lev[WORDS * 32];      // its union events
     __shared__ uint32_t n_ev;
-    const int s = blockIdx.x / kSuFillChunks, p = blockIdx.x % kSuFillChunks, j = blockIdx.y;
+    const int s = blockIdx.x / (kSrWords / WORDS), p = blockIdx.x % (kSrWords / WORDS), j = blockIdx.y;
     const int tid = threadIdx.x;
     const OccTables T = load_tables(tabs + j);
-    if (tid < kSuFillWords) lw[tid] = T.br[static_cast<size_t>(s) * kSrWords + p * kSuFillWords + tid];
+    if (tid < WORDS) lw[tid] = T.br[static_cast<size_t>(s) * kSrWords + p * WORDS + tid];
     const int a = elt_off[j], J = elt_off[j + 1] - a;
     for (int q = tid; q < J; q += blockDim.x) lk[q] = elt_ids[a + q];
     __syncthreads();
     {
         const uint32_t rank0 = lw[0].y;
 #pragma unroll
-        for (int it = 0; it < kSuFillWords * 32 / kSuThreads; ++it) {
+        for (int it = 0; it < WORDS * 32 / kSuThreads; ++it) {
             const int local = it * kSuThreads + tid, bit = local & 31;
             const uint2 q2 = lw[local >> 5];
             if ((q2.x >> bit) & 1u) lev[q2.y - rank0 + __popc(q2.x & ((1u << bit) - 1u))] = static_cast<uint16_t>(local);
         }
-        if (tid == 0) n_ev = lw[kSuFillWords - 1].y - rank0 + __popc(lw[kSuFillWords - 1].x);
+        if (tid == 0) n_ev = lw[WORDS - 1].y - rank0 + __popc(lw[WORDS - 1].x);
     }
     __syncthreads();
     const uint64_t cap = ecap[j];
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(kSuThreads) void k_su_fill(const float *__restrict_
     const uint32_t *oo = ooff + (static_cast<size_t>(j) * n_sr + s) * kSr;
     const uint32_t r0 = lw[0].y, nev = n_ev;
     for (uint32_t i = tid; i < nev; i += kSuThreads) {
-        const int local = p * (kSuFillWords * 32) + lev[i];   // event within the super-range
+        const int local = p * (WORDS * 32) + lev[i];   // event within the super-range
         const int64_t ev = static_cast<int64_t>(s) * kSr + local;
         const uint32_t r = r0 + i;
         const uint32_t nb = T.cnt[static_cast<size_t>(s) * kSr + r];
@@ -327,6 +331,7 @@ __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ 
     if (used > cap) return;   // nothing laid out (flagged by k_su_base)
     SuEntry *E = ent + eregion[j];
     uint32_t low = 0;
+    const bool streamed = bound[j].stream != 0u;
     for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < used;
          i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
         SuEntry &e = E[i];
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(256) void k_su_params(const uint64_t *__restrict__ 
         const double s2 = log1p(rr * rr);
         e.m = log(mu) - 0.5 * s2;
         e.s = sqrt(s2);
-        low = max(low, su_least(scale * exp(e.m - kZMost * e.s)));
+        if (!streamed) low = max(low, su_least(scale * exp(e.m - kZMost * e.s)));
     }
     for (int o = 32; o > 0; o >>= 1) low = max(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), o)));
     __shared__ uint32_t most;   // one atomic per workgroup, and few of those: most workgroups' is no news
@@ -1167,9 +1172,14 @@ extern "C" int32_t ara_ylt_forward_su(const ara_tables *tables, const float *sig
                                                                                                     ooff, otot);
         k_su_base<<<static_cast<unsigned>(L), kSuThreads, 0, st>>>(d_tabs, otot, n_sr, d_cap, ubase, obase, d_used,
                                                                   d_err, d_off, d_ids, elt_terms, layer_terms, bound);
-        k_su_fill<<<dim3(static_cast<unsigned>(n_sr * kSuFillChunks), static_cast<unsigned>(L)), kSuThreads, 0, st>>>(
-            tables->loss, sigma, tables->present, tables->catalog, tables->words, d_off, d_ids, d_tabs, n_sr, ooff,
-            ubase, obase, d_cap, d_region, ent, uev);
+        const int64_t few_chunks = static_cast<int64_t>(n_sr) * (kSrWords / kSuFillFew) * L;
+        const bool few = few_chunks <= 2 * device_cu_count() ||
+                         static_cast<double>(S.n_ent) > 0.5 * static_cast<double>(tables->catalog) * L;
+        const int chunks = n_sr * (kSrWords / (few ? kSuFillFew : kSuFillWords));
+        (few ? k_su_fill<kSuFillFew> : k_su_fill<kSuFillWords>)
+            <<<dim3(static_cast<unsigned>(chunks), static_cast<unsigned>(L)), kSuThreads, 0, st>>>(
+                tables->loss, sigma, tables->present, tables->catalog, tables->words, d_off, d_ids, d_tabs, n_sr, ooff,
+                ubase, obase, d_cap, d_region, ent, uev);
         const uint64_t most = *std::max_element(S.cap.begin(), S.cap.end());
         const unsigned px = static_cast<unsigned>(std::max<uint64_t>(1, std::min<uint64_t>((most + 255) / 256, 1024)));
         k_su_params<<<dim3(px, static_cast<unsigned>(L)), 256, 0, st>>>(d_region, d_cap, d_used, ent, elt_terms, bound);
