@@ -18,12 +18,12 @@
 
 namespace ara {
 
-template <bool HITS, bool F32, bool SHARED>
+template <bool HITS, bool F32, bool SHARED, bool FEW>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd(FwdParams P) {
     __shared__ __align__(16) unsigned char smem[kLdsBytes];
     const FwdItem I = fwd_item(P, blockIdx.x);
     if (I.block < 0) return;   // uniform over the workgroup, before any barrier
-    fwd_block<HITS, F32, SHARED>(P, I, smem);
+    fwd_block<HITS, F32, SHARED, FEW>(P, I, smem);
 }
 
 // LDS of one forward workgroup: the per-trial totals (and hit counts), the
@@ -64,6 +64,19 @@ int32_t fwd_params(const ara_yet *yet, bool hits, bool f32, FwdParams &P) {
     return fwd_lds_plan(P.tb, P.n_ranges, hits, f32, &P.buf_bytes, &P.capv);
 }
 
+// Whether binary32 totals are streamed four codes a lane and chunk instead of
+// eight.  A wavefront's run in one range is padded to four codes a lane, so
+// that of a run of four or of twelve a chunk of eight is half skip codes; one
+// of eight is a chunk of eight.  A whole call over 2M events, 15 ELTs of 20k, us
+// of four codes and of eight by the mean run: 4.0 (100,000 x 1000) 200, 233;
+// 7.5 (3M x 20) 345, 324; 7.9 (3M x 50) 355, 333; 9.6 (250,000 x 1000) 304,
+// 324; 11.9 329, 359; 20 508, 529; 32 767, 778.
+static bool fwd_few(const ara_yet *yet) {
+    const double lanes = static_cast<double>(yet->n_blocks) * yet->n_ranges * kGroups * 64;
+    const double run = static_cast<double>(yet->n_codes) / lanes;
+    return run < 7.0 || run > 8.0;
+}
+
 int32_t launch_forward(const ara_yet *yet, int n_sr, bool hits, bool f32, const FwdItem *d_items, int n_items,
                        hipStream_t st, const FwdRegular *reg, bool shared) {
     (void)n_sr;
@@ -85,17 +98,18 @@ int32_t launch_forward(const ara_yet *yet, int n_sr, bool hits, bool f32, const 
         P.reg_nl = reg->nl;
         shared = reg->nl > 1;
     }
-#define ARA_FWD_LAUNCH(H, F)                                                   \
+#define ARA_FWD_LAUNCH(H, F, FEW)                                              \
     do {                                                                     \
-        if (shared) k_fwd<H, F, true><<<n_items, 1024, 0, st>>>(P);          \
-        else k_fwd<H, F, false><<<n_items, 1024, 0, st>>>(P);                \
+        if (shared) k_fwd<H, F, true, FEW><<<n_items, 1024, 0, st>>>(P);     \
+        else k_fwd<H, F, false, FEW><<<n_items, 1024, 0, st>>>(P);           \
     } while (0)
     if (f32) {
-        if (hits) ARA_FWD_LAUNCH(true, true);
-        else ARA_FWD_LAUNCH(false, true);
+        if (hits) ARA_FWD_LAUNCH(true, true, false);
+        else if (fwd_few(yet)) ARA_FWD_LAUNCH(false, true, true);
+        else ARA_FWD_LAUNCH(false, true, false);
     } else {
-        if (hits) ARA_FWD_LAUNCH(true, false);
-        else ARA_FWD_LAUNCH(false, false);
+        if (hits) ARA_FWD_LAUNCH(true, false, false);
+        else ARA_FWD_LAUNCH(false, false, false);
     }
 #undef ARA_FWD_LAUNCH
     ARA_HIP(hipGetLastError());

@@ -122,21 +122,15 @@ struct RangeInfo {
 // accumulated in binary32 (the aggregate terms are still applied in
 // binary64); otherwise both are binary64.
 // SHARED: several workgroups of the launch stream the same block's codes.
-// FEW: four codes a chunk at any rate, for a caller that loops over blocks
-// (with eight the loop's registers would be spilled; the additions are made in
-// the same order).
+// FEW: four codes a lane and chunk (the additions are made in the same order).
+// For a caller that loops over blocks, whose registers would be spilled with
+// eight, and for binary32 totals as forward.hip's rule has it.
 template <bool HITS, bool F32, bool SHARED, bool FEW = false>
 __device__ __forceinline__ void fwd_block(const FwdParams &P, const FwdItem &I, unsigned char *smem) {
     using V = typename std::conditional<F32, float, double>::type;
-    // Codes per lane and chunk: half as many with hit counts, whose extra
-    // per-code state would not fit the registers of eight codes; and with
-    // binary32 totals.  A wavefront's run in one range is padded to four codes
-    // a lane, and up to some 200k years of 1000 occurrences it is little
-    // longer than that, so that half of a chunk of eight was skip codes.  Over
-    // 2M events, 15 ELTs of 20k, a whole call, eight codes against four: 100k
-    // years 209 us, 177; 300k 336, 306; 800k 646, 621; at runs of just eight
-    // (200k) 243, 244.
-    constexpr int kUn = HITS || F32 || FEW ? kUnroll / 2 : kUnroll;
+    // codes per lane and chunk: half as many with hit counts, whose extra
+    // per-code state would not fit the registers of eight codes
+    constexpr int kUn = HITS || FEW ? kUnroll / 2 : kUnroll;
     constexpr uint32_t kV = sizeof(V);             // bytes per value and per trial total
     constexpr int kVSh = F32 ? 2 : 3;              // log2(kV)
     constexpr uint32_t kVPer16 = 16 / kV;          // values per 16-byte copy

@@ -166,3 +166,25 @@ def test_config1_full_size_sampled(ara):
     m32, _ = ara.metrics(torch.tensor(y, device="cuda"), w.p)
     m64, _ = ara.metrics(torch.tensor(y64, device="cuda"), w.p)
     assert np.all(np.abs(m32.cpu().numpy() - m64.cpu().numpy()) <= TOL32 * s64.max())
+
+
+@pytest.mark.parametrize("mean,lo,hi", [(40, 4.0, 5.0), (95, 7.0, 8.0), (140, 11.0, 12.0)])
+@pytest.mark.parametrize("n_layers", [1, 3])
+def test_runs_of_four_eight_and_twelve_codes(ara, mean, lo, hi, n_layers):
+    """Mean runs of a lane in a range on either side of one chunk of eight."""
+    g = np.random.default_rng(mean)
+    catalog, n = 3 << 15, 100_000
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(g.poisson(mean, size=n), out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    elts = synth.lognormal_elts(mean, [3000, 5000, 9000], catalog, mu=11.0, sigma=1.5)
+    lists = [[0, 1, 2], [1], [2, 0]][:n_layers]
+    elt_off = np.cumsum([0] + [len(x) for x in lists]).astype(np.int32)
+    layers = synth.Layers(elt_off, np.concatenate(lists).astype(np.int32), np.tile([1e4, 5e6, 1e4, 5e8], (n_layers, 1)))
+    e = Engine(ara, synth.Workload("runs", synth.Yet(catalog, off, ids), elts, layers, 0.9))
+    h = e.yet.handle
+    run = h.n_codes / (h.n_blocks * h.n_ranges * h.groups * 64)
+    _say(f"runs of {run:.2f} codes, {n_layers} layers")
+    assert lo - 0.1 <= run <= hi
+    y, s, _ = e.forward()
+    assert_close32(y, s, oracle_ref(e.w, threads=8))
