@@ -480,8 +480,10 @@ __global__ __launch_bounds__(1024) void k_scan_top(int64_t *__restrict__ bsum, i
     if (threadIdx.x == 0) *total = run;
 }
 
+// bsum null: one block alone, and *total gets the sum.
 __global__ __launch_bounds__(1024) void k_scan_bases(const int32_t *__restrict__ seg_run, int64_t n,
-                                                     const int64_t *__restrict__ bsum, int64_t *__restrict__ seg_base) {
+                                                     const int64_t *__restrict__ bsum, int64_t *__restrict__ seg_base,
+                                                     int64_t *__restrict__ total) {
     __shared__ int64_t wsum[16];
     int64_t c[kScanPer], v = 0, tot = 0;
     const int64_t i0 = blockIdx.x * static_cast<int64_t>(kScanBlock) + threadIdx.x * kScanPer;
@@ -489,7 +491,9 @@ __global__ __launch_bounds__(1024) void k_scan_bases(const int32_t *__restrict__
         c[q] = i0 + q < n ? static_cast<int64_t>(seg_run[i0 + q]) * kWave : 0;
         v += c[q];
     }
-    int64_t at = bsum[blockIdx.x] + scan1024_i64(v, wsum, &tot);
+    int64_t at = scan1024_i64(v, wsum, &tot);
+    if (bsum) at += bsum[blockIdx.x];
+    else if (threadIdx.x == 0) *total = tot;
     for (int q = 0; q < kScanPer; ++q) {
         if (i0 + q < n) seg_base[i0 + q] = at;
         at += c[q];
@@ -864,9 +868,12 @@ static int32_t prepare(const char *what, const int64_t *offsets, const int32_t *
     const int64_t n_segs = static_cast<int64_t>(g.nseg);
     k_prep_sizes<<<static_cast<unsigned>((n_segs + 255) / 256), 256, 0, st>>>(P, n_groups, p.seg_run);
     const int64_t n_scan = (n_segs + kScanBlock - 1) / kScanBlock;
-    k_scan_sums<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, p.bsum);
-    k_scan_top<<<1, 1024, 0, st>>>(p.bsum, n_scan, p.misc + kMiscCodes);
-    k_scan_bases<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, p.bsum, p.seg_base);
+    if (n_scan > 1) {
+        k_scan_sums<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, p.bsum);
+        k_scan_top<<<1, 1024, 0, st>>>(p.bsum, n_scan, p.misc + kMiscCodes);
+    }
+    k_scan_bases<<<static_cast<unsigned>(n_scan), 1024, 0, st>>>(p.seg_run, n_segs, n_scan > 1 ? p.bsum : nullptr, p.seg_base,
+                                                                p.misc + kMiscCodes);
     ARA_HIP(hipGetLastError());
     int64_t head[8] = {};
     ARA_HIP(hipMemcpyAsync(head, p.misc, sizeof(head), hipMemcpyDeviceToHost, st));
