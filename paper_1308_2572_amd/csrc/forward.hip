@@ -269,7 +269,6 @@ int32_t forward_run(const ara_tables *tables, const ara_yet *yet, const ara_laye
     }
     ProfScope prof(ARA_PROF_FWD, st);
     if (ev) {
-        reg.ev_et = B.et;
         reg.ev_b0 = static_cast<int32_t>(trial_begin / B.et);
         reg.ev_nb = static_cast<int32_t>((trial_end + B.et - 1) / B.et) - reg.ev_b0;
         const size_t slot = ev_slot_bytes(B.et, want_hits);

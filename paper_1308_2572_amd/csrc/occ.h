@@ -188,7 +188,7 @@ struct FwdRegular {
     // the event-ordered forward: its blocks, the workgroups each (layer, block)
     // is split over, and the partial totals' room (parts > 1)
     unsigned char *partial;
-    int32_t parts, ev_b0, ev_nb, ev_et;
+    int32_t parts, ev_b0, ev_nb;
     // ... or, with sweep > 0 and uneven layers, the workgroups of each block, and
     // room for the table that deals them to the layers ([sweep + nl + 2])
     int32_t sweep;

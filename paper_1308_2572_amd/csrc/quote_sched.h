@@ -80,7 +80,7 @@ class SchedExecutor {
     // arena bytes a launch over this many slots can make use of, if they are
     // free until it has run (0: none); the launch that follows gets what
     // scratch() names, or nothing when it names no bytes
-    virtual size_t scratch_bytes(size_t n_slots) { return n_slots * 0; }
+    virtual size_t scratch_bytes(size_t) { return 0; }
     virtual void scratch(size_t off, size_t bytes) { (void)off, (void)bytes; }
     // one launch over the items in slot order; shared: some block has several items
     virtual int32_t launch(const std::vector<SchedItem> &items, bool shared, std::string *err) = 0;
