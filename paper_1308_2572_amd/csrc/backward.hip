@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kBwdEvThreads) void k_bwd_w1(BwdGather P) {
     if (hot < P.ev_least) {   // uniform, and the same in every workgroup
         // the gather, one layer after another over all the workgroups, so that
         // an XCD's L2 holds one slice of one layer's v (of three layers at once
-        // 1239 us where this order takes 855)
+        // some 1240 us where this order took 810 to 855)
         static_assert(kXcds == kSlices, "a slice per XCD");
         for (int l = 0; l < P.n_layers; ++l)
             if (!P.use_sp || form_of(P.sp, l) == kDense)

@@ -1,13 +1,13 @@
 // Building the event-ordered blocks (evblk.h) and what is derived from them:
 // the events' occurrence counts and the event-major copy of the backward.
 //
-// A block's 8 million occurrences (8131 trials x 1000) are sorted by event in
+// A block's 8 million occurrences (8065 trials x 1000) are sorted by event in
 // two levels, each inside LDS and written as runs: chunks of 16384
 // occurrences by tile of 2^te_bits events (k_ev_part), then each tile's
 // 16,600 records by event (k_ev_sort).  Each level reads and writes every
 // occurrence once and is bound by that and by keeping enough loads in flight
-// (3.1 and 2.7 ms at 1M x 1000: 8 and 6.3 GB).  The event-major lists are
-// then gathered from the blocks (2.8 ms; scattering each entry to its place
+// (2.7-3.1 and 2.7 ms at 1M x 1000: 8 and 6.3 GB).  The event-major lists are
+// then gathered from the blocks (3.1 ms; scattering each entry to its place
 // cost one memory write per entry: 26.7 ms), and the events' counts from the
 // headers (0.24 ms; from the code stream, one workgroup per range, 8.7 ms).
 // With positions each record carries its occurrence's position through both
@@ -46,8 +46,8 @@ static_assert(kEvItems * kWave == kEvMark, "a wavefront's share of a chunk start
 EvGeometry ev_geometry(int64_t n_trials, int64_t nnz, int32_t catalog) {
     EvGeometry g{};
     // blocks of equal size, as few as 8128 trials allow (longer lists per
-    // event: at 1M x 1000 and 7% of the events read, blocks of 7872 trials
-    // took 302 us where 3936 took 390 and 1968 took 510), and of less than
+    // event: at 1M x 1000 and 7% of the events read, a prototype took 302 us
+    // over blocks of 7872 trials, 390 over 3936 and 510 over 1968), and of less than
     // 2^31 entries on average
     const int64_t neb = std::max<int64_t>({1, (n_trials + kEvBlockTrials - 1) / kEvBlockTrials, nnz >> 31});
     g.et = static_cast<int32_t>(std::max<int64_t>(1, (n_trials + neb - 1) / neb));
@@ -75,7 +75,8 @@ __device__ __forceinline__ bool ev_failed(const int64_t *misc) { return *reinter
 
 // A value the compiler does not know: what is computed from it is computed
 // again instead of being kept in registers from an earlier loop over the same
-// array (the difference between 117 and 64 registers in k_ev_part).
+// array (in k_ev_part without positions 117 registers, and with this 64, 18
+// of them spilled: 76 bytes a lane).
 __device__ __forceinline__ void keep_apart(int &v) { asm("" : "+v"(v)); }
 
 __device__ __forceinline__ uint32_t uni32(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }

@@ -3,19 +3,19 @@
 // trials' totals in LDS.
 //
 // What bounds it is memory: it reads the lists of the layer's events and the
-// headers that tell where they are, 1.1-1.7 GB of the 2.3 GB that a 1M x 1000
-// YET's blocks take with 7% of the catalogue set (lists of four 16-bit
-// entries, so most 128-byte lines hold some set event's list), where the code
-// stream reads 2.1 GB and spends some 27 instructions on every occurrence.
-// One workgroup per (layer, block, part): the totals of 8192 trials take 96
-// KB of LDS, so a workgroup has a CU for itself; its 16 wavefronts take 64
-// set events at a time, one per lane, with the next 64 events' headers and
-// the ones' after lists in flight.  Larger blocks make longer lists and fewer
-// bytes: 7872 trials in two parts 302 us, 3936 trials 390 us, 1968 trials 510
-// us, the code stream 560 us (one layer, 1M x 1000, 146,000 of 2,000,000
-// events set).  Layers of one block run together on one XCD and share its
-// lists in L2: four uneven layers 778 us (the code stream grouped by four 1750
-// us).
+// headers that tell where they are, 1.8 GB of the 2.25 GB that a 1M x 1000
+// YET's blocks take with 7.6% of the catalogue set (152,000 of 2,000,000
+// events; lists of four 16-bit entries, so most 128-byte lines hold some set
+// event's list), in 304 us (124 blocks of 8065 trials in two parts).  The code
+// stream reads 2.1 GB and spends some 27 instructions on every occurrence: 560
+// us.  One workgroup per (layer, block, part): a block's totals take 96 KB of
+// LDS, so a workgroup has a CU for itself; its 16 wavefronts take 64 set
+// events at a time, one per lane, with the next 64 events' headers and the
+// ones' after lists in flight.  Larger blocks make longer lists and fewer
+// bytes: a prototype took 302 us with 7872 trials, 390 with 3936 and 510 with
+// 1968.  Layers of one block run together on one XCD and share its lists in
+// L2: four uneven layers 722 us and 47 of adding the parts up (the code stream
+// grouped by four 1750 us).
 //
 // The totals are integers (EvLayer): O in fixed point, two words, exact, so
 // the sum does not depend on the order in which wavefronts add, on the parts

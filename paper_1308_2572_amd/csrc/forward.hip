@@ -122,7 +122,7 @@ int32_t launch_forward(const ara_yet *yet, int n_sr, bool hits, bool f32, const 
 // 353).  Blocks of 6M occurrences, 12 MB of lists beside 16 parts' 1.5 MB of
 // totals (1M x 250, four layers: 402 and 486).  And at least eight blocks per
 // XCD, since a block stays on one (150,000 x 1000, 19 blocks: 202 and 237;
-// 1M x 1000, 122 blocks: 1161 and 783).
+// 1M x 1000, some 120 blocks: 1161 and 783).
 constexpr int kSweep = 16;
 constexpr int kSweepLeast = 4, kSweepMost = 16;   // layers
 constexpr int64_t kSweepEntries = 6'000'000;

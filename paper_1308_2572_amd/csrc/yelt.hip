@@ -18,6 +18,10 @@
 // slices (staged in LDS, each lane then holding four consecutive
 // occurrences): a prefix inside the lane, one wavefront scan (DPP) across
 // lanes, the previous slices' total carried in.
+// Bound by instruction issue: some 52 vector instructions per occurrence, the
+// scan, clamps and differences of all of them where one in seven at most has
+// a loss; 55% of the wavefronts' time ready and waiting to issue, 25% waiting
+// on memory (1M x 1000: 3.5 ms, 3.4 TB/s of IDs and losses).
 #include "occ.h"
 #include "wave.h"
 
