@@ -1337,7 +1337,11 @@ extern "C" int32_t ara_ylt_backward(const ara_tables *tables, const ara_yet *yet
             const size_t lds = static_cast<size_t>(Q.two_bytes);
             if (wide) k_bwd_count<16><<<grid, 256, lds, st>>>(Q, cx, ncut);
             else k_bwd_count<4><<<grid, 256, lds, st>>>(Q, cx, ncut);
-            k_bwd_wsparse<<<dim3(2 * cu, L), kSparseThreads, 0, st>>>(Q);
+            // two workgroups a CU, of many layers four rounds: each lays out its
+            // layer's filter before it walks a trial (64 layers 76 us, two a CU and
+            // layer 117)
+            const unsigned gs = static_cast<unsigned>(std::max(16, std::min(2 * cu, 8 * cu / L)));
+            k_bwd_wsparse<<<dim3(gs, L), kSparseThreads, 0, st>>>(Q);
         }
         if (wide) launch_bwd_w<16>(B.cs, grid, st, S, mean_list);
         else launch_bwd_w<4>(B.cs, grid, st, S, mean_list);
