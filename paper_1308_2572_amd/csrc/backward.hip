@@ -1039,8 +1039,8 @@ __device__ __forceinline__ int grad_groups(const int32_t *hot_base, int n_sr, in
 }
 
 // (7) fixed-order sums into the outputs: one workgroup per output value,
-// each thread a fixed stride of the (chunk, wavefront) partials, then a
-// fixed-order tree.
+// each thread a fixed stride of the (chunk, wavefront) partials, eight of them
+// in flight, then a fixed-order tree.
 __global__ __launch_bounds__(256) void k_bwd_final(const int32_t *__restrict__ elt_off, const int32_t *__restrict__ elt_ids,
                                                   int n_layers, int n_elts, int n_cot, int n_cw,
                                                   const int32_t *__restrict__ hot_base, int n_sr, int n_elt_slots,
@@ -1058,7 +1058,8 @@ __global__ __launch_bounds__(256) void k_bwd_final(const int32_t *__restrict__ e
             for (int q = elt_off[j]; q < elt_off[j + 1]; ++q) {
                 if (elt_ids[q] != k) continue;
                 const int used = grad_groups(hot_base, n_sr, j);
-                for (int i = tid; i < used; i += blockDim.x)
+#pragma unroll 8
+                for (int i = tid; i < used; i += 256)
                     v += part_elt[((static_cast<size_t>(i) * n_elt_slots + q) * n_cot + c) * 3 + m];
             }
     } else {
@@ -1066,7 +1067,8 @@ __global__ __launch_bounds__(256) void k_bwd_final(const int32_t *__restrict__ e
         const int c = i / (n_layers * 4), j = (i / 4) % n_layers, m = i % 4;
         if (m < 2) {
             const int used = grad_groups(hot_base, n_sr, j) * kGradWaves;
-            for (int cw = tid; cw < used; cw += blockDim.x)
+#pragma unroll 8
+            for (int cw = tid; cw < used; cw += 256)
                 v += part_occ[((static_cast<size_t>(j) * n_cw + cw) * n_cot + c) * 2 + m];
         } else {
             for (int wg = tid; wg < nwg_v; wg += blockDim.x)
