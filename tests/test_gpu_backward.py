@@ -494,3 +494,26 @@ def test_deviating_trials_of_several_wavefronts(ara, mean):
     cot[2, :, torch.as_tensor(g.choice(n, size=20, replace=False), device="cuda")] = -0.5
     a, b = sparse(s_pre, cot), dense(s_pre, cot)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("n_layers", [5, 128])
+def test_deviating_trials_of_many_layers(ara, n_layers):
+    """More trials to walk than the layer's wavefronts, which are fewer the more
+    layers there are; bit for bit the gather."""
+    import torch
+    g = np.random.default_rng(n_layers)
+    n, catalog = 80_000 if n_layers == 5 else 10_000, 5000
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(g.poisson(20, size=n), out=off[1:])
+    ids = g.integers(0, catalog, size=int(off[-1]), dtype=np.int32)
+    elts = synth.lognormal_elts(5, [300] * n_layers, catalog, mu=11.0, sigma=1.5)
+    elts.terms = np.tile([1.0, 1e3, 5e6], (n_layers, 1))
+    layers = synth.Layers(np.arange(n_layers + 1, dtype=np.int32), np.arange(n_layers, dtype=np.int32),
+                          np.tile([1e4, 5e6, 1e4, 5e8], (n_layers, 1)))
+    _, s_pre, sparse, dense = _both_forms(ara, synth.Workload("layers", synth.Yet(catalog, off, ids), elts, layers, 0.9))
+    c = np.full((2, n_layers, n), 1.0 / n)
+    idx = g.choice(n, size=n // 16, replace=False)
+    c[:, :, idx] = g.uniform(-2.0, 2.0, size=(2, n_layers, idx.size)) / n
+    cot = torch.tensor(c, device="cuda")
+    for a, b in zip(sparse(s_pre, cot), dense(s_pre, cot)):
+        assert np.array_equal(a, b) and np.any(a != 0.0)
